@@ -28,6 +28,14 @@ constexpr int kRsrcFlags = 0x00020000;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRsrcFlags);
 }
+// 64 lanes x 16 bytes from global memory straight into LDS: lane l's bytes land at byte offset dst + 16 l of
+// the dynamic LDS array (dst wave-uniform).  (A device-only function: the host pass does not know that this
+// GPU takes 16 bytes per lane in this instruction, and inside a lambda it would be checked there.)
+__device__ __forceinline__ void load_to_lds16(__amdgpu_buffer_rsrc_t r, f32x4 *lds_base, unsigned dst, unsigned voff,
+                                              unsigned soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        r, (__attribute__((address_space(3))) void *)(reinterpret_cast<char *>(lds_base) + dst), 16, voff, soff, 0, 0);
+}
 // Four (vec) or one consecutive input elements as fp32.
 template <typename TIN> __device__ __forceinline__ f32x4 buf_load_in(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, int vec);
 template <> __device__ __forceinline__ f32x4 buf_load_in<float>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, int vec) {

@@ -133,6 +133,7 @@ int prepare_conv(const void *input, const gspc_packed_t *pw, int N, int Cin, int
     p->wx = pw->geom.wino_bytes
                 ? reinterpret_cast<const float *>(static_cast<const char *>(pw->dev) + pw->geom.wino_offset)
                 : nullptr;
+    p->ws = pw->geom.split_bytes ? static_cast<const char *>(pw->dev) + pw->geom.split_offset : nullptr;
     p->wr = pw->geom.row_bytes ? static_cast<const char *>(pw->dev) + pw->geom.row_offset : nullptr;
     p->y = static_cast<float *>(output);
     p->res = nullptr;
@@ -193,6 +194,7 @@ int dispatch_conv(const gspc::ConvParams &p, const gspc_packed_t *pw) {
         q.wb = nullptr;
         q.wx = nullptr;
         q.wr = nullptr;
+        q.ws = nullptr;
         const gspc::PackGeom gm = gspc::merged_geom(pw->geom, 0, p.KH, p.KW);
         if (gspc::mfma_supported(q, gm)) {
             const char *name = "";
@@ -323,6 +325,14 @@ PackGeom make_pack_geom(int Cin, int Cout, int KH, int KW, int groups, int dtype
             d.bytes = (size_t)d.groups * d.CPG * 9 * d.KPGd * sizeof(float);
             g.total_bytes = d.offset + d.bytes;
         }
+    }
+    if (KH == 1 && KW == 1 && g.KPG >= 16 && g.CPG >= 8) {
+        g.split_chunks = (g.CPG + 31) / 32;
+        g.split_mtiles = (g.KPG + 15) / 16;
+        g.split_parts = dtype != GSPC_F32 ? 1 : (long)g.CPG * g.KPG > 16384 ? 3 : 0;
+        g.split_offset = (g.total_bytes + 255) / 256 * 256;
+        g.split_bytes = (size_t)groups * g.split_chunks * g.split_mtiles * (g.split_parts ? g.split_parts * 1024 : 2048);
+        g.total_bytes = g.split_offset + g.split_bytes;
     }
     // (the Winograd section stays the last one)
     if (dtype == GSPC_F32 && KH == 3 && KW == 3 && g.KPG >= 12 && g.CPG % 4 == 0 && g.CPG >= 8) {

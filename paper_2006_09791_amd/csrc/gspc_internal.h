@@ -78,6 +78,15 @@ struct PackGeom {
     // the layer itself.
     int qk_m, qk_groups, qk_CPG, qk_KPG;
     size_t qk_bytes, qk_offset;
+    // Pointwise section (1x1 layers, KPG >= 16, CPG >= 8): [g][chunk][ceil(KPG/16)] operand blocks, the A operand of
+    // v_mfma_f32_16x16x32_bf16 per (chunk of 32 channels, filter tile): lane l, element e holds filter l % 16 of its
+    // tile at channel 32*chunk + 8*(l/16) + e, zeros past CPG and KPG.  split_parts = 3: bf16 [part][64 lanes][8],
+    // the parts of the exact split h + m + l of an fp32 weight (split_common.h); 1: the same with the one part of a
+    // GSPC_BF16 handle; 0: fp32 [64 lanes][8], split by the kernel (matrices of up to 64 KB, which stay a mere
+    // reordering of the weights in two thirds of the bytes: level with the split section at 32 .. 128 channels,
+    // 1 % behind it at 160 and 4-12 % at 256 .. 1024).
+    int split_chunks, split_mtiles, split_parts;
+    size_t split_bytes, split_offset;
     struct MergedDirect {
         int m, groups, CPG, KPG, KPGd;
         size_t bytes, offset;
@@ -109,6 +118,7 @@ struct ConvParams {
     const void *wb;     // bf16 mfma section (nullptr if none)
     const float *wx;    // Winograd section (nullptr if none)
     const void *wr;     // bf16 row-product section (nullptr if none)
+    const void *ws;     // pointwise section (nullptr if none)
     float *y;           // [N][Cout][Hout][Wout]
     const float *res;   // optional residual, same shape as y
     int N, Cin, H, W, Cout, KH, KW, stride, pad, groups;
@@ -166,6 +176,15 @@ struct WinoPlan {
 bool plan_wino(const ConvParams &p, const PackGeom &g, bool must_fill, WinoPlan *out);
 hipError_t launch_wino(const ConvParams &p, const WinoPlan &plan, hipStream_t s, const char **name);
 int winograd_mode();
+
+// Pointwise layers on the bf16 matrix instruction (split_kernels.hip).
+struct SplitPlan {
+    int inst;
+    int data[16];
+};
+// any_size: also for launches too small for it to pay (no other matrix-core kernel takes the layer).
+bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan *out);
+hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t s, const char **name);
 
 // 4x4x1 MFMA kernel (weights held in registers); plan is opaque to the caller.
 struct Mfma4Plan {

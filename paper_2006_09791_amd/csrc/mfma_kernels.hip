@@ -382,7 +382,6 @@ const Cfg16 kCfg16[] = {
     {4, 4, 1, 4, 0}, {2, 4, 1, 4, 0}, {4, 2, 1, 4, 0}, {2, 2, 1, 4, 0}, {1, 4, 1, 4, 0}, {2, 2, 2, 2, 0},
     {1, 2, 1, 4, 0}, {2, 1, 1, 4, 0}, {1, 1, 1, 4, 0},
     {2, 2, 1, 4, 1}, {1, 2, 1, 4, 1}, {2, 1, 1, 4, 1}, {1, 1, 1, 4, 1},
-    {4, 2, 2, 4, 0},   // eight waves, 128 filters x 128 pixels per block: dense pointwise layers (see plan16)
 };
 constexpr int kNumCfg16 = sizeof(kCfg16) / sizeof(kCfg16[0]);
 constexpr int kFirstKsplit = 9, kEndKsplit = 13;
@@ -507,9 +506,7 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
     const int forced = force ? std::atoi(force) : tuned_config(p, 'm');
     if (forced >= 0) {
         const int i = forced;
-        // (eight-wave blocks: two per compute unit, hence 64 KB each)
-        if (i >= 0 && i < kNumCfg16 &&
-            plan16_cfg(p, g, kCfg16[i], t_out, i >= 13 ? 64 * 1024 : kLdsBudget16)) {
+        if (i >= 0 && i < kNumCfg16 && plan16_cfg(p, g, kCfg16[i], t_out)) {
             *cfg_idx = i;
             return true;
         }
@@ -531,19 +528,6 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
         if (plan16_cfg(p, g, kCfg16[5], &t) &&
             (long)t.row_blocks * t.img_blocks * t.oc_blocks * p.groups >= 2 * kNumCU) {
             *cfg_idx = 5;
-            *t_out = t;
-            return true;
-        }
-    }
-    // Dense pointwise layers on larger planes: a block of eight waves with 128 filters x 128 pixels reads the input
-    // half as often as the 64-filter shapes (two blocks of 64 KB per compute unit).  At N = 256: 128 -> 256 on 56x56
-    // 800 -> 705 us, 256 -> 512 on 28x28 602 -> 555 us, 512 -> 1024 on 14x14 627 -> 570 us; wider or taller blocks
-    // (128 x 256, 256 x 64) and four-wave blocks of 128 x 128 measured behind it.
-    if (pointwise && p.groups == 1 && p.stride == 1) {
-        Tile16 t;
-        if (plan16_cfg(p, g, kCfg16[kEndKsplit], &t, 64 * 1024) &&
-            (long)t.row_blocks * t.img_blocks * t.oc_blocks >= 2 * kNumCU) {
-            *cfg_idx = kEndKsplit;
             *t_out = t;
             return true;
         }
@@ -698,7 +682,6 @@ hipError_t launch16_cfg(int i, const ConvParams &p, const Tile16 &t, hipStream_t
     case 10: return launch16_shape<1, 2, 1, 4, TIN>(p, t, s);
     case 11: return launch16_shape<2, 1, 1, 4, TIN>(p, t, s);
     case 12: return launch16_shape<1, 1, 1, 4, TIN>(p, t, s);
-    case 13: return launch16_shape<4, 2, 2, 4, TIN>(p, t, s);
     }
     return hipErrorNotSupported;
 }
@@ -717,7 +700,7 @@ struct PlanKeyHash {
     }
 };
 struct Plan {
-    int kind;  // 0 none, 32 (bf16), 33 (bf16 row products), 64 (Winograd), 17 (resident filters), 16, 4
+    int kind;  // 0 none, 18 (pointwise, bf16 instruction), 32 (bf16), 33 (bf16 row products), 64 (Winograd), 17 (resident filters), 16, 4
     int idx;
     Tile16 t16;
     Mfma4Plan p4;
@@ -725,17 +708,20 @@ struct Plan {
     RowB16Plan pr;
     Mfma16wPlan pw;
     WinoPlan px;
+    SplitPlan ps;
 };
 
 const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
     thread_local std::unordered_map<PlanKey, Plan, PlanKeyHash> cache;
     PlanKey k{{p.N, p.Cin, p.H, p.W, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16,
-               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr), winograd_mode()}};
+               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr), winograd_mode()}};
     auto it = cache.find(k);
     if (it != cache.end()) return it->second;
     Plan pl{};
     const char fam = tuned_family(p);   // offline tile table: may prefer the plain 16x16x4 kernel
-    if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
+    // (configuration 13 of family 'm' is the 128-filter block of the pointwise kernel)
+    if ((fam == '\0' || (fam == 'm' && tuned_config(p, 'm') == kNumCfg16)) && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
+    else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
     else if ((winograd_mode() != 0 || fam == 'x') && (fam == 'x' || fam == '\0') &&
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
@@ -746,6 +732,7 @@ const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
     else if (g.variant == kMfma4 && fam != 'm' && plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
+    else if (plan_split(p, g, true, &pl.ps)) pl.kind = 18;
     return cache.emplace(k, pl).first->second;
 }
 
@@ -764,6 +751,7 @@ hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, hipStream_t s, co
                             (c.ksplit ? "/ksplit" : ""));
         return p.in_bf16 ? launch16_cfg<uint16_t>(pl.idx, p, pl.t16, s) : launch16_cfg<float>(pl.idx, p, pl.t16, s);
     }
+    if (pl.kind == 18) return launch_split(p, pl.ps, s, name);
     if (pl.kind == 32) return launch_mfma_bf16(p, g, pl.pb, s, name);
     if (pl.kind == 33) return launch_row_bf16(p, pl.pr, s, name);
     if (pl.kind == 64) return launch_wino(p, pl.px, s, name);

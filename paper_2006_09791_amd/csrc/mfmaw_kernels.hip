@@ -56,15 +56,6 @@ __device__ unsigned long long g_phase_w[8 * 4096];
 #define GSPC_STAMPW(i)
 #endif
 
-// 64 lanes x 16 bytes from global memory straight into LDS: lane l's bytes land at byte offset dst + 16 l of
-// the dynamic LDS array (dst wave-uniform).  (A device-only function: the host pass does not know that this
-// GPU takes 16 bytes per lane in this instruction, and inside a lambda it would be checked there.)
-__device__ __forceinline__ void load_to_lds16(__amdgpu_buffer_rsrc_t r, f32x4 *lds_base, unsigned dst, unsigned voff,
-                                              unsigned soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        r, (__attribute__((address_space(3))) void *)(reinterpret_cast<char *>(lds_base) + dst), 16, voff, soff, 0, 0);
-}
-
 template <int MI, int NI, int S, int CKB, bool PERSIST, int XS, typename TIN>
 __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
     GSPC_STAMPW(0)

@@ -1,6 +1,6 @@
 // Stage 1 of GSPC (kernel reshape, Section III-B of arXiv 2006.09791) for the
 // GPU layouts, its inverse, and the fp32 -> bf16 input cast.
-#include "gspc_internal.h"
+#include "split_common.h"
 
 namespace gspc {
 
@@ -193,6 +193,32 @@ __global__ void pack_row_kernel(const float *__restrict__ w, uint16_t *__restric
     out[d] = v;
 }
 
+// Pointwise section, one thread per operand element: the element's parts, 512 elements apart, or (parts = 0) its fp32 value.
+__global__ void pack_split_kernel(const float *__restrict__ w, uint16_t *__restrict__ out, PackArgs a, int chunks,
+                                  int mtiles, int parts, size_t total) {
+    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= total) return;
+    const int e = (int)(d % 8);
+    size_t r = d / 8;
+    const int lane = (int)(r % 64);
+    r /= 64;
+    const size_t tile = r;
+    const int mt = (int)(r % mtiles);
+    r /= mtiles;
+    const int chunk = (int)(r % chunks);
+    const int j = (int)(r / chunks);
+    const int f = mt * 16 + lane % 16, c = chunk * 32 + lane / 16 * 8 + e;
+    float v = 0.f;
+    if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + c];
+    if (!parts) {
+        reinterpret_cast<float *>(out)[tile * 512 + lane * 8 + e] = v;
+        return;
+    }
+    unsigned s[3];
+    split3(v, 0.f, s);
+    for (int q = 0; q < parts; ++q) out[(tile * parts + q) * 512 + lane * 8 + e] = (uint16_t)s[q];
+}
+
 __global__ void unpack_kernel(const float *__restrict__ sec, float *__restrict__ w, PackArgs a,
                               int from_mfma, size_t total) {
     size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -269,6 +295,14 @@ hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t
         float *qsec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.qk_offset);
         const size_t nq = h->geom.qk_bytes / sizeof(float);
         hipLaunchKernelGGL(pack_quadk_kernel, dim3(blocks_for(nq, 256)), dim3(256), 0, s, w, qsec, a, h->geom.qk_m, nq);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (h->geom.split_bytes) {
+        uint16_t *ssec = reinterpret_cast<uint16_t *>(static_cast<char *>(h->dev) + h->geom.split_offset);
+        const size_t ns = h->geom.split_bytes / (h->geom.split_parts ? 2 * h->geom.split_parts : 4);
+        hipLaunchKernelGGL(pack_split_kernel, dim3(blocks_for(ns, 256)), dim3(256), 0, s, w, ssec, a,
+                           h->geom.split_chunks, h->geom.split_mtiles, h->geom.split_parts, ns);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
