@@ -134,6 +134,9 @@ int prepare_conv(const void *input, const gspc_packed_t *pw, int N, int Cin, int
                 ? reinterpret_cast<const float *>(static_cast<const char *>(pw->dev) + pw->geom.wino_offset)
                 : nullptr;
     p->ws = pw->geom.split_bytes ? static_cast<const char *>(pw->dev) + pw->geom.split_offset : nullptr;
+    p->wu = pw->geom.unit_bytes
+                ? reinterpret_cast<const float *>(static_cast<const char *>(pw->dev) + pw->geom.unit_offset)
+                : nullptr;
     p->wr = pw->geom.row_bytes ? static_cast<const char *>(pw->dev) + pw->geom.row_offset : nullptr;
     p->y = static_cast<float *>(output);
     p->res = nullptr;
@@ -195,6 +198,7 @@ int dispatch_conv(const gspc::ConvParams &p, const gspc_packed_t *pw) {
         q.wx = nullptr;
         q.wr = nullptr;
         q.ws = nullptr;
+        q.wu = nullptr;
         const gspc::PackGeom gm = gspc::merged_geom(pw->geom, 0, p.KH, p.KW);
         if (gspc::mfma_supported(q, gm)) {
             const char *name = "";
@@ -333,6 +337,11 @@ PackGeom make_pack_geom(int Cin, int Cout, int KH, int KW, int groups, int dtype
         g.split_offset = (g.total_bytes + 255) / 256 * 256;
         g.split_bytes = (size_t)groups * g.split_chunks * g.split_mtiles * (g.split_parts ? g.split_parts * 1024 : 2048);
         g.total_bytes = g.split_offset + g.split_bytes;
+    }
+    if (dtype == GSPC_F32 && g.mfma_bytes && KH == KW && (KH == 3 || KH == 1)) {
+        g.unit_offset = (g.total_bytes + 255) / 256 * 256;
+        g.unit_bytes = KH == 3 ? g.mfma_bytes : (size_t)groups * ((g.CPG + 15) / 16) * g.mtiles * 1024;
+        g.total_bytes = g.unit_offset + g.unit_bytes;
     }
     // (the Winograd section stays the last one)
     if (dtype == GSPC_F32 && KH == 3 && KW == 3 && g.KPG >= 12 && g.CPG % 4 == 0 && g.CPG >= 8) {

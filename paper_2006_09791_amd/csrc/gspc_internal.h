@@ -87,6 +87,11 @@ struct PackGeom {
     // 1 % behind it at 160 and 4-12 % at 256 .. 1024).
     int split_chunks, split_mtiles, split_parts;
     size_t split_bytes, split_offset;
+    // Unit section (GSPC_F32 handles with an mfma section; 3x3 and 1x1 layers): the same operands in the order one
+    // lane multiplies them, 3x3: fp32 [g][CPGp/4][ceil(KPG/16)][3 kh][64 lanes][3 kw]; 1x1: fp32
+    // [g][ceil(CPG/16)][ceil(KPG/16)][64 lanes][4], element e at channel 16*block + 4*e + lane/16
+    // (unit_kernels.hip).
+    size_t unit_bytes, unit_offset;
     struct MergedDirect {
         int m, groups, CPG, KPG, KPGd;
         size_t bytes, offset;
@@ -119,6 +124,7 @@ struct ConvParams {
     const float *wx;    // Winograd section (nullptr if none)
     const void *wr;     // bf16 row-product section (nullptr if none)
     const void *ws;     // pointwise section (nullptr if none)
+    const float *wu;    // unit section (nullptr if none)
     float *y;           // [N][Cout][Hout][Wout]
     const float *res;   // optional residual, same shape as y
     int N, Cin, H, W, Cout, KH, KW, stride, pad, groups;
@@ -185,6 +191,14 @@ struct SplitPlan {
 // any_size: also for launches too small for it to pay (no other matrix-core kernel takes the layer).
 bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan *out);
 hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t s, const char **name);
+
+// 16x16x4 MFMA kernel for small launches: no staging, the waves of a block split the reduction.
+struct UnitPlan {
+    int nw;
+    int data[16];
+};
+bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out);
+hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name);
 
 // 4x4x1 MFMA kernel (weights held in registers); plan is opaque to the caller.
 struct Mfma4Plan {

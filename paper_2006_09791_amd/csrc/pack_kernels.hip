@@ -219,6 +219,29 @@ __global__ void pack_split_kernel(const float *__restrict__ w, uint16_t *__restr
     for (int q = 0; q < parts; ++q) out[(tile * parts + q) * 512 + lane * 8 + e] = (uint16_t)s[q];
 }
 
+// Unit section, one thread per element.
+__global__ void pack_unit_kernel(const float *__restrict__ w, float *__restrict__ out, PackArgs a, size_t total) {
+    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= total) return;
+    const int taps = a.KH * a.KW, E = taps == 9 ? 3 : 4;
+    const int e = (int)(d % E);
+    size_t r = d / E;
+    const int lane = (int)(r % 64);
+    r /= 64;
+    const int kh = taps == 9 ? (int)(r % 3) : 0;
+    if (taps == 9) r /= 3;
+    const int mt = (int)(r % a.mtiles);
+    r /= a.mtiles;
+    const int blks = taps == 9 ? (a.CPG + 3) / 4 : (a.CPG + 15) / 16;
+    const int blk = (int)(r % blks);
+    const int j = (int)(r / blks);
+    const int f = mt * 16 + lane % 16;
+    const int c = taps == 9 ? blk * 4 + lane / 16 : blk * 16 + e * 4 + lane / 16;
+    float v = 0.f;
+    if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + (size_t)c * taps + (taps == 9 ? kh * 3 + e : 0)];
+    out[d] = v;
+}
+
 __global__ void unpack_kernel(const float *__restrict__ sec, float *__restrict__ w, PackArgs a,
                               int from_mfma, size_t total) {
     size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -295,6 +318,13 @@ hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t
         float *qsec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.qk_offset);
         const size_t nq = h->geom.qk_bytes / sizeof(float);
         hipLaunchKernelGGL(pack_quadk_kernel, dim3(blocks_for(nq, 256)), dim3(256), 0, s, w, qsec, a, h->geom.qk_m, nq);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (h->geom.unit_bytes) {
+        float *usec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.unit_offset);
+        const size_t nu = h->geom.unit_bytes / sizeof(float);
+        hipLaunchKernelGGL(pack_unit_kernel, dim3(blocks_for(nu, 256)), dim3(256), 0, s, w, usec, a, nu);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1,0 +1,211 @@
+// Small launches (batch 1 and the like): per-group implicit GEMM on v_mfma_f32_16x16x4_f32 without staging.
+//
+// A block owns one tile of 16 filters x 16 output pixels and its waves split the reduction; every operand
+// goes from global memory (L2) straight into the registers of the lane that multiplies it, so that all loads
+// of a wave are on their way before the first product, and the only barrier is the one before the partial
+// sums are added.  Such a launch is a chain of latencies - kernel start, addresses, one trip to memory,
+// products, the sum, the store - and conv_mfma16's chunks put three or four more trips into it.
+//
+// A unit of the reduction is four channels (lane / 16) and, for 3x3 layers, one kernel row: a lane loads the
+// three taps of its pixel (lane % 16) and the three weights of its filter with one 12-byte load each and
+// multiplies three times; for 1x1 layers sixteen channels, one 16-byte load of weights and four of inputs.
+// A unit costs the vector memory path two (1x1: five) instructions of up to 16 clocks for one tile, and nothing
+// is shared between tiles: that is what bounds it, and why the dispatch rule counts loads.  One 14x14 layer of
+// 256 channels in 4 groups at N = 1: 8.9 -> 3.5 us in the kernel trace.
+#include <cstring>
+
+#include "conv_common.h"
+
+namespace gspc {
+
+typedef float f32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
+
+struct TileUnit {
+    int units, cblks, mtiles;        // units of the reduction, blocks of four channels, filter tiles per group
+    unsigned npix, m_Wout;           // N * Hout * Wout; reciprocal
+    unsigned x_bytes, w_bytes;
+};
+static_assert(sizeof(TileUnit) <= sizeof(((UnitPlan *)0)->data), "plan storage too small");
+
+template <int MI, int NI, int WM, int NW, int KH, int KW, int S, typename TIN, bool VO>
+__global__ __launch_bounds__(64 * NW) void conv_mfma16(ConvParams p, TileUnit t) {
+    static_assert(MI == 1 && NI == 1 && WM == 1 && sizeof(TIN) == 4 && !VO, "one 16 x 16 tile per block");
+    constexpr bool ROW = KH == 3;
+    constexpr int UB = ROW ? 6 : 4;                     // units in flight per wave
+    __shared__ float part[NW][16][17];
+
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned j = blockIdx.z, mt = blockIdx.y;
+    const unsigned HWo = p.Hout * p.Wout, HW = p.H * p.W;
+
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wu, t.w_bytes);
+
+    // weights: [g][unit block][filter tile]([kernel row])[64 lanes][3 or 4]
+    constexpr unsigned WLANE = ROW ? 12 : 16, WUNIT = 64 * WLANE;
+    auto w_off = [&](int u) -> unsigned {               // wave-uniform
+        if (ROW) return ((j * t.cblks + u / 3) * t.mtiles + mt) * (3 * WUNIT) + (u % 3) * WUNIT;
+        return ((j * t.units + u) * t.mtiles + mt) * WUNIT;
+    };
+    u32x4 wv[UB];
+    auto fetch_w = [&](int u, int s) __attribute__((always_inline)) {
+        const unsigned vo = u < t.units ? lane * WLANE : kOob;
+        if (ROW) {
+            const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(rw, vo, w_off(u), 0);
+            wv[s] = u32x4{v.x, v.y, v.z, 0u};
+        } else {
+            wv[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, w_off(u), 0);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < UB; ++s) fetch_w(wave + s * NW, s);   // (they do not wait for the pixel arithmetic)
+
+    // ---- this lane's pixel ------------------------------------------------------------------------
+    const unsigned q = blockIdx.x * 16 + li;
+    const bool live = q < t.npix;
+    const unsigned n = q / HWo, rem = q - n * HWo;
+    const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * p.Wout;
+    const int ih0 = (int)oh * S - p.pad, iw0 = (int)ow * S - p.pad;
+    // 3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
+    // place up (down) and a zero takes the place of the column outside
+    const int start = ROW ? min(max(iw0, 0), p.W - 3) : iw0;
+    const int shift = start - iw0;
+    const unsigned xpix = ((n * p.Cin + j * p.CPG + lg) * HW + start) * 4u;
+    u32x3 xr[ROW ? UB : 1];
+    unsigned xs[ROW ? 1 : UB][4];
+    auto fetch_x = [&](int u, int s) __attribute__((always_inline)) {
+        if constexpr (ROW) {
+            const int cb = u / 3, ih = ih0 + u % 3;
+            const bool ok = live && u < t.units && cb * 4 + lg < p.CPG && (unsigned)ih < (unsigned)p.H;
+            xr[s] = __builtin_amdgcn_raw_buffer_load_b96(rx, ok ? xpix + (cb * 4 * HW + ih * p.W) * 4u : kOob, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int cb = u * 4 + e;
+                const bool ok = live && cb * 4 + lg < p.CPG;
+                xs[s][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, ok ? xpix + (cb * 4 * HW + ih0 * p.W) * 4u : kOob, 0, 0);
+            }
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < UB; ++s) fetch_x(wave + s * NW, s);
+    __builtin_amdgcn_sched_barrier(0);
+
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int u0 = wave; u0 < t.units; u0 += UB * NW) {
+        const bool more = u0 + UB * NW < t.units;
+#pragma unroll
+        for (int s = 0; s < UB; ++s) {
+            float b[4];
+            if constexpr (ROW) {
+                const float x0 = __uint_as_float(xr[s].x), x1 = __uint_as_float(xr[s].y), x2 = __uint_as_float(xr[s].z);
+                b[0] = shift > 0 ? 0.f : shift < 0 ? x1 : x0;
+                b[1] = shift > 0 ? x0 : shift < 0 ? x2 : x1;
+                b[2] = shift > 0 ? x1 : shift < 0 ? 0.f : x2;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) b[e] = __uint_as_float(xs[s][e]);
+            }
+#pragma unroll
+            for (int e = 0; e < (ROW ? 3 : 4); ++e)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wv[s][e]), b[e], acc, 0, 0, 0);
+            if (more) {
+                const int u = u0 + (s + UB) * NW;
+                fetch_w(u, s);
+                fetch_x(u, s);
+            }
+        }
+    }
+
+    // ---- the waves' partial sums; residual, ReLU, NCHW store ---------------------------------------
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave][4 * lg + r][li] = acc[r];
+    __syncthreads();
+    constexpr int OT = NW * 64 < 256 ? NW * 64 : 256;    // threads that store
+    if (tid >= OT) return;
+#pragma unroll
+    for (int o = tid; o < 256; o += OT) {
+        const int f = o >> 4, px = o & 15;
+        float v = part[0][f][px];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) v += part[k][f][px];
+        const unsigned qo = blockIdx.x * 16 + px, fo = mt * 16 + f;
+        if (qo < t.npix && fo < (unsigned)p.KPG) {
+            const unsigned no = qo / HWo;
+            const size_t at = (size_t)(no * p.Cout + j * p.KPG + fo) * HWo + (qo - no * HWo);
+            if (p.res) v += p.res[at];
+            p.y[at] = p.relu ? fmaxf(v, 0.f) : v;
+        }
+    }
+}
+
+namespace {
+
+template <int NW, int KH, int S>
+hipError_t launchU(const ConvParams &p, const TileUnit &t, hipStream_t s) {
+    auto kern = static_cast<void (*)(ConvParams, TileUnit)>(conv_mfma16<1, 1, 1, NW, KH, KH, S, float, false>);
+    hipLaunchKernelGGL(kern, dim3((t.npix + 15) / 16, t.mtiles, p.groups), dim3(64 * NW), 0, s, p, t);
+    return hipGetLastError();
+}
+
+template <int NW>
+hipError_t launchU_shape(const ConvParams &p, const TileUnit &t, hipStream_t s) {
+    if (p.KH == 3) return p.stride == 1 ? launchU<NW, 3, 1>(p, t, s) : launchU<NW, 3, 2>(p, t, s);
+    return p.stride == 1 ? launchU<NW, 1, 1>(p, t, s) : launchU<NW, 1, 2>(p, t, s);
+}
+
+}  // namespace
+
+bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
+    if (!p.wu || p.in_bf16 || (p.stride != 1 && p.stride != 2)) return false;
+    const bool row = p.KH == 3;
+    if (row ? p.pad != 1 || p.W < 3 : p.pad != 0) return false;
+    const double npix = (double)p.N * p.Hout * p.Wout;
+    const double xb = (double)p.N * p.Cin * p.H * p.W * 4;
+    if (xb >= (double)kOob || npix >= 1e6 || (double)g.unit_bytes >= (double)kOob) return false;
+    if (p.groups > 65535 || g.mtiles > 65535 || (long)p.Hout * p.Wout >= 65536) return false;
+    TileUnit t{};
+    t.cblks = g.CPGp / 4;
+    t.units = row ? t.cblks * 3 : (t.cblks + 3) / 4;
+    t.mtiles = g.mtiles;
+    t.npix = (unsigned)npix;
+    t.m_Wout = div_magic(p.Wout);
+    t.x_bytes = (unsigned)xb;
+    t.w_bytes = (unsigned)g.unit_bytes;
+    // Where it pays (layers of the WRN-, ResNet-34- and MobileNet-shaped networks at N = 1 .. 64, us, conv_mfma16 with
+    // staging / this kernel): 2 x 256 -> 256 on 14x14, g = 4 7.2 / 4.8; 1024 -> 1024 pointwise on 7x7, N = 1 19.1 / 6.6;
+    // 60 -> 84 on 29x37, g = 3, N = 5 9.1 / 6.9.  Operands are loaded once per tile that uses them, so the loads decide:
+    //  - 3x3, stride 1, rows of a multiple of 4 (16-byte staging on the other side): 75k loads 8.3 / 6.5 and 9.4 / 6.6,
+    //    150k 9.1 / 10.0 and 13.1 / 10.0, 300k 13.4 / 16.6;
+    //  - stride 2, other widths, 1x1: 150k 12.7 / 10.2 and 18.2 / 9.9, 300k 16.7 / 18.0 and 20.0 / 22.2.
+    // With fewer than six units a block is mostly its start and its sum: 3 -> 32 on 32x32, N = 8 4.9 / 4.7, N = 32 5.2 / 6.8.
+    const long tiles = (long)((t.npix + 15) / 16) * g.mtiles * p.groups;
+    const double loads = (double)tiles * t.units * (row ? 2 : 5);
+    if (loads > (row && p.stride == 1 && p.W % 4 == 0 ? 80e3 : 200e3)) return false;
+    if (row && t.units < 6 && tiles > 4 * kNumCU) return false;
+    // waves per block: what lets every wave request all of its units at once, more while the launch is small
+    int nw = 2;
+    while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw < 8 * kNumCU && t.units > nw))) nw *= 2;
+    out->nw = nw;
+    std::memcpy(out->data, &t, sizeof(t));
+    return true;
+}
+
+hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name) {
+    TileUnit t;
+    std::memcpy(&t, plan.data, sizeof(t));
+    const std::string k = std::to_string(p.KH);
+    *name = intern_name("conv_mfma16<1,1,1," + std::to_string(plan.nw) + "," + k + "," + k + "," + std::to_string(p.stride) +
+                        ",f32,false>/unit");
+    switch (plan.nw) {
+    case 2: return launchU_shape<2>(p, t, s);
+    case 4: return launchU_shape<4>(p, t, s);
+    case 8: return launchU_shape<8>(p, t, s);
+    case 16: return launchU_shape<16>(p, t, s);
+    }
+    return hipErrorNotSupported;
+}
+
+}  // namespace gspc

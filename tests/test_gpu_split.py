@@ -30,7 +30,7 @@ SHAPES = [
     (S(200, 144, 12, 12, 160, 1, 1, 1, 0, 1), "4,2,1,4"),  # filters split at packing time in 64-filter blocks
     (S(165, 160, 13, 13, 130, 1, 1, 1, 0, 1), "4,2,1,4"),  # the same on odd planes
     (S(8, 128, 14, 14, 512, 1, 1, 1, 0, 1), "2,2,1,2"),    # the smallest blocks
-    (S(1, 250, 9, 11, 77, 1, 1, 1, 0, 1), "2,2,1,2"),      # no other matrix-core kernel takes it: any size
+    (S(1, 250, 9, 11, 77, 1, 1, 1, 0, 1), "2,2,1,2"),      # bf16, no other matrix-core kernel takes it: any size
     (S(4000, 24, 1, 1, 200, 1, 1, 1, 0, 1), "2,2,1,"),     # planes of one pixel
 ]
 
@@ -39,6 +39,8 @@ SHAPES = [
 @pytest.mark.parametrize("s,shape", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
 def test_pointwise_split(gpu, s, shape, bf16):
     torch, b = gpu
+    if s.N == 1 and not bf16:
+        pytest.skip("a small fp32 launch: conv_mfma16 without staging (test_gpu_unit.py)")
     y, x, w, name = run_conv(gpu, s, seed=51, dtype=b.GSPC_BF16 if bf16 else b.GSPC_F32)
     assert name.startswith("conv_mfma16<" + shape) and name.endswith("/bf16" if bf16 else "/split3" if s.Cin * s.Cout > 16384 else "/split3w"), name
     if bf16:

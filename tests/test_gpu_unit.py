@@ -1,0 +1,66 @@
+"""Small launches: the 16x16x4 kernel without staging, against the oracle's plain definition of the grouped
+convolution (Section II, Fig. 2)."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import err_metrics, rel_err
+from paper_2006_09791_amd import workloads as wl
+from test_gpu_parity import gpu, run_conv  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+S = wl.ConvShape
+SHAPES = [
+    # N Cin H W Cout KH KW stride pad groups
+    S(1, 64, 32, 32, 64, 3, 3, 1, 1, 4),
+    S(1, 16, 1, 3, 16, 3, 3, 1, 1, 1),        # the narrowest row: every pixel at an edge
+    S(2, 24, 3, 3, 24, 3, 3, 2, 1, 2),        # stride 2, odd width: the last window ends outside
+    S(3, 40, 6, 4, 48, 3, 3, 2, 1, 1),        # stride 2, even width
+    S(3, 70, 9, 5, 33, 3, 3, 1, 1, 1),        # padded channels and filters, 54 units in 16 waves
+    S(5, 60, 29, 37, 84, 3, 3, 1, 1, 3),      # ragged last tile
+    S(1, 512, 7, 7, 512, 3, 3, 1, 1, 2),      # 192 units: two rounds of loads per wave
+    S(1, 256, 14, 14, 512, 1, 1, 2, 0, 1),    # 1x1, stride 2
+    S(2, 50, 9, 7, 24, 1, 1, 2, 0, 1),        # 50 channels: a block of sixteen partly empty
+    S(1, 960, 7, 7, 160, 1, 1, 1, 0, 1),
+    S(3, 36, 5, 5, 20, 1, 1, 1, 0, 2),        # 18 channels and 10 filters per group
+    S(17, 128, 4, 4, 64, 1, 1, 1, 0, 4),
+]
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_unit_kernel(gpu, s):
+    y, x, w, name = run_conv(gpu, s, seed=61)
+    assert name.startswith("conv_mfma16<1,1,1,") and name.endswith("/unit"), name
+    assert not np.isnan(y).any(), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, return_abs=True, threads=8)
+    m = err_metrics(y, ref, absum)
+    # a product and a sum per term, each rounded once at most: K + 16 roundings of the running sum
+    K = s.Cin // s.groups * s.KH * s.KW
+    assert m["bound"] < (K + 17) * 2.0 ** -24, (name, m)
+    assert m["floored"] < 1e-5, (name, m)
+
+
+@pytest.mark.parametrize("s", [S(2, 48, 9, 7, 40, 3, 3, 1, 1, 2), S(3, 40, 7, 7, 24, 1, 1, 2, 0, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
+    """Residual and ReLU; inputs and outputs at the ends of larger buffers: nothing outside is written, and
+    what lies outside (NaN) is not read into a result."""
+    torch, b = gpu
+    dev = torch.device("cuda:0")
+    x, w = wl.make_input((s.N, s.Cin, s.H, s.W), 63), wl.make_weight(s.Cout, s.Cin // s.groups, s.KH, s.KW, 64)
+    ho, wo = b.gspc_output_dims(s.H, s.W, s.KH, s.KW, s.stride, s.pad)
+    res = wl.make_input((s.N, s.Cout, ho, wo), 65)
+    guard = 1024
+    big = [torch.full((a.size + 2 * guard,), float("nan"), device=dev) for a in (x, res, res)]
+    xd, rd, yd = (t[guard:guard + a.size] for t, a in zip(big, (x, res, res)))
+    xd.copy_(torch.from_numpy(x).reshape(-1))
+    rd.copy_(torch.from_numpy(res).reshape(-1))
+    pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), s.groups)
+    layer = wl.Layer("conv", 0, 1, 2, s.N, s.Cin, s.H, s.W, s.Cout, s.KH, s.KW, s.stride, s.pad, s.groups, True, 0)
+    b.gspc_run_layer_chain(b.LayerChain([layer], [pw], [xd, rd, yd]))
+    torch.cuda.synchronize()
+    assert b.gspc_last_kernel().endswith("/unit"), b.gspc_last_kernel()
+    out = big[2].cpu().numpy()
+    assert np.isnan(out[:guard]).all() and np.isnan(out[guard + res.size:]).all()
+    ref = oracle.relu(oracle.add(oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, threads=8), res))
+    assert rel_err(out[guard:guard + res.size].reshape(res.shape), ref) < 1e-5
