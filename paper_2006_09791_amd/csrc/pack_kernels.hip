@@ -18,10 +18,8 @@ __device__ __forceinline__ float round_bf16(float v) {
 }
 
 // total covers the section plus the alignment gap behind it, which is zeroed.
-__global__ void pack_direct_kernel(const float *__restrict__ w, float *__restrict__ out,
-                                   PackArgs a, size_t section, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_direct(size_t d, const float *__restrict__ w, float *__restrict__ out,
+                                            const PackArgs &a, size_t section) {
     if (d >= section) {
         out[d] = 0.f;
         return;
@@ -38,10 +36,8 @@ __global__ void pack_direct_kernel(const float *__restrict__ w, float *__restric
     out[d] = v;
 }
 
-__global__ void pack_mfma_kernel(const float *__restrict__ w, float *__restrict__ out,
-                                 PackArgs a, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_mfma(size_t d, const float *__restrict__ w, float *__restrict__ out,
+                                          const PackArgs &a) {
     const int lane = (int)(d % 64);
     size_t r = d / 64;
     const int mt = (int)(r % a.mtiles);
@@ -64,9 +60,8 @@ __global__ void pack_mfma_kernel(const float *__restrict__ w, float *__restrict_
 
 // Winograd section: U = G g G^T of every 3x3 filter slice (G of F(2x2, 3x3): rows (1, 0, 0),
 // (1/2, 1/2, 1/2), (1/2, -1/2, 1/2), (0, 0, 1)), one thread per element.
-__global__ void pack_wino_kernel(const float *__restrict__ w, float *__restrict__ out, PackArgs a, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_wino(size_t d, const float *__restrict__ w, float *__restrict__ out,
+                                          const PackArgs &a) {
     const int e = (int)(d % 4);
     size_t r = d / 4;
     const int lane = (int)(r % 64);
@@ -106,10 +101,8 @@ __device__ __forceinline__ float merged_weight(const float *__restrict__ w, cons
 
 // Merged direct section [groups/m][m*CPG*9][KPGd2] (3x3 layers): the direct section of the layer
 // seen as groups / m block-diagonal groups.
-__global__ void pack_direct_merged_kernel(const float *__restrict__ w, float *__restrict__ out, PackArgs a, int m,
-                                          int KPGd2, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_direct_merged(size_t d, const float *__restrict__ w,
+                                                   float *__restrict__ out, const PackArgs &a, int m, int KPGd2) {
     const int o = (int)(d % KPGd2);
     const size_t r = d / KPGd2;
     const int kred2 = a.CPG * m * 9;
@@ -121,9 +114,8 @@ __global__ void pack_direct_merged_kernel(const float *__restrict__ w, float *__
 }
 
 // Quad-k section [groups/m][k-steps/4][m*KPG/16][64 lanes][4], taps = KH*KW (9 or 1).
-__global__ void pack_quadk_kernel(const float *__restrict__ w, float *__restrict__ out, PackArgs a, int m, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_quadk(size_t d, const float *__restrict__ w, float *__restrict__ out,
+                                           const PackArgs &a, int m) {
     const int taps = a.KH * a.KW;
     const int e = (int)(d % 4);
     size_t r = d / 4;
@@ -142,10 +134,8 @@ __global__ void pack_quadk_kernel(const float *__restrict__ w, float *__restrict
 }
 
 // bf16 matrix-core section, one thread per 2-byte element; m = groups merged per section group.
-__global__ void pack_bf16_kernel(const float *__restrict__ w, uint16_t *__restrict__ out, PackArgs a,
-                                 int ckb, int ks_b, int nchunks, int m, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_bf16(size_t d, const float *__restrict__ w, uint16_t *__restrict__ out,
+                                          const PackArgs &a, int ckb, int ks_b, int nchunks, int m) {
     const int e = (int)(d % 8);
     size_t r = d / 8;
     const int lane = (int)(r % 64);
@@ -168,10 +158,8 @@ __global__ void pack_bf16_kernel(const float *__restrict__ w, uint16_t *__restri
 }
 
 // bf16 row-product section: banded operands [merged group][filter quad][kh][channel quad][lane][8].
-__global__ void pack_row_kernel(const float *__restrict__ w, uint16_t *__restrict__ out, PackArgs a, int m,
-                                size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_row(size_t d, const float *__restrict__ w, uint16_t *__restrict__ out,
+                                         const PackArgs &a, int m) {
     const int e = (int)(d % 8);
     size_t r = d / 8;
     const int lane = (int)(r % 64);
@@ -194,10 +182,8 @@ __global__ void pack_row_kernel(const float *__restrict__ w, uint16_t *__restric
 }
 
 // Pointwise section, one thread per operand element: the element's parts, 512 elements apart, or (parts = 0) its fp32 value.
-__global__ void pack_split_kernel(const float *__restrict__ w, uint16_t *__restrict__ out, PackArgs a, int chunks,
-                                  int mtiles, int parts, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_split(size_t d, const float *__restrict__ w, uint16_t *__restrict__ out,
+                                           const PackArgs &a, int chunks, int mtiles, int parts) {
     const int e = (int)(d % 8);
     size_t r = d / 8;
     const int lane = (int)(r % 64);
@@ -220,9 +206,8 @@ __global__ void pack_split_kernel(const float *__restrict__ w, uint16_t *__restr
 }
 
 // Unit section, one thread per element.
-__global__ void pack_unit_kernel(const float *__restrict__ w, float *__restrict__ out, PackArgs a, size_t total) {
-    size_t d = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total) return;
+__device__ __forceinline__ void pack_unit(size_t d, const float *__restrict__ w, float *__restrict__ out,
+                                          const PackArgs &a) {
     const int taps = a.KH * a.KW, E = taps == 9 ? 3 : 4;
     const int e = (int)(d % E);
     size_t r = d / E;
@@ -240,6 +225,43 @@ __global__ void pack_unit_kernel(const float *__restrict__ w, float *__restrict_
     float v = 0.f;
     if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + (size_t)c * taps + (taps == 9 ? kh * 3 + e : 0)];
     out[d] = v;
+}
+
+// One launch reorders a layer into all of its sections: blocks jobs[i].first .. write section i.
+enum PackKind { kPackDirect, kPackMfma, kPackWino, kPackMerged, kPackQuadk, kPackBf16, kPackRow, kPackSplit, kPackUnit };
+struct PackJob {
+    int kind;
+    unsigned first;      // first block of 256 elements
+    void *out;
+    size_t total;        // elements
+    size_t section;      // kPackDirect: elements of the section itself, zeros behind it
+    int i[4];
+};
+constexpr int kMaxJobs = 10;
+struct PackJobs {
+    int n;
+    PackJob job[kMaxJobs];
+};
+
+__global__ void pack_kernel(const float *__restrict__ w, PackArgs a, PackJobs jobs) {
+    int k = 0;
+    while (k + 1 < jobs.n && blockIdx.x >= jobs.job[k + 1].first) ++k;
+    const PackJob &jb = jobs.job[k];
+    const size_t d = (size_t)(blockIdx.x - jb.first) * blockDim.x + threadIdx.x;
+    if (d >= jb.total) return;
+    float *f = static_cast<float *>(jb.out);
+    uint16_t *b = static_cast<uint16_t *>(jb.out);
+    switch (jb.kind) {
+    case kPackDirect: pack_direct(d, w, f, a, jb.section); break;
+    case kPackMfma: pack_mfma(d, w, f, a); break;
+    case kPackWino: pack_wino(d, w, f, a); break;
+    case kPackMerged: pack_direct_merged(d, w, f, a, jb.i[0], jb.i[1]); break;
+    case kPackQuadk: pack_quadk(d, w, f, a, jb.i[0]); break;
+    case kPackBf16: pack_bf16(d, w, b, a, jb.i[0], jb.i[1], jb.i[2], jb.i[3]); break;
+    case kPackRow: pack_row(d, w, b, a, jb.i[0]); break;
+    case kPackSplit: pack_split(d, w, b, a, jb.i[0], jb.i[1], jb.i[2]); break;
+    case kPackUnit: pack_unit(d, w, f, a); break;
+    }
 }
 
 __global__ void unpack_kernel(const float *__restrict__ sec, float *__restrict__ w, PackArgs a,
@@ -285,74 +307,29 @@ static unsigned blocks_for(size_t total, int threads) {
 
 hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t s) {
     const PackArgs a = make_args(h);
-    float *dsec = static_cast<float *>(h->dev);
-    const size_t nd = h->geom.direct_bytes / sizeof(float);
-    const size_t nd_gap = h->geom.mfma_offset / sizeof(float);
-    hipLaunchKernelGGL(pack_direct_kernel, dim3(blocks_for(nd_gap, 256)), dim3(256), 0, s, w, dsec, a,
-                       nd, nd_gap);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (h->geom.bf16_bytes) {
-        uint16_t *bsec = reinterpret_cast<uint16_t *>(static_cast<char *>(h->dev) + h->geom.bf16_offset);
-        const size_t nb = h->geom.bf16_bytes / 2;
-        hipLaunchKernelGGL(pack_bf16_kernel, dim3(blocks_for(nb, 256)), dim3(256), 0, s, w, bsec, a,
-                           h->geom.ckb, h->geom.ks_b, h->geom.nchunks_b, h->geom.mb, nb);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.row_bytes) {
-        uint16_t *rsec = reinterpret_cast<uint16_t *>(static_cast<char *>(h->dev) + h->geom.row_offset);
-        const size_t nr = h->geom.row_bytes / 2;
-        hipLaunchKernelGGL(pack_row_kernel, dim3(blocks_for(nr, 256)), dim3(256), 0, s, w, rsec, a, h->geom.mt, nr);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.wino_bytes) {
-        float *xsec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.wino_offset);
-        const size_t nx = h->geom.wino_bytes / sizeof(float);
-        hipLaunchKernelGGL(pack_wino_kernel, dim3(blocks_for(nx, 256)), dim3(256), 0, s, w, xsec, a, nx);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.qk_bytes) {
-        float *qsec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.qk_offset);
-        const size_t nq = h->geom.qk_bytes / sizeof(float);
-        hipLaunchKernelGGL(pack_quadk_kernel, dim3(blocks_for(nq, 256)), dim3(256), 0, s, w, qsec, a, h->geom.qk_m, nq);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.unit_bytes) {
-        float *usec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.unit_offset);
-        const size_t nu = h->geom.unit_bytes / sizeof(float);
-        hipLaunchKernelGGL(pack_unit_kernel, dim3(blocks_for(nu, 256)), dim3(256), 0, s, w, usec, a, nu);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.split_bytes) {
-        uint16_t *ssec = reinterpret_cast<uint16_t *>(static_cast<char *>(h->dev) + h->geom.split_offset);
-        const size_t ns = h->geom.split_bytes / (h->geom.split_parts ? 2 * h->geom.split_parts : 4);
-        hipLaunchKernelGGL(pack_split_kernel, dim3(blocks_for(ns, 256)), dim3(256), 0, s, w, ssec, a,
-                           h->geom.split_chunks, h->geom.split_mtiles, h->geom.split_parts, ns);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    for (int which = 0; which < 2; ++which) {
-        const PackGeom::MergedDirect &md = h->geom.md[which];
-        if (!md.m) continue;
-        float *dsec2 = reinterpret_cast<float *>(static_cast<char *>(h->dev) + md.offset);
-        const size_t n2 = md.bytes / sizeof(float);
-        hipLaunchKernelGGL(pack_direct_merged_kernel, dim3(blocks_for(n2, 256)), dim3(256), 0, s, w, dsec2, a, md.m,
-                           md.KPGd, n2);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (h->geom.mfma_bytes) {
-        float *msec = reinterpret_cast<float *>(static_cast<char *>(h->dev) + h->geom.mfma_offset);
-        const size_t nm = h->geom.mfma_bytes / sizeof(float);
-        hipLaunchKernelGGL(pack_mfma_kernel, dim3(blocks_for(nm, 256)), dim3(256), 0, s, w, msec, a, nm);
-        e = hipGetLastError();
-    }
-    return e;
+    const PackGeom &g = h->geom;
+    PackJobs jobs{};
+    size_t blocks = 0;
+    auto add = [&](int kind, size_t offset, size_t total, int i0 = 0, int i1 = 0, int i2 = 0, int i3 = 0) {
+        if (!total) return;
+        jobs.job[jobs.n++] = PackJob{kind, (unsigned)blocks, static_cast<char *>(h->dev) + offset, total, 0, {i0, i1, i2, i3}};
+        blocks += (total + 255) / 256;
+    };
+    add(kPackDirect, 0, g.mfma_offset / sizeof(float));
+    jobs.job[0].section = g.direct_bytes / sizeof(float);
+    add(kPackBf16, g.bf16_offset, g.bf16_bytes / 2, g.ckb, g.ks_b, g.nchunks_b, g.mb);
+    add(kPackRow, g.row_offset, g.row_bytes / 2, g.mt);
+    add(kPackWino, g.wino_offset, g.wino_bytes / sizeof(float));
+    add(kPackQuadk, g.qk_offset, g.qk_bytes / sizeof(float), g.qk_m);
+    add(kPackUnit, g.unit_offset, g.unit_bytes / sizeof(float));
+    add(kPackSplit, g.split_offset, g.split_bytes / (g.split_parts ? 2 * g.split_parts : 4), g.split_chunks, g.split_mtiles,
+        g.split_parts);
+    for (const PackGeom::MergedDirect &md : g.md)
+        if (md.m) add(kPackMerged, md.offset, md.bytes / sizeof(float), md.m, md.KPGd);
+    add(kPackMfma, g.mfma_offset, g.mfma_bytes / sizeof(float));
+    if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(256), 0, s, w, a, jobs);
+    return hipGetLastError();
 }
 
 hipError_t launch_unpack_weights(const gspc_packed *h, int which, float *w, hipStream_t s) {
