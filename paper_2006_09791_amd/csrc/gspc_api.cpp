@@ -134,6 +134,7 @@ int prepare_conv(const void *input, const gspc_packed_t *pw, int N, int Cin, int
                 ? reinterpret_cast<const float *>(static_cast<const char *>(pw->dev) + pw->geom.wino_offset)
                 : nullptr;
     p->ws = pw->geom.split_bytes ? static_cast<const char *>(pw->dev) + pw->geom.split_offset : nullptr;
+    p->wh = pw->geom.h3_bytes ? static_cast<const char *>(pw->dev) + pw->geom.h3_offset : nullptr;
     p->wu = pw->geom.unit_bytes
                 ? reinterpret_cast<const float *>(static_cast<const char *>(pw->dev) + pw->geom.unit_offset)
                 : nullptr;
@@ -198,6 +199,7 @@ int dispatch_conv(const gspc::ConvParams &p, const gspc_packed_t *pw) {
         q.wx = nullptr;
         q.wr = nullptr;
         q.ws = nullptr;
+        q.wh = nullptr;
         q.wu = nullptr;
         const gspc::PackGeom gm = gspc::merged_geom(pw->geom, 0, p.KH, p.KW);
         if (gspc::mfma_supported(q, gm)) {
@@ -342,6 +344,12 @@ PackGeom make_pack_geom(int Cin, int Cout, int KH, int KW, int groups, int dtype
         g.unit_offset = (g.total_bytes + 255) / 256 * 256;
         g.unit_bytes = KH == 3 ? g.mfma_bytes : (size_t)groups * ((g.CPG + 15) / 16) * g.mtiles * 1024;
         g.total_bytes = g.unit_offset + g.unit_bytes;
+    }
+    if (KH == 3 && KW == 3 && g.KPG >= 16 && g.CPG >= 8 &&
+        (dtype == GSPC_F32 ? (long)g.CPG * g.KPG * 9 > 16384 || g.CPG % 4 != 0 : g.bf16_bytes == 0)) {
+        g.h3_offset = (g.total_bytes + 255) / 256 * 256;
+        g.h3_bytes = (size_t)groups * ((g.CPG + 7) / 8) * 9 * ((g.KPG + 15) / 16) * (dtype == GSPC_F32 ? 768 : 256);
+        g.total_bytes = g.h3_offset + g.h3_bytes;
     }
     // (the Winograd section stays the last one)
     if (dtype == GSPC_F32 && KH == 3 && KW == 3 && g.KPG >= 12 && g.CPG % 4 == 0 && g.CPG >= 8) {

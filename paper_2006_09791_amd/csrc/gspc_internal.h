@@ -92,6 +92,11 @@ struct PackGeom {
     // [g][ceil(CPG/16)][ceil(KPG/16)][64 lanes][4], element e at channel 16*block + 4*e + lane/16
     // (unit_kernels.hip).
     size_t unit_bytes, unit_offset;
+    // Split 3x3 section (3x3, KPG >= 16, CPG >= 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
+    // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles, with more than 16384 weights per
+    // group or CPG % 4 != 0: the three parts of the exact split of a weight; GSPC_BF16 handles with CPG % 8 != 0
+    // (no 16x16x32 section): the weight.
+    size_t h3_bytes, h3_offset;
     struct MergedDirect {
         int m, groups, CPG, KPG, KPGd;
         size_t bytes, offset;
@@ -123,8 +128,6 @@ struct ConvParams {
     const void *wb;     // bf16 mfma section (nullptr if none)
     const float *wx;    // Winograd section (nullptr if none)
     const void *wr;     // bf16 row-product section (nullptr if none)
-    const void *ws;     // pointwise section (nullptr if none)
-    const float *wu;    // unit section (nullptr if none)
     float *y;           // [N][Cout][Hout][Wout]
     const float *res;   // optional residual, same shape as y
     int N, Cin, H, W, Cout, KH, KW, stride, pad, groups;
@@ -132,6 +135,9 @@ struct ConvParams {
     int CPG, KPG, Hout, Wout, KPGd;
     int relu;
     int in_bf16;
+    const void *ws;     // pointwise section (nullptr if none)
+    const void *wh;     // split 3x3 section (nullptr if none)
+    const float *wu;    // unit section (nullptr if none)
 };
 
 // Each launcher returns hipSuccess / a HIP error, or hipErrorNotSupported when
@@ -191,6 +197,16 @@ struct SplitPlan {
 // any_size: also for launches too small for it to pay (no other matrix-core kernel takes the layer).
 bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan *out);
 hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t s, const char **name);
+
+// fp32 3x3 layers on the bf16 matrix instruction through the exact three-way split (split3_kernels.hip).
+struct Split3Plan {
+    int inst, cgs;
+    int data[24];
+};
+// when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; any.
+enum { kSplit3BeforeWinograd, kSplit3Else, kSplit3Any };
+bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out);
+hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_t s, const char **name);
 
 // 16x16x4 MFMA kernel for small launches: no staging, the waves of a block split the reduction.
 struct UnitPlan {

@@ -700,7 +700,7 @@ struct PlanKeyHash {
     }
 };
 struct Plan {
-    int kind;  // 0 none, 19 (small launches, no staging), 18 (pointwise, bf16 instruction), 32 (bf16), 33 (bf16 row products), 64 (Winograd), 17 (resident filters), 16, 4
+    int kind;  // 0 none, 20 (3x3, split), 19 (small launches, no staging), 18 (pointwise, bf16 instruction), 32 (bf16), 33 (bf16 row products), 64 (Winograd), 17 (resident filters), 16, 4
     int idx;
     Tile16 t16;
     Mfma4Plan p4;
@@ -710,12 +710,13 @@ struct Plan {
     WinoPlan px;
     SplitPlan ps;
     UnitPlan pu;
+    Split3Plan ph;
 };
 
 const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
     thread_local std::unordered_map<PlanKey, Plan, PlanKeyHash> cache;
     PlanKey k{{p.N, p.Cin, p.H, p.W, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16,
-               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr) + 8 * (p.wu != nullptr), winograd_mode()}};
+               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr) + 8 * (p.wu != nullptr) + 16 * (p.wh != nullptr), winograd_mode()}};
     auto it = cache.find(k);
     if (it != cache.end()) return it->second;
     Plan pl{};
@@ -724,10 +725,14 @@ const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
     if ((fam == '\0' || (fam == 'm' && tuned_config(p, 'm') == kNumCfg16)) && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
+    else if (fam == '\0' && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
+    else if (fam == '\0' && winograd_mode() < 0 && !plan_unit(p, g, &pl.pu) && plan_split3(p, g, kSplit3BeforeWinograd, &pl.ph))
+        pl.kind = 20;
     else if ((winograd_mode() != 0 || fam == 'x') && (fam == 'x' || fam == '\0') &&
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
         pl.kind = 64;
     else if (fam == '\0' && plan_unit(p, g, &pl.pu)) pl.kind = 19;
+    else if (fam == '\0' && winograd_mode() != 0 && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
     // few filters per group: the 4x4x1 kernel where it has an instance, else padded 16-filter tiles
@@ -754,6 +759,7 @@ hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, hipStream_t s, co
         return p.in_bf16 ? launch16_cfg<uint16_t>(pl.idx, p, pl.t16, s) : launch16_cfg<float>(pl.idx, p, pl.t16, s);
     }
     if (pl.kind == 19) return launch_unit(p, pl.pu, s, name);
+    if (pl.kind == 20) return launch_split3(p, pl.ph, s, name);
     if (pl.kind == 18) return launch_split(p, pl.ps, s, name);
     if (pl.kind == 32) return launch_mfma_bf16(p, g, pl.pb, s, name);
     if (pl.kind == 33) return launch_row_bf16(p, pl.pr, s, name);

@@ -227,8 +227,31 @@ __device__ __forceinline__ void pack_unit(size_t d, const float *__restrict__ w,
     out[d] = v;
 }
 
+// Split 3x3 section, one thread per weight: its parts, 128 elements apart.
+__device__ __forceinline__ void pack_split3(size_t d, const float *__restrict__ w, uint16_t *__restrict__ out,
+                                            const PackArgs &a, int parts) {
+    const int e = (int)(d % 8);
+    size_t r = d / 8;
+    const int li = (int)(r % 16);
+    r /= 16;
+    const size_t block = r;
+    const int mtiles = (a.KPG + 15) / 16, ncg = (a.CPG + 7) / 8;
+    const int mt = (int)(r % mtiles);
+    r /= mtiles;
+    const int tap = (int)(r % 9);
+    r /= 9;
+    const int cg = (int)(r % ncg);
+    const int j = (int)(r / ncg);
+    const int f = mt * 16 + li, c = cg * 8 + e;
+    float v = 0.f;
+    if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + (size_t)c * 9 + tap];
+    unsigned s[3];
+    split3(v, 0.f, s);
+    for (int q = 0; q < parts; ++q) out[(block * parts + q) * 128 + li * 8 + e] = (uint16_t)s[q];
+}
+
 // One launch reorders a layer into all of its sections: blocks jobs[i].first .. write section i.
-enum PackKind { kPackDirect, kPackMfma, kPackWino, kPackMerged, kPackQuadk, kPackBf16, kPackRow, kPackSplit, kPackUnit };
+enum PackKind { kPackDirect, kPackMfma, kPackWino, kPackMerged, kPackQuadk, kPackBf16, kPackRow, kPackSplit, kPackUnit, kPackSplit3 };
 struct PackJob {
     int kind;
     unsigned first;      // first block of 256 elements
@@ -237,7 +260,7 @@ struct PackJob {
     size_t section;      // kPackDirect: elements of the section itself, zeros behind it
     int i[4];
 };
-constexpr int kMaxJobs = 10;
+constexpr int kMaxJobs = 11;
 struct PackJobs {
     int n;
     PackJob job[kMaxJobs];
@@ -261,6 +284,7 @@ __global__ void pack_kernel(const float *__restrict__ w, PackArgs a, PackJobs jo
     case kPackRow: pack_row(d, w, b, a, jb.i[0]); break;
     case kPackSplit: pack_split(d, w, b, a, jb.i[0], jb.i[1], jb.i[2]); break;
     case kPackUnit: pack_unit(d, w, f, a); break;
+    case kPackSplit3: pack_split3(d, w, b, a, jb.i[0]); break;
     }
 }
 
@@ -322,6 +346,7 @@ hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t
     add(kPackWino, g.wino_offset, g.wino_bytes / sizeof(float));
     add(kPackQuadk, g.qk_offset, g.qk_bytes / sizeof(float), g.qk_m);
     add(kPackUnit, g.unit_offset, g.unit_bytes / sizeof(float));
+    add(kPackSplit3, g.h3_offset, g.h3_bytes / (a.to_bf16 ? 2 : 6), a.to_bf16 ? 1 : 3);
     add(kPackSplit, g.split_offset, g.split_bytes / (g.split_parts ? 2 * g.split_parts : 4), g.split_chunks, g.split_mtiles,
         g.split_parts);
     for (const PackGeom::MergedDirect &md : g.md)

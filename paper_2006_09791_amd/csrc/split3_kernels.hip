@@ -1,0 +1,523 @@
+// 3x3 layers with padding 1 on v_mfma_f32_16x16x32_bf16, fp32 layers through the exact three-way split
+// (split_common.h), bf16 layers as they are: implicit GEMM per group over a staged input tile.
+//
+// Output pixels of all images are numbered flat; a block owns 16*NI*WP consecutive ones and 16*MI*WM
+// filters of a group.  Rows are numbered over the padded images too, P = n * (H + 2) + ih + 1: the rows a
+// tile needs are then one contiguous range of P (rows -1 and H of an image are zeros), whatever the plane
+// and wherever images meet, and no pixel of a tile is padding.  Per chunk of 8*CGS channels the block
+// stages that range once, split and channel-innermost - [part][8 channels][row][column] units of 16 bytes -
+// and multiplies it nine taps long; the filters are split at packing time and go from memory (L2) straight
+// into the registers of the wave that multiplies them.
+//
+// A unit of the reduction is 8 channels at one tap; a k-step is four units: with CGS = 4 one tap, the lane
+// group lane/16 picks the channels; with CGS = 2 (tiles too large for four, or fewer channels) two taps.
+//
+// Small launches: WK groups of waves split the chunks, each with a tile of its own, and the partial sums
+// meet in LDS.
+//
+// What bounds it: a wave tile of 32 filters x 64 pixels takes 768 matrix clocks per k-step, 12 KB of operands
+// from LDS (64 of 128 bytes per clock with all four SIMDs busy) and six 1 KB filter loads (half of what the
+// vector memory path issues).
+#include <cstring>
+
+#include "split_common.h"
+
+namespace gspc {
+
+struct TileH {
+    int nchunks, ncg, mtiles;     // chunks of 8*CGS channels, blocks of 8 channels, 16-filter tiles per group
+    int oc_blocks, px_blocks;
+    int LW, PW, ROWS, PLANE;      // row pitch in units, column pairs per row, rows allocated, units per 8 channels
+    unsigned npix, HWo;
+    unsigned m_HWo, m_Wout, m_PW, m_H2;
+    unsigned x_bytes, w_bytes, y_bytes;
+};
+static_assert(sizeof(TileH) <= sizeof(((Split3Plan *)0)->data), "plan storage too small");
+
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool VO>
+__global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p, TileH t) {
+    constexpr int NP = sizeof(TIN) == 4 ? 3 : 1, ES = (int)sizeof(TIN);
+    constexpr int NT = 64 * WM * WP, PB = 16 * NI * WP, KS = CGS == 4 ? 9 : 5;
+    constexpr int TS = 4;                         // staging tasks (32 column pairs x 8 channels) per wave in flight
+    extern __shared__ f32x4 smem4[];
+
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave_all / (WM * WP), wave = wave_all % (WM * WP);
+    const int wm = wave / WP, wp = wave % WP;
+    const unsigned part_bytes = CGS * t.PLANE * 16, tile_bytes = NP * part_bytes;
+    char *tile = reinterpret_cast<char *>(smem4) + wk * tile_bytes;
+
+    // the blocks of one XCD (block % 8) take consecutive (pixel tile, filter block) pairs
+    const unsigned per = gridDim.x >> 3;
+    const unsigned id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (id >= (unsigned)(t.px_blocks * t.oc_blocks)) return;
+    const unsigned pt = id / (unsigned)t.oc_blocks, ob = id - pt * t.oc_blocks;
+    const unsigned j = blockIdx.y;
+    const unsigned q0 = pt * PB;
+    const unsigned n0 = q0 / t.HWo, r0 = q0 - n0 * t.HWo;
+    const unsigned H2 = p.H + 2, HW = p.H * p.W;
+    const unsigned P0 = fast_div(r0, t.m_Wout) * S;              // first padded row, relative to image n0
+    // pixel q0 + d: its image relative to n0, row and column
+    auto pixel = [&](unsigned d, unsigned &img, unsigned &oh, unsigned &ow) {
+        const unsigned r = r0 + d;
+        img = fast_div(r, t.m_HWo);
+        const unsigned rem = r - img * t.HWo;
+        oh = fast_div(rem, t.m_Wout);
+        ow = rem - oh * p.Wout;
+    };
+    const unsigned dlast = min((unsigned)PB, t.npix - q0) - 1;
+    unsigned li_img, li_oh, li_ow;
+    pixel(dlast, li_img, li_oh, li_ow);
+    const unsigned rows = li_img * H2 + li_oh * S + 3 - P0;      // <= ROWS
+
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wh, t.w_bytes);
+
+    // ---- filters: [g][8 channels][tap][filter tile][part][16 filters][8] -------------------------------
+    const unsigned wtap = t.mtiles * (NP * 256u);
+    const unsigned wlane = (CGS == 4 ? lg * 9 * wtap : (lg & 1) * 9 * wtap + (lg >> 1) * wtap) + li * 16;
+    const unsigned mt0 = ob * (MI * WM) + wm * MI;
+    u32x4 wv[3][MI][NP];                          // filters of k-step ks in set ks % 3, requested two k-steps ahead
+    auto fetch_w = [&](int ch, int ks, u32x4 (&v)[MI][NP]) __attribute__((always_inline)) {
+        const unsigned so = ((j * t.ncg + ch * CGS) * 9 + (CGS == 4 ? ks : 2 * ks)) * wtap + mt0 * (NP * 256u);
+        const bool live = ch * CGS + (CGS == 4 ? lg : lg & 1) < t.ncg && (CGS == 4 || ks < 4 || lg < 2);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                v[mi][q] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rw, live && (int)mt0 + mi < t.mtiles ? wlane : kOob, so + mi * (NP * 256u) + q * 256u, 0);
+    };
+
+    // ---- staging: a wave's task is 32 column pairs of one 8-channel block; lower lanes load channels 0-3,
+    // upper lanes 4-7 of both pixels, then exchange, so that a lane writes all eight channels of one pixel
+    const unsigned pairs = rows * t.PW, pgroups = (pairs + 31) >> 5, tasks = pgroups * CGS;
+    u32x2 xv[TS][4];
+    auto fetch_x = [&](int ch, unsigned task, u32x2 (&v)[4]) __attribute__((always_inline)) {
+        const unsigned cg = task & (CGS - 1), pair = (task / CGS) * 32 + (lane & 31);   // (CGS is a power of two)
+        const unsigned row = fast_div(pair, t.m_PW), col = 2 * (pair - row * t.PW);
+        const unsigned P = P0 + row, img = fast_div(P, t.m_H2);
+        const int ih = (int)(P - img * H2) - 1;
+        const int c0 = (ch * CGS + (int)cg) * 8 + (lane >> 5) * 4;
+        const bool ok = task < tasks && pair < pairs && (unsigned)ih < (unsigned)p.H && n0 + img < (unsigned)p.N;
+        const unsigned at = (((n0 + img) * p.Cin + j * p.CPG + c0) * HW + ih * p.W + col) * (unsigned)ES;
+        const bool pair_ok = (p.W & 1) == 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned vo = ok && c0 + e < p.CPG ? at + e * HW * ES : kOob;
+            const unsigned v1 = vo != kOob && col + 1 < (unsigned)p.W ? vo + ES : kOob;
+            if (ES == 4) {
+                if (pair_ok) {
+                    v[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rx, vo, 0, 0));
+                } else {
+                    v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, 0, 0);
+                    v[e].y = __builtin_amdgcn_raw_buffer_load_b32(rx, v1, 0, 0);
+                }
+            } else if (pair_ok) {       // both pixels in x
+                v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, 0, 0);
+            } else {
+                v[e].x = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, vo, 0, 0);
+                v[e].y = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, v1, 0, 0);
+            }
+        }
+    };
+    auto put_x = [&](unsigned task, const u32x2 (&v)[4]) __attribute__((always_inline)) {
+        const unsigned cg = task & (CGS - 1), pair = (task / CGS) * 32 + (lane & 31);
+        const unsigned row = fast_div(pair, t.m_PW), col = 2 * (pair - row * t.PW) + (lane >> 5);
+        unsigned s[2][2][NP];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                if constexpr (NP == 3) {
+                    split3(__uint_as_float(v[2 * c][i]), __uint_as_float(v[2 * c + 1][i]), s[i][c]);
+                } else {
+                    const bool both = (p.W & 1) == 0;
+                    const unsigned a0 = i && !both ? v[2 * c].y : v[2 * c].x, a1 = i && !both ? v[2 * c + 1].y : v[2 * c + 1].x;
+                    s[i][c][0] = __builtin_amdgcn_perm(a1, a0, i && both ? 0x07060302u : 0x05040100u);
+                }
+            }
+        const bool in = task < tasks && pair < pairs && col < (unsigned)p.W;
+        char *d = tile + (cg * t.PLANE + row * t.LW + 1 + col) * 16;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            u32x4 u;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const auto r = __builtin_amdgcn_permlane32_swap(s[0][c][q], s[1][c][q], false, false);
+                u[c] = r[0];
+                u[2 + c] = r[1];
+            }
+            if (in) *reinterpret_cast<u32x4 *>(d + q * part_bytes) = u;
+        }
+    };
+
+    fetch_w(wk, 0, wv[0]);
+    fetch_w(wk, 1, wv[1]);
+#pragma unroll
+    for (int k = 0; k < TS; ++k) fetch_x(wk, wave + k * (WM * WP), xv[k]);
+
+    // columns -1 and W of every row, never written by the staging: zeros
+    for (unsigned i = tid % NT; i < (unsigned)NP * CGS * t.ROWS * 2; i += NT) {
+        const unsigned side = i & 1, r = i >> 1, row = r % t.ROWS, pl = r / t.ROWS;   // pl: (part, 8 channels)
+        *reinterpret_cast<u32x4 *>(tile + ((pl / CGS) * part_bytes) + ((pl % CGS) * t.PLANE + row * t.LW + side * (p.W + 1)) * 16) =
+            u32x4{0u, 0u, 0u, 0u};
+    }
+
+    // ---- operand addresses ---------------------------------------------------------------------------
+    // unit offset of a lane's pixel, and what its taps add to it (CGS = 2: the lane's tap of each k-step)
+    unsigned bpix[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        unsigned img, oh, ow;
+        pixel(min((unsigned)((wp * NI + ni) * 16 + li), dlast), img, oh, ow);
+        bpix[ni] = ((CGS == 4 ? lg : lg & 1) * t.PLANE + (img * H2 + oh * S - P0) * t.LW + ow * S) * 16;
+    }
+    auto tap_off = [&](int ks) -> unsigned {
+        if (CGS == 4) return ((ks / 3) * t.LW + ks % 3) * 16u;
+        const int t0 = 2 * ks, t1 = 2 * ks + 1 < 9 ? 2 * ks + 1 : 8;
+        return (lg >> 1) ? ((t1 / 3) * t.LW + t1 % 3) * 16u : ((t0 / 3) * t.LW + t0 % 3) * 16u;
+    };
+
+    f32x4 acc[MI][NI], low[NP == 3 ? MI : 1][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (NP == 3) low[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    auto mma = [](bf16x8 a, bf16x8 b, f32x4 c) __attribute__((always_inline)) {
+        // VO: pixels are the rows of the product, a lane ends up with four consecutive pixels of a filter
+        return VO ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0)
+                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    };
+
+    const int rounds = (t.nchunks + WK - 1) / WK;
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int ch = rd * WK + wk;
+        if (rd) __syncthreads();                  // the previous chunk has been read
+#pragma unroll
+        for (int k = 0; k < TS; ++k) put_x(wave + k * (WM * WP), xv[k]);
+        for (unsigned k = TS * (WM * WP); k < tasks; k += WM * WP) {   // (wide planes: more tasks than slots)
+            fetch_x(ch, wave + k, xv[0]);
+            put_x(wave + k, xv[0]);
+        }
+        __syncthreads();
+        // A k-step goes pixel tile by pixel tile: the inputs of the next one are read from LDS while the matrix
+        // unit works on this one; the next chunk's inputs are requested one task per k-step.
+        bf16x8 opb[2][NP];
+        auto load_b = [&](int ks, int ni) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                opb[(ks * NI + ni) & 1][q] = *reinterpret_cast<const bf16x8 *>(tile + q * part_bytes + bpix[ni] + tap_off(ks));
+        };
+        load_b(0, 0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks + 2 < KS) fetch_w(ch, ks + 2, wv[(ks + 2) % 3]);
+            else fetch_w(ch + WK, ks + 2 - KS, wv[(ks + 2) % 3]);
+            if (ks < TS) fetch_x(ch + WK, wave + ks * (WM * WP), xv[ks]);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                if (ni + 1 < NI) load_b(ks, ni + 1);
+                else if (ks + 1 < KS) load_b(ks + 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < (NP == 3 ? 6 : 1); ++e)
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi) {
+                        f32x4 &c = NP == 1 || e == 5 ? acc[mi][ni] : low[NP == 3 ? mi : 0][ni];
+                        c = mma(__builtin_bit_cast(bf16x8, wv[ks % 3][mi][NP == 3 ? kSplitA[e] : 0]),
+                                opb[(ks * NI + ni) & 1][NP == 3 ? kSplitB[e] : 0], c);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (KS % 3 == 2) {                        // the next chunk's first filters move to sets 0 and 1
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    wv[1][mi][q] = wv[0][mi][q];
+                    wv[0][mi][q] = wv[2][mi][q];
+                }
+        }
+    }
+
+    ResultRange range;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            if (NP == 3) acc[mi][ni] += low[mi][ni];
+    if (WK > 1) {
+        // partial sums of the other groups, [group - 1][wave][tile][lane]
+        __syncthreads();
+        f32x4 *ps = smem4;
+        if (wk > 0) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    ps[((((wk - 1) * (WM * WP) + wave) * MI + mi) * NI + ni) * 64 + lane] = acc[mi][ni];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int k = 1; k < WK; ++k)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    acc[mi][ni] += ps[((((k - 1) * (WM * WP) + wave) * MI + mi) * NI + ni) * 64 + lane];
+    }
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (NP == 3) range.see(acc[mi][ni][r]);
+
+    // ---- epilogue: residual, ReLU, NCHW stores ---------------------------------------------------------
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
+    const unsigned ystep = t.HWo * 4, ybase = (n0 * p.Cout + j * p.KPG) * ystep;
+    unsigned poff[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        const unsigned d = (wp * NI + ni) * 16 + (VO ? 4 * lg : li);
+        const unsigned r = r0 + d, img = fast_div(r, t.m_HWo);
+        poff[ni] = q0 + d < t.npix ? ybase + (img * (p.Cout - 1) * t.HWo + r) * 4 : kOob;
+    }
+    const unsigned f0 = mt0 * 16 + (VO ? li : 4 * lg);           // a lane's first filter
+    auto out_off = [&](int mi, int ni, int r) -> unsigned {
+        const unsigned f = f0 + mi * 16 + r;
+        return f < (unsigned)p.KPG && poff[ni] != kOob ? poff[ni] + f * ystep : kOob;
+    };
+    if (p.res) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                if (VO) {
+                    acc[mi][ni] += __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, out_off(mi, ni, 0), 0, 0));
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[mi][ni][r] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, out_off(mi, ni, r), 0, 0));
+                }
+            }
+    }
+    if (p.relu) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[mi][ni][r] = fmaxf(acc[mi][ni][r], 0.f);
+    }
+    // (all results first, then the stores: a store's data registers are not written again)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            if (VO) {
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[mi][ni]), ry, out_off(mi, ni, 0), 0, 0);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mi][ni][r]), ry, out_off(mi, ni, r), 0, 0);
+            }
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    if (NP == 3 && __ballot(range.outside())) {
+        // plain fp32 sums of this wave's outputs
+        wait_vmem0();   // the stores above come first
+        const float *wd = p.wd + (size_t)j * p.CPG * 9 * p.KPGd;
+        const float *x = static_cast<const float *>(p.x);
+#pragma unroll 1
+        for (int o = 0; o < MI * NI * 4; ++o) {
+            const int mi = o / (NI * 4), ni = o / 4 % NI, r = o % 4;
+            const unsigned d = (wp * NI + ni) * 16 + (VO ? 4 * lg + r : li);
+            const unsigned f = f0 + mi * 16 + (VO ? 0 : r);
+            if (q0 + d >= t.npix || f >= (unsigned)p.KPG) continue;
+            unsigned img, oh, ow;
+            pixel(d, img, oh, ow);
+            const float *xp = x + (size_t)((n0 + img) * p.Cin + j * p.CPG) * HW;
+            float s = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < p.CPG * 9; ++k) {
+                const int ih = (int)oh * S - 1 + k % 9 / 3, iw = (int)ow * S - 1 + k % 3;
+                if ((unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
+                    s = fmaf(xp[(size_t)(k / 9) * HW + ih * p.W + iw], wd[(size_t)k * p.KPGd + f], s);
+            }
+            const size_t yo = (size_t)((n0 + img) * p.Cout + j * p.KPG + f) * t.HWo + oh * p.Wout + ow;
+            if (p.res) s += p.res[yo];
+            p.y[yo] = p.relu ? fmaxf(s, 0.f) : s;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side.
+// ---------------------------------------------------------------------------
+namespace {
+
+struct CfgH {
+    int MI, NI, WM, WP, WK;
+    float kstep;      // microseconds per k-step of a block alone on its compute unit
+};
+const CfgH kCfgH[] = {{2, 4, 2, 2, 1, 0.75f}, {2, 4, 2, 1, 2, 0.75f}, {2, 2, 2, 2, 1, 0.5f}, {2, 2, 1, 1, 4, 0.5f}, {2, 4, 1, 1, 4, 0.75f}};
+constexpr int kNumCfgH = sizeof(kCfgH) / sizeof(kCfgH[0]);
+constexpr int kLdsBlockH = 78 * 1024;   // two blocks per compute unit
+
+size_t lds_bytes_h(const CfgH &c, int cgs, int parts, const TileH &t) {
+    const size_t tiles = (size_t)c.WK * parts * cgs * t.PLANE * 16;
+    const size_t sums = (size_t)(c.WK - 1) * c.WM * c.WP * c.MI * c.NI * 1024;
+    return tiles > sums ? tiles : sums;
+}
+
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool VO>
+hipError_t launchH(const ConvParams &p, const TileH &t, hipStream_t s) {
+    const size_t lds = lds_bytes_h(CfgH{MI, NI, WM, WP, WK, 0.f}, CGS, sizeof(TIN) == 4 ? 3 : 1, t);
+    auto kern = conv_split3<MI, NI, WM, WP, WK, CGS, S, TIN, VO>;
+    if (lds > 64 * 1024) {
+        static thread_local bool raised = false;   // per instantiation and thread
+        if (!raised) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBlockH);
+            if (e != hipSuccess) return e;
+            raised = true;
+        }
+    }
+    const unsigned blocks = (unsigned)round_up(t.px_blocks * t.oc_blocks, 8);
+    hipLaunchKernelGGL(kern, dim3(blocks, p.groups), dim3(64 * WM * WP * WK), lds, s, p, t);
+    return hipGetLastError();
+}
+
+template <int MI, int NI, int WM, int WP, int WK, int CGS, typename TIN>
+hipError_t launchH_s(const ConvParams &p, const TileH &t, bool vo, hipStream_t s) {
+    if (p.stride == 1)
+        return vo ? launchH<MI, NI, WM, WP, WK, CGS, 1, TIN, true>(p, t, s) : launchH<MI, NI, WM, WP, WK, CGS, 1, TIN, false>(p, t, s);
+    return vo ? launchH<MI, NI, WM, WP, WK, CGS, 2, TIN, true>(p, t, s) : launchH<MI, NI, WM, WP, WK, CGS, 2, TIN, false>(p, t, s);
+}
+
+template <int MI, int NI, int WM, int WP, int WK>
+hipError_t launchH_cgs(const ConvParams &p, const TileH &t, int cgs, bool vo, hipStream_t s) {
+    if (p.in_bf16)
+        return cgs == 4 ? launchH_s<MI, NI, WM, WP, WK, 4, uint16_t>(p, t, vo, s) : launchH_s<MI, NI, WM, WP, WK, 2, uint16_t>(p, t, vo, s);
+    return cgs == 4 ? launchH_s<MI, NI, WM, WP, WK, 4, float>(p, t, vo, s) : launchH_s<MI, NI, WM, WP, WK, 2, float>(p, t, vo, s);
+}
+
+bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, TileH *out) {
+    const int PB = 16 * c.NI * c.WP, MT = c.MI * c.WM;
+    const double npix = (double)p.N * p.Hout * p.Wout;
+    const double xb = (double)p.N * p.Cin * p.H * p.W * (p.in_bf16 ? 2 : 4), yb = (double)p.N * p.Cout * p.Hout * p.Wout * 4;
+    if (xb >= (double)kOob || yb >= (double)kOob || (double)g.h3_bytes >= (double)kOob || p.groups > 65535) return false;
+    TileH t{};
+    t.ncg = (g.CPG + 7) / 8;
+    t.nchunks = (t.ncg + cgs - 1) / cgs;
+    t.mtiles = (g.KPG + 15) / 16;
+    t.oc_blocks = (t.mtiles + MT - 1) / MT;
+    const long pxb = (long)((npix + PB - 1) / PB);
+    if (pxb * t.oc_blocks > 0x7ffffff0L) return false;
+    t.px_blocks = (int)pxb;
+    t.HWo = p.Hout * p.Wout;
+    t.npix = (unsigned)npix;
+    // rows of a tile: those its pixels span, three taps, and at every change of image the rows between the last
+    // window of one and the first of the next
+    const int span = (PB - 2) / p.Wout + 2, cross = p.N > 1 ? (PB - 2) / (int)t.HWo + 1 : 0;
+    const int out_rows = span, extra = p.H + 2 - p.Hout * p.stride;
+    const int crossings = cross < out_rows - 1 ? cross : out_rows - 1;
+    t.ROWS = (out_rows - 1) * p.stride + 3 + crossings * (extra > 0 ? extra : 0);
+    t.LW = p.W + 2;
+    t.PW = (p.W + 1) / 2;
+    t.PLANE = t.ROWS * t.LW;
+    t.m_HWo = div_magic(t.HWo);
+    t.m_Wout = div_magic(p.Wout);
+    t.m_PW = div_magic(t.PW);
+    t.m_H2 = div_magic(p.H + 2);
+    t.x_bytes = (unsigned)xb;
+    t.y_bytes = (unsigned)yb;
+    t.w_bytes = (unsigned)g.h3_bytes;
+    // exact reciprocals: offsets inside a tile stay below 2^32 / divisor
+    if ((double)(t.HWo + PB) * t.HWo >= 4.0e9 || (double)(t.ROWS + p.H + 2) * (p.H + 2) >= 4.0e9 ||
+        (double)(t.ROWS * t.PW + 64) * t.PW >= 4.0e9)
+        return false;
+    if (lds_bytes_h(c, cgs, p.in_bf16 ? 1 : 3, t) > (size_t)kLdsBlockH) return false;
+    *out = t;
+    return true;
+}
+
+}  // namespace
+
+// Block shape: the one with the shortest estimated launch.  A block alone on its compute unit needs `kstep` per k-step
+// (1.3 times that for the half-size chunks), 1 us per chunk and 1.5 us besides; two share the unit at 1.45 times that,
+// more follow in pairs (N = 64, us, estimate / measured: 256 -> 256 on 14x14 g = 2 47 / 42, 512 -> 512 on 7x7 g = 2
+// 47 / 44, 128 -> 128 on 8x8 10.2 / 10.3, and 13 / 13.7 for the next best shape).
+//
+// Which layers (N = 64 unless stated, us, before / with this kernel):
+//  - rows that are not a multiple of 4 or channels per group that are not: the fp32 kernels stage those 4 bytes at a
+//    time, or in one chunk: 256 -> 256 on 14x14 g = 2 68 / 42, g = 4 38 / 25, 512 -> 512 on 7x7 g = 2 89 / 44,
+//    192 -> 192 on 13x17 g = 2 104 / 35, 50 -> 75 on 31x23 at N = 100 423 / 58, 110 -> 100 on 40x40 stride 2 at N = 20
+//    281 / 25.  Not where Winograd takes the layer and more than a third of the filters would be padding (144 -> 144
+//    on 14x14, g = 2: 33.7 / 35.9);
+//  - stride 2 from two blocks per compute unit on: 128 -> 256 on 28x28 g = 2 50 / 37, 256 -> 512 on 14x14 g = 2 59 / 33,
+//    64 -> 128 on 56x56 83 / 68; with one block the fp32 kernels are level (64 -> 128 on 16x16: 11.7 / 13.7);
+//  - other stride-1 layers: with at least 128 channels per group where neither Winograd (64 -> 64 on 16x16 at N = 256
+//    25.5 / 27, 128 -> 128 on 28x28 g = 2 47 / 46) nor a launch of more blocks than the chip holds covers the fp32
+//    kernel's waits: 128 -> 128 on 8x8 13.4 / 10.3 (64 channels per group: 8.6 / 10.2).
+// With Winograd switched off (gspc_set_winograd(0)) every layer stays on the fp32 kernels, bit for bit.
+bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out) {
+    if (!p.wh || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2)) return false;
+    const bool odd = p.W % 4 != 0 || g.CPG % 4 != 0;
+    const int ft = (g.KPG + 63) / 64 * 64;
+    if (when == kSplit3BeforeWinograd && (!odd || p.stride != 1 || 3 * ft > 4 * g.KPG)) return false;
+    if (when == kSplit3Else && !odd && p.stride == 1 && g.CPG < 128) return false;
+    double best = 0.0;
+    for (int i = 0; i < kNumCfgH; ++i) {
+        const CfgH &c = kCfgH[i];
+        for (int cgs : {4, 2}) {
+            TileH t;
+            if (cgs == 4 && (g.CPG + 15) / 16 * 16 < (g.CPG + 31) / 32 * 32 - 8) continue;
+            if (!planH_cfg(p, g, c, cgs, &t)) continue;
+            const long blocks = (long)t.px_blocks * t.oc_blocks * p.groups, n = (blocks + kNumCU - 1) / kNumCU;
+            if (blocks < kNumCU / 4 || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
+                (when == kSplit3Else && !odd && p.stride == 1 && n > 2))
+                continue;
+            const double rounds = (t.nchunks + c.WK - 1) / c.WK, ks = rounds * (cgs == 4 ? 9 : 5 * 1.3);
+            const double one = ks * c.kstep * (p.stride == 2 && c.NI == 4 ? 1.4 : 1.0) + rounds + 1.5;
+            const double est = one * (1.45 * (double)(n / 2) + (double)(n % 2));
+            if (best != 0.0 && est >= best) continue;
+            best = est;
+            out->inst = i;
+            out->cgs = cgs;
+            std::memcpy(out->data, &t, sizeof(t));
+        }
+    }
+    return best != 0.0;
+}
+
+hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_t s, const char **name) {
+    TileH t;
+    std::memcpy(&t, plan.data, sizeof(t));
+    const CfgH &c = kCfgH[plan.inst];
+    const bool vo = t.HWo % 4 == 0;
+    *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
+                        "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +
+                        std::to_string(p.stride) + (p.in_bf16 ? ",bf16" : ",f32") + (vo ? ",true>" : ",false>"));
+    switch (plan.inst) {
+    case 0: return launchH_cgs<2, 4, 2, 2, 1>(p, t, plan.cgs, vo, s);
+    case 1: return launchH_cgs<2, 4, 2, 1, 2>(p, t, plan.cgs, vo, s);
+    case 2: return launchH_cgs<2, 2, 2, 2, 1>(p, t, plan.cgs, vo, s);
+    case 3: return launchH_cgs<2, 2, 1, 1, 4>(p, t, plan.cgs, vo, s);
+    case 4: return launchH_cgs<2, 4, 1, 1, 4>(p, t, plan.cgs, vo, s);
+    }
+    return hipErrorNotSupported;
+}
+
+}  // namespace gspc

@@ -46,4 +46,7 @@ struct ResultRange {
     __device__ __forceinline__ bool outside() const { return most >= 0x7f800000u || least < (127u - 90u) << 23; }
 };
 
+// All of the wave's vector-memory operations are done (the compiler does not wait for loads that go into LDS).
+__device__ __forceinline__ void wait_vmem0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 }  // namespace gspc

@@ -41,9 +41,6 @@ template <typename TIN> struct SplitTraits;
 template <> struct SplitTraits<float> { static constexpr int parts = 3; };
 template <> struct SplitTraits<uint16_t> { static constexpr int parts = 1; };
 
-// All of the wave's vector-memory operations are done (the compiler does not wait for loads that go into LDS).
-__device__ __forceinline__ void wait_vmem0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
 template <int MI, int NI, int WM, int WP, int KH, int KW, int S, typename TIN, bool VO, bool PRE>
 __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvParams p, TileSplit t) {
     static_assert(KH == 1 && KW == 1 && S == 1, "pointwise layers");

@@ -179,11 +179,12 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     // 60 -> 84 on 29x37, g = 3, N = 5 9.1 / 6.9.  Operands are loaded once per tile that uses them, so the loads decide:
     //  - 3x3, stride 1, rows of a multiple of 4 (16-byte staging on the other side): 75k loads 8.3 / 6.5 and 9.4 / 6.6,
     //    150k 9.1 / 10.0 and 13.1 / 10.0, 300k 13.4 / 16.6;
-    //  - stride 2, other widths, 1x1: 150k 12.7 / 10.2 and 18.2 / 9.9, 300k 16.7 / 18.0 and 20.0 / 22.2.
+    //  - stride 2, other widths, 1x1: 150k 12.7 / 10.2 and 18.2 / 9.9, 200k (32 -> 64 on 32x32 at stride 2) 10.2 / 11.4,
+    //    300k 16.7 / 18.0 and 20.0 / 22.2.
     // With fewer than six units a block is mostly its start and its sum: 3 -> 32 on 32x32, N = 8 4.9 / 4.7, N = 32 5.2 / 6.8.
     const long tiles = (long)((t.npix + 15) / 16) * g.mtiles * p.groups;
     const double loads = (double)tiles * t.units * (row ? 2 : 5);
-    if (loads > (row && p.stride == 1 && p.W % 4 == 0 ? 80e3 : 200e3)) return false;
+    if (loads > (row && p.W % 4 == 0 ? p.stride == 1 ? 80e3 : 160e3 : 200e3)) return false;
     if (row && t.units < 6 && tiles > 4 * kNumCU) return false;
     // waves per block: what lets every wave request all of its units at once, more while the launch is small
     int nw = 2;
