@@ -202,24 +202,24 @@ int dispatch_conv(const gspc::ConvParams &p, const gspc_packed_t *pw) {
         q.wh = nullptr;
         q.wu = nullptr;
         const gspc::PackGeom gm = gspc::merged_geom(pw->geom, 0, p.KH, p.KW);
-        if (gspc::mfma_supported(q, gm)) {
-            const char *name = "";
-            const hipError_t e = gspc::launch_mfma(q, gm, t_stream, &name);
+        if (const gspc::MfmaPlan *plan = gspc::mfma_plan(q, gm)) {
+            const hipError_t e = gspc::launch_mfma(q, gm, plan, t_stream);
             if (e != hipSuccess) return hip_fail(e, "convolution launch");
             t_last_path = GSPC_PATH_MFMA;
-            t_last_kernel = name;
+            t_last_kernel = gspc::mfma_plan_name(plan);
             return GSPC_OK;
         }
     }
-    const bool can_mfma = gspc::mfma_supported(p, pw->geom);
+    const gspc::MfmaPlan *plan = t_force_path == GSPC_PATH_DIRECT ? nullptr : gspc::mfma_plan(p, pw->geom);
     int path = t_force_path;
-    if (path == GSPC_PATH_AUTO) path = can_mfma ? GSPC_PATH_MFMA : GSPC_PATH_DIRECT;
-    if (path == GSPC_PATH_MFMA && !can_mfma)
+    if (path == GSPC_PATH_AUTO) path = plan ? GSPC_PATH_MFMA : GSPC_PATH_DIRECT;
+    if (path == GSPC_PATH_MFMA && !plan)
         return fail(GSPC_ERR_ARG, "matrix-core path forced but not available for this layer");
     const char *name = "";
-    hipError_t e = path == GSPC_PATH_MFMA ? gspc::launch_mfma(p, pw->geom, t_stream, &name)
-                                          : gspc::launch_direct(p, t_stream, &name);
+    const hipError_t e = path == GSPC_PATH_MFMA ? gspc::launch_mfma(p, pw->geom, plan, t_stream)
+                                                : gspc::launch_direct(p, t_stream, &name);
     if (e != hipSuccess) return hip_fail(e, "convolution launch");
+    if (path == GSPC_PATH_MFMA) name = gspc::mfma_plan_name(plan);
     t_last_path = path;
     t_last_kernel = name;
     return GSPC_OK;

@@ -144,9 +144,12 @@ struct ConvParams {
 // the kernel family has no instance for this layer.  *name receives a static
 // string naming the kernel that ran.
 hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name);
-hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, hipStream_t s,
-                       const char **name);
-bool mfma_supported(const ConvParams &p, const PackGeom &g);
+// Matrix-core kernels: the calling thread's remembered choice for a layer (nullptr: no kernel takes it; valid for the
+// life of the thread), its launch, and the kernel's name after the first launch.
+struct MfmaPlan;
+const MfmaPlan *mfma_plan(const ConvParams &p, const PackGeom &g);
+hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, const MfmaPlan *plan, hipStream_t s);
+const char *mfma_plan_name(const MfmaPlan *plan);
 
 // Offline tile table (GSPC_TUNE_FILE, see tune_table.cpp): family letter forced for this layer
 // ('\0' = none) and the configuration index forced within a family (-1 = none).

@@ -385,7 +385,7 @@ bool plan_mfma4(const ConvParams &p, const PackGeom &g, Mfma4Plan *out) {
 hipError_t launch_mfma4(const ConvParams &p, const Mfma4Plan &plan, hipStream_t s, const char **name) {
     Tile4 t;
     std::memcpy(&t, plan.data, sizeof(t));
-    *name = intern_name("conv_mfma4r<" + std::to_string(p.CPG) + "," + std::to_string(p.KPG / 4) + "," +
+    if (!*name) *name = intern_name("conv_mfma4r<" + std::to_string(p.CPG) + "," + std::to_string(p.KPG / 4) + "," +
                         std::to_string(plan.inst) + "," + std::to_string(p.stride) +
                         (p.in_bf16 ? ",bf16>" : ",f32>"));
     const int MT = p.KPG / 4;

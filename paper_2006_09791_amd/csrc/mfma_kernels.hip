@@ -699,7 +699,10 @@ struct PlanKeyHash {
         return (size_t)h;
     }
 };
-struct Plan {
+}  // namespace
+
+struct MfmaPlan {
+    mutable const char *name = nullptr;   // kernel name, filled in by the first launch
     int kind;  // 0 none, 20 (3x3, split), 19 (small launches, no staging), 18 (pointwise, bf16 instruction), 32 (bf16), 33 (bf16 row products), 64 (Winograd), 17 (resident filters), 16, 4
     int idx;
     Tile16 t16;
@@ -713,13 +716,15 @@ struct Plan {
     Split3Plan ph;
 };
 
-const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
-    thread_local std::unordered_map<PlanKey, Plan, PlanKeyHash> cache;
+namespace {
+
+const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
+    thread_local std::unordered_map<PlanKey, MfmaPlan, PlanKeyHash> cache;
     PlanKey k{{p.N, p.Cin, p.H, p.W, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16,
                g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr) + 8 * (p.wu != nullptr) + 16 * (p.wh != nullptr), winograd_mode()}};
     auto it = cache.find(k);
     if (it != cache.end()) return it->second;
-    Plan pl{};
+    MfmaPlan pl{};
     const char fam = tuned_family(p);   // offline tile table: may prefer the plain 16x16x4 kernel
     // (configuration 13 of family 'm' is the 128-filter block of the pointwise kernel)
     if ((fam == '\0' || (fam == 'm' && tuned_config(p, 'm') == kNumCfg16)) && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
@@ -745,13 +750,20 @@ const Plan &get_plan(const ConvParams &p, const PackGeom &g) {
 
 }  // namespace
 
-bool mfma_supported(const ConvParams &p, const PackGeom &g) { return get_plan(p, g).kind != 0; }
+const MfmaPlan *mfma_plan(const ConvParams &p, const PackGeom &g) {
+    const MfmaPlan &pl = get_plan(p, g);
+    return pl.kind ? &pl : nullptr;
+}
 
-hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, hipStream_t s, const char **name) {
-    const Plan &pl = get_plan(p, g);
+const char *mfma_plan_name(const MfmaPlan *plan) { return plan->name; }
+
+// (building and interning the name's text costs about as much host time as the launch itself: only once per plan)
+hipError_t launch_mfma(const ConvParams &p, const PackGeom &g, const MfmaPlan *plan, hipStream_t s) {
+    const MfmaPlan &pl = *plan;
+    const char **name = &pl.name;
     if (pl.kind == 16) {
         const Cfg16 &c = kCfg16[pl.idx];
-        *name = intern_name("conv_mfma16<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
+        if (!*name) *name = intern_name("conv_mfma16<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
                             std::to_string(c.WM) + "," + std::to_string(c.WP) + "," + std::to_string(p.KH) +
                             "," + std::to_string(p.KW) + "," + std::to_string(p.stride) +
                             (p.in_bf16 ? ",bf16," : ",f32,") + (pl.t16.vec_out && p.KH != 7 ? "true>" : "false>") +

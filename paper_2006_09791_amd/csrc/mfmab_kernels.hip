@@ -628,7 +628,7 @@ hipError_t launch_mfma_bf16(const ConvParams &p0, const PackGeom &g, const MfmaB
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgB &c = kCfgB[plan.inst];
     const int vw = vw_of(p.W);
-    *name = intern_name("conv_mfma16b<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
+    if (!*name) *name = intern_name("conv_mfma16b<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
                         std::to_string(c.WM) + "," + std::to_string(c.WP) + "," + std::to_string(p.stride) + "," +
                         std::to_string(g.ckb) + "," + std::to_string(vw) + (t.vec_out ? ",true>" : ",false>") +
                         (g.mb > 1 ? "/merge" + std::to_string(g.mb) : ""));

@@ -580,7 +580,7 @@ hipError_t launch_mfma16w(const ConvParams &p, const Mfma16wPlan &plan, hipStrea
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgW &c = kCfgW[plan.inst];
     const bool persist = grid_x_w(p, t, lds_bytes_w(t)) < t.tile_groups;
-    *name = intern_name("conv_mfma16w<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
+    if (!*name) *name = intern_name("conv_mfma16w<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," +
                         std::to_string(p.stride) + "," + std::to_string(plan.ckb) + "," +
                         (persist ? "true" : "false") + "," + std::to_string(t.xs) + ",f32>");
     switch (plan.inst) {

@@ -508,7 +508,7 @@ hipError_t launch_row_bf16(const ConvParams &p, const RowB16Plan &plan, hipStrea
     TileR t;
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgR &c = kCfgR[plan.inst];
-    *name = c.D == 0 ? intern_name("conv_row16q<" + std::to_string(c.CQ) + "," + std::to_string(c.FQ) + ">/" +
+    if (!*name) *name = c.D == 0 ? intern_name("conv_row16q<" + std::to_string(c.CQ) + "," + std::to_string(c.FQ) + ">/" +
                                    std::to_string(t.bands) + "b")
                      : intern_name("conv_row16b<" + std::to_string(c.CQ) + "," + std::to_string(c.FQ) + "," +
                                    std::to_string(c.D) + "," + std::to_string(c.OCC) + ">/" + std::to_string(t.bands) + "b");

@@ -426,7 +426,7 @@ hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t 
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgS &c = kCfgS[plan.inst];
     const bool vo = t.HW % 4 == 0;
-    *name = intern_name("conv_mfma16<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
+    if (!*name) *name = intern_name("conv_mfma16<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
                         "," + std::to_string(c.WP) + ",1,1,1," + (p.in_bf16 ? "bf16," : "f32,") + (vo ? "true>" : "false>") +
                         (p.in_bf16 ? "/bf16" : t.pre ? "/split3" : "/split3w"));
     switch (plan.inst) {

@@ -197,9 +197,11 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
 hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name) {
     TileUnit t;
     std::memcpy(&t, plan.data, sizeof(t));
-    const std::string k = std::to_string(p.KH);
-    *name = intern_name("conv_mfma16<1,1,1," + std::to_string(plan.nw) + "," + k + "," + k + "," + std::to_string(p.stride) +
-                        ",f32,false>/unit");
+    if (!*name) {
+        const std::string k = std::to_string(p.KH);
+        *name = intern_name("conv_mfma16<1,1,1," + std::to_string(plan.nw) + "," + k + "," + k + "," + std::to_string(p.stride) +
+                            ",f32,false>/unit");
+    }
     switch (plan.nw) {
     case 2: return launchU_shape<2>(p, t, s);
     case 4: return launchU_shape<4>(p, t, s);

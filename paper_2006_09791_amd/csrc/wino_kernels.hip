@@ -607,7 +607,7 @@ hipError_t launch_wino(const ConvParams &p, const WinoPlan &plan, hipStream_t s,
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgX &c = kCfgX[plan.inst];
     const bool rt = t.rt != 0;
-    *name = intern_name("conv_wino<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
+    if (!*name) *name = intern_name("conv_wino<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
                         "," + std::to_string(c.WP) + "," + std::to_string(plan.ckb) + "," + (rt ? "true" : "false") + ">");
     return plan.ckb == 2 ? launchx_cfg<2>(plan.inst, p, t, rt, s) : launchx_cfg<1>(plan.inst, p, t, rt, s);
 }
