@@ -34,10 +34,11 @@ struct TileH {
 };
 static_assert(sizeof(TileH) <= sizeof(((Split3Plan *)0)->data), "plan storage too small");
 
-template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool VO>
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO>
 __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p, TileH t) {
     constexpr int NP = sizeof(TIN) == 4 ? 3 : 1, ES = (int)sizeof(TIN);
     constexpr int NT = 64 * WM * WP, PB = 16 * NI * WP, KS = CGS == 4 ? 9 : 5;
+    constexpr int NA = 3;           // filter sets: k-step ks in set ks % NA, requested NA - 1 k-steps ahead
     constexpr int TS = 4;                         // staging tasks (32 column pairs x 8 channels) per wave in flight
     extern __shared__ f32x4 smem4[];
 
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
     const unsigned wtap = t.mtiles * (NP * 256u);
     const unsigned wlane = (CGS == 4 ? lg * 9 * wtap : (lg & 1) * 9 * wtap + (lg >> 1) * wtap) + li * 16;
     const unsigned mt0 = ob * (MI * WM) + wm * MI;
-    u32x4 wv[3][MI][NP];                          // filters of k-step ks in set ks % 3, requested two k-steps ahead
+    u32x4 wv[NA][MI][NP];
     auto fetch_w = [&](int ch, int ks, u32x4 (&v)[MI][NP]) __attribute__((always_inline)) {
         const unsigned so = ((j * t.ncg + ch * CGS) * 9 + (CGS == 4 ? ks : 2 * ks)) * wtap + mt0 * (NP * 256u);
         const bool live = ch * CGS + (CGS == 4 ? lg : lg & 1) < t.ncg && (CGS == 4 || ks < 4 || lg < 2);
@@ -91,40 +92,57 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
     };
 
     // ---- staging: a wave's task is 32 column pairs of one 8-channel block; lower lanes load channels 0-3,
-    // upper lanes 4-7 of both pixels, then exchange, so that a lane writes all eight channels of one pixel
+    // upper lanes 4-7 of both pixels, then exchange, so that a lane writes all eight channels of one pixel.
+    // Addresses are the same for every chunk and computed once for the tasks that have a slot.
     const unsigned pairs = rows * t.PW, pgroups = (pairs + 31) >> 5, tasks = pgroups * CGS;
-    u32x2 xv[TS][4];
-    auto fetch_x = [&](int ch, unsigned task, u32x2 (&v)[4]) __attribute__((always_inline)) {
+    struct Task {
+        unsigned at;     // byte offset of (first channel of the lane, first pixel) in chunk 0, kOob: nothing to load;
+                         // bit 0: the second pixel is outside the row
+        unsigned lds;    // byte offset in the tile of the pixel the lane writes, kOob: nothing to write
+    };
+    // first channel of a task's lanes within a chunk
+    auto task_c0 = [&](unsigned task) -> int { return (int)(task & (CGS - 1)) * 8 + (lane >> 5) * 4; };
+    auto make_task = [&](unsigned task) __attribute__((always_inline)) -> Task {
         const unsigned cg = task & (CGS - 1), pair = (task / CGS) * 32 + (lane & 31);   // (CGS is a power of two)
         const unsigned row = fast_div(pair, t.m_PW), col = 2 * (pair - row * t.PW);
         const unsigned P = P0 + row, img = fast_div(P, t.m_H2);
         const int ih = (int)(P - img * H2) - 1;
-        const int c0 = (ch * CGS + (int)cg) * 8 + (lane >> 5) * 4;
-        const bool ok = task < tasks && pair < pairs && (unsigned)ih < (unsigned)p.H && n0 + img < (unsigned)p.N;
-        const unsigned at = (((n0 + img) * p.Cin + j * p.CPG + c0) * HW + ih * p.W + col) * (unsigned)ES;
-        const bool pair_ok = (p.W & 1) == 0;
+        const bool in = task < tasks && pair < pairs;
+        Task k;
+        k.at = in && (unsigned)ih < (unsigned)p.H && n0 + img < (unsigned)p.N
+                   ? ((((n0 + img) * p.Cin + j * p.CPG + task_c0(task)) * HW + ih * p.W + col) * (unsigned)ES |
+                      (col + 1 >= (unsigned)p.W ? 1u : 0u))
+                   : kOob;
+        const unsigned wcol = col + (lane >> 5);
+        k.lds = in && wcol < (unsigned)p.W ? (cg * t.PLANE + row * t.LW + 1 + wcol) * 16 : kOob;
+        return k;
+    };
+    Task slot[TS];
+#pragma unroll
+    for (int k = 0; k < TS; ++k) slot[k] = make_task(wave + k * (WM * WP));
+    u32x2 xv[TS][4];
+    auto fetch_x = [&](int ch, unsigned task, const Task &k, u32x2 (&v)[4]) __attribute__((always_inline)) {
+        const int left = p.CPG - ch * CGS * 8;      // channels from the chunk's first one on
+        const unsigned so = (unsigned)(ch * CGS * 8) * HW * ES;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const unsigned vo = ok && c0 + e < p.CPG ? at + e * HW * ES : kOob;
-            const unsigned v1 = vo != kOob && col + 1 < (unsigned)p.W ? vo + ES : kOob;
-            if (ES == 4) {
-                if (pair_ok) {
-                    v[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rx, vo, 0, 0));
-                } else {
-                    v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, 0, 0);
-                    v[e].y = __builtin_amdgcn_raw_buffer_load_b32(rx, v1, 0, 0);
-                }
-            } else if (pair_ok) {       // both pixels in x
-                v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, 0, 0);
+            const unsigned vo = task_c0(task) + e < left ? k.at & ~1u : kOob, se = so + e * HW * ES;
+            if constexpr (EVEN) {
+                if (ES == 4) v[e] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rx, vo, se, 0));
+                else v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, se, 0);       // both pixels
             } else {
-                v[e].x = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, vo, 0, 0);
-                v[e].y = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, v1, 0, 0);
+                const unsigned v1 = vo != kOob && !(k.at & 1u) ? vo + ES : kOob;
+                if (ES == 4) {
+                    v[e].x = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, se, 0);
+                    v[e].y = __builtin_amdgcn_raw_buffer_load_b32(rx, v1, se, 0);
+                } else {
+                    v[e].x = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, vo, se, 0);
+                    v[e].y = (unsigned)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rx, v1, se, 0);
+                }
             }
         }
     };
-    auto put_x = [&](unsigned task, const u32x2 (&v)[4]) __attribute__((always_inline)) {
-        const unsigned cg = task & (CGS - 1), pair = (task / CGS) * 32 + (lane & 31);
-        const unsigned row = fast_div(pair, t.m_PW), col = 2 * (pair - row * t.PW) + (lane >> 5);
+    auto put_x = [&](const Task &k, const u32x2 (&v)[4]) __attribute__((always_inline)) {
         unsigned s[2][2][NP];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -133,13 +151,12 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
                 if constexpr (NP == 3) {
                     split3(__uint_as_float(v[2 * c][i]), __uint_as_float(v[2 * c + 1][i]), s[i][c]);
                 } else {
-                    const bool both = (p.W & 1) == 0;
+                    const bool both = EVEN;
                     const unsigned a0 = i && !both ? v[2 * c].y : v[2 * c].x, a1 = i && !both ? v[2 * c + 1].y : v[2 * c + 1].x;
                     s[i][c][0] = __builtin_amdgcn_perm(a1, a0, i && both ? 0x07060302u : 0x05040100u);
                 }
             }
-        const bool in = task < tasks && pair < pairs && col < (unsigned)p.W;
-        char *d = tile + (cg * t.PLANE + row * t.LW + 1 + col) * 16;
+        char *d = tile + k.lds;
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             u32x4 u;
@@ -149,14 +166,14 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
                 u[c] = r[0];
                 u[2 + c] = r[1];
             }
-            if (in) *reinterpret_cast<u32x4 *>(d + q * part_bytes) = u;
+            if (k.lds != kOob) *reinterpret_cast<u32x4 *>(d + q * part_bytes) = u;
         }
     };
 
     fetch_w(wk, 0, wv[0]);
-    fetch_w(wk, 1, wv[1]);
+    if (NA == 3) fetch_w(wk, 1, wv[1]);
 #pragma unroll
-    for (int k = 0; k < TS; ++k) fetch_x(wk, wave + k * (WM * WP), xv[k]);
+    for (int k = 0; k < TS; ++k) fetch_x(wk, wave + k * (WM * WP), slot[k], xv[k]);
 
     // columns -1 and W of every row, never written by the staging: zeros
     for (unsigned i = tid % NT; i < (unsigned)NP * CGS * t.ROWS * 2; i += NT) {
@@ -199,26 +216,32 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
         const int ch = rd * WK + wk;
         if (rd) __syncthreads();                  // the previous chunk has been read
 #pragma unroll
-        for (int k = 0; k < TS; ++k) put_x(wave + k * (WM * WP), xv[k]);
+        for (int k = 0; k < TS; ++k) put_x(slot[k], xv[k]);
         for (unsigned k = TS * (WM * WP); k < tasks; k += WM * WP) {   // (wide planes: more tasks than slots)
-            fetch_x(ch, wave + k, xv[0]);
-            put_x(wave + k, xv[0]);
+            const Task more = make_task(wave + k);
+            fetch_x(ch, wave + k, more, xv[0]);
+            put_x(more, xv[0]);
         }
         __syncthreads();
         // A k-step goes pixel tile by pixel tile: the inputs of the next one are read from LDS while the matrix
         // unit works on this one; the next chunk's inputs are requested one task per k-step.
         bf16x8 opb[2][NP];
+        // (an offset the compiler cannot see through: it would otherwise keep the operand addresses of all k-steps,
+        // a hundred registers, across the chunks)
+        unsigned opaque = 0;
+        asm volatile("" : "+s"(opaque));
         auto load_b = [&](int ks, int ni) __attribute__((always_inline)) {
 #pragma unroll
             for (int q = 0; q < NP; ++q)
-                opb[(ks * NI + ni) & 1][q] = *reinterpret_cast<const bf16x8 *>(tile + q * part_bytes + bpix[ni] + tap_off(ks));
+                opb[(ks * NI + ni) & 1][q] = *reinterpret_cast<const bf16x8 *>(tile + q * part_bytes + bpix[ni] + (tap_off(ks) + opaque));
         };
         load_b(0, 0);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            if (ks + 2 < KS) fetch_w(ch, ks + 2, wv[(ks + 2) % 3]);
-            else fetch_w(ch + WK, ks + 2 - KS, wv[(ks + 2) % 3]);
-            if (ks < TS) fetch_x(ch + WK, wave + ks * (WM * WP), xv[ks]);
+            constexpr int AH = NA - 1;
+            if (ks + AH < KS) fetch_w(ch, ks + AH, wv[(ks + AH) % NA]);
+            else fetch_w(ch + WK, ks + AH - KS, wv[(ks + AH) % NA]);
+            if (ks < TS) fetch_x(ch + WK, wave + ks * (WM * WP), slot[ks], xv[ks]);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
                 if (ni + 1 < NI) load_b(ks, ni + 1);
@@ -229,19 +252,19 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
 #pragma unroll
                     for (int mi = 0; mi < MI; ++mi) {
                         f32x4 &c = NP == 1 || e == 5 ? acc[mi][ni] : low[NP == 3 ? mi : 0][ni];
-                        c = mma(__builtin_bit_cast(bf16x8, wv[ks % 3][mi][NP == 3 ? kSplitA[e] : 0]),
+                        c = mma(__builtin_bit_cast(bf16x8, wv[ks % NA][mi][NP == 3 ? kSplitA[e] : 0]),
                                 opb[(ks * NI + ni) & 1][NP == 3 ? kSplitB[e] : 0], c);
                     }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (KS % 3 == 2) {                        // the next chunk's first filters move to sets 0 and 1
+        if (KS % NA) {                            // the next chunk's first filters move to set 0 (and 1)
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
-                    wv[1][mi][q] = wv[0][mi][q];
-                    wv[0][mi][q] = wv[2][mi][q];
+                    if (NA == 3) wv[1][mi][q] = wv[0][mi][q];
+                    wv[0][mi][q] = wv[NA - 1][mi][q];
                 }
         }
     }
@@ -371,7 +394,8 @@ struct CfgH {
     int MI, NI, WM, WP, WK;
     float kstep;      // microseconds per k-step of a block alone on its compute unit
 };
-const CfgH kCfgH[] = {{2, 4, 2, 2, 1, 0.75f}, {2, 4, 2, 1, 2, 0.75f}, {2, 2, 2, 2, 1, 0.5f}, {2, 2, 1, 1, 4, 0.5f}, {2, 4, 1, 1, 4, 0.75f}};
+// (bf16 layers: the first two, which do not split the chunks)
+const CfgH kCfgH[] = {{2, 4, 2, 2, 1, 0.75f}, {2, 2, 2, 2, 1, 0.5f}, {2, 4, 2, 1, 2, 0.75f}, {2, 2, 1, 1, 4, 0.5f}};
 constexpr int kNumCfgH = sizeof(kCfgH) / sizeof(kCfgH[0]);
 constexpr int kLdsBlockH = 78 * 1024;   // two blocks per compute unit
 
@@ -381,10 +405,10 @@ size_t lds_bytes_h(const CfgH &c, int cgs, int parts, const TileH &t) {
     return tiles > sums ? tiles : sums;
 }
 
-template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool VO>
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO>
 hipError_t launchH(const ConvParams &p, const TileH &t, hipStream_t s) {
     const size_t lds = lds_bytes_h(CfgH{MI, NI, WM, WP, WK, 0.f}, CGS, sizeof(TIN) == 4 ? 3 : 1, t);
-    auto kern = conv_split3<MI, NI, WM, WP, WK, CGS, S, TIN, VO>;
+    auto kern = conv_split3<MI, NI, WM, WP, WK, CGS, S, TIN, EVEN, VO>;
     if (lds > 64 * 1024) {
         static thread_local bool raised = false;   // per instantiation and thread
         if (!raised) {
@@ -399,18 +423,19 @@ hipError_t launchH(const ConvParams &p, const TileH &t, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int MI, int NI, int WM, int WP, int WK, int CGS, typename TIN>
-hipError_t launchH_s(const ConvParams &p, const TileH &t, bool vo, hipStream_t s) {
-    if (p.stride == 1)
-        return vo ? launchH<MI, NI, WM, WP, WK, CGS, 1, TIN, true>(p, t, s) : launchH<MI, NI, WM, WP, WK, CGS, 1, TIN, false>(p, t, s);
-    return vo ? launchH<MI, NI, WM, WP, WK, CGS, 2, TIN, true>(p, t, s) : launchH<MI, NI, WM, WP, WK, CGS, 2, TIN, false>(p, t, s);
+// 16-byte stores (VO) go with 8-byte loads: an odd row width takes the 4-byte forms of both
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN>
+hipError_t launchH_form(const ConvParams &p, const TileH &t, hipStream_t s) {
+    if (p.W & 1) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, false, false>(p, t, s);
+    if (t.HWo % 4) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, false>(p, t, s);
+    return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, true>(p, t, s);
 }
 
-template <int MI, int NI, int WM, int WP, int WK>
-hipError_t launchH_cgs(const ConvParams &p, const TileH &t, int cgs, bool vo, hipStream_t s) {
-    if (p.in_bf16)
-        return cgs == 4 ? launchH_s<MI, NI, WM, WP, WK, 4, uint16_t>(p, t, vo, s) : launchH_s<MI, NI, WM, WP, WK, 2, uint16_t>(p, t, vo, s);
-    return cgs == 4 ? launchH_s<MI, NI, WM, WP, WK, 4, float>(p, t, vo, s) : launchH_s<MI, NI, WM, WP, WK, 2, float>(p, t, vo, s);
+template <int MI, int NI, int WM, int WP, int WK, typename TIN>
+hipError_t launchH_cgs(const ConvParams &p, const TileH &t, int cgs, hipStream_t s) {
+    if (cgs == 4)
+        return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 4, 1, TIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 4, 2, TIN>(p, t, s);
+    return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 2, 1, TIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 2, 2, TIN>(p, t, s);
 }
 
 bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, TileH *out) {
@@ -457,17 +482,18 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 
 // Block shape: the one with the shortest estimated launch.  A block alone on its compute unit needs `kstep` per k-step
 // (1.3 times that for the half-size chunks), 1 us per chunk and 1.5 us besides; two share the unit at 1.45 times that,
-// more follow in pairs (N = 64, us, estimate / measured: 256 -> 256 on 14x14 g = 2 47 / 42, 512 -> 512 on 7x7 g = 2
-// 47 / 44, 128 -> 128 on 8x8 10.2 / 10.3, and 13 / 13.7 for the next best shape).
+// more follow in pairs; the sum of split chunks adds a tenth (N = 64, us, estimate / measured: 256 -> 256 on 14x14 g = 2
+// 47 / 40, 512 -> 512 on 7x7 g = 2 47 / 43, 128 -> 128 on 8x8 11.2 / 10.8, 50 -> 75 on 31x23 at N = 100 66 / 58 and 69 / 65
+// for the next best shape).
 //
 // Which layers (N = 64 unless stated, us, before / with this kernel):
 //  - rows that are not a multiple of 4 or channels per group that are not: the fp32 kernels stage those 4 bytes at a
-//    time, or in one chunk: 256 -> 256 on 14x14 g = 2 68 / 42, g = 4 38 / 25, 512 -> 512 on 7x7 g = 2 89 / 44,
-//    192 -> 192 on 13x17 g = 2 104 / 35, 50 -> 75 on 31x23 at N = 100 423 / 58, 110 -> 100 on 40x40 stride 2 at N = 20
-//    281 / 25.  Not where Winograd takes the layer and more than a third of the filters would be padding (144 -> 144
+//    time, or in one chunk: 256 -> 256 on 14x14 g = 2 68 / 40, g = 4 38 / 24, 512 -> 512 on 7x7 g = 2 89 / 43,
+//    192 -> 192 on 13x17 g = 2 104 / 33, 50 -> 75 on 31x23 at N = 100 423 / 58, 110 -> 100 on 40x40 stride 2 at N = 20
+//    281 / 22.  Not where Winograd takes the layer and more than a third of the filters would be padding (144 -> 144
 //    on 14x14, g = 2: 33.7 / 35.9);
-//  - stride 2 from two blocks per compute unit on: 128 -> 256 on 28x28 g = 2 50 / 37, 256 -> 512 on 14x14 g = 2 59 / 33,
-//    64 -> 128 on 56x56 83 / 68; with one block the fp32 kernels are level (64 -> 128 on 16x16: 11.7 / 13.7);
+//  - stride 2 from two blocks per compute unit on: 128 -> 256 on 28x28 g = 2 50 / 31, 256 -> 512 on 14x14 g = 2 59 / 30,
+//    64 -> 128 on 56x56 83 / 62; with one block the fp32 kernels are level (64 -> 128 on 16x16: 11.7 / 13.7);
 //  - other stride-1 layers: with at least 128 channels per group where neither Winograd (64 -> 64 on 16x16 at N = 256
 //    25.5 / 27, 128 -> 128 on 28x28 g = 2 47 / 46) nor a launch of more blocks than the chip holds covers the fp32
 //    kernel's waits: 128 -> 128 on 8x8 13.4 / 10.3 (64 channels per group: 8.6 / 10.2).
@@ -481,17 +507,18 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     double best = 0.0;
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
+        if (p.in_bf16 && i > 1) continue;
         for (int cgs : {4, 2}) {
             TileH t;
             if (cgs == 4 && (g.CPG + 15) / 16 * 16 < (g.CPG + 31) / 32 * 32 - 8) continue;
             if (!planH_cfg(p, g, c, cgs, &t)) continue;
             const long blocks = (long)t.px_blocks * t.oc_blocks * p.groups, n = (blocks + kNumCU - 1) / kNumCU;
-            if (blocks < kNumCU / 4 || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
+            if ((when != kSplit3Any && blocks < kNumCU / 4) || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
                 (when == kSplit3Else && !odd && p.stride == 1 && n > 2))
                 continue;
             const double rounds = (t.nchunks + c.WK - 1) / c.WK, ks = rounds * (cgs == 4 ? 9 : 5 * 1.3);
             const double one = ks * c.kstep * (p.stride == 2 && c.NI == 4 ? 1.4 : 1.0) + rounds + 1.5;
-            const double est = one * (1.45 * (double)(n / 2) + (double)(n % 2));
+            const double est = (c.WK > 1 ? 1.1 : 1.0) * one * (1.45 * (double)(n / 2) + (double)(n % 2));
             if (best != 0.0 && est >= best) continue;
             best = est;
             out->inst = i;
@@ -506,16 +533,17 @@ hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_
     TileH t;
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgH &c = kCfgH[plan.inst];
-    const bool vo = t.HWo % 4 == 0;
-    *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
-                        "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +
-                        std::to_string(p.stride) + (p.in_bf16 ? ",bf16" : ",f32") + (vo ? ",true>" : ",false>"));
+    const bool even = p.W % 2 == 0;
+    if (!*name)
+        *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
+                            "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +
+                            std::to_string(p.stride) + (p.in_bf16 ? ",bf16" : ",f32") + (even ? ",true" : ",false") +
+                            (even && t.HWo % 4 == 0 ? ",true>" : ",false>"));
     switch (plan.inst) {
-    case 0: return launchH_cgs<2, 4, 2, 2, 1>(p, t, plan.cgs, vo, s);
-    case 1: return launchH_cgs<2, 4, 2, 1, 2>(p, t, plan.cgs, vo, s);
-    case 2: return launchH_cgs<2, 2, 2, 2, 1>(p, t, plan.cgs, vo, s);
-    case 3: return launchH_cgs<2, 2, 1, 1, 4>(p, t, plan.cgs, vo, s);
-    case 4: return launchH_cgs<2, 4, 1, 1, 4>(p, t, plan.cgs, vo, s);
+    case 0: return p.in_bf16 ? launchH_cgs<2, 4, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 4, 2, 2, 1, float>(p, t, plan.cgs, s);
+    case 1: return p.in_bf16 ? launchH_cgs<2, 2, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 2, 2, 2, 1, float>(p, t, plan.cgs, s);
+    case 2: return launchH_cgs<2, 4, 2, 1, 2, float>(p, t, plan.cgs, s);
+    case 3: return launchH_cgs<2, 2, 1, 1, 4, float>(p, t, plan.cgs, s);
     }
     return hipErrorNotSupported;
 }

@@ -13,17 +13,17 @@ pytestmark = pytest.mark.gpu
 S = wl.ConvShape
 SHAPES = [
     # N Cin H W Cout KH KW stride pad groups
-    (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), "f32,true"),     # tiles that start inside rows and span images
-    (S(150, 96, 7, 7, 64, 3, 3, 1, 1, 1), "f32,false"),       # 49-pixel planes: three images per tile, 4-byte stores
-    (S(30, 66, 13, 17, 66, 3, 3, 1, 1, 1), "f32,false"),      # odd rows, padded channels and filters
-    (S(33, 100, 9, 22, 128, 3, 3, 1, 1, 2), "f32,false"),     # two groups of 50 channels, even width, odd plane
-    (S(64, 128, 8, 8, 128, 3, 3, 1, 1, 1), "f32,true"),       # the chunks split over four waves
-    (S(160, 64, 16, 16, 128, 3, 3, 2, 1, 1), "f32,true"),     # stride 2, even planes
-    (S(300, 70, 15, 9, 64, 3, 3, 2, 1, 1), "f32,true"),       # stride 2, odd planes (40 outputs each)
-    (S(9, 49, 60, 50, 48, 3, 3, 1, 1, 1), "f32,true"),        # more staging tasks than slots; a last chunk of one channel
-    (S(900, 64, 3, 2, 64, 3, 3, 1, 1, 1), "f32,false"),       # planes of six pixels: twenty images per tile
-    (S(50, 36, 11, 13, 40, 3, 3, 1, 1, 1), "bf16,false"),     # bf16, 36 channels
-    (S(40, 42, 12, 14, 48, 3, 3, 2, 1, 2), "bf16,false"),     # bf16, stride 2, two groups of 21
+    (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), "f32,true,true"),     # tiles that start inside rows and span images
+    (S(150, 96, 7, 7, 64, 3, 3, 1, 1, 1), "f32,false,false"),       # 49-pixel planes: three images per tile, 4-byte stores
+    (S(30, 66, 13, 17, 66, 3, 3, 1, 1, 1), "f32,false,false"),      # odd rows, padded channels and filters
+    (S(33, 100, 9, 22, 128, 3, 3, 1, 1, 2), "f32,true,false"),     # two groups of 50 channels, even width, odd plane
+    (S(64, 128, 8, 8, 128, 3, 3, 1, 1, 1), "f32,true,true"),       # the chunks split over four waves
+    (S(160, 64, 16, 16, 128, 3, 3, 2, 1, 1), "f32,true,true"),     # stride 2, even planes
+    (S(300, 70, 15, 9, 64, 3, 3, 2, 1, 1), "f32,false,false"),     # stride 2, odd planes (40 outputs each)
+    (S(9, 49, 60, 50, 48, 3, 3, 1, 1, 1), "f32,true,true"),        # more staging tasks than slots; a last chunk of one channel
+    (S(900, 64, 3, 2, 64, 3, 3, 1, 1, 1), "f32,true,false"),       # planes of six pixels: twenty images per tile
+    (S(50, 36, 11, 13, 40, 3, 3, 1, 1, 1), "bf16,false,false"),     # bf16, 36 channels
+    (S(40, 42, 12, 14, 48, 3, 3, 2, 1, 2), "bf16,true,false"),     # bf16, stride 2, two groups of 21
 ]
 
 
