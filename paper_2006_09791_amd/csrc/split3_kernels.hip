@@ -490,19 +490,27 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 //  - rows that are not a multiple of 4 or channels per group that are not: the fp32 kernels stage those 4 bytes at a
 //    time, or in one chunk: 256 -> 256 on 14x14 g = 2 68 / 40, g = 4 38 / 24, 512 -> 512 on 7x7 g = 2 89 / 43,
 //    192 -> 192 on 13x17 g = 2 104 / 33, 50 -> 75 on 31x23 at N = 100 423 / 58, 110 -> 100 on 40x40 stride 2 at N = 20
-//    281 / 22.  Not where Winograd takes the layer and more than a third of the filters would be padding (144 -> 144
-//    on 14x14, g = 2: 33.7 / 35.9);
+//    281 / 22, 80 -> 72 on 18x18 at N = 128 76 / 48, with almost half of the filters padding 144 -> 144 on 14x14 g = 2
+//    33.7 / 31.3;
+//  - planes of more than 256 pixels whose 2x2 tiles leave a tenth of Winograd's 32-tile blocks empty, in whole chunks and
+//    filter tiles (40 -> 48 on 28x28: 17.5 / 22.4) and with more than a block per compute unit (128 -> 128 on 28x28 g = 2
+//    at N = 16, 196 blocks: 15.9 / 16.8; at N = 24 24.7 / 23.5): 128 -> 128 on 28x28 g = 2 47.4 / 43.5, g = 1 85 / 77,
+//    256 -> 256 g = 4 92 / 76, 128 -> 128 on 20x20 g = 2 at N = 100 49 / 34, 64 -> 64 25.8 / 22.7.  Planes that fill the
+//    blocks are level or Winograd's (64 -> 64 on 32x32 25.8 / 25.4, on 56x56 91 / 95);
 //  - stride 2 from two blocks per compute unit on: 128 -> 256 on 28x28 g = 2 50 / 31, 256 -> 512 on 14x14 g = 2 59 / 30,
 //    64 -> 128 on 56x56 83 / 62; with one block the fp32 kernels are level (64 -> 128 on 16x16: 11.7 / 13.7);
 //  - other stride-1 layers: with at least 128 channels per group where neither Winograd (64 -> 64 on 16x16 at N = 256
-//    25.5 / 27, 128 -> 128 on 28x28 g = 2 47 / 46) nor a launch of more blocks than the chip holds covers the fp32
+//    25.6 / 25.3) nor a launch of more blocks than the chip holds covers the fp32
 //    kernel's waits: 128 -> 128 on 8x8 13.4 / 10.3 (64 channels per group: 8.6 / 10.2).
-// With Winograd switched off (gspc_set_winograd(0)) every layer stays on the fp32 kernels, bit for bit.
+// With Winograd switched off (gspc_set_winograd(0)) every fp32 3x3 layer stays on the fp32 instruction.
 bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out) {
     if (!p.wh || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2)) return false;
     const bool odd = p.W % 4 != 0 || g.CPG % 4 != 0;
     const int ft = (g.KPG + 63) / 64 * 64;
-    if (when == kSplit3BeforeWinograd && (!odd || p.stride != 1 || 3 * ft > 4 * g.KPG)) return false;
+    const int wt = (p.Hout + 1) / 2 * ((p.Wout + 1) / 2), wr = (wt + 31) / 32 * 32;
+    const bool ragged = p.H * p.W > 256 && 10 * (wr - wt) > wr && g.CPG % 32 == 0 && ft == g.KPG &&
+                        (double)p.N * p.Hout * p.Wout * p.Cout > kNumCU * 64 * 128.0;
+    if (when == kSplit3BeforeWinograd && (!(odd || ragged) || p.stride != 1 || ft >= 2 * g.KPG)) return false;
     if (when == kSplit3Else && !odd && p.stride == 1 && g.CPG < 128) return false;
     double best = 0.0;
     for (int i = 0; i < kNumCfgH; ++i) {

@@ -14,6 +14,7 @@ S = wl.ConvShape
 SHAPES = [
     # N Cin H W Cout KH KW stride pad groups
     (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), "f32,true,true"),     # tiles that start inside rows and span images
+    (S(24, 64, 28, 28, 128, 3, 3, 1, 1, 1), "f32,true,true"),      # whole float4 rows, 2x2 tiles that fill no block
     (S(150, 96, 7, 7, 64, 3, 3, 1, 1, 1), "f32,false,false"),       # 49-pixel planes: three images per tile, 4-byte stores
     (S(30, 66, 13, 17, 66, 3, 3, 1, 1, 1), "f32,false,false"),      # odd rows, padded channels and filters
     (S(33, 100, 9, 22, 128, 3, 3, 1, 1, 2), "f32,true,false"),     # two groups of 50 channels, even width, odd plane
