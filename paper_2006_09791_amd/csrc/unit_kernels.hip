@@ -180,12 +180,20 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     //  - 3x3, stride 1, rows of a multiple of 4 (16-byte staging on the other side): 75k loads 8.3 / 6.5 and 9.4 / 6.6,
     //    150k 9.1 / 10.0 and 13.1 / 10.0, 300k 13.4 / 16.6;
     //  - stride 2, other widths, 1x1: 150k 12.7 / 10.2 and 18.2 / 9.9, 200k (32 -> 64 on 32x32 at stride 2) 10.2 / 11.4,
-    //    300k 16.7 / 18.0 and 20.0 / 22.2.
-    // With fewer than six units a block is mostly its start and its sum: 3 -> 32 on 32x32, N = 8 4.9 / 4.7, N = 32 5.2 / 6.8.
+    //    300k 16.7 / 18.0 and 20.0 / 22.2; pointwise on planes of a multiple of 4 174k 15.4 / 11.6, 189k 13.9 / 16.8.
+    // With few units a block is mostly its start and its sum, and once the blocks no longer run together that counts:
+    //  - fewer than six: 3 -> 32 on 32x32, N = 8 4.9 / 4.7, N = 32 5.2 / 6.8; pointwise on planes that are staged 16 bytes
+    //    at a time 64 -> 64 on 16x16, N = 16 (1024 tiles) 5.0 / 4.7, 64 -> 128 (2048) 5.0 / 5.3, 64 -> 64 on 56x56, N = 3
+    //    (2352) 5.4 / 6.6, on other planes 64 -> 80 on 55x55, N = 2 (1895) 8.0 / 6.5;
+    //  - six, 3x3 with stride 1: 64 -> 64, g = 8 on 16-pixel rows (2048) 4.8 / 4.7, on 20x20, N = 16 (3200) 5.1 / 6.1, on
+    //    13x13, N = 50 (4232) 6.6 / 7.7; with nine 96 -> 96, g = 8 on 17x17 (2312) 7.4 / 5.9;
+    //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 9.0 / 5.9, N = 10 (2250) 8.7 / 9.8.
     const long tiles = (long)((t.npix + 15) / 16) * g.mtiles * p.groups;
     const double loads = (double)tiles * t.units * (row ? 2 : 5);
-    if (loads > (row && p.W % 4 == 0 ? p.stride == 1 ? 80e3 : 160e3 : 200e3)) return false;
-    if (row && t.units < 6 && tiles > 4 * kNumCU) return false;
+    const bool wide = p.stride == 1 && (row ? p.W % 4 == 0 : (p.Hout * p.Wout) % 4 == 0);   // staged 16 bytes at a time
+    if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
+    if (t.units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
+    if ((row ? p.stride == 1 && t.units < 9 : wide && t.units < 12) && tiles > 8 * kNumCU) return false;
     // waves per block: what lets every wave request all of its units at once, more while the launch is small
     int nw = 2;
     while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw < 8 * kNumCU && t.units > nw))) nw *= 2;
