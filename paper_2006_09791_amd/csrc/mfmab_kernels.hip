@@ -173,6 +173,9 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_mfma16b(ConvParams p, Ti
     auto unit_off = [&](int ks) -> unsigned {
         return TAPK ? uoff[0] + ((ks / 3) * t.LW + ks % 3) * t.PPB : uoff[ks];
     };
+    // Units past the last one have zero weights; their inputs must be zeros too (0 * inf): the lanes of the last
+    // k-step that have no unit read the unused end of the tile's first pixel, which is cleared below.
+    constexpr bool IDLE = KS * 4 > UPC;
 
     // Origin of pixel tile tg (an image group and a band of output rows): first image, the
     // number of output elements left in a plane from the band's first row, byte offset of
@@ -215,6 +218,7 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_mfma16b(ConvParams p, Ti
             const int col = hp < p.pad ? hp : p.W + hp;   // left columns, then right columns
             *reinterpret_cast<f32x4 *>(xs + (row * t.LW + col) * t.PPB + pc * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
         }
+        if (IDLE && tid == 0) *reinterpret_cast<f32x4 *>(xs + t.PPB - 16) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
     // ---- a block walks over (pixel tile, channel chunk) steps, tiles blockIdx.x,
@@ -323,8 +327,11 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_mfma16b(ConvParams p, Ti
             for (int mi = 0; mi < MI; ++mi)
                 opa[set][mi] = *reinterpret_cast<const bf16x8 *>(wcur + ((ks * MIWM + wm * MI + mi) * 64 + lane) * 16);
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                opb[set][ni] = *reinterpret_cast<const bf16x8 *>(xs + pixb[ni] + unit_off(ks));
+            for (int ni = 0; ni < NI; ++ni) {
+                const char *b = xs + pixb[ni] + unit_off(ks);
+                if (IDLE && ks == KS - 1 && 4 * ks + (lane >> 4) >= UPC) b = xs + t.PPB - 16;
+                opb[set][ni] = *reinterpret_cast<const bf16x8 *>(b);
+            }
         };
         if (DB) load_ops(0, 0);
 #pragma unroll

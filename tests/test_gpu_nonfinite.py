@@ -16,6 +16,9 @@ BF16 = [
     (S(50, 36, 11, 13, 40, 3, 3, 1, 1, 1), "conv_split3<"),      # 36 channels in chunks of sixteen: tap 9 does not exist
     (S(40, 44, 12, 14, 48, 3, 3, 2, 1, 1), "conv_split3<"),      # the same, stride 2, even rows
     (S(3, 36, 9, 16, 48, 3, 3, 1, 1, 3), "conv_split3<"),        # three groups of 12 channels
+    (S(2, 48, 10, 10, 32, 3, 3, 1, 1, 2), "conv_mfma16b<"),      # chunks of 8 channels: three of the last four units empty
+    (S(3, 32, 9, 12, 64, 3, 3, 2, 1, 2), "conv_mfma16b<"),       # chunks of 16: two empty
+    (S(2, 48, 10, 12, 32, 3, 3, 1, 0, 2), "conv_mfma16b<"),      # no padding
 ]
 
 
