@@ -193,13 +193,8 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
     }
     auto tap_off = [&](int ks) -> unsigned {
         if (CGS == 4) return ((ks / 3) * t.LW + ks % 3) * 16u;
-        const int t0 = 2 * ks, t1 = 2 * ks + 1;
+        const int t0 = 2 * ks, t1 = 2 * ks + 1 < 9 ? 2 * ks + 1 : 8;
         return (lg >> 1) ? ((t1 / 3) * t.LW + t1 % 3) * 16u : ((t0 / 3) * t.LW + t0 % 3) * 16u;
-    };
-    // (CGS = 2: the last k-step's second tap does not exist.  Its weights are zeros, and so must the inputs be, lest
-    // an infinity times zero come into the sum: those lanes read the first unit of the tile, column -1 of a row.)
-    auto b_off = [&](int ks, int ni) -> unsigned {
-        return CGS == 2 && ks == KS - 1 && lg >= 2 ? 0u : bpix[ni] + tap_off(ks);
     };
 
     f32x4 acc[MI][NI], low[NP == 3 ? MI : 1][NI];
@@ -237,8 +232,13 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
         asm volatile("" : "+s"(opaque));
         auto load_b = [&](int ks, int ni) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < NP; ++q)
-                opb[(ks * NI + ni) & 1][q] = *reinterpret_cast<const bf16x8 *>(tile + q * part_bytes + (b_off(ks, ni) + opaque));
+            for (int q = 0; q < NP; ++q) {
+                const char *b = tile + q * part_bytes + bpix[ni] + (tap_off(ks) + opaque);
+                // (CGS = 2: the last k-step's second tap does not exist.  Its weights are zeros, and so must the inputs
+                // be, lest an infinity times zero come into the sum: a unit of column -1)
+                if (CGS == 2 && ks == KS - 1 && lg >= 2) b = tile + q * part_bytes;
+                opb[(ks * NI + ni) & 1][q] = *reinterpret_cast<const bf16x8 *>(b);
+            }
         };
         load_b(0, 0);
 #pragma unroll
