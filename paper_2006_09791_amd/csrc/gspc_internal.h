@@ -81,7 +81,7 @@ struct PackGeom {
     // Pointwise section (1x1 layers, KPG >= 16, CPG >= 8): [g][chunk][ceil(KPG/16)] operand blocks, the A operand of
     // v_mfma_f32_16x16x32_bf16 per (chunk of 32 channels, filter tile): lane l, element e holds filter l % 16 of its
     // tile at channel 32*chunk + 8*(l/16) + e, zeros past CPG and KPG.  split_parts = 3: bf16 [part][64 lanes][8],
-    // the parts of the exact split h + m + l of an fp32 weight (split_common.h); 1: the same with the one part of a
+    // the parts of the exact split h + m + l of 2^24 times an fp32 weight (split_common.h); 1: the same with the one part of a
     // GSPC_BF16 handle; 0: fp32 [64 lanes][8], split by the kernel (matrices of up to 64 KB, which stay a mere
     // reordering of the weights in two thirds of the bytes: level with the split section at 32 .. 128 channels,
     // 1 % behind it at 160 and 4-12 % at 256 .. 1024).
@@ -94,7 +94,7 @@ struct PackGeom {
     size_t unit_bytes, unit_offset;
     // Split 3x3 section (3x3, KPG >= 16, CPG >= 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
     // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles, with more than 16384 weights per
-    // group or CPG % 4 != 0: the three parts of the exact split of a weight; GSPC_BF16 handles with CPG % 8 != 0
+    // group or CPG % 4 != 0: the three parts of the exact split of 2^24 times a weight; GSPC_BF16 handles with CPG % 8 != 0
     // (no 16x16x32 section): the weight.
     size_t h3_bytes, h3_offset;
     struct MergedDirect {

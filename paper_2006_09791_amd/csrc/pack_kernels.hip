@@ -201,7 +201,7 @@ __device__ __forceinline__ void pack_split(size_t d, const float *__restrict__ w
         return;
     }
     unsigned s[3];
-    split3(v, 0.f, s);
+    split3(parts == 3 ? v * kSplitScale : v, 0.f, s);
     for (int q = 0; q < parts; ++q) out[(tile * parts + q) * 512 + lane * 8 + e] = (uint16_t)s[q];
 }
 
@@ -246,7 +246,7 @@ __device__ __forceinline__ void pack_split3(size_t d, const float *__restrict__ 
     float v = 0.f;
     if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + (size_t)c * 9 + tap];
     unsigned s[3];
-    split3(v, 0.f, s);
+    split3(parts == 3 ? v * kSplitScale : v, 0.f, s);
     for (int q = 0; q < parts; ++q) out[(block * parts + q) * 128 + li * 8 + e] = (uint16_t)s[q];
 }
 

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 if constexpr (NP == 3) {
-                    split3(__uint_as_float(v[2 * c][i]), __uint_as_float(v[2 * c + 1][i]), s[i][c]);
+                    split3(__uint_as_float(v[2 * c][i]) * kSplitScale, __uint_as_float(v[2 * c + 1][i]) * kSplitScale, s[i][c]);
                 } else {
                     const bool both = EVEN;
                     const unsigned a0 = i && !both ? v[2 * c].y : v[2 * c].x, a1 = i && !both ? v[2 * c + 1].y : v[2 * c + 1].x;
@@ -274,7 +274,6 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
         }
     }
 
-    ResultRange range;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -301,13 +300,17 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
                 for (int ni = 0; ni < NI; ++ni)
                     acc[mi][ni] += ps[((((k - 1) * (WM * WP) + wave) * MI + mi) * NI + ni) * 64 + lane];
     }
+    SplitOverflow over;
+    if (NP == 3) {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+            for (int ni = 0; ni < NI; ++ni) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (NP == 3) range.see(acc[mi][ni][r]);
+                for (int r = 0; r < 4; ++r) over.see(acc[mi][ni][r]);
+                acc[mi][ni] *= kSplitUnscale;
+            }
+    }
 
     // ---- epilogue: residual, ReLU, NCHW stores ---------------------------------------------------------
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
             }
         }
     __builtin_amdgcn_sched_barrier(0);
-    if (NP == 3 && __ballot(range.outside())) {
+    if (NP == 3 && __ballot(over.any())) {
         // plain fp32 sums of this wave's outputs
         wait_vmem0();   // the stores above come first
         const float *wd = p.wd + (size_t)j * p.CPG * 9 * p.KPGd;

@@ -18,9 +18,8 @@
 //    bytes.  Even and odd pixels lie apart (and 64 bytes off), so that the writes of a wave and the
 //    operand reads each fall on all banks.
 //
-// The sum of a split product is not the fp32 sum where a part overflows, is multiplied by an infinity, or
-// would need bits below bf16's 2^-133: a wave that finds a result that is not finite, or not zero and below
-// 2^-90, recomputes its outputs as plain fp32 sums.
+// The sum of a split product is not the fp32 sum where a part overflows or is multiplied by an infinity: a wave
+// that finds a scaled sum that is not finite recomputes its outputs as plain fp32 sums.
 #include <cstring>
 
 #include "split_common.h"
@@ -123,7 +122,7 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvPar
     unsigned xs[2][2][NP];      // [pixel][channel pair][part]
     auto split_x = [&](int k, int i, int c) __attribute__((always_inline)) {
         if constexpr (NP == 3) {
-            split3(__uint_as_float(xv[k][2 * c][i]), __uint_as_float(xv[k][2 * c + 1][i]), xs[i][c]);
+            split3(__uint_as_float(xv[k][2 * c][i]) * kSplitScale, __uint_as_float(xv[k][2 * c + 1][i]) * kSplitScale, xs[i][c]);
         } else {
             // two pixels per dword when loaded together, one otherwise
             xs[i][c][0] = __builtin_amdgcn_perm(xv[k][2 * c + 1][VO ? 0 : i], xv[k][2 * c][VO ? 0 : i],
@@ -177,7 +176,8 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvPar
                 unsigned u[4][3];
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    split3(__uint_as_float(wv[k][c / 2][c % 2 * 2]), __uint_as_float(wv[k][c / 2][c % 2 * 2 + 1]), u[c]);
+                    split3(__uint_as_float(wv[k][c / 2][c % 2 * 2]) * kSplitScale,
+                           __uint_as_float(wv[k][c / 2][c % 2 * 2 + 1]) * kSplitScale, u[c]);
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(smem4) + (piece * 3 + q) * 1024 + lane * 16) =
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvPar
     const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
     const unsigned oc0 = ob * (MT * 16) + wm * (MI * 16);
     const unsigned ystep = t.HW * 4, ybase = (n0 * p.Cout + j * p.KPG) * ystep;
-    ResultRange range;
+    SplitOverflow over;
     if (NP == 3) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
@@ -261,7 +261,8 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvPar
             for (int ni = 0; ni < NI; ++ni) {
                 acc[mi][ni] += low[mi][ni];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) range.see(acc[mi][ni][r]);
+                for (int r = 0; r < 4; ++r) over.see(acc[mi][ni][r]);
+                acc[mi][ni] *= kSplitUnscale;
             }
     }
     // offset of a lane's first output of column block ni (its filter 0): pixel 4*lg (VO) or li of the block
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvPar
             }
         }
     __builtin_amdgcn_sched_barrier(0);
-    if (NP == 3 && __ballot(range.outside())) {
+    if (NP == 3 && __ballot(over.any())) {
         // plain fp32 sums of this wave's outputs
         wait_vmem0();   // the stores above come first
         const float *wd = p.wd + (size_t)j * p.CPG * p.KPGd;

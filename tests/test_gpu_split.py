@@ -92,6 +92,38 @@ def test_pointwise_split_keeps_its_precision_at_any_scale(gpu, exponent):
     assert np.max(np.abs(y - ref) - (split_bound(32) + 32 * 2.0 ** -24) * absum) <= 33 * 2.0 ** -150
 
 
+# Exponents of inputs and weights: operands with fewer than 24 bits above bf16's 2^-133 against a second factor that
+# makes the result an ordinary number; results below fp32's normal range; products near the largest number.
+SCALES = [(-120, 45), (45, -120), (-126, 60), (-140, 99), (99, -140), (-60, -70), (-100, 100), (60, 60)]
+
+
+def scaled(x, w, ex, ew):
+    """The operands, none of them next to zero, at these exponents."""
+    x = np.ldexp(np.where(np.abs(x) < 0.01, 0.01, x).astype(np.float64), ex)
+    w = np.ldexp(np.where(np.abs(w) < 0.01, 0.01, w).astype(np.float64), ew)
+    return x.astype(np.float32), w.astype(np.float32)
+
+
+@pytest.mark.parametrize("ex,ew", SCALES)
+@pytest.mark.parametrize("cin,cout", [(32, 64), (160, 128)], ids=["words", "parts"])
+def test_pointwise_split_keeps_its_precision_in_either_operand(gpu, ex, ew, cin, cout):
+    torch, b = gpu
+    dev = torch.device("cuda:0")
+    N, hw = 150, 16
+    x, w = scaled(wl.make_input((N, cin, hw, hw), 93), wl.make_weight(cout, cin, 1, 1, 94), ex, ew)
+    x[:, :, 3, :] = 0.0                       # sums of zeros stay zeros
+    x[:, 1:, 5, 5] = 0.0                      # sums of one term
+    pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), 1)
+    y = b.gspc_conv2d_grouped(torch.from_numpy(x).to(dev), pw, N, cin, hw, hw, cout, 1, 1, 1, 0, 1)
+    torch.cuda.synchronize()
+    assert b.gspc_last_kernel().endswith("/split3" if cin * cout > 16384 else "/split3w"), b.gspc_last_kernel()
+    y = y.cpu().numpy().astype(np.float64)
+    ref, absum = oracle.conv2d_grouped(x, w, 1, 0, 1, return_abs=True, threads=8)
+    assert np.isfinite(y).all()
+    # (plus half a unit of the smallest denormal per product and for the result)
+    assert np.max(np.abs(y - ref) - (split_bound(cin) + cin * 2.0 ** -24) * absum) <= (cin + 1) * 2.0 ** -150
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, np.finfo(np.float32).max])
 @pytest.mark.parametrize("hw,cout", [(16, 128), (15, 128), (16, 512)])
 def test_pointwise_split_of_values_that_do_not_split(gpu, value, hw, cout):

@@ -7,7 +7,7 @@ import oracle
 from helpers import err_metrics, rel_err
 from paper_2006_09791_amd import workloads as wl
 from test_gpu_parity import gpu, run_conv  # noqa: F401  (fixture)
-from test_gpu_split import split_bound
+from test_gpu_split import SCALES, scaled, split_bound
 
 pytestmark = pytest.mark.gpu
 S = wl.ConvShape
@@ -67,6 +67,26 @@ def test_split3_epilogue_and_buffer_ends(gpu, s):
     assert np.isnan(out[:guard]).all() and np.isnan(out[guard + res.size:]).all()
     ref = oracle.relu(oracle.add(oracle.conv2d_grouped(x, w, 1, 1, 1, threads=8), res))
     assert rel_err(out[guard:guard + res.size].reshape(res.shape), ref) < 1e-5
+
+
+@pytest.mark.parametrize("ex,ew", SCALES)
+def test_split3_keeps_its_precision_in_either_operand(gpu, ex, ew):
+    """bf16 has no bits below 2^-133: no factor whose lower parts would need them may lose precision."""
+    torch, b = gpu
+    dev = torch.device("cuda:0")
+    N, C, hw = 60, 64, 14
+    x, w = scaled(wl.make_input((N, C, hw, hw), 95), wl.make_weight(64, C, 3, 3, 96), ex, ew)
+    x[:, :, 4:8, :] = 0.0
+    x[:, 1:, :, 5:8] = 0.0
+    pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), 1)
+    y = b.gspc_conv2d_grouped(torch.from_numpy(x).to(dev), pw, N, C, hw, hw, 64, 3, 3, 1, 1, 1)
+    torch.cuda.synchronize()
+    assert b.gspc_last_kernel().startswith("conv_split3<"), b.gspc_last_kernel()
+    y = y.cpu().numpy().astype(np.float64)
+    ref, absum = oracle.conv2d_grouped(x, w, 1, 1, 1, return_abs=True, threads=8)
+    assert np.isfinite(y).all()
+    K = 9 * C
+    assert np.max(np.abs(y - ref) - (split_bound(K) + (4 + K) * 2.0 ** -24) * absum) <= (K + 1) * 2.0 ** -150
 
 
 @pytest.mark.parametrize("value", [np.inf, np.nan, np.finfo(np.float32).max, 1e-36])
