@@ -250,7 +250,8 @@ __device__ __forceinline__ void pack_split3(size_t d, const float *__restrict__ 
     for (int q = 0; q < parts; ++q) out[(block * parts + q) * 128 + li * 8 + e] = (uint16_t)s[q];
 }
 
-// One launch reorders a layer into all of its sections: blocks jobs[i].first .. write section i.
+// One launch reorders a layer into all of its sections: blocks jobs[i].first .. write section i.  (A launch has fewer
+// than 2^32 threads: the sections of the largest layers take several, which begin at block `base`.)
 enum PackKind { kPackDirect, kPackMfma, kPackWino, kPackMerged, kPackQuadk, kPackBf16, kPackRow, kPackSplit, kPackUnit, kPackSplit3 };
 struct PackJob {
     int kind;
@@ -266,11 +267,12 @@ struct PackJobs {
     PackJob job[kMaxJobs];
 };
 
-__global__ void pack_kernel(const float *__restrict__ w, PackArgs a, PackJobs jobs) {
+__global__ void pack_kernel(const float *__restrict__ w, PackArgs a, PackJobs jobs, unsigned base) {
+    const unsigned block = base + blockIdx.x;
     int k = 0;
-    while (k + 1 < jobs.n && blockIdx.x >= jobs.job[k + 1].first) ++k;
+    while (k + 1 < jobs.n && block >= jobs.job[k + 1].first) ++k;
     const PackJob &jb = jobs.job[k];
-    const size_t d = (size_t)(blockIdx.x - jb.first) * blockDim.x + threadIdx.x;
+    const size_t d = (size_t)(block - jb.first) * blockDim.x + threadIdx.x;
     if (d >= jb.total) return;
     float *f = static_cast<float *>(jb.out);
     uint16_t *b = static_cast<uint16_t *>(jb.out);
@@ -353,8 +355,14 @@ hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t
         if (md.m) add(kPackMerged, md.offset, md.bytes / sizeof(float), md.m, md.KPGd);
     add(kPackMfma, g.mfma_offset, g.mfma_bytes / sizeof(float));
     if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(256), 0, s, w, a, jobs);
-    return hipGetLastError();
+    constexpr unsigned kMaxBlocks = 1u << 23;   // 2^31 threads
+    for (unsigned base = 0; base < blocks; base += kMaxBlocks) {
+        const unsigned n = (unsigned)blocks - base < kMaxBlocks ? (unsigned)blocks - base : kMaxBlocks;
+        hipLaunchKernelGGL(pack_kernel, dim3(n), dim3(256), 0, s, w, a, jobs, base);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_unpack_weights(const gspc_packed *h, int which, float *w, hipStream_t s) {

@@ -173,3 +173,17 @@ def test_depthwise_batched_fp32():
     # batched re-run of the MobileNet-shaped depthwise layers (HBM-bound kernel at a size that fills the GPU)
     for i, (dw, _) in enumerate(wl.depthwise_pairs(32)):
         _sampled_check(dw, wl.make_seed(4, 300 + i, dw.groups), False, n_img=2, n_oc=6, tol_same=TOL_F32)
+
+
+def test_pack_of_more_elements_than_one_launch_has_threads():
+    """764 M weights are 4.4 G elements over all sections of the packed buffer; a launch has at most 2^32 threads.
+    The section that is written last is read back."""
+    import torch
+    from paper_2006_09791_amd import binding as b
+    b.gspc_set_stream()
+    w = torch.empty((9216, 9216, 3, 3), device="cuda").uniform_(-1.0, 1.0)
+    pw = b.gspc_pack_weights(w, 1)
+    for which in (b.PATH_MFMA, b.PATH_DIRECT):
+        back = b.gspc_unpack_weights(pw, which)
+        assert torch.equal(back, w)
+        del back
