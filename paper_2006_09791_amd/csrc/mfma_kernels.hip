@@ -382,6 +382,7 @@ const Cfg16 kCfg16[] = {
     {4, 4, 1, 4, 0}, {2, 4, 1, 4, 0}, {4, 2, 1, 4, 0}, {2, 2, 1, 4, 0}, {1, 4, 1, 4, 0}, {2, 2, 2, 2, 0},
     {1, 2, 1, 4, 0}, {2, 1, 1, 4, 0}, {1, 1, 1, 4, 0},
     {2, 2, 1, 4, 1}, {1, 2, 1, 4, 1}, {2, 1, 1, 4, 1}, {1, 1, 1, 4, 1},
+    {4, 2, 2, 4, 0},   // eight waves, 128 filters x 128 pixels per block: dense pointwise layers (see plan16)
 };
 constexpr int kNumCfg16 = sizeof(kCfg16) / sizeof(kCfg16[0]);
 constexpr int kFirstKsplit = 9, kEndKsplit = 13;
@@ -506,7 +507,9 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
     const int forced = force ? std::atoi(force) : tuned_config(p, 'm');
     if (forced >= 0) {
         const int i = forced;
-        if (i >= 0 && i < kNumCfg16 && plan16_cfg(p, g, kCfg16[i], t_out)) {
+        // (eight-wave blocks: two per compute unit, hence 64 KB each)
+        if (i >= 0 && i < kNumCfg16 &&
+            plan16_cfg(p, g, kCfg16[i], t_out, i >= kEndKsplit ? 64 * 1024 : kLdsBudget16)) {
             *cfg_idx = i;
             return true;
         }
@@ -528,6 +531,20 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
         if (plan16_cfg(p, g, kCfg16[5], &t) &&
             (long)t.row_blocks * t.img_blocks * t.oc_blocks * p.groups >= 2 * kNumCU) {
             *cfg_idx = 5;
+            *t_out = t;
+            return true;
+        }
+    }
+    // Dense pointwise layers on larger planes that the split kernel does not take (planes of more than 60000 pixels):
+    // a block of eight waves with 128 filters x 128 pixels reads the input half as often as the 64-filter shapes (two
+    // blocks of 64 KB per compute unit).  At N = 256: 128 -> 256 on 56x56 800 -> 705 us, 256 -> 512 on 28x28 602 ->
+    // 555 us, 512 -> 1024 on 14x14 627 -> 570 us; wider or taller blocks (128 x 256, 256 x 64) and four-wave blocks of
+    // 128 x 128 measured behind it.
+    if (pointwise && p.groups == 1 && p.stride == 1) {
+        Tile16 t;
+        if (plan16_cfg(p, g, kCfg16[kEndKsplit], &t, 64 * 1024) &&
+            (long)t.row_blocks * t.img_blocks * t.oc_blocks >= 2 * kNumCU) {
+            *cfg_idx = kEndKsplit;
             *t_out = t;
             return true;
         }
@@ -682,6 +699,7 @@ hipError_t launch16_cfg(int i, const ConvParams &p, const Tile16 &t, hipStream_t
     case 10: return launch16_shape<1, 2, 1, 4, TIN>(p, t, s);
     case 11: return launch16_shape<2, 1, 1, 4, TIN>(p, t, s);
     case 12: return launch16_shape<1, 1, 1, 4, TIN>(p, t, s);
+    case 13: return launch16_shape<4, 2, 2, 4, TIN>(p, t, s);
     }
     return hipErrorNotSupported;
 }
@@ -726,8 +744,7 @@ const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
     if (it != cache.end()) return it->second;
     MfmaPlan pl{};
     const char fam = tuned_family(p);   // offline tile table: may prefer the plain 16x16x4 kernel
-    // (configuration 13 of family 'm' is the 128-filter block of the pointwise kernel)
-    if ((fam == '\0' || (fam == 'm' && tuned_config(p, 'm') == kNumCfg16)) && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
+    if (fam == '\0' && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
     else if (fam == '\0' && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;

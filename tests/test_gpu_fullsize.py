@@ -187,3 +187,10 @@ def test_pack_of_more_elements_than_one_launch_has_threads():
         back = b.gspc_unpack_weights(pw, which)
         assert torch.equal(back, w)
         del back
+
+
+def test_pointwise_on_planes_of_65536_pixels():
+    """Dense pointwise layers on planes past the split kernel's pixel arithmetic keep the 128-filter blocks."""
+    name = _sampled_check(wl.ConvShape(2, 128, 512, 128, 256, 1, 1, 1, 0, 1), wl.make_seed(7, 512, 1), False, n_img=1,
+                          n_oc=4, tol_same=TOL_F32)
+    assert name.startswith("conv_mfma16<4,2,2,4,1,1,1,f32,"), name

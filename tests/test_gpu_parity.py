@@ -507,3 +507,39 @@ def test_pointwise_on_odd_planes_bf16(gpu):
 def test_pointwise_in_128_filter_blocks(gpu, s):
     name = check(gpu, s, seed=wl.make_seed(7, s.Cin, s.H))
     assert name.startswith("conv_mfma16<4,2,2,4,1,1,1,f32"), name
+
+
+def _kernels_in_child(shapes, env=None, before=""):
+    """Kernel names of one launch per (shape, dtype) in a process of its own: the tile table and the tile
+    switches are read once per process."""
+    import subprocess, sys, os, textwrap
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = textwrap.dedent(f"""
+        import sys
+        sys.path.insert(0, {root!r})
+        import torch
+        from paper_2006_09791_amd import binding as b, workloads as wl
+        b.gspc_set_stream()
+        {before}
+        for s, dtype in {[(tuple(s), d) for s, d in shapes]!r}:
+            s = wl.ConvShape(*s)
+            pw = b.gspc_pack_weights(torch.randn(s.Cout, s.Cin // s.groups, s.KH, s.KW, device="cuda"), s.groups, dtype)
+            x = torch.randn(s.N, s.Cin, s.H, s.W, device="cuda")
+            x = b.gspc_pack_input_bf16(x) if dtype == b.GSPC_BF16 else x
+            b.gspc_conv2d_grouped(x, pw, s.N, s.Cin, s.H, s.W, s.Cout, s.KH, s.KW, s.stride, s.pad, s.groups)
+            torch.cuda.synchronize()
+            print("kernel", b.gspc_last_kernel())
+    """)
+    clean = {k: v for k, v in os.environ.items() if not k.startswith("GSPC_")}
+    out = subprocess.run([sys.executable, "-c", code], env=dict(clean, **(env or {})), check=True, capture_output=True,
+                         text=True).stdout
+    return [l.split()[1] for l in out.splitlines() if l.startswith("kernel ")]
+
+
+def test_last_tile_of_the_plain_family_from_the_table(gpu, tmp_path):
+    """Index 13 of family 'm' is the eight-wave block of 128 filters x 128 pixels, for every layer it fits."""
+    shapes = [(S(64, 256, 14, 14, 512, 1, 1, 1, 0, 1), 0), (S(64, 32, 16, 16, 128, 3, 3, 1, 1, 1), 0)]
+    table = tmp_path / "t.tune"
+    table.write_text("".join(" ".join(map(str, tuple(s) + (d, "m 13"))) + "\n" for s, d in shapes))
+    names = _kernels_in_child(shapes, {"GSPC_TUNE_FILE": str(table)})
+    assert names == ["conv_mfma16<4,2,2,4,1,1,1,f32,true>", "conv_mfma16<4,2,2,4,3,3,1,f32,true>"], names
