@@ -196,7 +196,13 @@ int gspc_set_chain_fusion(int on);
  * to it; since the input transform forms differences of inputs, an infinite input
  * can give NaN where the direct sum gives an infinity.  on < 0 (the default): used for such a layer when the launch is large enough
  * to fill the GPU, where it is the faster method; on = 0: never (every layer is the
- * direct sum); on > 0: for every such layer.  Per calling thread.  The environment
+ * direct sum); on > 0: for every such layer.
+ * on = 0 also keeps every fp32 layer on the fp32 matrix instruction.  Otherwise large
+ * pointwise layers and 3x3 layers that suit neither Winograd nor the fp32 kernels are
+ * direct sums on the bf16 one: both operands as exact sums of three bf16 parts, six of
+ * the nine products of a pair, fp32 accumulation.  Over dense sums that is closer to the
+ * exact result than the fp32 instruction; a sum with one non-zero term is off by up to
+ * 1.7 instead of 1.0 times 2^-24 of it.  Per calling thread.  The environment
  * variable GSPC_WINOGRAD=0|1 sets the initial mode of every thread. */
 int gspc_set_winograd(int on);
 

@@ -535,7 +535,7 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
             return true;
         }
     }
-    // Dense pointwise layers on larger planes that the split kernel does not take (planes of more than 60000 pixels):
+    // Dense pointwise layers on larger planes that the split kernel does not take (planes of more than 60000 pixels, Winograd off):
     // a block of eight waves with 128 filters x 128 pixels reads the input half as often as the 64-filter shapes (two
     // blocks of 64 KB per compute unit).  At N = 256: 128 -> 256 on 56x56 800 -> 705 us, 256 -> 512 on 28x28 602 ->
     // 555 us, 512 -> 1024 on 14x14 627 -> 570 us; wider or taller blocks (128 x 256, 256 x 64) and four-wave blocks of
@@ -744,7 +744,9 @@ const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
     if (it != cache.end()) return it->second;
     MfmaPlan pl{};
     const char fam = tuned_family(p);   // offline tile table: may prefer the plain 16x16x4 kernel
-    if (fam == '\0' && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
+    // (Winograd off means fp32 products in the definition's sums: fp32 layers are not split either)
+    const bool may_split = p.in_bf16 || winograd_mode() != 0;
+    if (fam == '\0' && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
     else if (fam == '\0' && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
@@ -754,14 +756,14 @@ const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
         pl.kind = 64;
     else if (fam == '\0' && plan_unit(p, g, &pl.pu)) pl.kind = 19;
-    else if (fam == '\0' && winograd_mode() != 0 && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
+    else if (fam == '\0' && may_split && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
     // few filters per group: the 4x4x1 kernel where it has an instance, else padded 16-filter tiles
     else if (g.variant == kMfma4 && fam != 'm' && plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
-    else if (plan_split(p, g, true, &pl.ps)) pl.kind = 18;
+    else if (may_split && plan_split(p, g, true, &pl.ps)) pl.kind = 18;
     return cache.emplace(k, pl).first->second;
 }
 

@@ -543,3 +543,12 @@ def test_last_tile_of_the_plain_family_from_the_table(gpu, tmp_path):
     table.write_text("".join(" ".join(map(str, tuple(s) + (d, "m 13"))) + "\n" for s, d in shapes))
     names = _kernels_in_child(shapes, {"GSPC_TUNE_FILE": str(table)})
     assert names == ["conv_mfma16<4,2,2,4,1,1,1,f32,true>", "conv_mfma16<4,2,2,4,3,3,1,f32,true>"], names
+
+
+def test_direct_sums_on_request(gpu):
+    """gspc_set_winograd(0): every fp32 layer is the direct sum on the fp32 instruction, pointwise layers included."""
+    shapes = [(S(64, 256, 14, 14, 512, 1, 1, 1, 0, 1), 0), (S(64, 33, 15, 15, 128, 1, 1, 1, 0, 1), 0),
+              (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), 0)]
+    names = _kernels_in_child(shapes, before="b.gspc_set_winograd(0)")
+    assert names[0] == "conv_mfma16<4,2,2,4,1,1,1,f32,true>", names
+    assert not any("split" in n for n in names), names
