@@ -155,6 +155,11 @@ const char *mfma_plan_name(const MfmaPlan *plan);
 // ('\0' = none) and the configuration index forced within a family (-1 = none).
 char tuned_family(const ConvParams &p);
 int tuned_config(const ConvParams &p, char family);
+// While one lives the calling thread sees an empty table.
+struct TuneTableOff {
+    TuneTableOff();
+    ~TuneTableOff();
+};
 
 // bf16 16x16x32 MFMA kernel; plan is opaque to the caller.
 struct MfmaB16Plan {

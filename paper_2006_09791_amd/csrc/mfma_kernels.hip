@@ -736,14 +736,9 @@ struct MfmaPlan {
 
 namespace {
 
-const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
-    thread_local std::unordered_map<PlanKey, MfmaPlan, PlanKeyHash> cache;
-    PlanKey k{{p.N, p.Cin, p.H, p.W, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16,
-               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr) + 8 * (p.wu != nullptr) + 16 * (p.wh != nullptr), winograd_mode()}};
-    auto it = cache.find(k);
-    if (it != cache.end()) return it->second;
+// The kernel for a layer; fam: the family that the tile table asks for ('\0': none).
+MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     MfmaPlan pl{};
-    const char fam = tuned_family(p);   // offline tile table: may prefer the plain 16x16x4 kernel
     // (Winograd off means fp32 products in the definition's sums: fp32 layers are not split either)
     const bool may_split = p.in_bf16 || winograd_mode() != 0;
     if (fam == '\0' && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
@@ -764,6 +759,34 @@ const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
     else if (plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (may_split && plan_split(p, g, true, &pl.ps)) pl.kind = 18;
+    return pl;
+}
+
+// Whether the plan is the kernel and configuration of a tile-table entry.
+bool realises(const MfmaPlan &pl, char fam, int index) {
+    switch (fam) {
+    case 'm': return pl.kind == 16 && pl.idx == index;
+    case 'w': return pl.kind == 17 && pl.pw.inst == index;
+    case 'b': return pl.kind == 32 && pl.pb.inst == index;
+    case 'r': return pl.kind == 33 && pl.pr.inst == index;
+    case 'x': return pl.kind == 64 && pl.px.inst == index;
+    case 'q': return pl.kind == 4 && pl.p4.inst == index;
+    }
+    return false;
+}
+
+const MfmaPlan &get_plan(const ConvParams &p, const PackGeom &g) {
+    thread_local std::unordered_map<PlanKey, MfmaPlan, PlanKeyHash> cache;
+    PlanKey k{{p.N, p.Cin, p.H, p.W, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16,
+               g.variant, p.wm != nullptr, (p.wb != nullptr) + 2 * (p.wr != nullptr) + 4 * (p.ws != nullptr) + 8 * (p.wu != nullptr) + 16 * (p.wh != nullptr), winograd_mode()}};
+    auto it = cache.find(k);
+    if (it != cache.end()) return it->second;
+    const char fam = tuned_family(p);
+    MfmaPlan pl = choose(p, g, fam);
+    if (fam && !realises(pl, fam, tuned_config(p, fam))) {   // the layer as if the table did not have it
+        const TuneTableOff off;
+        pl = choose(p, g, '\0');
+    }
     return cache.emplace(k, pl).first->second;
 }
 

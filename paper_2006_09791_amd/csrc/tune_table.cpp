@@ -8,8 +8,10 @@
 //   N Cin H W Cout KH KW stride pad groups dtype family index
 // dtype 0 = fp32, 1 = bf16; family 'w' = 16x16x4 kernel with resident filters, 'm' = 16x16x4
 // kernel, 'b' = bf16 16x16x32 kernel, 'q' = 4x4x1 kernel, 'x' = Winograd F(2x2, 3x3) kernel, 'r' = bf16 row-product kernel; index = position in that family's
-// configuration list (for 'q': pixel runs per wave, 1 | 2 | 4).  Entries that a planner cannot
-// realise are ignored (the heuristic choice is used).
+// configuration list (for 'q': pixel runs per wave, 1 | 2 | 4).  The kernels without a letter
+// (pointwise and 3x3 on split operands, small launches without staging) are what the heuristics
+// choose between; an entry takes a layer away from them.  Entries that a planner cannot realise
+// are ignored (the heuristic choice is used).
 #include <array>
 #include <cstdio>
 #include <cstdlib>
@@ -29,6 +31,7 @@ struct Entry {
 };
 std::map<Key, Entry> g_table;
 std::once_flag g_once;
+thread_local bool t_off = false;
 
 void load_table() {
     const char *path = std::getenv("GSPC_TUNE_FILE");
@@ -54,7 +57,7 @@ void load_table() {
 
 const Entry *find(const ConvParams &p) {
     std::call_once(g_once, load_table);
-    if (g_table.empty()) return nullptr;
+    if (t_off || g_table.empty()) return nullptr;
     // keyed by the caller's plane size: 1x1 layers reach the planners with re-pitched planes
     const Key k{p.N, p.Cin, p.H0, p.W0, p.Cout, p.KH, p.KW, p.stride, p.pad, p.groups, p.in_bf16 ? 1 : 0};
     auto it = g_table.find(k);
@@ -62,6 +65,9 @@ const Entry *find(const ConvParams &p) {
 }
 
 }  // namespace
+
+TuneTableOff::TuneTableOff() { t_off = true; }
+TuneTableOff::~TuneTableOff() { t_off = false; }
 
 char tuned_family(const ConvParams &p) {
     const Entry *e = find(p);

@@ -552,3 +552,17 @@ def test_direct_sums_on_request(gpu):
     names = _kernels_in_child(shapes, before="b.gspc_set_winograd(0)")
     assert names[0] == "conv_mfma16<4,2,2,4,1,1,1,f32,true>", names
     assert not any("split" in n for n in names), names
+
+
+def test_tile_table_lines_that_cannot_be_realised(gpu, tmp_path):
+    """A line that names a family or a configuration which does not take its layer changes nothing: the layer keeps
+    the kernel it has without a table."""
+    shapes = [(S(64, 256, 14, 14, 512, 1, 1, 1, 0, 1), 0), (S(1, 64, 32, 32, 64, 3, 3, 1, 1, 4), 0),
+              (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), 0), (S(64, 64, 16, 16, 64, 3, 3, 1, 1, 1), 0),
+              (S(8, 50, 11, 13, 50, 3, 3, 1, 1, 1), 1), (S(64, 64, 14, 14, 64, 3, 3, 1, 1, 2), 1)]
+    lines = ["x 2", "w 99", "m 99", "m 99", "r 3", "r 3"]
+    table = tmp_path / "t.tune"
+    table.write_text("".join(" ".join(map(str, tuple(s) + (d, l))) + "\n" for (s, d), l in zip(shapes, lines)))
+    plain = _kernels_in_child(shapes)
+    assert len(set(plain)) == len(shapes) == len(plain), plain
+    assert _kernels_in_child(shapes, {"GSPC_TUNE_FILE": str(table)}) == plain
