@@ -741,17 +741,20 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     MfmaPlan pl{};
     // (Winograd off means fp32 products in the definition's sums: fp32 layers are not split either)
     const bool may_split = p.in_bf16 || winograd_mode() != 0;
-    if (fam == '\0' && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
+    // (GSPC_TILE16, a tuning aid, fixes the tile of the staged kernel: the layers that it shares with these are its own)
+    static const bool tile16 = std::getenv("GSPC_TILE16") != nullptr;
+    const bool any = fam == '\0' && !tile16;
+    if (any && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
-    else if (fam == '\0' && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
-    else if (fam == '\0' && winograd_mode() < 0 && !plan_unit(p, g, &pl.pu) && plan_split3(p, g, kSplit3BeforeWinograd, &pl.ph))
+    else if (any && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
+    else if (any && winograd_mode() < 0 && !plan_unit(p, g, &pl.pu) && plan_split3(p, g, kSplit3BeforeWinograd, &pl.ph))
         pl.kind = 20;
     else if ((winograd_mode() != 0 || fam == 'x') && (fam == 'x' || fam == '\0') &&
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
         pl.kind = 64;
-    else if (fam == '\0' && plan_unit(p, g, &pl.pu)) pl.kind = 19;
-    else if (fam == '\0' && may_split && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
+    else if (any && plan_unit(p, g, &pl.pu)) pl.kind = 19;
+    else if (any && may_split && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
     // few filters per group: the 4x4x1 kernel where it has an instance, else padded 16-filter tiles

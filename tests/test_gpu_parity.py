@@ -566,3 +566,13 @@ def test_tile_table_lines_that_cannot_be_realised(gpu, tmp_path):
     plain = _kernels_in_child(shapes)
     assert len(set(plain)) == len(shapes) == len(plain), plain
     assert _kernels_in_child(shapes, {"GSPC_TUNE_FILE": str(table)}) == plain
+
+
+def test_tile16_switch_holds_for_every_layer_it_fits(gpu):
+    """GSPC_TILE16 names the tile of the plain 16x16x4 kernel; layers that the split kernels or the one without staging
+    would take from it obey too."""
+    shapes = [(S(64, 256, 14, 14, 512, 1, 1, 1, 0, 1), 0), (S(1, 64, 32, 32, 64, 3, 3, 1, 1, 4), 0),
+              (S(5, 60, 29, 37, 84, 3, 3, 1, 1, 3), 0)]
+    names = _kernels_in_child(shapes, {"GSPC_TILE16": "8"})
+    assert names == ["conv_mfma16<1,1,1,4,1,1,1,f32,true>", "conv_mfma16<1,1,1,4,3,3,1,f32,true>",
+                     "conv_mfma16<1,1,1,4,3,3,1,f32,false>"], names
