@@ -40,9 +40,8 @@ template <typename TIN> struct SplitTraits;
 template <> struct SplitTraits<float> { static constexpr int parts = 3; };
 template <> struct SplitTraits<uint16_t> { static constexpr int parts = 1; };
 
-template <int MI, int NI, int WM, int WP, int KH, int KW, int S, typename TIN, bool VO, bool PRE>
-__global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16(ConvParams p, TileSplit t) {
-    static_assert(KH == 1 && KW == 1 && S == 1, "pointwise layers");
+template <int MI, int NI, int WM, int WP, typename TIN, bool VO, bool PRE>
+__global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16s(ConvParams p, TileSplit t) {
     constexpr int NT = 64 * WM * WP, MT = MI * WM, PB = 16 * NI * WP;
     constexpr int NP = SplitTraits<TIN>::parts, ES = (int)sizeof(TIN);
     constexpr int HALF = PB / 2 + 4, PLANE = 2 * HALF;           // 16-byte units: even pixels, odd pixels
@@ -362,7 +361,7 @@ template <int MI, int NI, int WM, int WP, typename TIN, bool VO, bool PRE>
 hipError_t launchS(const ConvParams &p, const TileSplit &t, hipStream_t s) {
     constexpr int NP = SplitTraits<TIN>::parts, PB = 16 * NI * WP;
     constexpr size_t lds = (PRE ? 2 : 1) * (size_t)MI * WM * NP * 1024 + (size_t)NP * 4 * (PB + 8) * 16;
-    auto kern = static_cast<void (*)(ConvParams, TileSplit)>(conv_mfma16<MI, NI, WM, WP, 1, 1, 1, TIN, VO, PRE>);
+    auto kern = conv_mfma16s<MI, NI, WM, WP, TIN, VO, PRE>;
     if (lds > 64 * 1024) {
         static thread_local bool raised = false;   // per instantiation and thread
         if (!raised) {
@@ -427,9 +426,10 @@ hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t 
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgS &c = kCfgS[plan.inst];
     const bool vo = t.HW % 4 == 0;
-    if (!*name) *name = intern_name("conv_mfma16<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
-                        "," + std::to_string(c.WP) + ",1,1,1," + (p.in_bf16 ? "bf16," : "f32,") + (vo ? "true>" : "false>") +
-                        (p.in_bf16 ? "/bf16" : t.pre ? "/split3" : "/split3w"));
+    if (!*name)
+        *name = intern_name("conv_mfma16s<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) + "," +
+                            std::to_string(c.WP) + (p.in_bf16 ? ",bf16," : ",f32,") + (vo ? "true," : "false,") +
+                            (p.in_bf16 || t.pre ? "true>" : "false>"));
     switch (plan.inst) {
     case 0: return launchS_type<4, 2, 2, 4>(p, t, vo, s);
     case 1: return launchS_type<4, 2, 1, 4>(p, t, vo, s);

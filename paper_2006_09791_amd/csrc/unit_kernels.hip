@@ -28,9 +28,8 @@ struct TileUnit {
 };
 static_assert(sizeof(TileUnit) <= sizeof(((UnitPlan *)0)->data), "plan storage too small");
 
-template <int MI, int NI, int WM, int NW, int KH, int KW, int S, typename TIN, bool VO>
-__global__ __launch_bounds__(64 * NW) void conv_mfma16(ConvParams p, TileUnit t) {
-    static_assert(MI == 1 && NI == 1 && WM == 1 && sizeof(TIN) == 4 && !VO, "one 16 x 16 tile per block");
+template <int NW, int KH, int S>
+__global__ __launch_bounds__(64 * NW) void conv_mfma16u(ConvParams p, TileUnit t) {
     constexpr bool ROW = KH == 3;
     constexpr int UB = ROW ? 6 : 4;                     // units in flight per wave
     __shared__ float part[NW][16][17];
@@ -145,8 +144,7 @@ namespace {
 
 template <int NW, int KH, int S>
 hipError_t launchU(const ConvParams &p, const TileUnit &t, hipStream_t s) {
-    auto kern = static_cast<void (*)(ConvParams, TileUnit)>(conv_mfma16<1, 1, 1, NW, KH, KH, S, float, false>);
-    hipLaunchKernelGGL(kern, dim3((t.npix + 15) / 16, t.mtiles, p.groups), dim3(64 * NW), 0, s, p, t);
+    hipLaunchKernelGGL((conv_mfma16u<NW, KH, S>), dim3((t.npix + 15) / 16, t.mtiles, p.groups), dim3(64 * NW), 0, s, p, t);
     return hipGetLastError();
 }
 
@@ -205,11 +203,8 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
 hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name) {
     TileUnit t;
     std::memcpy(&t, plan.data, sizeof(t));
-    if (!*name) {
-        const std::string k = std::to_string(p.KH);
-        *name = intern_name("conv_mfma16<1,1,1," + std::to_string(plan.nw) + "," + k + "," + k + "," + std::to_string(p.stride) +
-                            ",f32,false>/unit");
-    }
+    if (!*name)
+        *name = intern_name("conv_mfma16u<" + std::to_string(plan.nw) + "," + std::to_string(p.KH) + "," + std::to_string(p.stride) + ">");
     switch (plan.nw) {
     case 2: return launchU_shape<2>(p, t, s);
     case 4: return launchU_shape<4>(p, t, s);

@@ -74,8 +74,8 @@ SWEEP = [
     S(2, 32, 16, 16, 64, 3, 3, 2, 1, 2),   # KPG = 32, CPG = 16
     S(1, 64, 8, 8, 64, 3, 3, 1, 1, 1),     # KPG = 64
     S(3, 128, 8, 8, 128, 3, 3, 1, 1, 1),   # KPG = 128, odd batch vs images per block
-    S(3, 32, 12, 20, 48, 3, 3, 1, 1, 1),   # resident-filter kernel: rows wider than a 16-pixel run, ragged row blocks
-    S(5, 64, 10, 12, 64, 3, 3, 2, 1, 2),   # the same, stride 2, odd output plane (5x6)
+    S(3, 32, 12, 20, 48, 3, 3, 1, 1, 1),   # rows wider than a 16-pixel run
+    S(5, 64, 10, 12, 64, 3, 3, 2, 1, 2),   # stride 2, odd output plane (5x6)
     S(2, 16, 6, 8, 16, 3, 3, 1, 0, 1),     # no padding
     S(1, 32, 4, 4, 32, 3, 3, 1, 1, 1),     # several images per wave tile, fewer images than that
     S(9, 32, 4, 4, 64, 3, 3, 1, 2, 2),     # pad 2, images per tile not dividing the batch
@@ -125,6 +125,38 @@ def test_sweep_mfma(gpu, s):
         assert e.code == -8      # family has no instance for this layer
         pytest.skip("no matrix-core instance for this shape")
     assert "mfma" in name
+
+
+# The forms of the staged and the resident-filter kernel that the small shapes above do not reach any more, since
+# small launches run without staging: batches past that kernel's limits, direct sums asked for.
+STAGED = [
+    # N Cin H W Cout KH KW stride pad groups; kernel
+    (S(38, 32, 12, 20, 48, 3, 3, 1, 1, 1), "conv_mfma16w<"),     # rows wider than a 16-pixel run, ragged row blocks
+    (S(57, 128, 10, 12, 128, 3, 3, 2, 1, 1), "conv_mfma16w<"),   # the same, stride 2, odd output plane (5x6)
+    (S(53, 64, 8, 8, 64, 3, 3, 1, 1, 1), "conv_mfma16w<"),       # odd batch vs images per block
+    (S(15, 128, 8, 8, 128, 3, 3, 1, 1, 1), "conv_mfma16<"),
+    (S(207, 32, 17, 19, 32, 3, 3, 1, 1, 2), "conv_mfma16<"),     # odd rows: 4-byte staging
+    (S(9, 3, 32, 32, 32, 3, 3, 1, 1, 1), "conv_mfma16<"),        # stem: 3 channels padded to 4
+    (S(17, 32, 32, 32, 64, 1, 1, 2, 0, 1), "conv_mfma16<"),      # 1x1 stride 2
+    (S(11, 64, 14, 14, 128, 1, 1, 1, 0, 1), "conv_mfma16<"),     # pointwise on re-pitched planes
+    (S(137, 32, 6, 10, 32, 1, 1, 1, 0, 2), "conv_mfma16<"),      # grouped pointwise, 60-element planes
+    (S(3, 64, 56, 56, 64, 3, 3, 1, 1, 2), "conv_mfma16"),        # row blocks with a ragged tail
+    (S(85, 512, 7, 7, 512, 3, 3, 1, 1, 32), "conv_mfma16"),      # 49-element planes, 16 filters per group
+    (S(1, 64, 16, 16, 64, 3, 3, 1, 0, 1), "conv_mfma16<"),       # no padding: few blocks, the reduction split over waves
+]
+
+
+@pytest.mark.parametrize("s,kernel", STAGED, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_staged_kernels_past_the_small_launches(gpu, s, kernel):
+    _, b = gpu
+    b.gspc_set_winograd(0)
+    try:
+        name = check(gpu, s, seed=14)
+    finally:
+        b.gspc_set_winograd(None)
+    assert name.startswith(kernel) and not name.startswith(("conv_mfma16u<", "conv_mfma16s<")), name
+    if s.pad == 0 and s.KH == 3:
+        assert name.endswith("/ksplit"), name
 
 
 @pytest.mark.parametrize("g", [1, 2, 4, 8, 16])
@@ -438,53 +470,68 @@ def test_tile_table_is_keyed_by_the_callers_plane_size(gpu, tmp_path):
 # Filters per group that are not a multiple of 16 (the G(g) forms of a MobileNetV2-shaped
 # network, Section IV-A: 96, 144, 192, 384, 576 and 960 channels over 2..16 groups): the plain
 # 16x16x4 kernel zero-pads the last filter tile and drops its padding filters at the store.
-PADDED_TILES = [
-    S(2, 960, 7, 7, 960, 3, 3, 1, 1, 8),     # 120 filters: 8 tiles, the last half empty; scalar stores
-    S(1, 144, 28, 28, 144, 3, 3, 1, 1, 2),   # 72: 5 tiles; 16-byte stores
-    S(3, 144, 28, 28, 144, 3, 3, 2, 1, 2),   # stride 2
-    S(2, 240, 14, 14, 240, 3, 3, 1, 1, 4),   # 60
-    S(2, 144, 20, 20, 144, 3, 3, 1, 1, 4),   # 36
-    S(1, 96, 56, 56, 96, 3, 3, 2, 1, 4),     # 24
-    S(2, 144, 14, 14, 144, 3, 3, 1, 1, 8),   # 18 filters and 18 channels: both edges padded
-    S(2, 192, 28, 28, 192, 3, 3, 2, 1, 16),  # 12
-    S(3, 144, 12, 12, 144, 3, 3, 1, 1, 16),  # 9
-    S(2, 96, 16, 16, 96, 3, 3, 2, 1, 16),    # 6
-    S(2, 20, 9, 9, 20, 3, 3, 1, 1, 4),       # 5, odd plane
-    S(2, 144, 28, 28, 24, 1, 1, 1, 0, 1),    # pointwise projection to 24 channels
-    S(3, 96, 7, 7, 40, 1, 1, 1, 0, 1),       # pointwise, 49-element planes
-    S(70, 144, 14, 14, 144, 3, 3, 1, 1, 2),  # 72 at a batch that fills the chip (larger block shapes)
+PADDED_TILES = [   # shape at a batch for the kernel without staging (None: not small); batch for the staged kernel
+    (S(2, 960, 7, 7, 960, 3, 3, 1, 1, 8), 7),      # 120 filters: 8 tiles, the last half empty; scalar stores
+    (S(1, 144, 28, 28, 144, 3, 3, 1, 1, 2), 3),    # 72: 5 tiles; 16-byte stores
+    (S(3, 144, 28, 28, 144, 3, 3, 2, 1, 2), 13),   # stride 2
+    (S(2, 240, 14, 14, 240, 3, 3, 1, 1, 4), 13),   # 60
+    (S(2, 144, 20, 20, 144, 3, 3, 1, 1, 4), 5),    # 36
+    (S(1, 96, 56, 56, 96, 3, 3, 2, 1, 4), 13),     # 24
+    (S(2, 144, 14, 14, 144, 3, 3, 1, 1, 8), 35),   # 18 filters and 18 channels: both edges padded
+    (S(2, 192, 28, 28, 192, 3, 3, 2, 1, 16), 47),  # 12
+    (S(3, 144, 12, 12, 144, 3, 3, 1, 1, 16), 31),  # 9
+    (S(2, 96, 16, 16, 96, 3, 3, 2, 1, 16), 209),   # 6
+    (S(2, 20, 9, 9, 20, 3, 3, 1, 1, 4), 103),      # 5, odd plane
+    (S(2, 144, 28, 28, 24, 1, 1, 1, 0, 1), 21),    # pointwise projection to 24 channels
+    (S(3, 96, 7, 7, 40, 1, 1, 1, 0, 1), 727),      # pointwise, 49-element planes
+    (None, S(70, 144, 14, 14, 144, 3, 3, 1, 1, 2)),  # 72 at a batch that fills the chip (larger block shapes)
 ]
+PADDED_CASES = [(s, "conv_mfma16u<") for s, _ in PADDED_TILES if s] + [
+    (s._replace(N=n) if s else n, "conv_mfma16<") for s, n in PADDED_TILES]
 
 
-@pytest.mark.parametrize("s", PADDED_TILES, ids=lambda s: "x".join(map(str, s)))
-def test_filters_per_group_not_a_multiple_of_16(gpu, s):
+@pytest.mark.parametrize("s,kernel", PADDED_CASES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_filters_per_group_not_a_multiple_of_16(gpu, s, kernel):
     _, b = gpu
     b.gspc_set_winograd(0)   # the direct kernel is the one under test (large launches would take Winograd)
     try:
         name = check(gpu, s, seed=23)
     finally:
         b.gspc_set_winograd(None)
-    assert name.startswith("conv_mfma16<"), name
+    assert name.startswith(kernel), name
 
 
 # 1x1 layers on planes whose size is not a multiple of 4: the plane travels as one row of H*W elements
-# and, where a block covers one image, four channels at a time are staged as one aligned row.
-ODD_PLANES = [
-    S(3, 64, 5, 5, 64, 1, 1, 1, 0, 1),
-    S(2, 32, 9, 9, 48, 1, 1, 1, 0, 2),       # grouped, three filter tiles
-    S(5, 128, 13, 13, 64, 1, 1, 1, 0, 1),    # 169-element planes
-    S(2, 64, 15, 15, 32, 1, 1, 1, 0, 1),     # 225
-    S(3, 24, 3, 3, 16, 1, 1, 1, 0, 1),       # 9: smaller than any tile
-    S(70, 160, 7, 7, 960, 1, 1, 1, 0, 1),    # MobileNetV2 expansion at a batch that fills the chip
-    S(1, 960, 7, 7, 160, 1, 1, 1, 0, 1),     # projection at batch 1: 240 k-steps
-    S(2, 6, 7, 7, 16, 1, 1, 1, 0, 1),        # padded channels: single row, but no four-channel staging
-    S(4, 40, 7, 9, 40, 1, 1, 1, 0, 2),       # non-square, 63 elements, 20 filters per group
+# and, where a block of the staged kernel covers one image, four channels at a time are staged as one aligned row.
+ODD_PLANES = [   # shape; the batch at which the staged kernel has it when direct sums are asked for
+    (S(3, 64, 5, 5, 64, 1, 1, 1, 0, 1), 1601),
+    (S(2, 32, 9, 9, 48, 1, 1, 1, 0, 2), 51),       # grouped, three filter tiles
+    (S(5, 128, 13, 13, 64, 1, 1, 1, 0, 1), 119),   # 169-element planes
+    (S(2, 64, 15, 15, 32, 1, 1, 1, 0, 1), 357),    # 225
+    (S(3, 24, 3, 3, 16, 1, 1, 1, 0, 1), 1821),     # 9: smaller than any tile
+    (S(70, 160, 7, 7, 960, 1, 1, 1, 0, 1), 70),    # MobileNetV2 expansion at a batch that fills the chip
+    (S(1, 960, 7, 7, 160, 1, 1, 1, 0, 1), 23),     # projection: 240 k-steps
+    (S(2, 6, 7, 7, 16, 1, 1, 1, 0, 1), 335),       # padded channels: single row, but no four-channel staging
+    (S(4, 40, 7, 9, 40, 1, 1, 1, 0, 2), 67),       # non-square, 63 elements, 20 filters per group
+    (S(4, 512, 7, 7, 512, 1, 1, 1, 0, 1), 17),     # one tile per wave
 ]
 
 
-@pytest.mark.parametrize("s", ODD_PLANES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("s", [s for s, _ in ODD_PLANES], ids=lambda s: "x".join(map(str, s)))
 def test_pointwise_on_odd_planes(gpu, s):
-    check(gpu, s, seed=29)
+    name = check(gpu, s, seed=29)
+    assert name.startswith("conv_mfma16s<" if s.N == 70 else "conv_mfma16u<"), name
+
+
+@pytest.mark.parametrize("s", [s._replace(N=n) for s, n in ODD_PLANES], ids=lambda s: "x".join(map(str, s)))
+def test_pointwise_on_odd_planes_staged(gpu, s):
+    _, b = gpu
+    b.gspc_set_winograd(0)
+    try:
+        name = check(gpu, s, seed=28)
+    finally:
+        b.gspc_set_winograd(None)
+    assert name.startswith("conv_mfma16<"), name
 
 
 def test_pointwise_on_odd_planes_bf16(gpu):
@@ -498,15 +545,22 @@ def test_pointwise_on_odd_planes_bf16(gpu):
 
 
 # Dense pointwise layers with at least 128 filters at batches that give every compute unit two blocks run in
-# eight-wave blocks of 128 filters x 128 pixels.
+# eight-wave blocks of 128 filters x 128 pixels, on split operands or, direct sums asked for, on the fp32 instruction.
+@pytest.mark.parametrize("winograd,kernel", [(None, "conv_mfma16s<4,2,2,4,f32,"), (0, "conv_mfma16<4,2,2,4,1,1,1,f32,")],
+                         ids=["split", "fp32"])
 @pytest.mark.parametrize("s", [
     S(48, 64, 28, 28, 256, 1, 1, 1, 0, 1),     # 784-pixel planes: tiles straddle images
     S(113, 96, 30, 20, 128, 1, 1, 1, 0, 1),    # ragged last pixel tile, one filter block
     S(140, 160, 14, 14, 384, 1, 1, 1, 0, 1),   # 14x14 planes (re-pitched to rows of 4), three filter blocks
 ], ids=lambda s: "x".join(map(str, s)))
-def test_pointwise_in_128_filter_blocks(gpu, s):
-    name = check(gpu, s, seed=wl.make_seed(7, s.Cin, s.H))
-    assert name.startswith("conv_mfma16<4,2,2,4,1,1,1,f32"), name
+def test_pointwise_in_128_filter_blocks(gpu, s, winograd, kernel):
+    _, b = gpu
+    b.gspc_set_winograd(winograd)
+    try:
+        name = check(gpu, s, seed=wl.make_seed(7, s.Cin, s.H))
+    finally:
+        b.gspc_set_winograd(None)
+    assert name.startswith(kernel), name
 
 
 def _kernels_in_child(shapes, env=None, before=""):
@@ -551,7 +605,7 @@ def test_direct_sums_on_request(gpu):
               (S(40, 128, 14, 14, 128, 3, 3, 1, 1, 1), 0)]
     names = _kernels_in_child(shapes, before="b.gspc_set_winograd(0)")
     assert names[0] == "conv_mfma16<4,2,2,4,1,1,1,f32,true>", names
-    assert not any("split" in n for n in names), names
+    assert not any(n.startswith(("conv_mfma16s<", "conv_split3<")) for n in names), names
 
 
 def test_tile_table_lines_that_cannot_be_realised(gpu, tmp_path):

@@ -40,9 +40,11 @@ SHAPES = [
 def test_pointwise_split(gpu, s, shape, bf16):
     torch, b = gpu
     if s.N == 1 and not bf16:
-        pytest.skip("a small fp32 launch: conv_mfma16 without staging (test_gpu_unit.py)")
+        pytest.skip("a small fp32 launch: the kernel without staging (test_gpu_unit.py)")
     y, x, w, name = run_conv(gpu, s, seed=51, dtype=b.GSPC_BF16 if bf16 else b.GSPC_F32)
-    assert name.startswith("conv_mfma16<" + shape) and name.endswith("/bf16" if bf16 else "/split3" if s.Cin * s.Cout > 16384 else "/split3w"), name
+    # last template argument: the filters were split when they were packed
+    form = ("bf16,", "true>") if bf16 else ("f32,", "true>" if s.Cin * s.Cout > 16384 else "false>")
+    assert name.startswith("conv_mfma16s<" + shape) and form[0] in name and name.endswith(form[1]), name
     if bf16:
         x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
     ref, absum = oracle.conv2d_grouped(x, w, 1, 0, s.groups, return_abs=True, threads=8)
@@ -68,7 +70,7 @@ def test_pointwise_split_epilogue_and_buffer_ends(gpu, hw, cout):
                                                         torch.from_numpy(res).to(dev).reshape(-1),
                                                         yd[guard:guard + res.size]]))
     torch.cuda.synchronize()
-    assert b.gspc_last_kernel().endswith(("/split3", "/split3w")), b.gspc_last_kernel()
+    assert b.gspc_last_kernel().startswith("conv_mfma16s<"), b.gspc_last_kernel()
     out = yd.cpu().numpy()
     assert np.isnan(out[:guard]).all() and np.isnan(out[guard + res.size:]).all()
     ref = oracle.relu(oracle.add(oracle.conv2d_grouped(x, w, 1, 0, 1, threads=8), res))
@@ -85,7 +87,7 @@ def test_pointwise_split_keeps_its_precision_at_any_scale(gpu, exponent):
     pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), 1)
     y = b.gspc_conv2d_grouped(torch.from_numpy(x).to(dev), pw, 150, 32, 16, 16, 64, 1, 1, 1, 0, 1)
     torch.cuda.synchronize()
-    assert b.gspc_last_kernel().endswith(("/split3", "/split3w")), b.gspc_last_kernel()
+    assert b.gspc_last_kernel().startswith("conv_mfma16s<"), b.gspc_last_kernel()
     y = y.cpu().numpy().astype(np.float64)
     ref, absum = oracle.conv2d_grouped(x, w, 1, 0, 1, return_abs=True, threads=8)
     # (plus half a unit of the smallest denormal per product and for the result)
@@ -116,7 +118,8 @@ def test_pointwise_split_keeps_its_precision_in_either_operand(gpu, ex, ew, cin,
     pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), 1)
     y = b.gspc_conv2d_grouped(torch.from_numpy(x).to(dev), pw, N, cin, hw, hw, cout, 1, 1, 1, 0, 1)
     torch.cuda.synchronize()
-    assert b.gspc_last_kernel().endswith("/split3" if cin * cout > 16384 else "/split3w"), b.gspc_last_kernel()
+    name = b.gspc_last_kernel()
+    assert name.startswith("conv_mfma16s<") and name.endswith("true>" if cin * cout > 16384 else "false>"), name
     y = y.cpu().numpy().astype(np.float64)
     ref, absum = oracle.conv2d_grouped(x, w, 1, 0, 1, return_abs=True, threads=8)
     assert np.isfinite(y).all()
@@ -137,7 +140,7 @@ def test_pointwise_split_of_values_that_do_not_split(gpu, value, hw, cout):
     pw = b.gspc_pack_weights(torch.from_numpy(w).to(dev), 1)
     y = b.gspc_conv2d_grouped(torch.from_numpy(x).to(dev), pw, N, cin, hw, hw, cout, 1, 1, 1, 0, 1)
     torch.cuda.synchronize()
-    assert b.gspc_last_kernel().endswith(("/split3", "/split3w")), b.gspc_last_kernel()
+    assert b.gspc_last_kernel().startswith("conv_mfma16s<"), b.gspc_last_kernel()
     y = y.cpu().numpy().astype(np.float64)
     ref = np.einsum("kc,nchw->nkhw", w[:, :, 0, 0].astype(np.float64), x.astype(np.float64))
     with np.errstate(invalid="ignore"):

@@ -30,7 +30,7 @@ SHAPES = [
 @pytest.mark.parametrize("s", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_unit_kernel(gpu, s):
     y, x, w, name = run_conv(gpu, s, seed=61)
-    assert name.startswith("conv_mfma16<1,1,1,") and name.endswith("/unit"), name
+    assert name.startswith("conv_mfma16u<"), name
     assert not np.isnan(y).any(), name
     ref, absum = oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, return_abs=True, threads=8)
     m = err_metrics(y, ref, absum)
@@ -59,7 +59,7 @@ def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
     layer = wl.Layer("conv", 0, 1, 2, s.N, s.Cin, s.H, s.W, s.Cout, s.KH, s.KW, s.stride, s.pad, s.groups, True, 0)
     b.gspc_run_layer_chain(b.LayerChain([layer], [pw], [xd, rd, yd]))
     torch.cuda.synchronize()
-    assert b.gspc_last_kernel().endswith("/unit"), b.gspc_last_kernel()
+    assert b.gspc_last_kernel().startswith("conv_mfma16u<"), b.gspc_last_kernel()
     out = big[2].cpu().numpy()
     assert np.isnan(out[:guard]).all() and np.isnan(out[guard + res.size:]).all()
     ref = oracle.relu(oracle.add(oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, threads=8), res))
