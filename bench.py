@@ -34,7 +34,6 @@ if ROOT not in sys.path:
 
 GROUPS = (1, 2, 4, 8, 16)
 BATCH = 64
-PEAK_F32_MFMA_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
@@ -50,27 +49,35 @@ def layer_flops_bytes(l):
     return 2 * macs, nbytes
 
 
+def compute_bound(name, flops, nbytes):
+    """Whether a layer of these Eq. 2 flops and bytes lies right of its kernel's ridge: 157.3 TFLOP/s / 8 TB/s = 19.7
+    flop/B on the fp32 instruction, 2500 / 6 / 8 = 52 on split operands."""
+    from paper_2006_09791_amd import layer_timing
+    _, executed, peak = layer_timing.executed_work(name)
+    return flops / nbytes > peak / max(executed, 1.0) * 1e3 / PEAK_HBM_GBS
+
+
 def _roofline_object(name, k, kernels):
     """Roofline object of one kernel instance: its summed algorithmic work over its summed event-timed
     duration, against the matrix-core peak (compute-bound layers) or the HBM peak."""
+    from paper_2006_09791_amd import layer_timing
     traffic = None
     if os.path.exists(TRAFFIC_FILE):
         try:
             traffic = json.load(open(TRAFFIC_FILE)).get(name)
         except Exception:
             traffic = None
-    if ("mfma" in name or "wino" in name) and k["compute_bound"]:
-        ach = k["flops"] / k["time"] / 1e12
-        roofline = {"bound": "mfma", "achieved": round(ach, 2), "peak": PEAK_F32_MFMA_TFLOPS,
-                    "unit": "TFLOP/s", "frac": round(ach / PEAK_F32_MFMA_TFLOPS, 4)}
-        if "wino" in name:
-            # Eq. 2 counts the multiplications of the direct sum; the Winograd kernel executes 16/36 of them.
-            # `achieved` and `frac` are the executed work against the matrix-core peak (a roofline fraction);
-            # the Eq. 2 rate is an effective figure and is reported as such, without a fraction.
-            roofline["algorithm"] = "winograd F(2x2,3x3): executes 16/36 of the Eq. 2 multiplications"
-            roofline["eq2_effective_tflops"] = round(ach, 2)
-            roofline["achieved"] = round(ach * 16.0 / 36.0, 2)
-            roofline["frac"] = round(ach * 16.0 / 36.0 / PEAK_F32_MFMA_TFLOPS, 4)
+    if any(f in name for f in ("mfma", "wino", "split3")) and k["compute_bound"]:
+        # Where a kernel executes another number of multiplications than Eq. 2 counts, `achieved` and `frac` are the
+        # executed work against the peak of the instruction that does it (a roofline fraction); the Eq. 2 rate is
+        # an effective figure and is reported as such, without a fraction.
+        algorithm, executed, peak = layer_timing.executed_work(name)
+        eq2 = k["flops"] / k["time"] / 1e12
+        roofline = {"bound": "mfma", "achieved": round(eq2 * executed, 2), "peak": peak,
+                    "unit": "TFLOP/s", "frac": round(eq2 * executed / peak, 4)}
+        if algorithm:
+            roofline["algorithm"] = algorithm
+            roofline["eq2_effective_tflops"] = round(eq2, 2)
     else:
         ach = k["bytes"] / k["time"] / 1e9
         roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS,
@@ -374,8 +381,7 @@ def main():
                 k["flops"] += flops * count
                 k["bytes"] += nbytes * count
                 k["launches"] += count
-                # fp32 ridge of this GPU: 157.3 TFLOP/s / 8 TB/s = 19.7 flop/B
-                if flops / nbytes > PEAK_F32_MFMA_TFLOPS * 1e3 / PEAK_HBM_GBS:
+                if compute_bound(name, flops, nbytes):
                     k["compute_bound"] = True
         name, k = max(kernels.items(), key=lambda kv: kv[1]["time"])
         roofline = _roofline_object(name, k, kernels)

@@ -3,8 +3,9 @@
 Each layer is replayed back to back inside one recorded layer chain (no host in
 the loop) and timed with events on the launch stream.  Returns rows with the
 Eq. 2 MAC count, the algorithmic bytes and the fractions of the nominal MI355X
-ceilings (fp32 MFMA 157.3 TFLOP/s, bf16 MFMA 2500 TFLOP/s, HBM 8 TB/s).  Rows of the
-Winograd kernel report the executed multiplications (16/36 of Eq. 2's) against the peak.
+ceilings (fp32 MFMA 157.3 TFLOP/s, bf16 MFMA 2500 TFLOP/s, HBM 8 TB/s).  Rows of kernels that
+execute another number of multiplications than Eq. 2 counts report the executed ones against the
+peak of the instruction that executes them (`executed_work`).
 """
 import numpy as np
 
@@ -13,6 +14,16 @@ from . import workloads as wl
 
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
+
+
+def executed_work(kernel, dtype="f32"):
+    """(algorithm or None, multiplications executed per one of Eq. 2, peak TFLOP/s of their instruction) of a
+    kernel that ran a layer of this dtype."""
+    if kernel.startswith("conv_wino<"):
+        return "winograd F(2x2,3x3): executes 16/36 of the Eq. 2 multiplications", 16.0 / 36.0, PEAK_TFLOPS["f32"]
+    if kernel.startswith(("conv_mfma16s<", "conv_split3<")) and ",f32," in kernel:
+        return "three-part bf16 split: executes six bf16 products per Eq. 2 multiplication", 6.0, PEAK_TFLOPS["bf16"]
+    return None, 1.0, PEAK_TFLOPS[dtype]
 
 
 def layer_bytes(s, in_bytes):
@@ -59,18 +70,16 @@ def time_layers(shapes, dtype="f32", inner=10, reps=10, rotate=1):
         us = e0.elapsed_time(e1) / (reps * inner) * 1e3
         macs = wl.conv_macs(s)
         nbytes = layer_bytes(s, 2 if dtype == "bf16" else 4)
+        algorithm, executed, peak = executed_work(name, dtype)
         row = {
             "layer": f"{s.Cin}->{s.Cout} {s.H}x{s.W} k{s.KH} s{s.stride} g{s.groups} N{s.N}",
             "kernel": name, "us": round(us, 2), "gmacs": round(macs / us / 1e3, 1),
             "tflops": round(2 * macs / us / 1e6, 2), "gbs": round(nbytes / us / 1e3, 1),
-            "frac_mfma": round(2 * macs / us / 1e6 / PEAK_TFLOPS[dtype], 4),
+            "frac_mfma": round(2 * macs * executed / us / 1e6 / peak, 4),
             "frac_hbm": round(nbytes / us / 1e3 / PEAK_HBM_GBS, 4),
         }
-        if name.startswith("conv_wino"):
-            # Winograd F(2x2, 3x3) executes 16/36 of the multiplications Eq. 2 counts: `tflops` is an
-            # effective rate (no fraction of a peak belongs to it), `frac_mfma` the executed work's share
-            row["algorithm"] = "winograd"
-            row["frac_mfma"] = round(row["frac_mfma"] * 16.0 / 36.0, 4)
+        if algorithm:   # `tflops` is an effective rate then: no fraction of a peak belongs to it
+            row["algorithm"] = algorithm
         rows.append(row)
         del bufs, lc
     b.gspc_set_chain_fusion(1)
