@@ -97,7 +97,9 @@ size_t gspc_packed_weight_bytes(int Cin, int Cout, int KH, int KW, int groups,
  * (nearest-even) on the way.  packed_dev (dev, packed_bytes >=
  * gspc_packed_weight_bytes(...), 256-byte aligned) is caller-owned and must
  * outlive the handle; *out receives a host descriptor to be released with
- * gspc_packed_free.  Meant to run once per layer, ahead of time. */
+ * gspc_packed_free.  Meant to run once per layer, ahead of time.  The buffer
+ * holds the weights once per kernel family that may run the layer: six to
+ * seven times their size for wide fp32 3x3 layers, four and a half to five for 1x1. */
 int gspc_pack_weights(const void *weight_dev, int Cin, int Cout, int KH, int KW,
                       int groups, int dtype, void *packed_dev,
                       size_t packed_bytes, gspc_packed_t **out);
@@ -133,7 +135,14 @@ int gspc_pack_input_bf16(const void *in_dev, size_t count, void *out_dev);
  * Both pointers must be 16-byte aligned (GSPC_ERR_ARG otherwise): the kernels
  * move 16 bytes per lane wherever the row width allows.
  * (Cin, Cout, KH, KW, groups) must equal those of the handle
- * (GSPC_ERR_MISMATCH otherwise).  Asynchronous on the selected stream. */
+ * (GSPC_ERR_MISMATCH otherwise).  Asynchronous on the selected stream.
+ * Infinities and NaN reach the outputs whose sums contain them.  Where a layer is
+ * evaluated with zero weights in between they can also turn other outputs into
+ * NaN: in neighbouring groups where several are evaluated as one (fp32: fewer than
+ * 8 channels or filters per group; bf16: fewer than 16 channels, or channels or
+ * filters that are no multiples of 8 and 4), and in neighbouring columns where bf16
+ * layers run as row products (at most 16 channels per group); with Winograd
+ * (below) in the outputs around theirs. */
 int gspc_conv2d_grouped(const void *input, const gspc_packed_t *packed_weight,
                         int N, int Cin, int H, int W, int Cout, int KH, int KW,
                         int stride, int pad, int groups, void *output);

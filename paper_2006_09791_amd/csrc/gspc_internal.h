@@ -94,7 +94,9 @@ struct PackGeom {
     size_t unit_bytes, unit_offset;
     // Split 3x3 section (3x3, KPG >= 16, CPG >= 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
     // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles, with more than 16384 weights per
-    // group or CPG % 4 != 0: the three parts of the exact split of 2^24 times a weight; GSPC_BF16 handles with CPG % 8 != 0
+    // group (smaller ones stay a mere reordering of the weights besides Winograd's section; with the section they would
+    // be faster where Winograd now has them: 32 -> 96 in two groups on 14x14 at N = 256 25.2 / 21.1 us, 16 -> 64 on
+    // 18x18 25.8 / 19.6, stride 2 24 -> 64 on 28x28 26.5 / 20.3, 32 -> 32 per group level or behind) or CPG % 4 != 0: the three parts of the exact split of 2^24 times a weight; GSPC_BF16 handles with CPG % 8 != 0
     // (no 16x16x32 section): the weight.
     size_t h3_bytes, h3_offset;
     struct MergedDirect {

@@ -8,8 +8,8 @@
 // What bounds it, at 128 filters x 128 pixels: a chunk is 3072 clocks of matrix work per SIMD for the two
 // blocks of a compute unit (128 registers, 76 KB of LDS each), during which the LDS moves 2 x 18 KB per wave
 // to the operands and 2 x 48 KB in; the two blocks cover each other's barriers, and the matrix unit is busy
-// 0.52 of the time (counters; 0.39 of it the LDS).  512 -> 1024 on 14x14, N = 256: 270 us = 195 TFLOP/s
-// (572 us on the fp32 instruction); a register loop of the same products reaches 300.
+// 0.60 of a compute unit's busy time, the LDS 0.38 (counters), at a clock of 1.84 GHz.  512 -> 1024 on 14x14,
+// N = 256: 278 us = 189 TFLOP/s (572 us on the fp32 instruction); a register loop of the same products reaches 300.
 //  - filters: in operand order; split at packing time (PRE): global -> LDS directly (no registers), the next
 //    chunk's while this one multiplies (two buffers); or, filter matrices of up to 64 KB, as fp32 words that
 //    are split on the way through registers;
@@ -347,7 +347,7 @@ struct CfgS {
     int cost;         // time per filter and pixel (padding included), relative to the first shape's 100
 };
 // Block shapes, measured on the pointwise layers of the MobileNet-shaped and paper-form networks (fp32, N = 1,
-// 16, 64, 256; us):
+// 16, 64, 256; us, the four shapes in one session):
 //   512 -> 1024 on 14x14, N = 256: 270 / 311 / 413 / 455 (572 for the fp32 instruction in 128 x 128 blocks);
 //   32 -> 64 on 112x112, N = 256: 281 / 237 / 273 / 322 (291); 96 -> 24 on 56x56, N = 64: 31 / 25 / 20.3 / 21.5 (26.9);
 //   512 -> 512 on 14x14, N = 64 (392 / 784 / .. blocks): 41 / 55 / 57 / 60 (77), N = 16 (100 / 200 / 400 / 800 blocks):
