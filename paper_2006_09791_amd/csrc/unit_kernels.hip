@@ -192,9 +192,11 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
     if (t.units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
     if ((row ? p.stride == 1 && t.units < 9 : wide && t.units < 12) && tiles > 8 * kNumCU) return false;
-    // waves per block: what lets every wave request all of its units at once, more while the launch is small
+    // waves per block: what lets every wave request all of its units at once, more as long as all of the launch's waves
+    // still start together, eight per compute unit: one block too many costs its start anew (8 -> 16 on 12x12, g = 2,
+    // N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time)
     int nw = 2;
-    while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw < 8 * kNumCU && t.units > nw))) nw *= 2;
+    while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw * 2 <= 8 * kNumCU && t.units > nw))) nw *= 2;
     out->nw = nw;
     std::memcpy(out->data, &t, sizeof(t));
     return true;

@@ -40,6 +40,18 @@ def test_unit_kernel(gpu, s):
     assert m["floored"] < 1e-5, (name, m)
 
 
+@pytest.mark.parametrize("s,waves", [
+    (S(1, 64, 32, 32, 64, 3, 3, 1, 1, 4), 8),      # 256 tiles
+    (S(21, 16, 12, 12, 32, 3, 3, 1, 1, 2), 4),     # 378 tiles of six units
+    (S(6, 64, 16, 16, 128, 3, 3, 1, 1, 4), 2),     # 768 tiles of twelve
+    (S(93, 96, 7, 7, 16, 1, 1, 1, 0, 2), 2),       # 570 tiles
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_unit_kernel_waves_start_together(gpu, s, waves):
+    """Blocks get more waves than their units need only while the launch keeps to eight waves per compute unit."""
+    name = run_conv(gpu, s, seed=62)[3]
+    assert name.startswith(f"conv_mfma16u<{waves},"), name
+
+
 @pytest.mark.parametrize("s", [S(2, 48, 9, 7, 40, 3, 3, 1, 1, 2), S(3, 40, 7, 7, 24, 1, 1, 2, 0, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
