@@ -744,6 +744,18 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     // (GSPC_TILE16, a tuning aid, fixes the tile of the staged kernel: the layers that it shares with these are its own)
     static const bool tile16 = std::getenv("GSPC_TILE16") != nullptr;
     const bool any = fam == '\0' && !tile16;
+    // fp32 3x3 layers with few filters per group, on rows of a multiple of 4, where only the channels per group are odd:
+    // the split kernel's tiles have 64 filters, so a group of 16 leaves three of four rows empty, and the staged kernel
+    // still reads four elements at a time.  Split / staged, us: 16 filters, 11 channels on 32x32, g = 2, N = 155 44.7 /
+    // 18.3, 18 on 24x24, g = 4, N = 72 34.5 / 21.7, 21 at stride 2 on 32x32, g = 8, N = 148 81 / 51, from 25 on level or
+    // the split kernel's (27 on 20x20 at stride 1, g = 2, N = 183 29.8 / 39.9); 24 filters, 9 channels on 32x32, g = 4,
+    // N = 32 20.6 / 14.9, 28 filters, 10 channels g = 4, N = 170 100 / 63.
+    const auto few_filters = [&] {
+        int idx;
+        Tile16 t;
+        return !p.in_bf16 && p.W % 4 == 0 && g.CPG % 4 != 0 && (g.KPG <= 16 ? g.CPG < 25 : g.KPG < 32 && g.CPG <= 12) &&
+               plan16(p, g, &idx, &t);
+    };
     if (any && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
@@ -754,7 +766,7 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
         pl.kind = 64;
     else if (any && plan_unit(p, g, &pl.pu)) pl.kind = 19;
-    else if (any && may_split && plan_split3(p, g, kSplit3Else, &pl.ph)) pl.kind = 20;
+    else if (any && may_split && plan_split3(p, g, kSplit3Else, &pl.ph) && !few_filters()) pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
     // few filters per group: the 4x4x1 kernel where it has an instance, else padded 16-filter tiles

@@ -45,6 +45,27 @@ def test_split3(gpu, s, kind):
     assert m["floored"] < 1e-5, (name, m)
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(40, 46, 24, 24, 32, 3, 3, 1, 1, 2), "conv_mfma16<"),       # 23 channels, 16 filters: rows read four at a time
+    (S(260, 46, 25, 24, 32, 3, 3, 2, 1, 2), "conv_mfma16<"),       # at stride 2
+    (S(40, 50, 24, 24, 32, 3, 3, 1, 1, 2), "conv_split3<"),       # 25 channels
+    (S(100, 46, 24, 22, 32, 3, 3, 1, 1, 2), "conv_split3<"),       # rows read one at a time
+    (S(40, 22, 24, 24, 56, 3, 3, 1, 1, 2), "conv_mfma16<"),       # 11 channels, 28 filters
+    (S(40, 22, 24, 24, 64, 3, 3, 1, 1, 2), "conv_split3<"),       # 32 filters
+    (S(40, 26, 24, 24, 56, 3, 3, 1, 1, 2), "conv_split3<"),       # 13 channels
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_layers_of_few_filters(gpu, s, kernel):
+    """Few filters per group leave most of the 64-filter tiles empty: the staged kernel, where it reads whole quads."""
+    y, x, w, name = run_conv(gpu, s, seed=72)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    m = err_metrics(y, ref, absum)
+    # (split: as above; else a product and a sum per term, each rounded once at most)
+    k = 9 * s.Cin // s.groups
+    bound = split_bound(k + 16) + 4 * 2.0 ** -24 if name.startswith("conv_split3<") else (k + 17) * 2.0 ** -24
+    assert m["bound"] < bound, (name, m)
+
+
 @pytest.mark.parametrize("s", [S(40, 64, 14, 14, 72, 3, 3, 1, 1, 1), S(64, 128, 8, 8, 128, 3, 3, 1, 1, 1),
                                S(150, 67, 7, 9, 80, 3, 3, 1, 1, 1)], ids=lambda s: "x".join(map(str, s)))
 def test_split3_epilogue_and_buffer_ends(gpu, s):
