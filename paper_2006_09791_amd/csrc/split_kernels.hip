@@ -392,6 +392,12 @@ bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan
     const double npix = (double)p.N * p.H * p.W;
     const double xb = npix * p.Cin * (p.in_bf16 ? 2 : 4), yb = npix * p.Cout * 4;
     if (xb >= (double)kOob || yb >= (double)kOob || (double)g.split_bytes >= (double)kOob || p.groups > 65535) return false;
+    // One filter tile and at most 12 channels per group leave half of this kernel's smallest block and two thirds of its
+    // k-step empty; where the staged kernel's planes need no ragged loads it is then ahead from 250k pixels times groups
+    // on (split / staged, us: 8 -> 16 on 56x56, N = 247 22.3 / 17.9; 64 -> 128 on 32x32, g = 8, N = 169 46.5 / 32.1;
+    // 48 -> 64 on 64x64, g = 4, N = 78 39.2 / 31.6; at 220k 32 -> 64 on 20x20, g = 4, N = 138 9.4 / 9.6).
+    if (!any_size && !p.in_bf16 && g.split_mtiles == 1 && g.CPG <= 12 && (p.H * p.W) % 4 == 0 && npix * p.groups > 250e3)
+        return false;
     if ((long)p.H * p.W > 60000) return false;   // offsets inside a block are divided by the plane size exactly
     TileSplit t{};
     t.nchunks = g.split_chunks;

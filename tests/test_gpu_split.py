@@ -54,6 +54,24 @@ def test_pointwise_split(gpu, s, shape, bf16):
     assert m["floored"] < 1e-5, (name, m)
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(80, 32, 28, 28, 64, 1, 1, 1, 0, 4), "conv_mfma16<"),       # 8 channels, 16 filters per group, 250880 pixels times groups
+    (S(80, 48, 28, 28, 64, 1, 1, 1, 0, 4), "conv_mfma16<"),       # 12 channels
+    (S(79, 48, 28, 28, 64, 1, 1, 1, 0, 4), "conv_mfma16s<"),      # 247744
+    (S(80, 52, 28, 28, 64, 1, 1, 1, 0, 4), "conv_mfma16s<"),      # 13 channels
+    (S(80, 48, 28, 28, 68, 1, 1, 1, 0, 4), "conv_mfma16s<"),      # 17 filters
+    (S(90, 48, 27, 27, 64, 1, 1, 1, 0, 4), "conv_mfma16s<"),      # planes that are no whole quads
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_layers_of_one_filter_tile(gpu, s, kernel):
+    """One filter tile and few channels per group: the staged kernel, from the launch size on where it is ahead."""
+    y, x, w, name = run_conv(gpu, s, seed=57)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, 1, 0, s.groups, return_abs=True, threads=8)
+    cpg = s.Cin // s.groups
+    bound = split_bound(cpg) if kernel == "conv_mfma16s<" else (cpg + 17) * 2.0 ** -24
+    assert err_metrics(y, ref, absum)["bound"] < bound, name
+
+
 @pytest.mark.parametrize("hw,cout", [(28, 64), (27, 40)])
 def test_pointwise_split_epilogue_and_buffer_ends(gpu, hw, cout):
     """Residual and ReLU; nothing outside the output tensor is written (odd planes: 4-byte stores)."""
