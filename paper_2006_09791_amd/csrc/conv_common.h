@@ -66,6 +66,13 @@ inline const char *intern_name(const std::string &s) {
 
 constexpr int kNumCU = 256;
 
+// Odd pointwise planes of 40 .. 63 pixels, handed over as one row: conv_mfma16 gives every image and 16 filters a block of
+// one 64-pixel tile, up to three blocks per compute unit (with more it takes two images per block, a third of it padding).
+inline bool fills_image_tiles(const ConvParams &p, int mtiles) {
+    return p.KH == 1 && p.stride == 1 && p.pad == 0 && p.H == 1 && p.W % 4 != 0 && p.W >= 40 && p.W < 64 && p.CPG % 4 == 0 &&
+           (long)((p.N + 1) / 2) * mtiles * p.groups < 3 * kNumCU / 2;
+}
+
 inline unsigned div_magic(int d) { return d > 1 ? (unsigned)(0xffffffffu / (unsigned)d + 1u) : 0u; }
 
 // Splits the output into NB images x TH rows per block for a pixel capacity PB.

@@ -398,6 +398,9 @@ bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan
     // 48 -> 64 on 64x64, g = 4, N = 78 39.2 / 31.6; at 220k 32 -> 64 on 20x20, g = 4, N = 138 9.4 / 9.6).
     if (!any_size && !p.in_bf16 && g.split_mtiles == 1 && g.CPG <= 12 && (p.H * p.W) % 4 == 0 && npix * p.groups > 250e3)
         return false;
+    // One filter tile on odd planes that the staged kernel's 64-pixel tiles fit: 640 -> 32 on 5x11, g = 2, N = 252 17.2 /
+    // 10.6, 2048 -> 128 on 7x7, g = 8, N = 82 14.6 / 11.4, 1280 -> 128, N = 81 10.5 / 8.9 (36 layers 0.79).
+    if (!any_size && !p.in_bf16 && g.split_mtiles == 1 && fills_image_tiles(p, 1)) return false;
     if ((long)p.H * p.W > 60000) return false;   // offsets inside a block are divided by the plane size exactly
     TileSplit t{};
     t.nchunks = g.split_chunks;

@@ -192,6 +192,15 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
     if (t.units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
     if ((row ? p.stride == 1 && t.units < 9 : wide && t.units < 12) && tiles > 8 * kNumCU) return false;
+    // Odd pointwise planes handed over as one row are staged 16 bytes at a time as well:
+    //  - 40 .. 63 pixels, which fill most of a 64-pixel tile: while the staged kernel has a block per image (see
+    //    fills_image_tiles) it is ahead from 4 tiles per compute unit on: 384 -> 32 on 7x7, g = 2, N = 178 (1092 tiles)
+    //    10.5 / 7.3 here / staged, 768 -> 192, g = 8, N = 27 (1328) 7.8 / 5.3, 192 -> 48, g = 2, N = 150 (1840) 9.3 / 6.4;
+    //  - more: from 12 on: 256 -> 40 on 9x9, g = 4, N = 170 (3444) 11.2 / 7.9, 512 -> 48 on 11x11, g = 4, N = 133 (4024)
+    //    18.0 / 11.5 (one of 19 layers the other way round: 320 -> 48 on 11x11, N = 212 19.1 / 26.5).
+    if (!row && p.stride == 1 && p.H == 1 && p.W % 4 != 0 && p.W >= 64 && p.W <= 256 && g.CPG % 4 == 0 && tiles > 12 * kNumCU)
+        return false;
+    if (tiles > 4 * kNumCU && fills_image_tiles(p, g.mtiles)) return false;
     // waves per block: what lets every wave request all of its units at once, more as long as all of the launch's waves
     // still start together, eight per compute unit: one block too many costs its start anew (8 -> 16 on 12x12, g = 2,
     // N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time)

@@ -52,6 +52,27 @@ def test_unit_kernel_waves_start_together(gpu, s, waves):
     assert name.startswith(f"conv_mfma16u<{waves},"), name
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(94, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16<"),         # 1728 tiles, 47 pairs of images times 6
+    (S(55, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),        # 1014 tiles: all blocks run together
+    (S(128, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),       # 384 pairs: no longer a block per image
+    (S(94, 66, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),        # channels that are no whole quads
+    (S(115, 64, 6, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16<"),        # 42 pixels
+    (S(120, 64, 5, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),       # 35
+    (S(151, 256, 9, 9, 48, 1, 1, 1, 0, 4), "conv_mfma16u<"),      # 81 pixels, 12 filters per group, 3060 tiles
+    (S(152, 256, 9, 9, 48, 1, 1, 1, 0, 4), "conv_mfma16<"),       # 3080
+    (S(190, 128, 7, 7, 32, 1, 1, 1, 0, 2), "conv_mfma16<"),       # one filter tile per group, 95 pairs times 2
+    (S(768, 128, 7, 7, 16, 1, 1, 1, 0, 1), "conv_mfma16s<"),      # 384 pairs
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_odd_planes_of_one_row(gpu, s, kernel):
+    """Odd pointwise planes, staged as one row where that fills the staged kernel's tiles and the launch is large enough."""
+    y, x, w, name = run_conv(gpu, s, seed=64)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, 1, 0, s.groups, return_abs=True, threads=8)
+    # (the split kernel: three dropped products, six roundings per 32 channels and the final sum, less than this)
+    assert err_metrics(y, ref, absum)["bound"] < (s.Cin // s.groups + 17) * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("s", [S(2, 48, 9, 7, 40, 3, 3, 1, 1, 2), S(3, 40, 7, 7, 24, 1, 1, 2, 0, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
