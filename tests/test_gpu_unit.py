@@ -53,6 +53,8 @@ def test_unit_kernel_waves_start_together(gpu, s, waves):
 
 
 @pytest.mark.parametrize("s,kernel", [
+    (S(4, 144, 64, 64, 24, 1, 1, 1, 0, 1), "conv_mfma16<"),       # 2048 tiles of nine units on whole quads
+    (S(4, 144, 62, 66, 24, 1, 1, 1, 0, 1), "conv_mfma16u<"),      # 2046
     (S(94, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16<"),         # 1728 tiles, 47 pairs of images times 6
     (S(55, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),        # 1014 tiles: all blocks run together
     (S(128, 64, 7, 7, 96, 1, 1, 1, 0, 1), "conv_mfma16u<"),       # 384 pairs: no longer a block per image
@@ -64,8 +66,8 @@ def test_unit_kernel_waves_start_together(gpu, s, waves):
     (S(190, 128, 7, 7, 32, 1, 1, 1, 0, 2), "conv_mfma16<"),       # one filter tile per group, 95 pairs times 2
     (S(768, 128, 7, 7, 16, 1, 1, 1, 0, 1), "conv_mfma16s<"),      # 384 pairs
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
-def test_odd_planes_of_one_row(gpu, s, kernel):
-    """Odd pointwise planes, staged as one row where that fills the staged kernel's tiles and the launch is large enough."""
+def test_pointwise_layers_return_to_staging(gpu, s, kernel):
+    """From the launch size on where the staged kernel is ahead; odd planes where one row fills its tiles."""
     y, x, w, name = run_conv(gpu, s, seed=64)
     assert name.startswith(kernel), name
     ref, absum = oracle.conv2d_grouped(x, w, 1, 0, s.groups, return_abs=True, threads=8)
