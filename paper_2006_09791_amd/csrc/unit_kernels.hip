@@ -185,6 +185,9 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     //    (2352) 5.4 / 6.6, on other planes 64 -> 80 on 55x55, N = 2 (1895) 8.0 / 6.5;
     //  - six, 3x3 with stride 1: 64 -> 64, g = 8 on 16-pixel rows (2048) 4.8 / 4.7, on 20x20, N = 16 (3200) 5.1 / 6.1, on
     //    13x13, N = 50 (4232) 6.6 / 7.7; with nine 96 -> 96, g = 8 on 17x17 (2312) 7.4 / 5.9;
+    //  - six at stride 2, from 17 filters per group on, which the other side then multiplies out of one staged tile: 32 -> 192
+    //    on 40x40, g = 4, N = 14 (4200) 7.5 / 8.6, 32 -> 128 on 16x16, g = 4, N = 187 (5984) 7.2 / 10.1, 78 layers 0.82;
+    //    with up to 16 filters 37 layers are level;
     //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 9.0 / 5.9, N = 10 (2250) 8.7 / 9.8, and with nine 144 -> 24 on 64x64,
     //    N = 4 (2048) 6.5 / 9.7, 576 -> 96 on 32x32, g = 4 6.6 / 9.0.
     const long tiles = (long)((t.npix + 15) / 16) * g.mtiles * p.groups;
@@ -193,6 +196,7 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
     if (t.units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
     if (row && p.stride == 1 && t.units < 9 && tiles > 8 * kNumCU) return false;
+    if (row && p.stride == 2 && t.units < 9 && g.KPG > 16 && tiles > 12 * kNumCU) return false;
     if (!row && wide && t.units < 12 && tiles >= 8 * kNumCU) return false;
     // Odd pointwise planes handed over as one row are staged 16 bytes at a time as well:
     //  - 40 .. 63 pixels, which fill most of a 64-pixel tile: while the staged kernel has a block per image (see

@@ -75,6 +75,19 @@ def test_pointwise_layers_return_to_staging(gpu, s, kernel):
     assert err_metrics(y, ref, absum)["bound"] < (s.Cin // s.groups + 17) * 2.0 ** -24, name
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(49, 16, 16, 16, 64, 3, 3, 2, 1, 2), "conv_mfma16u<"),      # 784 tiles of six units
+    (S(193, 32, 16, 16, 64, 3, 3, 2, 1, 4), "conv_mfma16u<"),     # 3088, 16 filters per group
+    (S(97, 32, 16, 16, 80, 3, 3, 2, 1, 4), "conv_mfma16<"),       # 3104, 20 filters
+    (S(96, 32, 16, 16, 80, 3, 3, 2, 1, 4), "conv_mfma16u<"),      # 3072
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_large_launches_return_to_staging(gpu, s, kernel):
+    y, x, w, name = run_conv(gpu, s, seed=65)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < (9 * s.Cin // s.groups + 17) * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("s", [S(2, 48, 9, 7, 40, 3, 3, 1, 1, 2), S(3, 40, 7, 7, 24, 1, 1, 2, 0, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
