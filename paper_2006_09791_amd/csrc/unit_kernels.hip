@@ -212,6 +212,15 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     // N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time)
     int nw = 2;
     while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw * 2 <= 8 * kNumCU && t.units > nw))) nw *= 2;
+    // Large 3x3 layers whose waves have places for a third more units than there are (9, 15, 18, 27, 30 of them) go to the
+    // kernel that keeps its filters where that takes the layer and the rows fill its 16-pixel tiles: 20 -> 64 on 32x32,
+    // N = 4, g = 2 (2048 tiles) 6.9 / 5.3 here / there, 144 -> 192 on 16x16, g = 4, N = 7 (1344) 8.6 / 6.5, 80 -> 256 on 16x16,
+    // g = 2, N = 5 (1280) 7.8 / 6.6; 128 layers 0.84.  On rows of 12, 20, 24, 28 and 40 pixels 28 layers are level (0.83 ..
+    // 1.09), and so are 12 and 24 units, which leave no place empty.
+    Mfma16wPlan pw;
+    if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * t.units <= 3 * 6 * nw && tiles * nw >= 24 * kNumCU &&
+        plan_mfma16w(p, g, &pw))
+        return false;
     out->nw = nw;
     std::memcpy(out->data, &t, sizeof(t));
     return true;

@@ -80,6 +80,11 @@ def test_pointwise_layers_return_to_staging(gpu, s, kernel):
     (S(193, 32, 16, 16, 64, 3, 3, 2, 1, 4), "conv_mfma16u<"),     # 3088, 16 filters per group
     (S(97, 32, 16, 16, 80, 3, 3, 2, 1, 4), "conv_mfma16<"),       # 3104, 20 filters
     (S(96, 32, 16, 16, 80, 3, 3, 2, 1, 4), "conv_mfma16u<"),      # 3072
+    (S(3, 40, 32, 32, 128, 3, 3, 1, 1, 2), "conv_mfma16w<"),      # 1536 tiles of 15 units, four waves each
+    (S(3, 40, 32, 31, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # rows that it does not read four at a time
+    (S(3, 32, 32, 32, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 12 units
+    (S(2, 40, 32, 32, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 1024 tiles
+    (S(22, 24, 12, 12, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),     # rows of 12
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_large_launches_return_to_staging(gpu, s, kernel):
     y, x, w, name = run_conv(gpu, s, seed=65)
