@@ -217,9 +217,12 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     // N = 4, g = 2 (2048 tiles) 6.9 / 5.3 here / there, 144 -> 192 on 16x16, g = 4, N = 7 (1344) 8.6 / 6.5, 80 -> 256 on 16x16,
     // g = 2, N = 5 (1280) 7.8 / 6.6; 128 layers 0.84.  On rows of 12, 20, 24, 28 and 40 pixels 28 layers are level (0.83 ..
     // 1.09), and so are 12 and 24 units, which leave no place empty.
+    // Six units leave half of the places empty, and five tiles per compute unit are enough: 16 -> 64 on 16x16, g = 2, N = 29
+    // (1856) 4.8 / 4.3, 8 -> 128 on 14x16, N = 15 (1680) 4.8 / 4.3, with 4.5 tiles level; not on planes that the 32 pixels of
+    // its two waves do not divide (16 -> 32 on 14x8, g = 2, N = 144 (2016) 4.9 / 5.3).
     Mfma16wPlan pw;
-    if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * t.units <= 3 * 6 * nw && tiles * nw >= 24 * kNumCU &&
-        plan_mfma16w(p, g, &pw))
+    if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * t.units <= 3 * 6 * nw &&
+        tiles * nw >= (t.units < 9 && p.H * p.W % 32 == 0 ? 10 : 24) * kNumCU && plan_mfma16w(p, g, &pw))
         return false;
     out->nw = nw;
     std::memcpy(out->data, &t, sizeof(t));

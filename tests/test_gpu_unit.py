@@ -84,6 +84,9 @@ def test_pointwise_layers_return_to_staging(gpu, s, kernel):
     (S(3, 40, 32, 31, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # rows that it does not read four at a time
     (S(3, 32, 32, 32, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 12 units
     (S(2, 40, 32, 32, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 1024 tiles
+    (S(20, 16, 16, 16, 64, 3, 3, 1, 1, 2), "conv_mfma16w<"),      # 1280 tiles of six units
+    (S(19, 16, 16, 16, 64, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 1216
+    (S(142, 16, 14, 8, 32, 3, 3, 1, 1, 2), "conv_mfma16u<"),      # 1988, planes of 112 pixels
     (S(22, 24, 12, 12, 128, 3, 3, 1, 1, 2), "conv_mfma16u<"),     # rows of 12
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_large_launches_return_to_staging(gpu, s, kernel):
