@@ -351,7 +351,7 @@ hipError_t launch_small(const ConvParams &p, const TileS &t, hipStream_t s) {
 
 hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) {
     static const bool no_small = std::getenv("GSPC_NO_SMALL") != nullptr;   // tuning aid
-    // depthwise planes small enough to sit whole in LDS (up to about 40x40)
+    // depthwise: the plane sizes that have an instance of their own
     DwPlan dw;
     if (plan_dw_planes(p, &dw)) return launch_dw_planes(p, dw, s, name);
     TileS ts;
@@ -361,6 +361,10 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
                             (p.in_bf16 ? ",bf16>" : ",f32>"));
         return p.in_bf16 ? launch_small<uint16_t>(p, ts, s) : launch_small<float>(p, ts, s);
     }
+    // depthwise on any other plane (whole-quad rows above: 96 channels at stride 1, us, strip kernel / this: 44x44 at N = 33
+    // 11.7 / 12.5, 56x56 at N = 20 9.7 / 12.0, 8x8 at N = 1954 22.6 / 26.1, 80x80 at N = 20 19.8 / 18.7; small launches 5-15 %
+    // the strip kernel's)
+    if (plan_dw_rows(p, &dw)) return launch_dw_planes(p, dw, s, name);
     TileF tf;
     if (plan_flat(p, &tf)) {
         *name = intern_name("conv_direct_flat<" + std::to_string(p.KPG) + (p.in_bf16 ? ",bf16>" : ",f32>"));

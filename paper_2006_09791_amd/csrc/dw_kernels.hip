@@ -1,182 +1,24 @@
-// Depthwise 3x3 convolution (g = Cin = Cout, the G(N) end of the paper's sweep,
-// Section IV of arXiv 2006.09791) for small planes of any width.
+// Depthwise 3x3 convolution, padding 1 (g = Cin = Cout, the G(N) end of the paper's sweep,
+// Section IV of arXiv 2006.09791).
 //
 // With one channel per group the input planes of consecutive (image, channel)
-// pairs are consecutive in NCHW memory, and so are the output planes: a block
-// takes PB whole planes as one contiguous piece, copies it with 16-byte loads
-// into zero-haloed LDS tiles (the paper's input reshape, here a re-pitch from
-// W to W+2 columns), and every thread then produces output elements that are
-// consecutive across the wavefront, so the stores are contiguous as well.
-// Nothing depends on W being a multiple of 4 or on the plane filling a
-// wavefront (14x14 and 7x7 planes, odd strides of planes).  HBM-bound.
+// pairs are consecutive in NCHW memory, and so are the output planes: a wavefront
+// takes a contiguous piece of the input (whole planes, or a band of rows of one),
+// copies it flat into an LDS region of its own with 16-byte accesses and reads its
+// windows there.  LDS operations of one wavefront execute in order, so nothing here
+// needs a barrier.  HBM-bound.
 //
-// For the plane widths of the MobileNet / ResNet tails (WT = 28, 14, 7) a thread produces a whole
-// output row: three tile rows pass through registers once, no index arithmetic per output, and
-// the row leaves as 16-, 8- or 4-byte stores; other widths take one output per thread and step.
-//
-// Launches that fill the chip on 56x56, 28x28, 14x14 and 7x7 planes take conv_dw_wave instead
-// (further down): whole planes per wavefront, no block-level barrier, every global and almost
-// every LDS access 16 bytes wide; on 112x112 planes conv_dw_band does the same with a band of 16
-// rows per wavefront.  The block form above keeps the small launches (it shrinks its tiles to
-// spread over the chip) and the other plane sizes.
+//   conv_dw_wave      whole 56x56, 28x28, 14x14 and 7x7 planes, launches that fill the chip;
+//   conv_dw_band      112x112 planes, a band of 16 rows per wavefront;
+//   conv_direct_rows  every other plane that the strip kernel (conv_direct_small) does not take.
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
-#include "conv_common.h"
+#include "split_common.h"
 
 namespace gspc {
-
-struct TileD {
-    int PB;                 // planes per block (4, 8, ..., 64)
-    int LWp, PL;            // tile row pitch (W+2) and floats per plane tile ((H+2)*(W+2), rounded up to 4)
-    int HW, HoWo;
-    unsigned planes;        // N * C
-    unsigned m_HW, m_W, m_HoWo, m_Wout, m_C, m_Hout;
-    unsigned x_bytes, y_bytes, w_bytes;
-};
-
-constexpr int kDwSlots = 8;   // 16-byte loads per thread: 32 KB of tiles at most
-
-template <int S, int WT>
-__global__ __launch_bounds__(256) void conv_direct_dw(ConvParams p, TileD t) {
-    extern __shared__ f32x4 smem4[];
-    float *tile = reinterpret_cast<float *>(smem4);
-    float *wl = tile + t.PB * t.PL;   // [plane][9]
-    const int tid = threadIdx.x;
-    const unsigned plane0 = blockIdx.x * t.PB;
-    const int np = (int)(t.planes - plane0 < (unsigned)t.PB ? t.planes - plane0 : (unsigned)t.PB);
-
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wd, t.w_bytes);
-
-    // ---- the block's planes: one contiguous piece of np*HW floats, requested first so that the
-    // memory latency passes while the tiles are cleared.  Elements past the tensor's end read
-    // as zero (the range check covers the vector offset) and are not used. ----
-    const int total = np * t.HW;
-    const unsigned gbase = plane0 * t.HW * 4;   // 16-byte aligned: PB is a multiple of 4
-    f32x4 pin[kDwSlots];
-#pragma unroll
-    for (int k = 0; k < kDwSlots; ++k) {
-        const int e4 = (tid + k * 256) * 4;
-        pin[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, e4 < total ? gbase + e4 * 4 : kOob, 0, 0));
-    }
-    // ---- clear the tiles (the halo must be zero; the interior is overwritten) ----
-    {
-        const int n4 = t.PB * t.PL / 4;
-        for (int i = tid; i < n4; i += 256) smem4[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    // ---- filters: direct section [g][9][KPGd], filter 0 of group c ------------
-    for (int i = tid; i < np * 9; i += 256) {
-        const unsigned pl = fast_div(i, 0x1c71c71du);   // i / 9, exact for i < 2^16
-        const unsigned k = i - pl * 9;
-        const unsigned pg = plane0 + pl;
-        const unsigned c = pg - fast_div(pg, t.m_C) * p.Cin;
-        wl[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ((c * 9 + k) * p.KPGd) * 4, 0, 0));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kDwSlots; ++k) {
-        const int e4 = (tid + k * 256) * 4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = e4 + i;
-            if (e < total) {
-                const int pl = fast_div(e, t.m_HW), r = e - pl * t.HW;
-                const int h = fast_div(r, t.m_W), w = r - h * p.W;
-                tile[pl * t.PL + (h + 1) * t.LWp + (w + 1)] = pin[k][i];
-            }
-        }
-    }
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
-    if constexpr (WT > 0) {
-        // ---- a thread per output row of a plane ----
-        constexpr int WO = (WT - 1) / S + 1, LW = WT + 2;
-        const int rows = np * p.Hout;
-        for (int row = tid; row < rows; row += 256) {
-            const int pl = fast_div(row, t.m_Hout), oh = row - pl * p.Hout;
-            float w[9];
-#pragma unroll
-            for (int k = 0; k < 9; ++k) w[k] = wl[pl * 9 + k];
-            float acc[WO];
-#pragma unroll
-            for (int x = 0; x < WO; ++x) acc[x] = 0.f;
-            const float *ip = tile + pl * t.PL + oh * S * LW;
-#pragma unroll
-            for (int kh = 0; kh < 3; ++kh) {
-                float xr[LW];
-                if (LW % 2 == 0) {   // tile rows start on 8-byte boundaries when the pitch is even
-#pragma unroll
-                    for (int x = 0; x < LW; x += 2) {
-                        const float2 v = *reinterpret_cast<const float2 *>(ip + kh * LW + x);
-                        xr[x] = v.x;
-                        xr[x + 1] = v.y;
-                    }
-                } else {
-#pragma unroll
-                    for (int x = 0; x < LW; ++x) xr[x] = ip[kh * LW + x];
-                }
-#pragma unroll
-                for (int kw = 0; kw < 3; ++kw)
-#pragma unroll
-                    for (int x = 0; x < WO; ++x) acc[x] = fmaf(xr[x * S + kw], w[kh * 3 + kw], acc[x]);
-            }
-            const unsigned ob = ((plane0 + pl) * t.HoWo + oh * WO) * 4;
-            constexpr int VW = WO % 4 == 0 ? 4 : WO % 2 == 0 ? 2 : 1;   // the row start is VW*4-byte aligned
-#pragma unroll
-            for (int x = 0; x < WO; x += VW) {
-                if (VW == 4) {
-                    f32x4 v = f32x4{acc[x], acc[x + 1], acc[x + 2], acc[x + 3]};
-                    if (p.res) v += __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rr, ob + x * 4, 0, 0));
-                    if (p.relu) v = f32x4{fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f)};
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ry, ob + x * 4, 0, 0);
-                } else if (VW == 2) {
-                    float a0 = acc[x], a1 = acc[x + 1];
-                    if (p.res) {
-                        const u32x2 rv = __builtin_amdgcn_raw_buffer_load_b64(rr, ob + x * 4, 0, 0);
-                        a0 += __uint_as_float(rv.x);
-                        a1 += __uint_as_float(rv.y);
-                    }
-                    if (p.relu) {
-                        a0 = fmaxf(a0, 0.f);
-                        a1 = fmaxf(a1, 0.f);
-                    }
-                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(a0), __float_as_uint(a1)}, ry, ob + x * 4, 0, 0);
-                } else {
-                    float a0 = acc[x];
-                    if (p.res) a0 += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, ob + x * 4, 0, 0));
-                    if (p.relu) a0 = fmaxf(a0, 0.f);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a0), ry, ob + x * 4, 0, 0);
-                }
-            }
-        }
-        return;
-    }
-    // ---- any width: 256 / PB threads per plane (PB is a power of two), so that a thread keeps its
-    // plane's nine weights in registers; the lanes of a plane produce consecutive elements ----
-    const int tpp = 256 / t.PB, pl = tid / tpp, sub = tid - pl * tpp;
-    if (pl < np) {
-        float w[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) w[k] = wl[pl * 9 + k];
-        const float *tp = tile + pl * t.PL;
-        const unsigned obase = (plane0 + pl) * t.HoWo * 4;
-        for (int o = sub; o < t.HoWo; o += tpp) {
-            const int oh = fast_div(o, t.m_Wout), ow = o - oh * p.Wout;
-            const float *ip = tp + oh * S * t.LWp + ow * S;
-            float acc = 0.f;
-#pragma unroll
-            for (int kh = 0; kh < 3; ++kh)
-#pragma unroll
-                for (int kw = 0; kw < 3; ++kw) acc = fmaf(ip[kh * t.LWp + kw], w[kh * 3 + kw], acc);
-            if (p.res) acc += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, obase + o * 4, 0, 0));
-            if (p.relu) acc = fmaxf(acc, 0.f);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc), ry, obase + o * 4, 0, 0);
-        }
-    }
-}
-
 
 // ---- whole planes per wavefront -------------------------------------------------------------
 // For the square planes of the network tails (28x28, 14x14, 7x7) a wavefront takes G consecutive
@@ -191,7 +33,7 @@ __global__ __launch_bounds__(256) void conv_direct_dw(ConvParams p, TileD t) {
 // coalesced stores (residual and ReLU applied there).  LDS operations of one wavefront execute in
 // order, so no barrier is needed anywhere; memory clobbers keep the compiler from reordering the
 // phases.  Per lane and R*Wout outputs this takes a few dozen wide LDS operations where the
-// per-output form above takes nine 4-byte reads per output.
+// sum read per output takes nine 4-byte reads.
 template <int S, int H, int W, int R, int CP = -1>
 struct DwWaveGeom {
     static constexpr int Hout = (H - 1) / S + 1, Wout = (W - 1) / S + 1;
@@ -388,7 +230,7 @@ bool plan_dw_wave_inst(const ConvParams &p, DwPlan *out) {
     if (p.stride != T::S || p.H != T::E || p.W != T::E) return false;
     const double planes = (double)p.N * p.Cin;
     const double chunks = (planes + Q::G - 1) / Q::G;
-    // small launches stay on the block form, which shrinks its tiles to spread over the chip
+    // small launches: the forms that spread over the chip
     static const bool force = std::getenv("GSPC_DW_WAVE") != nullptr;   // tuning aid
     if (!force && chunks < 4.0 * 2 * kNumCU) return false;
     const double xb = planes * Q::HW * 4, yb = planes * Q::HoWo * 4, wb = (double)p.groups * 9 * p.KPGd * 4;
@@ -616,6 +458,205 @@ hipError_t launch_dw_band(int inst, const ConvParams &p, const TileW &t, hipStre
     }
 }
 
+// ---- bands of rows or groups of planes per wavefront, any plane ----------------------------------------
+// Planes that none of the forms above takes: a wavefront owns one band of BR output rows of one plane or, of small
+// planes, G whole ones (MULTI).  Either way its input is one contiguous range of memory, which goes flat, from the 16-byte
+// boundary at or below its start, straight into a wave-private LDS region (16 bytes per lane, no registers in between).  Rows
+// above and below the plane are overwritten with zeros there, or, between planes, selected to zero.  A lane takes one
+// column of R consecutive output rows at a time - the (plane, strip, column) items are numbered flat, so odd widths fill
+// the lanes - and reads the three columns of its (R-1)*S + 3 input rows, 4.5 words per output at stride 1.  Neighbouring
+// lanes store neighbouring elements.
+struct TileRows {
+    unsigned chunks, planes;      // wavefronts with work, planes
+    int NBD, BR, G;               // bands per plane, output rows per band; planes per wavefront
+    int front, region, witem;     // floats before the rows, floats per wavefront, (strip, column) items of a plane
+    unsigned m_NBD, m_Wout, m_C, m_item;
+    unsigned x_bytes, y_bytes;
+};
+
+constexpr int kRowsStrip = 4;     // R
+constexpr int kRowsSlots = 8;     // 16-byte loads per lane, at most: 2048 floats per wavefront
+constexpr int kRowsLds = 150 * 1024;   // (rows of several hundred elements; square planes stay below 48 KB per block)
+
+template <int S, bool MULTI>
+__global__ __launch_bounds__(256) void conv_direct_rows(ConvParams p, TileRows t) {
+    constexpr int R = kRowsStrip, NR = (R - 1) * S + 3;
+    extern __shared__ f32x4 smem4[];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned chunk = blockIdx.x * 4 + wv;
+    if (chunk >= t.chunks) return;   // wave-uniform; the kernel has no barriers
+    float *reg = reinterpret_cast<float *>(smem4) + wv * t.region;
+    const unsigned plane = MULTI ? chunk * t.G : fast_div(chunk, t.m_NBD), band = MULTI ? 0 : chunk - plane * t.NBD;
+    const unsigned np = MULTI ? min((unsigned)t.G, t.planes - plane) : 1;
+    const int W = p.W, H = p.H;
+    const int oh0 = (int)band * t.BR, nr = min(t.BR, p.Hout - oh0);   // the band's output rows
+    const int ih0 = oh0 * S - 1, ih1 = ih0 + (nr - 1) * S + 3;        // its input rows [ih0, ih1)
+    const unsigned pbase = plane * (unsigned)(H * W);
+    const unsigned first = pbase + (unsigned)(max(ih0, 0) * W);       // floats
+    const unsigned last = MULTI ? pbase + np * (unsigned)(H * W) : pbase + (unsigned)(min(ih1, H) * W);
+    const unsigned a0 = first & ~3u, len = last - a0;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
+    for (unsigned j = 0; j < len; j += 256) {
+        const unsigned e = j + lane * 4;
+        load_to_lds16(rx, smem4, (wv * t.region + t.front + j) * 4, e < len ? (a0 + e) * 4 : kOob, 0);
+    }
+    float w[9];
+    float *wl = reg + t.region - t.G * 9;                             // (MULTI) the planes' weights
+    if constexpr (MULTI) {
+        for (unsigned i = lane; i < np * 9; i += 64) {
+            const unsigned pl = fast_div(i, 0x1c71c71du), pg = plane + pl;   // i / 9, exact for i < 2^16
+            wl[i] = p.wd[((pg - fast_div(pg, t.m_C) * p.Cin) * 9 + (i - pl * 9)) * p.KPGd];
+        }
+    } else {
+        const unsigned c = plane - fast_div(plane, t.m_C) * p.Cin;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) w[k] = p.wd[(c * 9 + k) * p.KPGd];
+    }
+    if (MULTI)               // a row of zeros before the data, which the rows between planes are read from
+        for (int i = lane; i < t.front; i += 64) reg[i] = 0.f;
+    wait_vmem0();
+    asm volatile("" ::: "memory");
+    // input row ih, column w: top[(ih - ih0) * W + w]
+    float *top = reg + t.front + (first - a0) - (ih0 < 0 ? W : 0);
+    if (!MULTI && ih0 < 0)
+        for (int i = lane; i < W; i += 64) top[i] = 0.f;
+    if (!MULTI && ih1 > H)   // (one row, at stride 2 too)
+        for (int i = lane; i < W; i += 64) top[(H - ih0) * W + i] = 0.f;
+    asm volatile("" ::: "memory");
+
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
+    const unsigned ybase = plane * (unsigned)(p.Hout * p.Wout) + (unsigned)(oh0 * p.Wout);   // floats
+    const unsigned Wout = p.Wout, items = MULTI ? np * t.witem : (unsigned)((nr + R - 1) / R) * Wout;
+    const unsigned qstrip = (unsigned)(R * S) * W, ostrip = (R - 1) * Wout;
+    for (unsigned it = lane; it < items; it += 64) {
+        const unsigned pl = MULTI ? fast_div(it, t.m_item) : 0, i0 = MULTI ? it - __umul24(pl, t.witem) : it;
+        const unsigned strip = fast_div(i0, t.m_Wout), ow = i0 - __umul24(strip, Wout);
+        const float *q = top + __umul24(strip, qstrip) + ow * S;
+        if (MULTI) q += __umul24(pl, (unsigned)(H * W));
+        float v[NR][3];      // (all reads before any selection: they are in bounds whatever the lane's column)
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const float *row = q + i * W;
+            if (MULTI && i != 1 && (unsigned)((int)(strip * (R * S)) - 1 + i) >= (unsigned)H) row = reg + 1;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[i][k] = row[k - 1];
+        }
+        if constexpr (MULTI) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) w[k] = wl[pl * 9 + k];
+        }
+        const bool lok = ow > 0, rok = (int)(ow * S) + 1 < W;
+        float acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const float v0 = lok ? v[i][0] : 0.f, v2 = rok ? v[i][2] : 0.f;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int kh = i - r * S;
+                if (kh < 0 || kh > 2) continue;
+                acc[r] = fmaf(v0, w[kh * 3], acc[r]);
+                acc[r] = fmaf(v[i][1], w[kh * 3 + 1], acc[r]);
+                acc[r] = fmaf(v2, w[kh * 3 + 2], acc[r]);
+            }
+        }
+        const unsigned o = (ybase + (MULTI ? __umul24(pl, (unsigned)(p.Hout * p.Wout)) : 0) + i0 + __umul24(strip, ostrip)) * 4u;
+        const int left = nr - (int)strip * R;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const unsigned off = r < left ? o + (unsigned)r * Wout * 4u : kOob;
+            if (p.res) acc[r] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, off, 0, 0));
+            if (p.relu) acc[r] = fmaxf(acc[r], 0.f);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[r]), ry, off, 0, 0);
+        }
+    }
+}
+
+static_assert(sizeof(TileRows) <= sizeof(int) * kDwInst, "plan storage too small");
+
+// The band height, or the planes per wavefront, with the shortest estimated launch: a wavefront's instructions (120, 10 per
+// load slot, 100 per round of items, 200 where planes are mixed), times the rounds of wavefronts over the chip's 1024
+// SIMDs, of which each after the first adds half (fitted to sweeps over plane sizes at 3 .. 1000 images of 96 channels).
+// us, a block of planes in LDS tiles or a thread per output (what these layers ran on before) / this: 95x95 with 1040 planes
+// 52 / 17, 86x86 with 4480 179 / 45, 27x79 at stride 2 with 18400 82 / 29, 43x43 with 3264 16.3 / 13.0 (stride 2 9.5 / 7.9),
+// 23x23 with 11424 15.0 / 11.9 (9.4 / 6.5), 15x15 with 26688 15.2 / 12.8 (10.2 / 6.2), 9x9 with 74112 16.9 / 15.7 (11.0 / 9.2).
+bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
+    if (p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2))
+        return false;
+    const int R = kRowsStrip, S = p.stride, HW = p.H * p.W, limit = kRowsSlots * 256;
+    const double planes = (double)p.N * p.Cin, xb = planes * HW * 4, yb = planes * p.Hout * p.Wout * 4;
+    if (xb + 65536 >= (double)kOob || yb + 65536 >= (double)kOob || planes * p.Cin >= 4.29e9 || p.W > 1024) return false;
+    TileRows t{};
+    double best = 0.0;
+    const auto consider = [&](int g, int br) {
+        const int rows = br < p.Hout ? br : p.Hout, nrb = (rows - 1) * S + 3;
+        const int len = g * (nrb < p.H ? nrb : p.H) * p.W + 3;      // floats loaded, with the alignment's
+        const int nbd = (p.Hout + br - 1) / br, strips = (rows + R - 1) / R, items = g * strips * p.Wout;
+        const double chunks = g > 1 ? std::ceil(planes / g) : planes * nbd;
+        // the last strip's window may reach past the band's rows, for outputs that are not stored
+        // (and the loads fill whole pieces of 64 lanes x 4 floats)
+        const int window = 3 + (g - 1) * HW + ((strips * R - 1) * S + 3) * p.W + 4, pieces = round_up(len, 256);
+        const int front = round_up(p.W, 4) + 4;
+        const int region = front + round_up(window > pieces ? window : pieces, 4) + (g > 1 ? round_up(g * 9, 4) : 0);
+        if (len > limit || chunks * nbd >= 4.29e9 || region * 16 > kRowsLds) return;
+        const double wave = 120.0 + 10.0 * ((len + 255) / 256) + (g > 1 ? 200.0 : 100.0) * ((items + 63) / 64);
+        const double est = wave * (0.5 + 0.5 * std::ceil(chunks / (4 * kNumCU)));
+        if (best != 0.0 && est >= best) return;
+        best = est;
+        t.chunks = (unsigned)chunks;
+        t.NBD = nbd;
+        t.BR = br;
+        t.G = g;
+        t.witem = strips * p.Wout;
+        t.front = front;
+        t.region = region;
+    };
+    // one plane or less: the largest bands that fit, and up to three more per plane
+    const int fit = ((limit - 3) / p.W - 3) / S + 1, brmax = HW + 3 <= limit ? p.Hout : fit / R * R;
+    if (brmax < 1) return false;
+    const int n0 = (p.Hout + brmax - 1) / brmax;
+    for (int n = n0, br = 0; n < n0 + 4; ++n) {
+        const int b = round_up((p.Hout + n - 1) / n, R);
+        if (b == br) break;
+        br = b;
+        consider(1, br);
+    }
+    // several planes, where that leaves no compute unit idle
+    if (planes > 4 * kNumCU)
+        for (int g = std::min(32, (limit - 3) / HW); g > 1; g = g > 8 ? g / 2 : g - 1) consider(g, round_up(p.Hout, R));
+    if (best == 0.0) return false;
+    t.planes = (unsigned)planes;
+    t.m_NBD = div_magic(t.NBD);
+    t.m_Wout = div_magic(p.Wout);
+    t.m_C = div_magic(p.Cin);
+    t.m_item = div_magic(t.witem);
+    t.x_bytes = (unsigned)xb;
+    t.y_bytes = (unsigned)yb;
+    std::memcpy(out->data, &t, sizeof(t));
+    out->data[kDwKind] = 3;
+    return true;
+}
+
+template <int S, bool MULTI>
+hipError_t launch_dw_rows(const ConvParams &p, const TileRows &t, hipStream_t s) {
+    const size_t lds = (size_t)4 * t.region * sizeof(float);
+    auto kern = conv_direct_rows<S, MULTI>;
+    if (lds > 64 * 1024) {
+        static thread_local bool raised = false;   // per instantiation and thread
+        if (!raised) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds);
+            if (e != hipSuccess) return e;
+            raised = true;
+        }
+    }
+    hipLaunchKernelGGL(kern, dim3((t.chunks + 3) / 4), dim3(256), lds, s, p, t);
+    return hipGetLastError();
+}
+
 bool plan_dw_planes(const ConvParams &p, DwPlan *out) {
     static const bool off = std::getenv("GSPC_NO_DWPLANES") != nullptr;   // tuning aid
     if (off || p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 ||
@@ -626,72 +667,19 @@ bool plan_dw_planes(const ConvParams &p, DwPlan *out) {
         static const bool off = std::getenv("GSPC_NO_DWBAND") != nullptr;   // tuning aid
         if (!off && plan_dw_band(p, out)) return true;
     }
-    out->data[kDwKind] = 0;
-    TileD t{};
-    t.LWp = p.W + 2;
-    t.PL = round_up((p.H + 2) * t.LWp, 4);
-    t.HW = p.H * p.W;
-    t.HoWo = p.Hout * p.Wout;
-    // as many planes as fit 32 KB of tiles, at most 64, a multiple of 4
-    int pb = (32 * 1024 / 4) / t.PL;
-    // measured: 8 planes per block for planes of 28x28 and more (32 threads per plane: 128-byte
-    // store segments), 16 for 14x14, 32 for smaller ones
-    static const int pb_force = std::getenv("GSPC_DW_PB") ? std::atoi(std::getenv("GSPC_DW_PB")) : 0;   // tuning aid
-    const int pb_cap = pb_force ? pb_force : (t.HW >= 512 ? 8 : t.HW >= 128 ? 16 : 32);
-    pb = pb > pb_cap ? pb_cap : pb;
-    if (pb < 4) return false;
-    {
-        int q = 4;   // a power of two: the block's 256 threads divide evenly over the planes
-        while (2 * q <= pb) q *= 2;
-        pb = q;
-    }
-    const double planes = (double)p.N * p.Cin;
-    // small batches: fewer planes per block rather than idle compute units
-    const long spread = (long)(planes / (2 * kNumCU));
-    while (pb > 4 && spread < pb) pb /= 2;
-    t.PB = pb;
-    const double xb = planes * t.HW * 4, yb = planes * t.HoWo * 4, wb = (double)p.groups * 9 * p.KPGd * 4;
-    if (planes >= 2147483648.0 || xb >= (double)kOob || yb >= (double)kOob || wb >= (double)kOob) return false;
-    // fast_div exactness: numerator * divisor < 2^32 at each step
-    if ((double)pb * t.HW * t.HW >= 4.29e9 || (double)pb * t.HoWo * t.HoWo >= 4.29e9 ||
-        planes * p.Cin >= 4.29e9 || pb * 9 >= 65536)
-        return false;
-    t.planes = (unsigned)planes;
-    t.m_HW = div_magic(t.HW);
-    t.m_W = div_magic(p.W);
-    t.m_HoWo = div_magic(t.HoWo);
-    t.m_Wout = div_magic(p.Wout);
-    t.m_C = div_magic(p.Cin);
-    t.m_Hout = div_magic(p.Hout);
-    t.x_bytes = (unsigned)xb;
-    t.y_bytes = (unsigned)yb;
-    t.w_bytes = (unsigned)wb;
-    static_assert(sizeof(TileD) <= sizeof(int) * kDwInst, "plan storage too small");
-    std::memcpy(out->data, &t, sizeof(t));
-    return true;
+    return false;
 }
-
-namespace {
-
-template <int S, int WT>
-hipError_t launch_dw_inst(const ConvParams &p, const TileD &t, hipStream_t s) {
-    const size_t lds = ((size_t)t.PB * t.PL + (size_t)t.PB * 9 + 4) * sizeof(float);
-    const dim3 grid((t.planes + t.PB - 1) / t.PB);
-    hipLaunchKernelGGL((conv_direct_dw<S, WT>), grid, dim3(256), lds, s, p, t);
-    return hipGetLastError();
-}
-
-// Measured at N = 256: a thread per output row pays for stride 2 at widths 28 and 7 (the row's
-// few outputs leave in one or two stores); for stride 1 and for width 14 the per-plane split is
-// as fast or faster.
-inline int dw_row_width(const ConvParams &p) {
-    static const bool generic = std::getenv("GSPC_DW_GENERIC") != nullptr;   // tuning aid
-    return (!generic && p.stride == 2 && (p.W == 28 || p.W == 7)) ? p.W : 0;
-}
-
-}  // namespace
 
 hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t s, const char **name) {
+    if (plan.data[kDwKind] == 3) {
+        TileRows tr;
+        std::memcpy(&tr, plan.data, sizeof(tr));
+        static const char *const names[2][2] = {{"conv_direct_rows<1,false>", "conv_direct_rows<1,true>"},
+                                                {"conv_direct_rows<2,false>", "conv_direct_rows<2,true>"}};
+        *name = names[p.stride - 1][tr.G > 1];
+        if (tr.G > 1) return p.stride == 1 ? launch_dw_rows<1, true>(p, tr, s) : launch_dw_rows<2, true>(p, tr, s);
+        return p.stride == 1 ? launch_dw_rows<1, false>(p, tr, s) : launch_dw_rows<2, false>(p, tr, s);
+    }
     if (plan.data[kDwKind] == 2) {
         TileW tw;
         std::memcpy(&tw, plan.data, sizeof(tw));
@@ -702,13 +690,7 @@ hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t
         std::memcpy(&tw, plan.data, sizeof(tw));
         return launch_dw_wave(plan.data[kDwInst], p, tw, s, name);
     }
-    TileD t;
-    std::memcpy(&t, plan.data, sizeof(t));
-    const int wt = dw_row_width(p);
-    *name = intern_name("conv_direct_dw<" + std::to_string(p.stride) + "," + std::to_string(wt) + ",f32>");
-    if (wt == 28) return launch_dw_inst<2, 28>(p, t, s);
-    if (wt == 7) return launch_dw_inst<2, 7>(p, t, s);
-    return p.stride == 1 ? launch_dw_inst<1, 0>(p, t, s) : launch_dw_inst<2, 0>(p, t, s);
+    return hipErrorNotSupported;
 }
 
 }  // namespace gspc

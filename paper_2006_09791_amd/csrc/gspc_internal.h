@@ -239,6 +239,7 @@ struct DwPlan {
     int data[24];
 };
 bool plan_dw_planes(const ConvParams &p, DwPlan *out);
+bool plan_dw_rows(const ConvParams &p, DwPlan *out);   // bands of rows per wavefront, any plane
 hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t s, const char **name);
 
 // Fused run of consecutive grouped 3x3 layers (fused_kernels.hip).

@@ -1,0 +1,86 @@
+"""Depthwise 3x3 layers on planes without an instance of their own (bands of rows, or several planes, per wavefront),
+against the oracle's plain definition of the grouped convolution (Section II, Fig. 2)."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import err_metrics
+from paper_2006_09791_amd import workloads as wl
+from test_gpu_parity import gpu, run_conv  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def dw(N, C, H, W, stride):
+    return wl.ConvShape(N, C, H, W, C, 3, 3, stride, 1, C)
+
+
+SHAPES = [
+    (dw(3, 5, 95, 95, 1), "1,false"),      # bands of one plane; planes that start at any alignment
+    (dw(3, 5, 95, 95, 2), "2,false"),
+    (dw(2, 7, 46, 85, 1), "1,false"),      # the last band shorter, its last strip ragged
+    (dw(2, 7, 27, 79, 2), "2,false"),      # odd height at stride 2: the row below the plane
+    (dw(2, 3, 90, 331, 1), "1,false"),     # long rows, four output rows per band
+    (dw(2, 3, 90, 201, 2), "2,false"),
+    (dw(1, 2, 1, 682, 1), "1,false"),      # one row: windows past the band, more than 64 KB of LDS
+    (dw(1, 2, 2, 901, 2), "2,false"),
+    (dw(1, 3, 5, 1, 1), "1,false"),        # one column
+    (dw(1, 1, 1, 1, 2), "2,false"),        # one element
+    (dw(400, 13, 9, 9, 1), "1,true"),      # several planes per wavefront, the last one with fewer
+    (dw(401, 13, 9, 11, 2), "2,true"),
+    (dw(700, 11, 2, 3, 1), "1,true"),      # planes of six elements
+    (dw(700, 11, 1, 1, 1), "1,true"),      # of one
+    (dw(300, 7, 8, 5, 2), "2,true"),
+]
+
+
+@pytest.mark.parametrize("s,kind", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_rows(gpu, s, kind):
+    y, x, w, name = run_conv(gpu, s, seed=81)
+    assert name == f"conv_direct_rows<{kind}>", name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert not np.isnan(y).any()
+    # nine fused multiply-adds: each rounds the running sum by 2^-24 of sum |x w| at most
+    assert err_metrics(y, ref, absum)["bound"] < 9 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,H,W", [(2, 61, 67), (600, 9, 9)])
+def test_rows_residual_relu(gpu, N, H, W):
+    torch, b = gpu
+    C, dev = 6, "cuda:0"
+    ch = wl.Chain("dw", (N, C, H, W))
+    ch.conv(0, 1, N, C, H, W, C, 3, 1, 1, C)
+    ch.conv(1, 2, N, C, H, W, C, 3, 1, 1, C, relu=True, residual=0)
+    x0, weights = wl.make_input(ch.input_shape, 6), ch.make_weights(7)
+    b.gspc_set_chain_fusion(0)
+    try:
+        packed = [b.gspc_pack_weights(torch.from_numpy(v).to(dev), g) for v, g in zip(weights, ch.weight_groups)]
+        bufs = [torch.empty(max(n, 1), device=dev) for n in ch.buf_elems]
+        bufs[0].copy_(torch.from_numpy(x0).reshape(-1))
+        b.gspc_run_layer_chain(b.LayerChain(ch.layers, packed, bufs))
+        torch.cuda.synchronize()
+    finally:
+        b.gspc_set_chain_fusion(1)
+    ref = oracle.run_chain(ch.layers, len(ch.buf_elems), x0, weights, threads=4)[ch.out_buf]
+    got = bufs[ch.out_buf][:ref.size].cpu().numpy().reshape(ref.shape)
+    rms = float(np.sqrt(np.mean(ref * ref)))
+    # two layers of nine terms: 20 roundings of values up to a few times the result's rms
+    assert float(np.max(np.abs(got - ref))) < 1e-5 * max(rms, 1.0)
+
+
+def test_rows_infinity(gpu):
+    """An infinity reaches the outputs whose windows hold it, and no other: neither across rows nor across planes."""
+    torch, b = gpu
+    for N, C, H, W in [(1, 2, 50, 49), (500, 5, 7, 9)]:
+        x = np.ones((N, C, H, W), np.float32)
+        x[0, 0, 3, W - 1] = np.inf
+        x[0, 0, H - 1, 0] = -np.inf
+        w = np.ones((C, 1, 3, 3), np.float32)
+        pw = b.gspc_pack_weights(torch.from_numpy(w).to("cuda:0"), C)
+        y = b.gspc_conv2d_grouped(torch.from_numpy(x).to("cuda:0"), pw, N, C, H, W, C, 3, 3, 1, 1, C).cpu().numpy()
+        assert b.gspc_last_kernel().startswith("conv_direct_rows<")
+        bad = ~np.isfinite(y)
+        want = np.zeros_like(bad)
+        want[0, 0, 2:5, W - 2:] = True
+        want[0, 0, H - 2:, :2] = True
+        assert (bad == want).all()
