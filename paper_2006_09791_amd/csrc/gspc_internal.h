@@ -92,12 +92,11 @@ struct PackGeom {
     // [g][ceil(CPG/16)][ceil(KPG/16)][64 lanes][4], element e at channel 16*block + 4*e + lane/16
     // (unit_kernels.hip).
     size_t unit_bytes, unit_offset;
-    // Split 3x3 section (3x3, KPG >= 16, CPG >= 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
-    // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles, with more than 16384 weights per
-    // group (smaller ones stay a mere reordering of the weights besides Winograd's section; with the section they would
-    // be faster where Winograd now has them: 32 -> 96 in two groups on 14x14 at N = 256 25.2 / 21.1 us, 16 -> 64 on
-    // 18x18 25.8 / 19.6, stride 2 24 -> 64 on 28x28 26.5 / 20.3, 32 -> 32 per group level or behind) or CPG % 4 != 0: the three parts of the exact split of 2^24 times a weight; GSPC_BF16 handles with CPG % 8 != 0
-    // (no 16x16x32 section): the weight.
+    // Split 3x3 section (3x3, CPG, KPG >= 5): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
+    // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles: the three parts of the exact split of
+    // 2^24 times a weight, or (h3_plain: up to 256 weights per tap and group, which stay a mere reordering) fp32
+    // [16 filters][8 channels], split by the kernel; GSPC_BF16 handles: the weight.
+    int h3_plain;
     size_t h3_bytes, h3_offset;
     struct MergedDirect {
         int m, groups, CPG, KPG, KPGd;
@@ -196,6 +195,7 @@ struct WinoPlan {
     int data[48];
 };
 bool plan_wino(const ConvParams &p, const PackGeom &g, bool must_fill, WinoPlan *out);
+double wino_estimate(const ConvParams &p, const WinoPlan &plan);   // microseconds
 hipError_t launch_wino(const ConvParams &p, const WinoPlan &plan, hipStream_t s, const char **name);
 int winograd_mode();
 
@@ -213,8 +213,9 @@ struct Split3Plan {
     int inst, cgs;
     int data[24];
 };
-// when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; any.
-enum { kSplit3BeforeWinograd, kSplit3Else, kSplit3Any };
+// when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; those that
+// no other matrix-core kernel takes; any.
+enum { kSplit3BeforeWinograd, kSplit3Else, kSplit3Rest, kSplit3Any };
 bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out);
 hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_t s, const char **name);
 

@@ -766,7 +766,9 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
              plan_wino(p, g, winograd_mode() < 0 && fam != 'x', &pl.px))
         pl.kind = 64;
     else if (any && plan_unit(p, g, &pl.pu)) pl.kind = 19;
-    else if (any && may_split && plan_split3(p, g, kSplit3Else, &pl.ph) && !few_filters()) pl.kind = 20;
+    else if (any && may_split && !(g.variant == kMfma4 && plan_mfma4(p, g, &pl.p4)) && plan_split3(p, g, kSplit3Else, &pl.ph) &&
+             !few_filters())
+        pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
     // few filters per group: the 4x4x1 kernel where it has an instance, else padded 16-filter tiles
@@ -774,6 +776,7 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     else if (plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (may_split && plan_split(p, g, true, &pl.ps)) pl.kind = 18;
+    else if (any && may_split && plan_split3(p, g, kSplit3Rest, &pl.ph)) pl.kind = 20;
     return pl;
 }
 

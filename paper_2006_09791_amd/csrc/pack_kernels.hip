@@ -227,7 +227,7 @@ __device__ __forceinline__ void pack_unit(size_t d, const float *__restrict__ w,
     out[d] = v;
 }
 
-// Split 3x3 section, one thread per weight: its parts, 128 elements apart.
+// Split 3x3 section, one thread per weight: its parts, 128 elements apart, or (parts = 0) the fp32 weight.
 __device__ __forceinline__ void pack_split3(size_t d, const float *__restrict__ w, uint16_t *__restrict__ out,
                                             const PackArgs &a, int parts) {
     const int e = (int)(d % 8);
@@ -245,6 +245,10 @@ __device__ __forceinline__ void pack_split3(size_t d, const float *__restrict__ 
     const int f = mt * 16 + li, c = cg * 8 + e;
     float v = 0.f;
     if (f < a.KPG && c < a.CPG) v = w[(size_t)(j * a.KPG + f) * a.Kred + (size_t)c * 9 + tap];
+    if (parts == 0) {
+        reinterpret_cast<float *>(out)[d] = v;
+        return;
+    }
     unsigned s[3];
     split3(parts == 3 ? v * kSplitScale : v, 0.f, s);
     for (int q = 0; q < parts; ++q) out[(block * parts + q) * 128 + li * 8 + e] = (uint16_t)s[q];
@@ -348,7 +352,7 @@ hipError_t launch_pack_weights(const float *w, const gspc_packed *h, hipStream_t
     add(kPackWino, g.wino_offset, g.wino_bytes / sizeof(float));
     add(kPackQuadk, g.qk_offset, g.qk_bytes / sizeof(float), g.qk_m);
     add(kPackUnit, g.unit_offset, g.unit_bytes / sizeof(float));
-    add(kPackSplit3, g.h3_offset, g.h3_bytes / (a.to_bf16 ? 2 : 6), a.to_bf16 ? 1 : 3);
+    add(kPackSplit3, g.h3_offset, g.h3_bytes / (a.to_bf16 ? 2 : g.h3_plain ? 4 : 6), a.to_bf16 ? 1 : g.h3_plain ? 0 : 3);
     add(kPackSplit, g.split_offset, g.split_bytes / (g.split_parts ? 2 * g.split_parts : 4), g.split_chunks, g.split_mtiles,
         g.split_parts);
     for (const PackGeom::MergedDirect &md : g.md)

@@ -30,13 +30,14 @@ struct TileH {
     int nchunks, ncg, mtiles;     // chunks of 8*CGS channels, blocks of 8 channels, 16-filter tiles per group
     int oc_blocks, px_blocks;
     int LW, PW, ROWS, PLANE;      // row pitch in units, column pairs per row, rows allocated, units per 8 channels
+    int plain;                    // the filters are not split yet
     unsigned npix, HWo;
     unsigned m_HWo, m_Wout, m_PW, m_H2;
     unsigned x_bytes, w_bytes, y_bytes;
 };
 static_assert(sizeof(TileH) <= sizeof(((Split3Plan *)0)->data), "plan storage too small");
 
-template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO>
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO, bool PLAIN>
 __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p, TileH t) {
     constexpr int NP = sizeof(TIN) == 4 ? 3 : 1, ES = (int)sizeof(TIN);
     constexpr int NT = 64 * WM * WP, PB = 16 * NI * WP, KS = CGS == 4 ? 9 : 5;
@@ -77,20 +78,36 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wh, t.w_bytes);
 
-    // ---- filters: [g][8 channels][tap][filter tile][part][16 filters][8] -------------------------------
-    const unsigned wtap = t.mtiles * (NP * 256u);
-    const unsigned wlane = (CGS == 4 ? lg * 9 * wtap : (lg & 1) * 9 * wtap + (lg >> 1) * wtap) + li * 16;
+    // ---- filters: [g][8 channels][tap][filter tile][part][16 filters][8], PLAIN: fp32 [16 filters][8], split below ------
+    constexpr unsigned WT = PLAIN ? 512 : NP * 256;      // bytes of a filter tile at one tap
+    const unsigned wtap = t.mtiles * WT;
+    const unsigned wlane = (CGS == 4 ? lg * 9 * wtap : (lg & 1) * 9 * wtap + (lg >> 1) * wtap) + li * (PLAIN ? 32 : 16);
     const unsigned mt0 = ob * (MI * WM) + wm * MI;
     u32x4 wv[NA][MI][NP];
     auto fetch_w = [&](int ch, int ks, u32x4 (&v)[MI][NP]) __attribute__((always_inline)) {
-        const unsigned so = ((j * t.ncg + ch * CGS) * 9 + (CGS == 4 ? ks : 2 * ks)) * wtap + mt0 * (NP * 256u);
+        const unsigned so = ((j * t.ncg + ch * CGS) * 9 + (CGS == 4 ? ks : 2 * ks)) * wtap + mt0 * WT;
         const bool live = ch * CGS + (CGS == 4 ? lg : lg & 1) < t.ncg && (CGS == 4 || ks < 4 || lg < 2);
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int q = 0; q < NP; ++q)
+            for (int q = 0; q < (PLAIN ? 2 : NP); ++q)
                 v[mi][q] = __builtin_amdgcn_raw_buffer_load_b128(
-                    rw, live && (int)mt0 + mi < t.mtiles ? wlane : kOob, so + mi * (NP * 256u) + q * 256u, 0);
+                    rw, live && (int)mt0 + mi < t.mtiles ? wlane : kOob, so + mi * WT + q * (PLAIN ? 16u : 256u), 0);
+    };
+    auto split_w = [&](u32x4 (&v)[MI][NP]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            u32x4 o[3];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                unsigned s[3];
+                split3(__uint_as_float(v[mi][c / 2][c % 2 * 2]) * kSplitScale, __uint_as_float(v[mi][c / 2][c % 2 * 2 + 1]) * kSplitScale, s);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) o[q][c] = s[q];
+            }
+#pragma unroll
+            for (int q = 0; q < NP; ++q) v[mi][q] = o[q];
+        }
     };
 
     // ---- staging: a wave's task is 32 column pairs of one 8-channel block; lower lanes load channels 0-3,
@@ -249,6 +266,7 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
             if (ks + AH < KS) fetch_w(ch, ks + AH, wv[(ks + AH) % NA]);
             else fetch_w(ch + WK, ks + AH - KS, wv[(ks + AH) % NA]);
             if (ks < TS) fetch_x(ch + WK, wave + ks * (WM * WP), slot[ks], xv[ks]);
+            if constexpr (PLAIN) split_w(wv[ks % NA]);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
                 if (ni + 1 < NI) load_b(ks, ni + 1);
@@ -402,10 +420,19 @@ namespace {
 
 struct CfgH {
     int MI, NI, WM, WP, WK;
-    float kstep;      // microseconds per k-step of a block alone on its compute unit
+    float kstep;      // fp32 layers: microseconds per k-step of a block alone on its compute unit
+    // bf16 layers: microseconds per launch and per block, chunk, k-step and 1000 staged units (16 bytes) of a compute unit
+    float launch, block, chunk, step, stage;
 };
-// (bf16 layers: the first two, which do not split the chunks)
-const CfgH kCfgH[] = {{2, 4, 2, 2, 1, 0.75f}, {2, 2, 2, 2, 1, 0.5f}, {2, 4, 2, 1, 2, 0.75f}, {2, 2, 1, 1, 4, 0.5f}};
+const CfgH kCfgH[] = {
+    {2, 4, 2, 2, 1, 0.75f, 5.3f, 0.59f, 0.36f, 0.027f, 0.49f},
+    {2, 2, 2, 2, 1, 0.5f, 4.5f, 0.53f, 0.30f, 0.040f, 0.22f},
+    {2, 4, 2, 1, 2, 0.75f},
+    {2, 2, 1, 1, 4, 0.5f},
+    {2, 4, 1, 4, 1, 0.82f, 5.3f, 0.74f, 0.19f, 0.f, 0.75f},     // up to 32 filters per group
+    {1, 4, 1, 4, 1, 0.52f, 5.3f, 0.58f, 0.034f, 0.f, 0.63f},     // up to 16
+    {1, 2, 1, 4, 1, 0.31f},
+};
 constexpr int kNumCfgH = sizeof(kCfgH) / sizeof(kCfgH[0]);
 constexpr int kLdsBlockH = 78 * 1024;   // two blocks per compute unit
 
@@ -415,10 +442,10 @@ size_t lds_bytes_h(const CfgH &c, int cgs, int parts, const TileH &t) {
     return tiles > sums ? tiles : sums;
 }
 
-template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO>
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO, bool PLAIN>
 hipError_t launchH(const ConvParams &p, const TileH &t, hipStream_t s) {
-    const size_t lds = lds_bytes_h(CfgH{MI, NI, WM, WP, WK, 0.f}, CGS, sizeof(TIN) == 4 ? 3 : 1, t);
-    auto kern = conv_split3<MI, NI, WM, WP, WK, CGS, S, TIN, EVEN, VO>;
+    const size_t lds = lds_bytes_h(CfgH{MI, NI, WM, WP, WK, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, CGS, sizeof(TIN) == 4 ? 3 : 1, t);
+    auto kern = conv_split3<MI, NI, WM, WP, WK, CGS, S, TIN, EVEN, VO, PLAIN>;
     if (lds > 64 * 1024) {
         static thread_local bool raised = false;   // per instantiation and thread
         if (!raised) {
@@ -434,18 +461,18 @@ hipError_t launchH(const ConvParams &p, const TileH &t, hipStream_t s) {
 }
 
 // 16-byte stores (VO) go with 8-byte loads: an odd row width takes the 4-byte forms of both
-template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN>
+template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool PLAIN>
 hipError_t launchH_form(const ConvParams &p, const TileH &t, hipStream_t s) {
-    if (p.W & 1) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, false, false>(p, t, s);
-    if (t.HWo % 4) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, false>(p, t, s);
-    return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, true>(p, t, s);
+    if (p.W & 1) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, false, false, PLAIN>(p, t, s);
+    if (t.HWo % 4) return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, false, PLAIN>(p, t, s);
+    return launchH<MI, NI, WM, WP, WK, CGS, S, TIN, true, true, PLAIN>(p, t, s);
 }
 
-template <int MI, int NI, int WM, int WP, int WK, typename TIN>
+template <int MI, int NI, int WM, int WP, int WK, typename TIN, bool PLAIN = false>
 hipError_t launchH_cgs(const ConvParams &p, const TileH &t, int cgs, hipStream_t s) {
     if (cgs == 4)
-        return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 4, 1, TIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 4, 2, TIN>(p, t, s);
-    return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 2, 1, TIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 2, 2, TIN>(p, t, s);
+        return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 4, 1, TIN, PLAIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 4, 2, TIN, PLAIN>(p, t, s);
+    return p.stride == 1 ? launchH_form<MI, NI, WM, WP, WK, 2, 1, TIN, PLAIN>(p, t, s) : launchH_form<MI, NI, WM, WP, WK, 2, 2, TIN, PLAIN>(p, t, s);
 }
 
 bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, TileH *out) {
@@ -463,6 +490,7 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
     t.px_blocks = (int)pxb;
     t.HWo = p.Hout * p.Wout;
     t.npix = (unsigned)npix;
+    t.plain = g.h3_plain;
     // rows of a tile: those its pixels span, three taps, and at every change of image the rows between the last
     // window of one and the first of the next
     const int span = (PB - 2) / p.Wout + 2, cross = p.N > 1 ? (PB - 2) / (int)t.HWo + 1 : 0;
@@ -512,31 +540,50 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 //  - other stride-1 layers: with at least 128 channels per group where neither Winograd (64 -> 64 on 16x16 at N = 256
 //    25.6 / 25.3) nor a launch of more blocks than the chip holds covers the fp32
 //    kernel's waits: 128 -> 128 on 8x8 13.4 / 10.3 (64 channels per group: 8.6 / 10.2).
+//  - other planes whose 2x2 tiles do not fill Winograd's blocks whole, where the estimate here is shorter than Winograd's:
+//    32 -> 32 per group on 18x18, g = 32 138 / 75, 92 on 24x24, g = 2, N = 198 325 / 176, 112 on 36x36, g = 3, N = 40 330 / 203,
+//    16 on 72x72, g = 32, N = 5 67.5 / 47.  Planes that fill them stay: 16 -> 16 on 32x32, g = 2 8.9 / 10.4, 32 -> 32 at N = 256
+//    34.9 / 34.4;
+//  - odd rows or channels with few weights, the same way against 9.5 Tera-products per second, which is the best of the kernels
+//    that these layers have otherwise: 16 -> 16 on 98x98, g = 16, N = 13 418 / 112, 32 -> 10 on 33x33, g = 4 41.6 / 23.9 with
+//    72, 126 -> 12 on 38x38, g = 3, N = 4 258 / 15, 80 -> 12 on 85x85, g = 2, N = 27 641 / 89; not: 8 -> 8 per group, which the
+//    4x4x1 kernel takes (29x29, g = 32, N = 143 106 / 219), and up to 256 weights per tap on small planes (16 -> 16 on 17x19,
+//    g = 2, N = 207 18.1 / 16.8, which is level where launches are smaller).
 // With Winograd switched off (gspc_set_winograd(0)) every fp32 3x3 layer stays on the fp32 instruction.
 bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out) {
     if (!p.wh || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2)) return false;
     const bool odd = p.W % 4 != 0 || g.CPG % 4 != 0;
+    // layers of more than 16384 weights per group, or whose channels only this kernel takes in whole chunks
+    const bool large = g.KPG >= 16 && g.CPG >= 8 && ((long)g.CPG * g.KPG * 9 > 16384 || g.CPG % 4 != 0);
     const int ft = (g.KPG + 63) / 64 * 64;
     const int wt = (p.Hout + 1) / 2 * ((p.Wout + 1) / 2), wr = (wt + 31) / 32 * 32;
     const bool ragged = p.H * p.W > 256 && 10 * (wr - wt) > wr && g.CPG % 32 == 0 && ft == g.KPG &&
                         (double)p.N * p.Hout * p.Wout * p.Cout > kNumCU * 64 * 128.0;
-    if (when == kSplit3BeforeWinograd && (!(odd || ragged) || p.stride != 1 || ft >= 2 * g.KPG)) return false;
-    if (when == kSplit3Else && !odd && p.stride == 1 && g.CPG < 128) return false;
+    const bool sure = large && (odd ? ft < 2 * g.KPG : ragged);   // Winograd's estimate is not asked
+    if (when == kSplit3BeforeWinograd && (p.stride != 1 || (!sure && (!g.wino_bytes || wt == wr || 32 % wt == 0)))) return false;
+    if (when == kSplit3Else && !odd && (p.stride == 1 ? g.CPG < 128 : !large)) return false;
+    if (when == kSplit3Else && !large && g.CPG * g.KPG <= 256 && p.H * p.W < 400) return false;
     double best = 0.0;
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
-        if (p.in_bf16 && i > 1) continue;
+        if (p.in_bf16 && c.launch == 0.f) continue;
+        if (g.h3_plain && i < 5) continue;
         for (int cgs : {4, 2}) {
             TileH t;
             if (cgs == 4 && (g.CPG + 15) / 16 * 16 < (g.CPG + 31) / 32 * 32 - 8) continue;
             if (!planH_cfg(p, g, c, cgs, &t)) continue;
             const long blocks = (long)t.px_blocks * t.oc_blocks * p.groups, n = (blocks + kNumCU - 1) / kNumCU;
-            if ((when != kSplit3Any && blocks < kNumCU / 4) || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
+            if ((when < kSplit3Rest && blocks < kNumCU / 4) || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
                 (when == kSplit3Else && !odd && p.stride == 1 && n > 2))
                 continue;
             const double rounds = (t.nchunks + c.WK - 1) / c.WK, ks = rounds * (cgs == 4 ? 9 : 5 * 1.3);
-            const double one = ks * c.kstep * (p.stride == 2 && c.NI == 4 ? 1.4 : 1.0) + rounds + 1.5;
-            const double est = (c.WK > 1 ? 1.1 : 1.0) * one * (1.45 * (double)(n / 2) + (double)(n % 2));
+            const double wide = p.stride == 1 ? 1.0 : c.WM == 1 ? (c.NI == 4 ? 1.4 : 1.35) : c.WK > 1 ? 1.4 : c.NI == 4 ? 1.15 : 0.75;
+            const double one = ks * c.kstep * wide + rounds + 1.5;
+            double est = (c.WK > 1 ? 1.1 : 1.0) * one * (1.45 * (double)(n / 2) + (double)(n % 2));
+            if (p.in_bf16) {
+                const double per_unit = n > 1 ? 0.5 * (double)n + 0.5 * (double)blocks / kNumCU : 1.0;
+                est = c.launch + per_unit * (c.block + t.nchunks * (c.chunk + (cgs == 4 ? 9 : 5) * c.step + 1e-3 * cgs * t.PLANE * c.stage));
+            }
             if (best != 0.0 && est >= best) continue;
             best = est;
             out->inst = i;
@@ -544,7 +591,15 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
             std::memcpy(out->data, &t, sizeof(t));
         }
     }
-    return best != 0.0;
+    if (best == 0.0) return false;
+    if (when == kSplit3BeforeWinograd && !sure) {
+        WinoPlan px;
+        return plan_wino(p, g, true, &px) && (g.h3_plain ? best + 4.0 : 0.82 * best + 3.0) < wino_estimate(p, px);
+    }
+    // (what is left runs at up to 9.5 Tera-products per second)
+    const double macs = (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9;
+    if ((when == kSplit3Else && !large) || when == kSplit3Rest) return 0.87 * best < 3.0 + macs / 9.5e6;
+    return true;
 }
 
 hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_t s, const char **name) {
@@ -556,12 +611,16 @@ hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_
         *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
                             "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +
                             std::to_string(p.stride) + (p.in_bf16 ? ",bf16" : ",f32") + (even ? ",true" : ",false") +
-                            (even && t.HWo % 4 == 0 ? ",true>" : ",false>"));
+                            (even && t.HWo % 4 == 0 ? ",true>" : ",false>") + (t.plain ? "/plain" : ""));
+    if (t.plain) return plan.inst == 5 ? launchH_cgs<1, 4, 1, 4, 1, float, true>(p, t, plan.cgs, s) : launchH_cgs<1, 2, 1, 4, 1, float, true>(p, t, plan.cgs, s);
     switch (plan.inst) {
     case 0: return p.in_bf16 ? launchH_cgs<2, 4, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 4, 2, 2, 1, float>(p, t, plan.cgs, s);
     case 1: return p.in_bf16 ? launchH_cgs<2, 2, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 2, 2, 2, 1, float>(p, t, plan.cgs, s);
     case 2: return launchH_cgs<2, 4, 2, 1, 2, float>(p, t, plan.cgs, s);
     case 3: return launchH_cgs<2, 2, 1, 1, 4, float>(p, t, plan.cgs, s);
+    case 4: return p.in_bf16 ? launchH_cgs<2, 4, 1, 4, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 4, 1, 4, 1, float>(p, t, plan.cgs, s);
+    case 5: return p.in_bf16 ? launchH_cgs<1, 4, 1, 4, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<1, 4, 1, 4, 1, float>(p, t, plan.cgs, s);
+    case 6: return launchH_cgs<1, 2, 1, 4, 1, float>(p, t, plan.cgs, s);
     }
     return hipErrorNotSupported;
 }

@@ -1,0 +1,59 @@
+"""3x3 layers of few filters per group on the bf16 matrix instruction: blocks of 16 and 32 filters, filters that the
+kernel splits itself; against the oracle's plain definition."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import err_metrics
+from paper_2006_09791_amd import workloads as wl
+from test_gpu_parity import gpu, run_conv  # noqa: F401  (fixture)
+from test_gpu_split import split_bound
+
+pytestmark = pytest.mark.gpu
+S = wl.ConvShape
+SHAPES = [
+    # N Cin H W Cout KH KW stride pad groups
+    (S(30, 56, 46, 46, 56, 3, 3, 1, 1, 2), "2,4,1,4,1,", "f32,true,true>"),          # 28 filters, padded channels
+    (S(30, 138, 29, 29, 138, 3, 3, 1, 1, 2), "", "f32,false,false>"),     # 69: two tiles of 32 and five left
+    (S(25, 160, 33, 33, 24, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,false,false>"),      # 12 filters, 80 channels
+    (S(120, 128, 23, 23, 128, 3, 3, 2, 1, 4), "", "f32,false,false>"),     # stride 2
+    (S(4, 378, 38, 38, 36, 3, 3, 1, 1, 3), "1,2,1,4,1,", "f32,true,true>"),         # 126 channels
+    (S(12, 64, 55, 55, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "f32,false,false>/plain"),  # 16 and 16: split in the kernel
+    (S(40, 64, 50, 46, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "f32,true,true>/plain"),
+    (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "f32,false,false>/plain"),  # stride 2, 15 and 9
+    (S(30, 20, 70, 94, 16, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,true,true>/plain"),    # 10 and 8
+    (S(40, 66, 60, 58, 6, 3, 3, 1, 1, 1), "1,4,1,4,1,", "f32,true,true>"),          # six filters
+]
+
+
+@pytest.mark.parametrize("s,block,form", SHAPES, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_blocks(gpu, s, block, form):
+    torch, b = gpu
+    bf16 = form.startswith("bf16")
+    y, x, w, name = run_conv(gpu, s, seed=91, dtype=b.GSPC_BF16 if bf16 else b.GSPC_F32)
+    assert name.startswith("conv_split3<" + block) and name.endswith(form), name
+    if bf16:
+        x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert not np.isnan(y).any(), name
+    m = err_metrics(y, ref, absum)
+    # (the bound of the pointwise form for nine times the terms, a quarter of a k-step lost per 16 channels)
+    assert m["bound"] < split_bound(9 * s.Cin // s.groups + 16), (name, m)
+
+
+@pytest.mark.parametrize("s", [S(12, 64, 55, 55, 64, 3, 3, 1, 1, 4), S(30, 138, 29, 29, 138, 3, 3, 1, 1, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("xs,ws", [(-110, 60), (60, -110), (70, 40)])
+def test_scales(gpu, s, xs, ws):
+    """Factors far from 1, and sums that overflow the scaled accumulators (recomputed as plain sums)."""
+    torch, b = gpu
+    x = wl.make_input((s.N, s.Cin, s.H, s.W), 92)
+    w = wl.make_weight(s.Cout, s.Cin // s.groups, 3, 3, 92)
+    xd = torch.from_numpy(np.ldexp(x, xs)).cuda()
+    pw = b.gspc_pack_weights(torch.from_numpy(np.ldexp(w, ws)).cuda(), s.groups)
+    y = b.gspc_conv2d_grouped(xd, pw, s.N, s.Cin, s.H, s.W, s.Cout, 3, 3, s.stride, s.pad, s.groups).cpu().numpy()
+    assert b.gspc_last_kernel().startswith("conv_split3<"), b.gspc_last_kernel()
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    m = err_metrics(np.ldexp(y.astype(np.float64), -xs - ws), ref, absum)
+    # (a plain sum rounds once per term: 9 * channels roundings of at most the sum of magnitudes)
+    assert m["bound"] < 9 * s.Cin // s.groups * 2.0 ** -24, m
