@@ -216,6 +216,7 @@ struct Split3Plan {
 // when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; those that
 // no other matrix-core kernel takes; any.
 enum { kSplit3BeforeWinograd, kSplit3Else, kSplit3Rest, kSplit3Any };
+bool prefers_split3_bf16(const ConvParams &p, const PackGeom &g);
 bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out);
 hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_t s, const char **name);
 

@@ -550,6 +550,25 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 //    4x4x1 kernel takes (29x29, g = 32, N = 143 106 / 219), and up to 256 weights per tap on small planes (16 -> 16 on 17x19,
 //    g = 2, N = 207 18.1 / 16.8, which is level where launches are smaller).
 // With Winograd switched off (gspc_set_winograd(0)) every fp32 3x3 layer stays on the fp32 instruction.
+//
+// bf16 layers that the 16x16x32 kernel takes too (us, that kernel / this one):
+//  - groups that it merges (channels not a multiple of 8), eight channels apart: 63 -> 63 on 8x8, g = 8 54 / 5.7, 80 -> 57 on 36x18
+//    at stride 2 166 / 25, 128 -> 25 on 88x88 597 / 98, 6 -> 64 on 72x72 60 / 39; 8 -> 8 merged in pairs stays (13.7 / 25.6);
+//  - 40 channels and more that it takes in chunks of 8 (104 on 20x79 127 / 63, 72 on 75x75 241 / 137) or, on rows of an even
+//    length, of 16 (48 on 44x44 151 / 83, 112 on 25x25 281 / 169; 48 on 21x21 18.5 / 21.3; 16 channels 0.5-0.9 of its speed);
+//  - from 64 channels in chunks of 32 at stride 1, on rows it loads in less than 16 bytes: 128 -> 128 on 14x14, g = 2, N = 256
+//    51.7 / 42.7, on 18x18 59 / 40, 64 on 52x52 18.7 / 13.9; rows of whole octets (32 on 56x56 72 / 91, 128 on 48x48 at stride 2
+//    83 / 104), long rows (96 on 110x110 61 / 75) and 7x7 planes (44 / 55) stay.
+bool prefers_split3_bf16(const ConvParams &p, const PackGeom &g) {
+    if (!p.in_bf16 || !p.wh || !g.bf16_bytes) return false;
+    if (g.mb > 1) return g.CPG != 8;
+    const double macs = (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9;
+    if (g.CPG < 40 || macs < 3e8) return false;
+    if (g.CPG % 16) return true;
+    if (g.KPG < 32 || p.W % 2) return false;
+    return g.CPG % 32 || (g.CPG >= 64 && p.stride == 1 && p.W % 8 && p.W <= 80 && p.H * p.W >= 100 && macs >= 1e9);
+}
+
 bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *out) {
     if (!p.wh || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2)) return false;
     const bool odd = p.W % 4 != 0 || g.CPG % 4 != 0;

@@ -1,5 +1,5 @@
 """3x3 layers of few filters per group on the bf16 matrix instruction: blocks of 16 and 32 filters, filters that the
-kernel splits itself; against the oracle's plain definition."""
+kernel splits itself, and the bf16 layers it takes from the 16x16x32 kernel; against the oracle's plain definition."""
 import numpy as np
 import pytest
 
@@ -23,6 +23,12 @@ SHAPES = [
     (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "f32,false,false>/plain"),  # stride 2, 15 and 9
     (S(30, 20, 70, 94, 16, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,true,true>/plain"),    # 10 and 8
     (S(40, 66, 60, 58, 6, 3, 3, 1, 1, 1), "1,4,1,4,1,", "f32,true,true>"),          # six filters
+    (S(10, 72, 33, 34, 72, 3, 3, 1, 1, 4), "", "bf16,true,false>"),                 # groups of 18
+    (S(6, 189, 18, 20, 189, 3, 3, 1, 1, 3), "", "bf16,true,true>"),                 # of 63
+    (S(20, 104, 20, 39, 104, 3, 3, 1, 1, 1), "", "bf16,false,false>"),              # 104 channels
+    (S(64, 256, 14, 14, 256, 3, 3, 1, 1, 2), "", "bf16,true,true>"),                # 128
+    (S(10, 80, 41, 44, 57, 3, 3, 2, 1, 1), "", "bf16,true,false>"),                 # stride 2, 57 filters
+    (S(3, 70, 40, 41, 49, 3, 3, 1, 1, 7), "", "bf16,false,false>"),                 # 10 and 7
 ]
 
 
