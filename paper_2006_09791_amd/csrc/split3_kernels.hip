@@ -551,12 +551,16 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 //    g = 2, N = 207 18.1 / 16.8, which is level where launches are smaller).
 // With Winograd switched off (gspc_set_winograd(0)) every fp32 3x3 layer stays on the fp32 instruction.
 //
+// (Blocks of 128 filters x 128 pixels and 64 x 256 for bf16 layers, with half the operand reads per product: 41.1 and 45.7 us
+// against 41.4 on the 14x14 layer below, up to 1.6 times the time elsewhere.)
+//
 // bf16 layers that the 16x16x32 kernel takes too (us, that kernel / this one):
 //  - groups that it merges (channels not a multiple of 8), eight channels apart: 63 -> 63 on 8x8, g = 8 54 / 5.7, 80 -> 57 on 36x18
 //    at stride 2 166 / 25, 128 -> 25 on 88x88 597 / 98, 6 -> 64 on 72x72 60 / 39; 8 -> 8 merged in pairs stays (13.7 / 25.6);
-//  - 40 channels and more that it takes in chunks of 8 (104 on 20x79 127 / 63, 72 on 75x75 241 / 137) or, on rows of an even
-//    length, of 16 (48 on 44x44 151 / 83, 112 on 25x25 281 / 169; 48 on 21x21 18.5 / 21.3; 16 channels 0.5-0.9 of its speed);
-//  - from 64 channels in chunks of 32 at stride 1, on rows it loads in less than 16 bytes: 128 -> 128 on 14x14, g = 2, N = 256
+//  - 40 channels and more that it takes in chunks of 8 (104 on 20x79 127 / 63, 72 on 75x75 241 / 137) or 16 (48 on 44x44
+//    151 / 83, 112 on 25x25 281 / 169; 16 channels 0.5-0.9 of its speed), below 80 channels on rows of an even length only (48 on
+//    21x21 18.5 / 21.3);
+//  - from 64 channels in chunks of 32 at stride 1, on rows it loads in less than 16 bytes (96 on 71x75 137 / 93): 128 -> 128 on 14x14, g = 2, N = 256
 //    51.7 / 42.7, on 18x18 59 / 40, 64 on 52x52 18.7 / 13.9; rows of whole octets (32 on 56x56 72 / 91, 128 on 48x48 at stride 2
 //    83 / 104), long rows (96 on 110x110 61 / 75) and 7x7 planes (44 / 55) stay.
 bool prefers_split3_bf16(const ConvParams &p, const PackGeom &g) {
@@ -565,7 +569,7 @@ bool prefers_split3_bf16(const ConvParams &p, const PackGeom &g) {
     const double macs = (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9;
     if (g.CPG < 40 || macs < 3e8) return false;
     if (g.CPG % 16) return true;
-    if (g.KPG < 32 || p.W % 2) return false;
+    if (g.KPG < 32 || (p.W % 2 && g.CPG < 80)) return false;
     return g.CPG % 32 || (g.CPG >= 64 && p.stride == 1 && p.W % 8 && p.W <= 80 && p.H * p.W >= 100 && macs >= 1e9);
 }
 
@@ -586,7 +590,6 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
         if (p.in_bf16 && c.launch == 0.f) continue;
-        if (g.h3_plain && i < 5) continue;
         for (int cgs : {4, 2}) {
             TileH t;
             if (cgs == 4 && (g.CPG + 15) / 16 * 16 < (g.CPG + 31) / 32 * 32 - 8) continue;
