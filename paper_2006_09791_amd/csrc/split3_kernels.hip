@@ -434,6 +434,7 @@ const CfgH kCfgH[] = {
     {1, 2, 1, 4, 1, 0.31f},
 };
 constexpr int kNumCfgH = sizeof(kCfgH) / sizeof(kCfgH[0]);
+constexpr int kFirstPlain = 5;   // shapes of one filter tile, which have an instance that splits the filters itself
 constexpr int kLdsBlockH = 78 * 1024;   // two blocks per compute unit
 
 size_t lds_bytes_h(const CfgH &c, int cgs, int parts, const TileH &t) {
@@ -590,6 +591,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
         if (p.in_bf16 && c.launch == 0.f) continue;
+        if (g.h3_plain && i < kFirstPlain) continue;
         for (int cgs : {4, 2}) {
             TileH t;
             if (cgs == 4 && (g.CPG + 15) / 16 * 16 < (g.CPG + 31) / 32 * 32 - 8) continue;

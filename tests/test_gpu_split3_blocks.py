@@ -22,6 +22,7 @@ SHAPES = [
     (S(40, 64, 50, 46, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "f32,true,true>/plain"),
     (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "f32,false,false>/plain"),  # stride 2, 15 and 9
     (S(30, 20, 70, 94, 16, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,true,true>/plain"),    # 10 and 8
+    (S(30, 48, 45, 47, 144, 3, 3, 1, 1, 6), "1,4,1,4,1,", "f32,false,false>/plain"),  # 8 and 24: two filter tiles
     (S(40, 66, 60, 58, 6, 3, 3, 1, 1, 1), "1,4,1,4,1,", "f32,true,true>"),          # six filters
     (S(10, 72, 33, 34, 72, 3, 3, 1, 1, 4), "", "bf16,true,false>"),                 # groups of 18
     (S(6, 189, 18, 20, 189, 3, 3, 1, 1, 3), "", "bf16,true,true>"),                 # of 63
