@@ -345,7 +345,7 @@ PackGeom make_pack_geom(int Cin, int Cout, int KH, int KW, int groups, int dtype
         g.unit_bytes = KH == 3 ? g.mfma_bytes : (size_t)groups * ((g.CPG + 15) / 16) * g.mtiles * 1024;
         g.total_bytes = g.unit_offset + g.unit_bytes;
     }
-    if (KH == 3 && KW == 3 && g.KPG >= 5 && g.CPG >= 5) {
+    if (KH == 3 && KW == 3 && g.CPG >= 2 && (g.KPG >= 5 || g.CPG > 8)) {
         g.h3_plain = dtype == GSPC_F32 && g.CPG * g.KPG <= 256;
         g.h3_offset = (g.total_bytes + 255) / 256 * 256;
         g.h3_bytes = (size_t)groups * ((g.CPG + 7) / 8) * 9 * ((g.KPG + 15) / 16) * (dtype != GSPC_F32 ? 256 : g.h3_plain ? 512 : 768);

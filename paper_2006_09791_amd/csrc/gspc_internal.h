@@ -92,7 +92,7 @@ struct PackGeom {
     // [g][ceil(CPG/16)][ceil(KPG/16)][64 lanes][4], element e at channel 16*block + 4*e + lane/16
     // (unit_kernels.hip).
     size_t unit_bytes, unit_offset;
-    // Split 3x3 section (3x3, CPG, KPG >= 5): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
+    // Split 3x3 section (3x3, CPG >= 2, KPG >= 5 or CPG > 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
     // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles: the three parts of the exact split of
     // 2^24 times a weight, or (h3_plain: up to 256 weights per tap and group, which stay a mere reordering) fp32
     // [16 filters][8 channels], split by the kernel; GSPC_BF16 handles: the weight.

@@ -20,6 +20,7 @@
 // vector memory path issues).  128 -> 128 on 28x28, g = 2, N = 64 (784 blocks on 512 slots): a compute unit is busy
 // 0.63 of the launch and its matrix unit 0.57 of that; 0.55 of the cycles of the LDS's operand accesses are bank
 // conflicts (counters).
+#include <algorithm>
 #include <cstring>
 
 #include "split_common.h"
@@ -585,6 +586,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
                         (double)p.N * p.Hout * p.Wout * p.Cout > kNumCU * 64 * 128.0;
     const bool sure = large && (odd ? ft < 2 * g.KPG : ragged);   // Winograd's estimate is not asked
     if (when == kSplit3BeforeWinograd && (p.stride != 1 || (!sure && (!g.wino_bytes || wt == wr || 32 % wt == 0)))) return false;
+    if (when != kSplit3Rest && (g.CPG < 5 || g.KPG < 5)) return false;
     if (when == kSplit3Else && !odd && (p.stride == 1 ? g.CPG < 128 : !large)) return false;
     if (when == kSplit3Else && !large && g.CPG * g.KPG <= 256 && p.H * p.W < 400) return false;
     double best = 0.0;
@@ -620,9 +622,12 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
         WinoPlan px;
         return plan_wino(p, g, true, &px) && (g.h3_plain ? best + 4.0 : 0.82 * best + 3.0) < wino_estimate(p, px);
     }
-    // (what is left runs at up to 9.5 Tera-products per second)
+    // (what is left runs at up to 9.5 Tera-products per second; with no other matrix-core kernel at 0.13 us or more per
+    // term of a sum: 40 -> 2 on 44x44, g = 3, N = 7 51 / 13 before / with this kernel, 100 -> 3 on 9x9, N = 8
+    // 119 / 11, 300 -> 6 on 17x17, g = 3, N = 40 in bf16 168 / 14)
     const double macs = (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9;
-    if ((when == kSplit3Else && !large) || when == kSplit3Rest) return 0.87 * best < 3.0 + macs / 9.5e6;
+    if (when == kSplit3Else && !large) return 0.87 * best < 3.0 + macs / 9.5e6;
+    if (when == kSplit3Rest) return 0.87 * best < 3.0 + std::max(macs / 9.5e6, 0.13 * 9 * g.CPG);
     return true;
 }
 

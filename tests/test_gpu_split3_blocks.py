@@ -22,8 +22,13 @@ SHAPES = [
     (S(40, 64, 50, 46, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "f32,true,true>/plain"),
     (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "f32,false,false>/plain"),  # stride 2, 15 and 9
     (S(30, 20, 70, 94, 16, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,true,true>/plain"),    # 10 and 8
-    (S(30, 48, 45, 47, 144, 3, 3, 1, 1, 6), "1,4,1,4,1,", "f32,false,false>/plain"),  # 8 and 24: two filter tiles
+    (S(30, 60, 45, 47, 144, 3, 3, 1, 1, 6), "1,4,1,4,1,", "f32,false,false>/plain"),  # 10 and 24: two filter tiles
     (S(40, 66, 60, 58, 6, 3, 3, 1, 1, 1), "1,4,1,4,1,", "f32,true,true>"),          # six filters
+    (S(7, 120, 44, 44, 6, 3, 3, 1, 1, 3), "1,4,1,4,1,", "f32,true,true>/plain"),     # two filters
+    (S(8, 100, 9, 9, 3, 3, 3, 1, 1, 1), "", "f32,false,false>"),                    # three
+    (S(9, 30, 21, 22, 4, 3, 3, 1, 1, 2), "", "f32,true,false>/plain"),              # 15 channels, two filters
+    (S(40, 300, 17, 17, 6, 3, 3, 1, 1, 3), "", "bf16,false,false>"),                # bf16, two filters
+    (S(186, 7, 66, 66, 7, 3, 3, 2, 1, 1), "", "bf16,true,false>"),                  # seven and seven, stride 2
     (S(10, 72, 33, 34, 72, 3, 3, 1, 1, 4), "", "bf16,true,false>"),                 # groups of 18
     (S(6, 189, 18, 20, 189, 3, 3, 1, 1, 3), "", "bf16,true,true>"),                 # of 63
     (S(20, 104, 20, 39, 104, 3, 3, 1, 1, 1), "", "bf16,false,false>"),              # 104 channels
