@@ -211,6 +211,7 @@ hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t 
 // fp32 3x3 layers on the bf16 matrix instruction through the exact three-way split (split3_kernels.hip).
 struct Split3Plan {
     int inst, cgs;
+    int plain;       // the handle's filters are not split yet (not in `data`, the kernel's argument: it has a template argument)
     int data[24];
 };
 // when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; those that

@@ -31,7 +31,6 @@ struct TileH {
     int nchunks, ncg, mtiles;     // chunks of 8*CGS channels, blocks of 8 channels, 16-filter tiles per group
     int oc_blocks, px_blocks;
     int LW, PW, ROWS, PLANE;      // row pitch in units, column pairs per row, rows allocated, units per 8 channels
-    int plain;                    // the filters are not split yet
     unsigned npix, HWo;
     unsigned m_HWo, m_Wout, m_PW, m_H2;
     unsigned x_bytes, w_bytes, y_bytes;
@@ -492,7 +491,6 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
     t.px_blocks = (int)pxb;
     t.HWo = p.Hout * p.Wout;
     t.npix = (unsigned)npix;
-    t.plain = g.h3_plain;
     // rows of a tile: those its pixels span, three taps, and at every change of image the rows between the last
     // window of one and the first of the next
     const int span = (PB - 2) / p.Wout + 2, cross = p.N > 1 ? (PB - 2) / (int)t.HWo + 1 : 0;
@@ -614,6 +612,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
             best = est;
             out->inst = i;
             out->cgs = cgs;
+            out->plain = g.h3_plain;
             std::memcpy(out->data, &t, sizeof(t));
         }
     }
@@ -640,8 +639,8 @@ hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_
         *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
                             "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +
                             std::to_string(p.stride) + (p.in_bf16 ? ",bf16" : ",f32") + (even ? ",true" : ",false") +
-                            (even && t.HWo % 4 == 0 ? ",true>" : ",false>") + (t.plain ? "/plain" : ""));
-    if (t.plain) return plan.inst == 5 ? launchH_cgs<1, 4, 1, 4, 1, float, true>(p, t, plan.cgs, s) : launchH_cgs<1, 2, 1, 4, 1, float, true>(p, t, plan.cgs, s);
+                            (even && t.HWo % 4 == 0 ? ",true>" : ",false>") + (plan.plain ? "/plain" : ""));
+    if (plan.plain) return plan.inst == 5 ? launchH_cgs<1, 4, 1, 4, 1, float, true>(p, t, plan.cgs, s) : launchH_cgs<1, 2, 1, 4, 1, float, true>(p, t, plan.cgs, s);
     switch (plan.inst) {
     case 0: return p.in_bf16 ? launchH_cgs<2, 4, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 4, 2, 2, 1, float>(p, t, plan.cgs, s);
     case 1: return p.in_bf16 ? launchH_cgs<2, 2, 2, 2, 1, uint16_t>(p, t, plan.cgs, s) : launchH_cgs<2, 2, 2, 2, 1, float>(p, t, plan.cgs, s);

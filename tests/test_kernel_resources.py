@@ -1,0 +1,45 @@
+"""Registers that the compiler reports for the library's kernels (the metadata notes of libgspc.so's own code objects)."""
+import struct
+
+import pytest
+
+from paper_2006_09791_amd import binding as b
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def kernels():
+    """Mangled name -> metadata of every kernel in the library."""
+    data, found, at = open(b.LIB_PATH, "rb").read(), {}, 0
+    while (at := data.find(b"\x7fELF\x02\x01\x01\x40", at)) >= 0:      # an embedded code object
+        elf = data[at:]
+        shoff, = struct.unpack_from("<Q", elf, 40)
+        size, count = struct.unpack_from("<HH", elf, 58)
+        for i in range(count):
+            kind, = struct.unpack_from("<I", elf, shoff + i * size + 4)
+            off, left = struct.unpack_from("<QQ", elf, shoff + i * size + 24)
+            while kind == 7 and left > 0:                              # notes
+                nl, dl, note = struct.unpack_from("<III", elf, off)
+                body = off + 12 + (nl + 3) // 4 * 4
+                if note == 32:
+                    for k in msgpack.unpackb(elf[body:body + dl])["amdhsa.kernels"]:
+                        found[k[".name"]] = k
+                step = body + (dl + 3) // 4 * 4 - off
+                off, left = off + step, left - step
+        at += 4
+    return found
+
+
+@pytest.mark.parametrize("form,most", [("Lb0ELb0ELb0E", 24), ("Lb1ELb0ELb0E", 20), ("Lb1ELb1ELb0E", 20)])
+def test_large_split_block_keeps_its_scalars(form, most):
+    """The block of the large fp32 3x3 layers: kernel arguments that it does not read, put between those that it reads,
+    shift its scalar loads and cost it registers (29 spills instead of 18 with even rows and 16-byte stores)."""
+    name = "_ZN4gspc11conv_split3ILi2ELi4ELi2ELi2ELi1ELi4ELi1Ef" + form
+    k, = [v for n, v in kernels().items() if n.startswith(name)]
+    assert k[".sgpr_spill_count"] <= most, k[".sgpr_spill_count"]
+
+
+def test_split_kernels_need_no_scratch():
+    for n, k in kernels().items():
+        if "conv_split3" in n or "conv_direct_rows" in n:
+            assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
