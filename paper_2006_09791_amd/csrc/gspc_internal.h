@@ -168,6 +168,7 @@ struct MfmaB16Plan {
     int data[48];
 };
 bool plan_mfma_bf16(const ConvParams &p, const PackGeom &g, MfmaB16Plan *out);
+double mfma_bf16_estimate(const ConvParams &p, const PackGeom &g, const MfmaB16Plan &plan);   // microseconds
 hipError_t launch_mfma_bf16(const ConvParams &p, const PackGeom &g, const MfmaB16Plan &plan, hipStream_t s,
                             const char **name);
 
@@ -212,6 +213,7 @@ hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t 
 struct Split3Plan {
     int inst, cgs;
     int plain;       // the handle's filters are not split yet (not in `data`, the kernel's argument: it has a template argument)
+    double us;       // bf16 layers: estimated microseconds
     int data[24];
 };
 // when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; those that

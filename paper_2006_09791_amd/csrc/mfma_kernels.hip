@@ -758,7 +758,9 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     };
     if (any && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
-    else if (any && prefers_split3_bf16(p, g) && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
+    else if (any && prefers_split3_bf16(p, g) && plan_split3(p, g, kSplit3Any, &pl.ph) &&
+             (!plan_mfma_bf16(p, g, &pl.pb) || pl.ph.us < mfma_bf16_estimate(p, g, pl.pb)))
+        pl.kind = 20;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
     else if (any && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
     else if (any && winograd_mode() < 0 && !plan_unit(p, g, &pl.pu) && plan_split3(p, g, kSplit3BeforeWinograd, &pl.ph))

@@ -628,6 +628,19 @@ bool plan_mfma_bf16(const ConvParams &p0, const PackGeom &g, MfmaB16Plan *out) {
     return true;
 }
 
+// Microseconds of a launch, for comparison with the split kernel's bf16 form: start and filters, then per tile of a block and
+// chunk the staging (per slot, and per pixel of its loads) and the products, per tile its stores; blocks that share a compute
+// unit take 1.4 times one's time (fitted to 738 layers of 3 .. 240 us: nine in ten within a fifth).
+double mfma_bf16_estimate(const ConvParams &p, const PackGeom &g, const MfmaB16Plan &plan) {
+    TileB t;
+    std::memcpy(&t, plan.data, sizeof(t));
+    const CfgB &c = kCfgB[plan.inst];
+    const double units = (double)t.gx * g.gb * t.oc_blocks / kNumCU, tiles = (t.tiles + t.gx - 1) / t.gx, mm = c.MI * c.NI;
+    const double shared = units <= 1.0 ? 1.0 : units <= 2.0 ? 1.0 + 0.4 * (units - 1.0) : 0.7 * units;
+    const double chunk = 0.21 + 0.0116 * g.ks_b * mm + t.tslots * (0.121 + 0.04 * vw_of(p.W)) + (t.wres ? 0.0 : 0.0158 * t.wslots);
+    return 2.46 + 0.408 * t.wslots + shared * tiles * (t.nchunks * chunk + 0.188 * mm);
+}
+
 hipError_t launch_mfma_bf16(const ConvParams &p0, const PackGeom &g, const MfmaB16Plan &plan, hipStream_t s,
                             const char **name) {
     const ConvParams p = merged_view(p0, g);

@@ -516,6 +516,17 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
     return true;
 }
 
+// Microseconds of a bf16 launch, for comparison with the 16x16x32 kernel: start and stores, then per chunk a fixed part, the
+// products, the staging of odd rows (element by element), and the tasks that have no slot; blocks that share a compute unit
+// take 1.43 times one's time (fitted to 1100 layers of 4 .. 240 us: nine in ten within a sixth).
+double bf16_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t, long blocks) {
+    const double mm = c.MI * c.NI, units = (double)blocks / kNumCU, n = (double)((blocks + kNumCU - 1) / kNumCU);
+    const double shared = n <= 1.0 ? 1.0 : n <= 2.0 ? 1.43 : 0.715 * (0.5 * n + 0.5 * units);
+    const int waves = c.WM * c.WP, tasks = ((t.ROWS * t.PW + 31) / 32 * cgs + waves - 1) / waves;
+    return 3.32 + 0.2 * mm + shared * t.nchunks * (0.577 + 0.0101 * (cgs == 4 ? 9 : 5) * mm + (p.W % 2 ? 0.182 * tasks : 0.0) +
+                                                   (tasks > 4 ? 0.219 * (tasks - 4) : 0.0));
+}
+
 }  // namespace
 
 // Block shape: the one with the shortest estimated launch.  A block alone on its compute unit needs `kstep` per k-step
@@ -554,7 +565,10 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
 // (Blocks of 128 filters x 128 pixels and 64 x 256 for bf16 layers, with half the operand reads per product: 41.1 and 45.7 us
 // against 41.4 on the 14x14 layer below, up to 1.6 times the time elsewhere.)
 //
-// bf16 layers that the 16x16x32 kernel takes too (us, that kernel / this one):
+// bf16 layers that the 16x16x32 kernel takes too, where the estimate here is shorter than that kernel's as well (738 random
+// layers of these kinds: level with the faster of the two within 0.4 % in the geometric mean; without the estimates 102 of them
+// were up to 2.6 times slower than that kernel: 6 -> 6 on 107x107, g = 16, N = 23 43 / 113, 12 -> 12 on 33x33 at stride 2, g = 4,
+// N = 4 4.3 / 5.6, 272 -> 68 on 90x13, g = 2, N = 2 13.8 / 27.5) (us, that kernel / this one):
 //  - groups that it merges (channels not a multiple of 8), eight channels apart: 63 -> 63 on 8x8, g = 8 54 / 5.7, 80 -> 57 on 36x18
 //    at stride 2 166 / 25, 128 -> 25 on 88x88 597 / 98, 6 -> 64 on 72x72 60 / 39; 8 -> 8 merged in pairs stays (13.7 / 25.6);
 //  - 40 channels and more that it takes in chunks of 8 (104 on 20x79 127 / 63, 72 on 75x75 241 / 137) or 16 (48 on 44x44
@@ -613,6 +627,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
             out->inst = i;
             out->cgs = cgs;
             out->plain = g.h3_plain;
+            out->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : 0.0;
             std::memcpy(out->data, &t, sizeof(t));
         }
     }

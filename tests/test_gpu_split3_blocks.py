@@ -53,6 +53,30 @@ def test_blocks(gpu, s, block, form):
     assert m["bound"] < split_bound(9 * s.Cin // s.groups + 16), (name, m)
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(4, 48, 33, 33, 48, 3, 3, 2, 1, 4), "conv_mfma16b<"),        # merged in pairs, few blocks
+    (S(15, 24, 9, 9, 112, 3, 3, 1, 1, 2), "conv_mfma16b<"),
+    (S(6, 24, 25, 25, 24, 3, 3, 2, 1, 4), "conv_mfma16b<"),        # four groups of 6 channels in one
+    (S(59, 24, 98, 98, 24, 3, 3, 2, 1, 4), "conv_mfma16b<"),       # at a launch that fills the chip
+    (S(4, 96, 107, 107, 96, 3, 3, 1, 1, 16), "conv_mfma16b<"),
+    (S(2, 544, 45, 13, 136, 3, 3, 1, 1, 2), "conv_mfma16b<"),      # 272 channels in chunks of 16, no merging
+    (S(8, 208, 15, 15, 208, 3, 3, 1, 1, 1), "conv_mfma16b<"),
+    (S(66, 160, 46, 16, 160, 3, 3, 2, 1, 32), "conv_split3<"),     # eight groups of 5 in one
+    (S(40, 63, 8, 8, 63, 3, 3, 1, 1, 1), "conv_split3<"),
+    (S(8, 192, 34, 34, 384, 3, 3, 1, 1, 32), "conv_split3<"),
+    (S(16, 104, 20, 79, 104, 3, 3, 1, 1, 1), "conv_split3<"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_bf16_layers_that_the_16x16x32_kernel_takes_too(gpu, s, kernel):
+    """The one with the shorter estimate: the split kernel's form leaves the other's layers alone where it is behind."""
+    torch, b = gpu
+    y, x, w, name = run_conv(gpu, s, seed=93, dtype=b.GSPC_BF16)
+    assert name.startswith(kernel), name
+    x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    # (merged groups add zeros only: the bound of their own terms, each k-step of either kernel rounded once)
+    assert err_metrics(y, ref, absum)["bound"] < split_bound(9 * s.Cin // s.groups + 16) + 4 * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("s", [S(12, 64, 55, 55, 64, 3, 3, 1, 1, 4), S(30, 138, 29, 29, 138, 3, 3, 1, 1, 2)],
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("xs,ws", [(-110, 60), (60, -110), (70, 40)])
