@@ -434,6 +434,7 @@ const CfgH kCfgH[] = {
     {1, 2, 1, 4, 1, 0.31f},
 };
 constexpr int kNumCfgH = sizeof(kCfgH) / sizeof(kCfgH[0]);
+constexpr int kFirstFew = 4;     // blocks of at most 32 filters
 constexpr int kFirstPlain = 5;   // shapes of one filter tile, which have an instance that splits the filters itself
 constexpr int kLdsBlockH = 78 * 1024;   // two blocks per compute unit
 
@@ -601,7 +602,8 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     if (when != kSplit3Rest && (g.CPG < 5 || g.KPG < 5)) return false;
     if (when == kSplit3Else && !odd && (p.stride == 1 ? g.CPG < 128 : !large)) return false;
     if (when == kSplit3Else && !large && g.CPG * g.KPG <= 256 && p.H * p.W < 400) return false;
-    double best = 0.0;
+    double best = 0.0, est64[2] = {0.0, 0.0};
+    Split3Plan plan64[2]{};   // bf16 layers: the blocks of 64 filters
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
         if (p.in_bf16 && c.launch == 0.f) continue;
@@ -622,16 +624,31 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
                 const double per_unit = n > 1 ? 0.5 * (double)n + 0.5 * (double)blocks / kNumCU : 1.0;
                 est = c.launch + per_unit * (c.block + t.nchunks * (c.chunk + (cgs == 4 ? 9 : 5) * c.step + 1e-3 * cgs * t.PLANE * c.stage));
             }
+            const auto keep = [&](Split3Plan *o) {
+                o->inst = i;
+                o->cgs = cgs;
+                o->plain = g.h3_plain;
+                o->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : 0.0;
+                std::memcpy(o->data, &t, sizeof(t));
+            };
+            if (p.in_bf16 && i < 2 && (est64[i] == 0.0 || est < est64[i])) {
+                est64[i] = est;
+                keep(&plan64[i]);
+            }
             if (best != 0.0 && est >= best) continue;
             best = est;
-            out->inst = i;
-            out->cgs = cgs;
-            out->plain = g.h3_plain;
-            out->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : 0.0;
-            std::memcpy(out->data, &t, sizeof(t));
+            keep(out);
         }
     }
     if (best == 0.0) return false;
+    // bf16 layers in blocks of few filters or at stride 2: the choice between near ties is asked again of the second estimate,
+    // which is fitted over all shapes at once.  Blocks of few filters stage the tile once per 16 or 32 filters, a cost for
+    // long reductions in few blocks (323 -> 32 on 17x17, g = 3, N = 3 33.5 / 29.2 us, 116 -> 72 on 19x19, g = 3, N = 9
+    // 15.7 / 12.7), and at stride 2 large blocks can leave one per compute unit (68 -> 68 on 56x56, N = 18 14.7 / 11.9).  Nearer
+    // than 5.5 % it is no better than the first (of 29 random layers that it moves 25 gain, 1.09 in the mean; the worst loses 6 %)
+    if (p.in_bf16 && (out->inst >= kFirstFew || p.stride == 2))
+        for (int i = 0; i < 2; ++i)
+            if (est64[i] != 0.0 && est64[i] < 1.06 * best && plan64[i].us < 0.945 * out->us) *out = plan64[i];
     if (when == kSplit3BeforeWinograd && !sure) {
         WinoPlan px;
         return plan_wino(p, g, true, &px) && (g.h3_plain ? best + 4.0 : 0.82 * best + 3.0) < wino_estimate(p, px);

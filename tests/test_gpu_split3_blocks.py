@@ -53,6 +53,24 @@ def test_blocks(gpu, s, block, form):
     assert m["bound"] < split_bound(9 * s.Cin // s.groups + 16), (name, m)
 
 
+@pytest.mark.parametrize("s,block", [
+    (S(9, 348, 19, 19, 216, 3, 3, 1, 1, 3), "2,4,2,2,1,"),         # 116 channels, 72 filters in 200 tiles
+    (S(3, 969, 17, 17, 96, 3, 3, 1, 1, 3), "2,2,2,2,1,"),          # 323 and 32
+    (S(1, 292, 14, 23, 75, 3, 3, 1, 1, 1), "2,2,2,2,1,"),
+    (S(18, 68, 56, 56, 68, 3, 3, 2, 1, 1), "2,2,2,2,1,"),          # stride 2: a block per compute unit, or two of half the size
+    (S(39, 33, 29, 29, 66, 3, 3, 1, 1, 3), "2,4,1,4,1,"),          # 11 and 22, many tiles: the block of 32 filters x 256 pixels
+    (S(102, 68, 10, 10, 68, 3, 3, 1, 1, 1), "1,4,1,4,1,"),         # 16 x 256
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_bf16_block_shapes(gpu, s, block):
+    """Blocks of few filters stage a tile once per 16 or 32 filters: long reductions in few blocks keep the 64-filter ones."""
+    torch, b = gpu
+    y, x, w, name = run_conv(gpu, s, seed=94, dtype=b.GSPC_BF16)
+    assert name.startswith("conv_split3<" + block), name
+    x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < split_bound(9 * s.Cin // s.groups + 16), name
+
+
 @pytest.mark.parametrize("s,kernel", [
     (S(4, 48, 33, 33, 48, 3, 3, 2, 1, 4), "conv_mfma16b<"),        # merged in pairs, few blocks
     (S(15, 24, 9, 9, 112, 3, 3, 1, 1, 2), "conv_mfma16b<"),
