@@ -756,13 +756,24 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
         return !p.in_bf16 && p.W % 4 == 0 && g.CPG % 4 != 0 && (g.KPG <= 16 ? g.CPG < 25 : g.KPG < 32 && g.CPG <= 12) &&
                plan16(p, g, &idx, &t);
     };
+    // bf16 3x3 layers without a 16x16x32 section and with few products: a block of the split kernel takes 4.2 us, on odd rows,
+    // which it stages element by element, 5.5, where the staged kernel needs 3.9-4.5.  Split / staged, us: 7 -> 7 on 11x7, g = 4,
+    // N = 24 5.6 / 4.2, 14 -> 15 on 7x7, N = 3 5.3 / 4.1, 7 -> 7 on 42x31, N = 16 6.4 / 5.2; from 100 instructions of 16 x 16 x 4
+    // per compute unit on, with 8 channels and more on even rows, and at stride 2 the split kernel is level or ahead (12 -> 12
+    // on 10x10, N = 26 4.3 / 5.3, 6 -> 12 on 22x22, g = 3, N = 17 4.8 / 5.5).  Of 244 random layers this keeps 61, of which three
+    // were 3-6 % faster on the split kernel; of 88 that were slower there 8 are left.
+    const auto few_products = [&] {
+        if (!p.in_bf16 || p.stride != 1 || g.CPG > 16 || (p.W % 2 == 0 && g.CPG >= 8)) return false;
+        const double instr = (double)p.N * p.Hout * p.Wout / 16.0 * p.groups * g.mtiles * g.ksteps;
+        return instr < 100.0 * kNumCU && plan16(p, g, &pl.idx, &pl.t16);
+    };
     if (any && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (any && prefers_split3_bf16(p, g) && plan_split3(p, g, kSplit3Any, &pl.ph) &&
              (!plan_mfma_bf16(p, g, &pl.pb) || pl.ph.us < mfma_bf16_estimate(p, g, pl.pb)))
         pl.kind = 20;
     else if (plan_mfma_bf16(p, g, &pl.pb)) pl.kind = 32;
-    else if (any && p.in_bf16 && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
+    else if (any && p.in_bf16 && !few_products() && plan_split3(p, g, kSplit3Any, &pl.ph)) pl.kind = 20;
     else if (any && winograd_mode() < 0 && !plan_unit(p, g, &pl.pu) && plan_split3(p, g, kSplit3BeforeWinograd, &pl.ph))
         pl.kind = 20;
     else if ((winograd_mode() != 0 || fam == 'x') && (fam == 'x' || fam == '\0') &&

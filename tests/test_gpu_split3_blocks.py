@@ -72,6 +72,27 @@ def test_bf16_block_shapes(gpu, s, block):
 
 
 @pytest.mark.parametrize("s,kernel", [
+    (S(24, 28, 11, 7, 28, 3, 3, 1, 1, 4), "conv_mfma16<"),         # groups of 7 on odd rows
+    (S(3, 14, 7, 7, 15, 3, 3, 1, 1, 1), "conv_mfma16<"),
+    (S(4, 10, 24, 22, 20, 3, 3, 1, 1, 2), "conv_mfma16<"),         # even rows, groups of 5
+    (S(16, 7, 42, 31, 7, 3, 3, 1, 1, 1), "conv_mfma16<"),          # 92 instructions per compute unit
+    (S(40, 7, 42, 31, 7, 3, 3, 1, 1, 1), "conv_split3<"),          # 230
+    (S(26, 12, 10, 10, 12, 3, 3, 1, 1, 1), "conv_split3<"),        # even rows, 12 channels
+    (S(24, 28, 11, 7, 28, 3, 3, 2, 1, 4), "conv_split3<"),         # stride 2
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_bf16_layers_of_few_products(gpu, s, kernel):
+    """Channel counts without a 16x16x32 section: small launches keep the staged kernel."""
+    torch, b = gpu
+    y, x, w, name = run_conv(gpu, s, seed=95, dtype=b.GSPC_BF16)
+    assert name.startswith(kernel), name
+    x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    # (the staged kernel: every instruction of four terms rounds its sum once, for each of up to 16 channels and 9 taps)
+    k = 9 * s.Cin // s.groups
+    assert err_metrics(y, ref, absum)["bound"] < max(split_bound(k + 16), (k + 17) * 2.0 ** -24), name
+
+
+@pytest.mark.parametrize("s,kernel", [
     (S(4, 48, 33, 33, 48, 3, 3, 2, 1, 4), "conv_mfma16b<"),        # merged in pairs, few blocks
     (S(15, 24, 9, 9, 112, 3, 3, 1, 1, 2), "conv_mfma16b<"),
     (S(6, 24, 25, 25, 24, 3, 3, 2, 1, 4), "conv_mfma16b<"),        # four groups of 6 channels in one
