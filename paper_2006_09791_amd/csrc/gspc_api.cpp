@@ -346,7 +346,10 @@ PackGeom make_pack_geom(int Cin, int Cout, int KH, int KW, int groups, int dtype
         g.total_bytes = g.unit_offset + g.unit_bytes;
     }
     if (KH == 3 && KW == 3 && g.CPG >= 2 && (g.KPG >= 5 || g.CPG > 8)) {
-        g.h3_plain = dtype == GSPC_F32 && g.CPG * g.KPG <= 256;
+        // (the blocks that split the filters themselves are those of one filter tile, which at stride 2 fit narrow planes only:
+        // channel counts that no fp32 kernel takes in whole chunks need the others too.  15 -> 17 on 54x54 at stride 2, g = 4,
+        // N = 28: 52 us on the generic kernel, 21)
+        g.h3_plain = dtype == GSPC_F32 && g.CPG * g.KPG <= 256 && (g.CPG < 8 || g.KPG < 16 || g.CPG % 4 == 0);
         g.h3_offset = (g.total_bytes + 255) / 256 * 256;
         g.h3_bytes = (size_t)groups * ((g.CPG + 7) / 8) * 9 * ((g.KPG + 15) / 16) * (dtype != GSPC_F32 ? 256 : g.h3_plain ? 512 : 768);
         g.total_bytes = g.h3_offset + g.h3_bytes;

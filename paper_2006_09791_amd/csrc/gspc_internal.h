@@ -94,7 +94,8 @@ struct PackGeom {
     size_t unit_bytes, unit_offset;
     // Split 3x3 section (3x3, CPG >= 2, KPG >= 5 or CPG > 8): bf16 [g][ceil(CPG/8)][tap][ceil(KPG/16)][part][16 filters]
     // [8 channels], zeros past CPG and KPG (split3_kernels.hip).  GSPC_F32 handles: the three parts of the exact split of
-    // 2^24 times a weight, or (h3_plain: up to 256 weights per tap and group, which stay a mere reordering) fp32
+    // 2^24 times a weight, or (h3_plain: up to 256 weights per tap and group, fewer than 8 channels
+    // or 16 filters of them or channels a multiple of 4, which stay a mere reordering) fp32
     // [16 filters][8 channels], split by the kernel; GSPC_BF16 handles: the weight.
     int h3_plain;
     size_t h3_bytes, h3_offset;

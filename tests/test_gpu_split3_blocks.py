@@ -22,7 +22,9 @@ SHAPES = [
     (S(40, 64, 50, 46, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "f32,true,true>/plain"),
     (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "f32,false,false>/plain"),  # stride 2, 15 and 9
     (S(30, 20, 70, 94, 16, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32,true,true>/plain"),    # 10 and 8
-    (S(30, 60, 45, 47, 144, 3, 3, 1, 1, 6), "1,4,1,4,1,", "f32,false,false>/plain"),  # 10 and 24: two filter tiles
+    (S(30, 60, 45, 47, 144, 3, 3, 1, 1, 6), "2,4,1,4,1,", "f32,false,false>"),      # 10 and 24: few weights, but split at packing
+    (S(28, 60, 54, 54, 68, 3, 3, 2, 1, 4), "2,2,2,2,1,", "f32,true,false>"),         # 15 and 17 at stride 2, whose tiles fit no other block
+    (S(24, 36, 76, 76, 72, 3, 3, 2, 1, 4), "2,2,2,2,1,", "f32,true,true>"),          # 9 and 18
     (S(40, 66, 60, 58, 6, 3, 3, 1, 1, 1), "1,4,1,4,1,", "f32,true,true>"),          # six filters
     (S(7, 120, 44, 44, 6, 3, 3, 1, 1, 3), "1,4,1,4,1,", "f32,true,true>/plain"),     # two filters
     (S(8, 100, 9, 9, 3, 3, 3, 1, 1, 1), "", "f32,false,false>"),                    # three
