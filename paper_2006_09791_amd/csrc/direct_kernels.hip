@@ -2,6 +2,7 @@
 // Algorithm 1 of arXiv 2006.09791 with the input and output reshapes fused
 // away.  These cover every shape; the matrix-core kernels take over where the
 // per-group contraction is wide.
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <unordered_map>
@@ -72,6 +73,15 @@ static hipError_t launch_generic(const ConvParams &p, hipStream_t s) {
     if (grid.y > 65535u || grid.z > 65535u) return hipErrorNotSupported;
     hipLaunchKernelGGL((conv_direct_generic<OCT, TIN>), grid, dim3(256), 0, s, p);
     return hipGetLastError();
+}
+
+// Microseconds of an fp32 3x3 launch, for comparison with the split kernel: per term of a sum the latency of its loads
+// and the issue of every wave's (fitted to 345 layers of 5 .. 500 us: nine in ten within a quarter).
+double generic_estimate(const ConvParams &p) {
+    const int oct = p.KPGd % 8 == 0 ? 8 : 4;
+    const double rows = (double)p.groups * (p.KPGd / oct), units = ((p.Hout * p.Wout + 255) / 256) * rows * p.N / kNumCU;
+    if (rows > 65535 || p.N > 65535) return HUGE_VAL;   // more than its grid holds
+    return 1.86 + 9.0 * p.CPG * (0.0976 + 0.0063 * oct + (0.0367 + 0.0009 * oct) * units);
 }
 
 // ---------------------------------------------------------------------------

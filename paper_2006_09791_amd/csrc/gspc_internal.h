@@ -214,7 +214,8 @@ hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t 
 struct Split3Plan {
     int inst, cgs;
     int plain;       // the handle's filters are not split yet (not in `data`, the kernel's argument: it has a template argument)
-    double us;       // bf16 layers: estimated microseconds
+    int sure;        // fp32 layers of many weights in blocks of 64 filters: ahead of the staged kernel without comparison
+    double us;       // estimated microseconds
     int data[24];
 };
 // when: the layers it takes from Winograd; those it takes from the fp32 kernels when Winograd has declined; those that
@@ -244,6 +245,7 @@ hipError_t launch_mfma4(const ConvParams &p, const Mfma4Plan &plan, hipStream_t 
 struct DwPlan {
     int data[24];
 };
+double generic_estimate(const ConvParams &p);          // microseconds on the generic direct kernel, fp32 3x3
 bool plan_dw_planes(const ConvParams &p, DwPlan *out);
 bool plan_dw_rows(const ConvParams &p, DwPlan *out);   // bands of rows per wavefront, any plane
 hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t s, const char **name);

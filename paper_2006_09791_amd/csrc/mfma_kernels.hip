@@ -7,6 +7,7 @@
 // zero-haloed input tile is staged in LDS (the paper's input reshape, fused)
 // and every lane reads its own (pixel, k) element from it.  Results go
 // straight to NCHW (the paper's output reshape, fused away).
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <unordered_map>
@@ -645,6 +646,21 @@ bool plan16(const ConvParams &p, const PackGeom &g, int *cfg_idx, Tile16 *t_out)
     return true;
 }
 
+// Microseconds of an fp32 3x3 launch, for comparison with the split kernel: one block's products, staging and filters per
+// chunk, once per set of blocks that fit a compute unit together, and what each further block adds to the shared matrix unit,
+// LDS and stores (fitted to 458 layers of 5 .. 300 us: nine in ten within a seventh).
+double estimate16(const ConvParams &p, int idx, const Tile16 &t) {
+    const Cfg16 &c = kCfg16[idx];
+    const double units = (double)t.row_blocks * t.img_blocks * t.oc_blocks * p.groups / kNumCU, mm = c.MI * c.NI;
+    const double lds = (t.one_buf ? 1 : 2) * (t.in_floats + t.w_floats + 4.0) * 4.0;
+    const int fit = (int)(160 * 1024 / lds), per_cu = fit < 1 ? 1 : fit > 8 ? 8 : fit;
+    const double products = t.ksteps * mm / (t.ksplit ? 4 : 1), slots = t.nchunks * t.xslots;
+    const double one = 0.0185 * products + 0.1247 * t.nchunks + slots * (t.vec ? 0.0217 : 0.1034) + 0.1754 * t.nchunks * t.wslots;
+    const double more = 0.0101 * products + slots * (t.vec ? 0.0447 : 0.0521) + 0.2724 * mm + 0.219;
+    const double sets = units / per_cu, extra = std::ceil(units) - 1.0;
+    return 3.26 + one * (sets > 1.0 ? sets : 1.0) + more * (extra > 0.0 ? extra : 0.0);
+}
+
 template <int MI, int NI, int WM, int WP, int KH, int KW, int S, typename TIN, bool VO>
 hipError_t launch16_vo(const ConvParams &p, const Tile16 &t, hipStream_t s) {
     size_t lds = (t.one_buf ? 1 : 2) * ((size_t)t.in_floats + t.w_floats + 4) * sizeof(float);
@@ -767,6 +783,17 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
         const double instr = (double)p.N * p.Hout * p.Wout / 16.0 * p.groups * g.mtiles * g.ksteps;
         return instr < 100.0 * kNumCU && plan16(p, g, &pl.idx, &pl.t16);
     };
+    // fp32 3x3 layers that the split kernel would take from what they have otherwise (its plan is in pl.ph).  Without the
+    // comparison, against the best rate of those kernels, 56 of 165 random layers were up to a third slower than on the staged
+    // kernel: 5 -> 32 on 24x24, g = 3, N = 11 5.2 / 7.6 us, 7 -> 24 on 23x23, g = 8, N = 5 5.9 / 8.3, 6 -> 32 on 31x31, g = 16,
+    // N = 18 30 / 40, 52 -> 104 on 58x16 at stride 2, g = 2, N = 11 15.7 / 19.3; 3 -> 6 on 14x23 at stride 2, g = 2, N = 106 6.6 on the
+    // generic kernel, 8.2.  The margins leave 4 and cost 6 that were faster.  (The kernel with resident filters: 19 Tera-products per second.)
+    const auto ahead = [&] {
+        if (plan_mfma16w(p, g, &pl.pw))
+            return pl.ph.sure || pl.ph.us < 0.95 * (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9 / 19e6;
+        if (plan16(p, g, &pl.idx, &pl.t16)) return pl.ph.sure || pl.ph.us < 0.9 * estimate16(p, pl.idx, pl.t16);
+        return pl.ph.us < 0.95 * generic_estimate(p);
+    };
     if (any && may_split && plan_split(p, g, false, &pl.ps)) pl.kind = 18;
     else if ((fam == '\0' || fam == 'r') && plan_row_bf16(p, g, &pl.pr)) pl.kind = 33;
     else if (any && prefers_split3_bf16(p, g) && plan_split3(p, g, kSplit3Any, &pl.ph) &&
@@ -781,7 +808,7 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
         pl.kind = 64;
     else if (any && plan_unit(p, g, &pl.pu)) pl.kind = 19;
     else if (any && may_split && !(g.variant == kMfma4 && plan_mfma4(p, g, &pl.p4)) && plan_split3(p, g, kSplit3Else, &pl.ph) &&
-             !few_filters())
+             !few_filters() && ahead())
         pl.kind = 20;
     else if (fam == 'm' && plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma16w(p, g, &pl.pw)) pl.kind = 17;
@@ -790,7 +817,7 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     else if (plan16(p, g, &pl.idx, &pl.t16)) pl.kind = 16;
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (may_split && plan_split(p, g, true, &pl.ps)) pl.kind = 18;
-    else if (any && may_split && plan_split3(p, g, kSplit3Rest, &pl.ph)) pl.kind = 20;
+    else if (any && may_split && plan_split3(p, g, kSplit3Rest, &pl.ph) && (p.in_bf16 || pl.ph.us < 0.95 * generic_estimate(p))) pl.kind = 20;
     return pl;
 }
 

@@ -528,6 +528,18 @@ double bf16_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t
                                                    (tasks > 4 ? 0.219 * (tasks - 4) : 0.0));
 }
 
+// Microseconds of an fp32 launch, for comparison with the kernels that have the layer otherwise: start and stores, then per
+// chunk a fixed part, the products and filter loads, and the staging of odd rows and of tasks that have no slot (fitted to
+// 2600 layers in each shape that takes them: nine in ten within a sixth).
+double f32_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t, bool plain, long blocks) {
+    const double mm = c.MI * c.NI, units = (double)blocks / kNumCU, n = (double)((blocks + kNumCU - 1) / kNumCU);
+    const double shared = n <= 1.0 ? 1.0 : n <= 2.0 ? 1.78 : 0.89 * (0.5 * n + 0.5 * units);
+    const int waves = c.WM * c.WP, tasks = ((t.ROWS * t.PW + 31) / 32 * cgs + waves - 1) / waves;
+    const double chunk = 1.26 + (cgs == 4 ? 9 : 5) * (0.0514 * mm + 0.0216 * c.MI + (plain ? 0.124 : 0.0)) +
+                         (p.W % 2 ? 0.1325 * tasks : 0.0) + (tasks > 4 ? 0.328 * (tasks - 4) : 0.0);
+    return 3.61 + 0.176 * mm * (p.W % 2 || t.HWo % 4 ? 1.83 : 1.0) + (c.WK > 1 ? 0.37 : 0.0) + shared * ((t.nchunks + c.WK - 1) / c.WK) * chunk;
+}
+
 }  // namespace
 
 // Block shape: the one with the shortest estimated launch.  A block alone on its compute unit needs `kstep` per k-step
@@ -602,6 +614,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     if (when != kSplit3Rest && (g.CPG < 5 || g.KPG < 5)) return false;
     if (when == kSplit3Else && !odd && (p.stride == 1 ? g.CPG < 128 : !large)) return false;
     if (when == kSplit3Else && !large && g.CPG * g.KPG <= 256 && p.H * p.W < 400) return false;
+    bool wide = false;        // a block of 64 filters passes the bounds below
     double best = 0.0, est64[2] = {0.0, 0.0};
     Split3Plan plan64[2]{};   // bf16 layers: the blocks of 64 filters
     for (int i = 0; i < kNumCfgH; ++i) {
@@ -616,9 +629,10 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
             if ((when < kSplit3Rest && blocks < kNumCU / 4) || (when == kSplit3Else && !odd && p.stride == 2 && n < 2) ||
                 (when == kSplit3Else && !odd && p.stride == 1 && n > 2))
                 continue;
+            wide |= i < kFirstFew;
             const double rounds = (t.nchunks + c.WK - 1) / c.WK, ks = rounds * (cgs == 4 ? 9 : 5 * 1.3);
-            const double wide = p.stride == 1 ? 1.0 : c.WM == 1 ? (c.NI == 4 ? 1.4 : 1.35) : c.WK > 1 ? 1.4 : c.NI == 4 ? 1.15 : 0.75;
-            const double one = ks * c.kstep * wide + rounds + 1.5;
+            const double stretch = p.stride == 1 ? 1.0 : c.WM == 1 ? (c.NI == 4 ? 1.4 : 1.35) : c.WK > 1 ? 1.4 : c.NI == 4 ? 1.15 : 0.75;
+            const double one = ks * c.kstep * stretch + rounds + 1.5;
             double est = (c.WK > 1 ? 1.1 : 1.0) * one * (1.45 * (double)(n / 2) + (double)(n % 2));
             if (p.in_bf16) {
                 const double per_unit = n > 1 ? 0.5 * (double)n + 0.5 * (double)blocks / kNumCU : 1.0;
@@ -628,7 +642,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
                 o->inst = i;
                 o->cgs = cgs;
                 o->plain = g.h3_plain;
-                o->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : 0.0;
+                o->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : f32_estimate(p, c, cgs, t, g.h3_plain, blocks);
                 std::memcpy(o->data, &t, sizeof(t));
             };
             if (p.in_bf16 && i < 2 && (est64[i] == 0.0 || est < est64[i])) {
@@ -641,6 +655,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
         }
     }
     if (best == 0.0) return false;
+    out->sure = large && wide;
     // bf16 layers in blocks of few filters or at stride 2: the choice between near ties is asked again of the second estimate,
     // which is fitted over all shapes at once.  Blocks of few filters stage the tile once per 16 or 32 filters, a cost for
     // long reductions in few blocks (323 -> 32 on 17x17, g = 3, N = 3 33.5 / 29.2 us, 116 -> 72 on 19x19, g = 3, N = 9

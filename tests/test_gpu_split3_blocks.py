@@ -55,6 +55,28 @@ def test_blocks(gpu, s, block, form):
     assert m["bound"] < split_bound(9 * s.Cin // s.groups + 16), (name, m)
 
 
+@pytest.mark.parametrize("s,kernel", [
+    (S(11, 15, 24, 24, 96, 3, 3, 1, 1, 3), "conv_mfma16<"),        # 5 channels, 32 filters, few blocks
+    (S(5, 56, 23, 23, 192, 3, 3, 1, 1, 8), "conv_mfma16<"),        # 7 and 24, odd rows
+    (S(18, 96, 31, 31, 512, 3, 3, 1, 1, 16), "conv_mfma16<"),      # 6 and 32 at a launch that fills the chip
+    (S(11, 104, 58, 16, 208, 3, 3, 2, 1, 2), "conv_mfma16<"),      # stride 2, 52 and 104: no block of 64 filters twice per unit
+    (S(127, 128, 12, 12, 128, 3, 3, 2, 1, 2), "conv_mfma16w<"),    # the kernel with resident filters
+    (S(106, 6, 14, 23, 12, 3, 3, 2, 1, 2), "conv_direct_generic<"),  # 3 channels: 27 terms
+    (S(72, 32, 35, 35, 32, 3, 3, 1, 1, 2), "conv_split3<"),        # 16 and 16
+    (S(55, 14, 8, 42, 14, 3, 3, 1, 1, 2), "conv_split3<"),         # 7 and 7
+    (S(20, 188, 14, 14, 188, 3, 3, 2, 1, 1), "conv_split3<"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_fp32_layers_that_other_kernels_take_too(gpu, s, kernel):
+    """The split kernel leaves layers of few products to the staged and the generic kernel where its estimate is behind."""
+    y, x, w, name = run_conv(gpu, s, seed=96)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    # (the others: a product and a sum per term, each rounded once at most)
+    k = 9 * s.Cin // s.groups
+    bound = split_bound(k + 16) + 4 * 2.0 ** -24 if name.startswith("conv_split3<") else (k + 17) * 2.0 ** -24
+    assert err_metrics(y, ref, absum)["bound"] < bound, name
+
+
 @pytest.mark.parametrize("s,block", [
     (S(9, 348, 19, 19, 216, 3, 3, 1, 1, 3), "2,4,2,2,1,"),         # 116 channels, 72 filters in 200 tiles
     (S(3, 969, 17, 17, 96, 3, 3, 1, 1, 3), "2,2,2,2,1,"),          # 323 and 32
