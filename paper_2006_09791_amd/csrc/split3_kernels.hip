@@ -615,8 +615,8 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     if (when == kSplit3Else && !odd && (p.stride == 1 ? g.CPG < 128 : !large)) return false;
     if (when == kSplit3Else && !large && g.CPG * g.KPG <= 256 && p.H * p.W < 400) return false;
     bool wide = false;        // a block of 64 filters passes the bounds below
-    double best = 0.0, est64[2] = {0.0, 0.0};
-    Split3Plan plan64[2]{};   // bf16 layers: the blocks of 64 filters
+    double best = 0.0, est64[kFirstFew] = {};
+    Split3Plan plan64[kFirstFew]{};   // the blocks of 64 filters (and of 32 in four chunks at a time)
     for (int i = 0; i < kNumCfgH; ++i) {
         const CfgH &c = kCfgH[i];
         if (p.in_bf16 && c.launch == 0.f) continue;
@@ -645,7 +645,7 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
                 o->us = p.in_bf16 ? bf16_estimate(p, c, cgs, t, blocks) : f32_estimate(p, c, cgs, t, g.h3_plain, blocks);
                 std::memcpy(o->data, &t, sizeof(t));
             };
-            if (p.in_bf16 && i < 2 && (est64[i] == 0.0 || est < est64[i])) {
+            if (i < kFirstFew && (est64[i] == 0.0 || est < est64[i])) {
                 est64[i] = est;
                 keep(&plan64[i]);
             }
@@ -656,14 +656,19 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
     }
     if (best == 0.0) return false;
     out->sure = large && wide;
-    // bf16 layers in blocks of few filters or at stride 2: the choice between near ties is asked again of the second estimate,
-    // which is fitted over all shapes at once.  Blocks of few filters stage the tile once per 16 or 32 filters, a cost for
-    // long reductions in few blocks (323 -> 32 on 17x17, g = 3, N = 3 33.5 / 29.2 us, 116 -> 72 on 19x19, g = 3, N = 9
-    // 15.7 / 12.7), and at stride 2 large blocks can leave one per compute unit (68 -> 68 on 56x56, N = 18 14.7 / 11.9).  Nearer
-    // than 5.5 % it is no better than the first (of 29 random layers that it moves 25 gain, 1.09 in the mean; the worst loses 6 %)
-    if (p.in_bf16 && (out->inst >= kFirstFew || p.stride == 2))
-        for (int i = 0; i < 2; ++i)
-            if (est64[i] != 0.0 && est64[i] < 1.06 * best && plan64[i].us < 0.945 * out->us) *out = plan64[i];
+    // The choice between near ties is asked again of the second estimate, which is fitted over all shapes at once.  Blocks of
+    // few filters stage the tile once per 16 or 32 filters, a cost for long reductions in few blocks (bf16, 323 -> 32 on 17x17,
+    // g = 3, N = 3 33.5 / 29.2 us, 116 -> 72 on 19x19, g = 3, N = 9 15.7 / 12.7), and at stride 2 large blocks can leave one per
+    // compute unit (bf16, 68 -> 68 on 56x56, N = 18 14.7 / 11.9) and smaller ones only share it (fp32, 76 -> 152 on 32x16, g = 3, N = 93
+    // 73.9 / 66.9, 96 -> 96 on 22x37, g = 8, N = 45 136 / 123).  Nearer than 5.5 % it is no better than the first (bf16: of 29
+    // random layers that it moves 25 gain, 1.09 in the mean, the worst loses 6 %; fp32: 10 of 1042, 7 gain, the worst loses 5 %), nor is
+    // it for bf16 layers in large blocks at stride 1.
+    if (!p.in_bf16 || out->inst >= kFirstFew || p.stride == 2)
+        for (int i = 0; i < kFirstFew; ++i)
+            if (est64[i] != 0.0 && est64[i] < 1.06 * best && plan64[i].us < 0.945 * out->us) {
+                plan64[i].sure = out->sure;
+                *out = plan64[i];
+            }
     if (when == kSplit3BeforeWinograd && !sure) {
         WinoPlan px;
         return plan_wino(p, g, true, &px) && (g.h3_plain ? best + 4.0 : 0.82 * best + 3.0) < wino_estimate(p, px);

@@ -55,6 +55,18 @@ def test_blocks(gpu, s, block, form):
     assert m["bound"] < split_bound(9 * s.Cin // s.groups + 16), (name, m)
 
 
+@pytest.mark.parametrize("s,block", [
+    (S(93, 228, 32, 16, 456, 3, 3, 2, 1, 3), "2,4,2,2,1,"),        # stride 2: near ties of 64 filters by 128 and by 64 pixels
+    (S(72, 48, 52, 52, 100, 3, 3, 2, 1, 1), "2,4,2,2,1,"),
+    (S(86, 336, 15, 8, 336, 3, 3, 2, 1, 1), "2,2,1,1,4,"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_fp32_block_shapes(gpu, s, block):
+    y, x, w, name = run_conv(gpu, s, seed=97)
+    assert name.startswith("conv_split3<" + block), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < split_bound(9 * s.Cin // s.groups + 16) + 4 * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("s,kernel", [
     (S(11, 15, 24, 24, 96, 3, 3, 1, 1, 3), "conv_mfma16<"),        # 5 channels, 32 filters, few blocks
     (S(5, 56, 23, 23, 192, 3, 3, 1, 1, 8), "conv_mfma16<"),        # 7 and 24, odd rows
