@@ -590,7 +590,7 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
     const double planes = (double)p.N * p.Cin, xb = planes * HW * 4, yb = planes * p.Hout * p.Wout * 4;
     if (xb + 65536 >= (double)kOob || yb + 65536 >= (double)kOob || planes * p.Cin >= 4.29e9 || p.W > 1024) return false;
     TileRows t{};
-    double best = 0.0;
+    double best = 0.0, best_wave = 0.0;
     const auto consider = [&](int g, int br) {
         const int rows = br < p.Hout ? br : p.Hout, nrb = (rows - 1) * S + 3;
         const int len = g * (nrb < p.H ? nrb : p.H) * p.W + 3;      // floats loaded, with the alignment's
@@ -606,6 +606,7 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         const double est = wave * (0.5 + 0.5 * std::ceil(chunks / (4 * kNumCU)));
         if (best != 0.0 && est >= best) return;
         best = est;
+        best_wave = wave;
         t.chunks = (unsigned)chunks;
         t.NBD = nbd;
         t.BR = br;
@@ -628,6 +629,16 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
     if (planes > 4 * kNumCU)
         for (int g = std::min(32, (limit - 3) / HW); g > 1; g = g > 8 ? g / 2 : g - 1) consider(g, round_up(p.Hout, R));
     if (best == 0.0) return false;
+    // Few planes of more than about 40x40: a wavefront works through its band for longer than a launch with a thread per output
+    // takes (both in microseconds, fitted to 122 launches of up to 3 million outputs: of 24 that were slower here, by up to
+    // 1.62 times, one is left, by 5 %; none that was faster returns): 98x98 with 20 planes 3.4 / 5.6, 66x66 with 10 2.7 / 4.1, 89x89 with
+    // 15 3.0 / 4.7; 52x52 with 87 2.8 / 2.8, 60x60 at stride 2 with 208 4.0 / 3.0.
+    const double outputs = planes * p.Hout * p.Wout;
+    if ((p.H + 2) * (p.W + 2) > 2048 && outputs < 3e6) {
+        const double sets = std::ceil(t.chunks / (4.0 * kNumCU));
+        const double rows = 1.53 + best_wave * (0.00439 + 0.0013 * (sets - 1.0)) + 0.332e-6 * planes * HW;
+        if (rows > 0.95 * (2.51 + 7.76e-6 * outputs)) return false;
+    }
     t.planes = (unsigned)planes;
     t.m_NBD = div_magic(t.NBD);
     t.m_Wout = div_magic(p.Wout);

@@ -16,14 +16,15 @@ def dw(N, C, H, W, stride):
 
 
 SHAPES = [
-    (dw(3, 5, 95, 95, 1), "1,false"),      # bands of one plane; planes that start at any alignment
-    (dw(3, 5, 95, 95, 2), "2,false"),
-    (dw(2, 7, 46, 85, 1), "1,false"),      # the last band shorter, its last strip ragged
-    (dw(2, 7, 27, 79, 2), "2,false"),      # odd height at stride 2: the row below the plane
-    (dw(2, 3, 90, 331, 1), "1,false"),     # long rows, four output rows per band
-    (dw(2, 3, 90, 201, 2), "2,false"),
-    (dw(1, 2, 1, 682, 1), "1,false"),      # one row: windows past the band, more than 64 KB of LDS
-    (dw(1, 2, 2, 901, 2), "2,false"),
+    (dw(5, 13, 95, 95, 1), "1,false"),     # bands of one plane; planes that start at any alignment
+    (dw(5, 13, 95, 95, 2), "2,false"),
+    (dw(11, 13, 46, 85, 1), "1,false"),    # the last band shorter, its last strip ragged
+    (dw(20, 13, 27, 79, 2), "2,false"),    # odd height at stride 2: the row below the plane
+    (dw(3, 6, 90, 331, 1), "1,false"),     # long rows, four output rows per band
+    (dw(3, 15, 90, 201, 2), "2,false"),
+    (dw(3, 341, 1, 682, 1), "1,false"),    # one row: windows past the band; the last wavefronts of a block above 64 KB of LDS,
+    (dw(4, 500, 2, 901, 2), "2,false"),    # 144 KB: the third and fourth load there as well
+    (dw(3, 667, 2, 901, 2), "2,false"),    # ... of a last block with one wavefront
     (dw(1, 3, 5, 1, 1), "1,false"),        # one column
     (dw(1, 1, 1, 1, 2), "2,false"),        # one element
     (dw(400, 13, 9, 9, 1), "1,true"),      # several planes per wavefront, the last one with fewer
@@ -44,10 +45,28 @@ def test_rows(gpu, s, kind):
     assert err_metrics(y, ref, absum)["bound"] < 9 * 2.0 ** -24
 
 
-@pytest.mark.parametrize("N,H,W", [(2, 61, 67), (600, 9, 9)])
-def test_rows_residual_relu(gpu, N, H, W):
+@pytest.mark.parametrize("s,kernel", [
+    (dw(3, 5, 89, 89, 1), "conv_direct_flat<"),       # 15 planes: a band per wavefront leaves most of the chip idle
+    (dw(2, 5, 66, 66, 1), "conv_direct_flat<"),
+    (dw(8, 1, 70, 70, 2), "conv_direct_flat<"),
+    (dw(2, 21, 45, 45, 1), "conv_direct_flat<"),
+    (dw(1, 208, 60, 60, 2), "conv_direct_rows<"),
+    (dw(3, 72, 23, 93, 2), "conv_direct_rows<"),
+    (dw(7, 37, 60, 61, 2), "conv_direct_rows<"),
+    (dw(1, 92, 87, 87, 1), "conv_direct_rows<"),
+    (dw(1, 3, 31, 31, 1), "conv_direct_rows<"),       # planes of up to about 40x40: at any launch size
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_launches_of_few_planes(gpu, s, kernel):
+    y, x, w, name = run_conv(gpu, s, seed=82)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < 9 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,C,H,W", [(9, 24, 61, 67), (600, 6, 9, 9)])
+def test_rows_residual_relu(gpu, N, C, H, W):
     torch, b = gpu
-    C, dev = 6, "cuda:0"
+    dev = "cuda:0"
     ch = wl.Chain("dw", (N, C, H, W))
     ch.conv(0, 1, N, C, H, W, C, 3, 1, 1, C)
     ch.conv(1, 2, N, C, H, W, C, 3, 1, 1, C, relu=True, residual=0)
@@ -59,6 +78,7 @@ def test_rows_residual_relu(gpu, N, H, W):
         bufs[0].copy_(torch.from_numpy(x0).reshape(-1))
         b.gspc_run_layer_chain(b.LayerChain(ch.layers, packed, bufs))
         torch.cuda.synchronize()
+        assert b.gspc_last_kernel().startswith("conv_direct_rows<"), b.gspc_last_kernel()
     finally:
         b.gspc_set_chain_fusion(1)
     ref = oracle.run_chain(ch.layers, len(ch.buf_elems), x0, weights, threads=4)[ch.out_buf]
@@ -71,7 +91,7 @@ def test_rows_residual_relu(gpu, N, H, W):
 def test_rows_infinity(gpu):
     """An infinity reaches the outputs whose windows hold it, and no other: neither across rows nor across planes."""
     torch, b = gpu
-    for N, C, H, W in [(1, 2, 50, 49), (500, 5, 7, 9)]:
+    for N, C, H, W in [(8, 26, 50, 49), (500, 5, 7, 9)]:
         x = np.ones((N, C, H, W), np.float32)
         x[0, 0, 3, W - 1] = np.inf
         x[0, 0, H - 1, 0] = -np.inf
