@@ -364,6 +364,14 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
     // depthwise: the plane sizes that have an instance of their own
     DwPlan dw;
     if (plan_dw_planes(p, &dw)) return launch_dw_planes(p, dw, s, name);
+    // Whole-quad rows at stride 1 that the bands kernel has before the strip kernel (us, strip / bands): small launches of planes
+    // of up to 8x8, which the strip kernel covers with one strip per lane of few waves (8x8 with 460 planes 3.6 / 2.9, 4x4 with 434
+    // 3.7 / 3.3, level from a few thousand planes on: 8x8 with 13000 4.1 / 4.2), and planes of 32x32 to 40x40 past the last-level
+    // cache (32x32 with 31500 planes 44.0 / 42.7, 36x36 with 25600 51.0 / 47.9, 40x40 with 23300 75 / 55; 32x32 with 17000 24.4 / 24.7).
+    const double planes = (double)p.N * p.Cin;
+    const int HW = p.H * p.W;
+    if (p.stride == 1 && (HW <= 64 ? planes <= 4 * kNumCU : HW >= 1024 && HW <= 1600 && planes * HW >= 24e6) && plan_dw_rows(p, &dw))
+        return launch_dw_planes(p, dw, s, name);
     TileS ts;
     if (!no_small && plan_small(p, &ts)) {
         *name = intern_name("conv_direct_small<" + std::to_string(p.CPG) + "," + std::to_string(p.KPG) + "," +
@@ -372,8 +380,7 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
         return p.in_bf16 ? launch_small<uint16_t>(p, ts, s) : launch_small<float>(p, ts, s);
     }
     // depthwise on any other plane (whole-quad rows above: 96 channels at stride 1, us, strip kernel / this: 44x44 at N = 33
-    // 11.7 / 12.5, 56x56 at N = 20 9.7 / 12.0, 8x8 at N = 1954 22.6 / 26.1, 80x80 at N = 20 19.8 / 18.7; small launches 5-15 %
-    // the strip kernel's)
+    // 11.7 / 12.5, 56x56 at N = 20 9.7 / 12.0, 8x8 at N = 1954 22.6 / 26.1, 80x80 at N = 20 19.8 / 18.7)
     if (plan_dw_rows(p, &dw)) return launch_dw_planes(p, dw, s, name);
     TileF tf;
     if (plan_flat(p, &tf)) {

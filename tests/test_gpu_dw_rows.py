@@ -54,6 +54,11 @@ def test_rows(gpu, s, kind):
     (dw(3, 72, 23, 93, 2), "conv_direct_rows<"),
     (dw(7, 37, 60, 61, 2), "conv_direct_rows<"),
     (dw(1, 92, 87, 87, 1), "conv_direct_rows<"),
+    (dw(4, 115, 8, 8, 1), "conv_direct_rows<"),       # whole-quad rows: small planes in small launches
+    (dw(2, 37, 4, 4, 1), "conv_direct_rows<"),
+    (dw(130, 100, 8, 8, 1), "conv_direct_small<"),
+    (dw(4, 115, 8, 8, 2), "conv_direct_small<"),
+    (dw(12, 30, 32, 32, 1), "conv_direct_small<"),
     (dw(1, 3, 31, 31, 1), "conv_direct_rows<"),       # planes of up to about 40x40: at any launch size
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_launches_of_few_planes(gpu, s, kernel):
