@@ -372,6 +372,11 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
     const int HW = p.H * p.W;
     if (p.stride == 1 && (HW <= 64 ? planes <= 4 * kNumCU : HW >= 1024 && HW <= 1600 && planes * HW >= 24e6) && plan_dw_rows(p, &dw))
         return launch_dw_planes(p, dw, s, name);
+    // Launches past the last-level cache (at stride 2 from half of it on) on planes of up to about 40x40: the strip kernel's rows of
+    // 16 bytes per lane are the slower ones there: 8x8 at 467 MB of input and output 157 / 108, 20x20 at 767 MB 213 / 143, 24x24 at
+    // 394 MB 98 / 74, 40x40 at 472 MB 114 / 86, 8x8 at stride 2 at 391 MB 128 / 86, 26x8 at stride 2 at 137 MB 34 / 24
+    if (planes * (HW + p.Hout * p.Wout) >= (p.stride == 1 ? 60e6 : 30e6) && (p.H + 2) * (p.W + 2) <= 2048 && plan_dw_rows(p, &dw))
+        return launch_dw_planes(p, dw, s, name);
     TileS ts;
     if (!no_small && plan_small(p, &ts)) {
         *name = intern_name("conv_direct_small<" + std::to_string(p.CPG) + "," + std::to_string(p.KPG) + "," +

@@ -466,21 +466,26 @@ hipError_t launch_dw_band(int inst, const ConvParams &p, const TileW &t, hipStre
 // column of R consecutive output rows at a time - the (plane, strip, column) items are numbered flat, so odd widths fill
 // the lanes - and reads the three columns of its (R-1)*S + 3 input rows, 4.5 words per output at stride 1.  Neighbouring
 // lanes store neighbouring elements.
+//
+// conv_direct_narrow is the same with R = 1: one output per item and nine words read for it, but every store of a wavefront is
+// one contiguous piece, where strips of four rows write segments of a row each time, and four stores fill a line.  Beyond
+// the last-level cache such partial lines cost memory bandwidth.  It has the launches of rows shorter than a line's half.
 struct TileRows {
     unsigned chunks, planes;      // wavefronts with work, planes
     int NBD, BR, G;               // bands per plane, output rows per band; planes per wavefront
     int front, region, witem;     // floats before the rows, floats per wavefront, (strip, column) items of a plane
+    int R;                        // output rows per item
     unsigned m_NBD, m_Wout, m_C, m_item;
     unsigned x_bytes, y_bytes;
 };
 
-constexpr int kRowsStrip = 4;     // R
+constexpr int kRowsStrip = 4;     // R of conv_direct_rows
 constexpr int kRowsSlots = 8;     // 16-byte loads per lane, at most: 2048 floats per wavefront
 constexpr int kRowsLds = 150 * 1024;   // (rows of several hundred elements; square planes stay below 48 KB per block)
 
-template <int S, bool MULTI>
-__global__ __launch_bounds__(256) void conv_direct_rows(ConvParams p, TileRows t) {
-    constexpr int R = kRowsStrip, NR = (R - 1) * S + 3;
+template <int S, bool MULTI, int R>
+__device__ __forceinline__ void rows_body(const ConvParams &p, const TileRows &t) {
+    constexpr int NR = (R - 1) * S + 3;
     extern __shared__ f32x4 smem4[];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -575,6 +580,16 @@ __global__ __launch_bounds__(256) void conv_direct_rows(ConvParams p, TileRows t
     }
 }
 
+template <int S, bool MULTI>
+__global__ __launch_bounds__(256) void conv_direct_rows(ConvParams p, TileRows t) {
+    rows_body<S, MULTI, kRowsStrip>(p, t);
+}
+
+template <int S, bool MULTI>
+__global__ __launch_bounds__(256) void conv_direct_narrow(ConvParams p, TileRows t) {
+    rows_body<S, MULTI, 1>(p, t);
+}
+
 static_assert(sizeof(TileRows) <= sizeof(int) * kDwInst, "plan storage too small");
 
 // The band height, or the planes per wavefront, with the shortest estimated launch: a wavefront's instructions (120, 10 per
@@ -639,6 +654,17 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         const double rows = 1.53 + best_wave * (0.00439 + 0.0013 * (sets - 1.0)) + 0.332e-6 * planes * HW;
         if (rows > 0.95 * (2.51 + 7.76e-6 * outputs)) return false;
     }
+    // Past the last-level cache (256 MB of input and output together), rows shorter than 16 outputs: us, four output rows per
+    // item / one: 87x9 at 459 MB 120 / 84, 33x11 at 650 MB 157 / 117, 79x15 at 694 MB 157 / 128, 11x10 at stride 2 at 898 MB
+    // 176 / 168, 19x19 and longer rows level; below it four are ahead (12x8 at 216 MB 44 / 53), and several planes of whole
+    // quads as well (12x12 at 876 MB 180 / 188).
+    // (a block that copied whole planes and stored them contiguously took 89, 130 and 132 on the first three;
+    // planes as tall as 47x6 in groups, 124 us at 553 MB, were 112 there)
+    t.R = kRowsStrip;
+    if (p.Wout < 16 && xb + yb >= 270e6 && (t.G == 1 || p.W % 4 != 0 || p.W < 8)) {
+        t.R = 1;       // (bands, planes and LDS as above: the windows reach less far)
+        t.witem = p.Hout * p.Wout;
+    }
     t.planes = (unsigned)planes;
     t.m_NBD = div_magic(t.NBD);
     t.m_Wout = div_magic(p.Wout);
@@ -654,6 +680,10 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
 template <int S, bool MULTI>
 hipError_t launch_dw_rows(const ConvParams &p, const TileRows &t, hipStream_t s) {
     const size_t lds = (size_t)4 * t.region * sizeof(float);
+    if (t.R == 1) {   // (rows of at most 31 elements: a region is far below 64 KB / 4)
+        hipLaunchKernelGGL((conv_direct_narrow<S, MULTI>), dim3((t.chunks + 3) / 4), dim3(256), lds, s, p, t);
+        return hipGetLastError();
+    }
     auto kern = conv_direct_rows<S, MULTI>;
     if (lds > 64 * 1024) {
         static thread_local bool raised = false;   // per instantiation and thread
@@ -685,9 +715,11 @@ hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t
     if (plan.data[kDwKind] == 3) {
         TileRows tr;
         std::memcpy(&tr, plan.data, sizeof(tr));
-        static const char *const names[2][2] = {{"conv_direct_rows<1,false>", "conv_direct_rows<1,true>"},
-                                                {"conv_direct_rows<2,false>", "conv_direct_rows<2,true>"}};
-        *name = names[p.stride - 1][tr.G > 1];
+        static const char *const names[2][2][2] = {{{"conv_direct_rows<1,false>", "conv_direct_rows<1,true>"},
+                                                    {"conv_direct_rows<2,false>", "conv_direct_rows<2,true>"}},
+                                                   {{"conv_direct_narrow<1,false>", "conv_direct_narrow<1,true>"},
+                                                    {"conv_direct_narrow<2,false>", "conv_direct_narrow<2,true>"}}};
+        *name = names[tr.R == 1][p.stride - 1][tr.G > 1];
         if (tr.G > 1) return p.stride == 1 ? launch_dw_rows<1, true>(p, tr, s) : launch_dw_rows<2, true>(p, tr, s);
         return p.stride == 1 ? launch_dw_rows<1, false>(p, tr, s) : launch_dw_rows<2, false>(p, tr, s);
     }

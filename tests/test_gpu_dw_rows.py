@@ -68,8 +68,26 @@ def test_launches_of_few_planes(gpu, s, kernel):
     assert err_metrics(y, ref, absum)["bound"] < 9 * 2.0 ** -24
 
 
-@pytest.mark.parametrize("N,C,H,W", [(9, 24, 61, 67), (600, 6, 9, 9)])
-def test_rows_residual_relu(gpu, N, C, H, W):
+@pytest.mark.parametrize("s,kernel", [
+    (dw(1000, 512, 8, 8, 1), "conv_direct_rows<1,true>"),        # whole-quad rows past the last-level cache
+    (dw(76, 512, 28, 32, 1), "conv_direct_rows<1,false>"),
+    (dw(800, 512, 8, 8, 2), "conv_direct_rows<2,true>"),
+    (dw(90, 512, 87, 9, 1), "conv_direct_narrow<1,false>"),      # short rows: one output row per item, bands
+    (dw(701, 511, 11, 9, 1), "conv_direct_narrow<1,true>"),      # several planes, the last wavefront with fewer
+    (dw(100, 512, 90, 13, 2), "conv_direct_narrow<2,false>"),
+    (dw(530, 511, 25, 8, 2), "conv_direct_rows<2,true>"),
+    (dw(530, 511, 25, 9, 2), "conv_direct_narrow<2,true>"),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_launches_past_the_cache(gpu, s, kernel):
+    y, x, w, name = run_conv(gpu, s, seed=83)
+    assert name == kernel, name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert not np.isnan(y).any()
+    assert err_metrics(y, ref, absum)["bound"] < 9 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,C,H,W,kernel", [(9, 24, 61, 67, "rows"), (600, 6, 9, 9, "rows"), (90, 512, 87, 9, "narrow")])
+def test_rows_residual_relu(gpu, N, C, H, W, kernel):
     torch, b = gpu
     dev = "cuda:0"
     ch = wl.Chain("dw", (N, C, H, W))
@@ -83,7 +101,7 @@ def test_rows_residual_relu(gpu, N, C, H, W):
         bufs[0].copy_(torch.from_numpy(x0).reshape(-1))
         b.gspc_run_layer_chain(b.LayerChain(ch.layers, packed, bufs))
         torch.cuda.synchronize()
-        assert b.gspc_last_kernel().startswith("conv_direct_rows<"), b.gspc_last_kernel()
+        assert b.gspc_last_kernel().startswith(f"conv_direct_{kernel}<"), b.gspc_last_kernel()
     finally:
         b.gspc_set_chain_fusion(1)
     ref = oracle.run_chain(ch.layers, len(ch.buf_elems), x0, weights, threads=4)[ch.out_buf]
@@ -96,14 +114,14 @@ def test_rows_residual_relu(gpu, N, C, H, W):
 def test_rows_infinity(gpu):
     """An infinity reaches the outputs whose windows hold it, and no other: neither across rows nor across planes."""
     torch, b = gpu
-    for N, C, H, W in [(8, 26, 50, 49), (500, 5, 7, 9)]:
+    for N, C, H, W in [(8, 26, 50, 49), (500, 5, 7, 9), (90, 512, 87, 9)]:
         x = np.ones((N, C, H, W), np.float32)
         x[0, 0, 3, W - 1] = np.inf
         x[0, 0, H - 1, 0] = -np.inf
         w = np.ones((C, 1, 3, 3), np.float32)
         pw = b.gspc_pack_weights(torch.from_numpy(w).to("cuda:0"), C)
         y = b.gspc_conv2d_grouped(torch.from_numpy(x).to("cuda:0"), pw, N, C, H, W, C, 3, 3, 1, 1, C).cpu().numpy()
-        assert b.gspc_last_kernel().startswith("conv_direct_rows<")
+        assert b.gspc_last_kernel().startswith("conv_direct_narrow<" if W * N * C * H > 3e7 else "conv_direct_rows<")
         bad = ~np.isfinite(y)
         want = np.zeros_like(bad)
         want[0, 0, 2:5, W - 2:] = True
