@@ -364,19 +364,18 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
     // depthwise: the plane sizes that have an instance of their own
     DwPlan dw;
     if (plan_dw_planes(p, &dw)) return launch_dw_planes(p, dw, s, name);
-    // Whole-quad rows at stride 1 that the bands kernel has before the strip kernel (us, strip / bands): small launches of planes
-    // of up to 8x8, which the strip kernel covers with one strip per lane of few waves (8x8 with 460 planes 3.6 / 2.9, 4x4 with 434
-    // 3.7 / 3.3, level from a few thousand planes on: 8x8 with 13000 4.1 / 4.2), and planes of 32x32 to 40x40 past the last-level
-    // cache (32x32 with 31500 planes 44.0 / 42.7, 36x36 with 25600 51.0 / 47.9, 40x40 with 23300 75 / 55; 32x32 with 17000 24.4 / 24.7).
-    const double planes = (double)p.N * p.Cin;
-    const int HW = p.H * p.W;
-    if (p.stride == 1 && (HW <= 64 ? planes <= 4 * kNumCU : HW >= 1024 && HW <= 1600 && planes * HW >= 24e6) && plan_dw_rows(p, &dw))
-        return launch_dw_planes(p, dw, s, name);
-    // Launches past the last-level cache (at stride 2 from half of it on) on planes of up to about 40x40: the strip kernel's rows of
-    // 16 bytes per lane are the slower ones there: 8x8 at 467 MB of input and output 157 / 108, 20x20 at 767 MB 213 / 143, 24x24 at
-    // 394 MB 98 / 74, 40x40 at 472 MB 114 / 86, 8x8 at stride 2 at 391 MB 128 / 86, 26x8 at stride 2 at 137 MB 34 / 24
-    if (planes * (HW + p.Hout * p.Wout) >= (p.stride == 1 ? 60e6 : 30e6) && (p.H + 2) * (p.W + 2) <= 2048 && plan_dw_rows(p, &dw))
-        return launch_dw_planes(p, dw, s, name);
+    // Whole-quad planes of up to about 40x40 that the bands kernel has before the strip kernel (us, strip / bands):
+    //  - small launches of planes of up to 8x8 at stride 1, which the strip kernel covers with one strip per lane of few waves
+    //    (8x8 with 460 planes 3.6 / 2.9, 4x4 with 434 3.7 / 3.3; level from a few thousand planes on);
+    //  - from 60 MB of input and output together, where buffers are no longer in the last-level cache when a program comes back to
+    //    them, and the strip kernel's rows of 16 bytes per lane cost memory bandwidth.  With buffers that take turns over 800 MB:
+    //    12x12 at 96 MB 33.4 / 25, 8x8 at 178 MB 62 / 47, 20x20 at 187 MB 54.7 / 45, 8x8 at stride 2 at 104 MB 38.6 / 29; over 45
+    //    random layers 1.12 .. 1.38 from 60 to 300 MB, and 0.98 .. 1.17 on one buffer in the cache (30 .. 60 MB: 1.13 and 0.99).  Past
+    //    the cache one buffer shows the same: 8x8 at 467 MB 157 / 108, 24x24 at 394 MB 98 / 74, 40x40 at 472 MB 114 / 86.
+    const double planes = (double)p.N * p.Cin, moved = planes * ((double)p.H * p.W + (double)p.Hout * p.Wout);
+    if ((p.stride == 1 && p.H * p.W <= 64 && planes <= 4 * kNumCU) || ((p.H + 2) * (p.W + 2) <= 2048 && moved >= 15e6)) {
+        if (plan_dw_rows(p, &dw)) return launch_dw_planes(p, dw, s, name);
+    }
     TileS ts;
     if (!no_small && plan_small(p, &ts)) {
         *name = intern_name("conv_direct_small<" + std::to_string(p.CPG) + "," + std::to_string(p.KPG) + "," +

@@ -654,14 +654,14 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         const double rows = 1.53 + best_wave * (0.00439 + 0.0013 * (sets - 1.0)) + 0.332e-6 * planes * HW;
         if (rows > 0.95 * (2.51 + 7.76e-6 * outputs)) return false;
     }
-    // Past the last-level cache (256 MB of input and output together), rows shorter than 16 outputs: us, four output rows per
+    // Past the last-level cache (256 MB, most of which one layer's input and output take), rows shorter than 16 outputs: us, four output rows per
     // item / one: 87x9 at 459 MB 120 / 84, 33x11 at 650 MB 157 / 117, 79x15 at 694 MB 157 / 128, 11x10 at stride 2 at 898 MB
     // 176 / 168, 19x19 and longer rows level; below it four are ahead (12x8 at 216 MB 44 / 53), and several planes of whole
-    // quads as well (12x12 at 876 MB 180 / 188).
+    // quads as well (12x12 at 876 MB 180 / 188), and single planes of a few hundred elements (15x15 at 244 MB 57 / 63).
     // (a block that copied whole planes and stored them contiguously took 89, 130 and 132 on the first three;
     // planes as tall as 47x6 in groups, 124 us at 553 MB, were 112 there)
     t.R = kRowsStrip;
-    if (p.Wout < 16 && xb + yb >= 270e6 && (t.G == 1 || p.W % 4 != 0 || p.W < 8)) {
+    if (p.Wout < 16 && xb + yb >= 240e6 && (t.G == 1 ? HW > 256 : p.W % 4 != 0 || p.W < 8)) {
         t.R = 1;       // (bands, planes and LDS as above: the windows reach less far)
         t.witem = p.Hout * p.Wout;
     }

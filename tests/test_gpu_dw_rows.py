@@ -69,7 +69,9 @@ def test_launches_of_few_planes(gpu, s, kernel):
 
 
 @pytest.mark.parametrize("s,kernel", [
-    (dw(1000, 512, 8, 8, 1), "conv_direct_rows<1,true>"),        # whole-quad rows past the last-level cache
+    (dw(230, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # whole-quad rows from 60 MB on
+    (dw(225, 512, 8, 8, 1), "conv_direct_small<1,1,1,4,f32>"),
+    (dw(1000, 512, 8, 8, 1), "conv_direct_rows<1,true>"),
     (dw(76, 512, 28, 32, 1), "conv_direct_rows<1,false>"),
     (dw(800, 512, 8, 8, 2), "conv_direct_rows<2,true>"),
     (dw(90, 512, 87, 9, 1), "conv_direct_narrow<1,false>"),      # short rows: one output row per item, bands
