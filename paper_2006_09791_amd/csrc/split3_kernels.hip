@@ -687,6 +687,8 @@ hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_
     std::memcpy(&t, plan.data, sizeof(t));
     const CfgH &c = kCfgH[plan.inst];
     const bool even = p.W % 2 == 0;
+    // (a plan for another form of the shape must not run with this one's filter layout)
+    if ((plan.plain && plan.inst < kFirstPlain) || (p.in_bf16 && (plan.plain || c.launch == 0.f))) return hipErrorNotSupported;
     if (!*name)
         *name = intern_name("conv_split3<" + std::to_string(c.MI) + "," + std::to_string(c.NI) + "," + std::to_string(c.WM) +
                             "," + std::to_string(c.WP) + "," + std::to_string(c.WK) + "," + std::to_string(plan.cgs) + "," +

@@ -1,4 +1,5 @@
 """Registers that the compiler reports for the library's kernels (the metadata notes of libgspc.so's own code objects)."""
+import ctypes
 import struct
 
 import pytest
@@ -43,3 +44,14 @@ def test_split_kernels_need_no_scratch():
     for n, k in kernels().items():
         if "conv_split3" in n or "conv_direct_rows" in n:
             assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
+
+
+@pytest.mark.parametrize("inst", range(5))
+def test_split_kernel_refuses_a_plan_without_an_instance(inst):
+    """Blocks of more than one filter tile have no instance that splits the filters itself: such a plan is an error and does
+    not run on the filter layout of another shape (checked before anything is launched)."""
+    launch = b.load()["_ZN4gspc13launch_split3ERKNS_10ConvParamsERKNS_10Split3PlanEP12ihipStream_tPPKc"]
+    params, plan, name = (ctypes.c_char * 1024)(), (ctypes.c_int * 256)(), ctypes.c_char_p()
+    plan[0], plan[1], plan[2] = inst, 4, 1                              # shape, 32 channels per chunk, unsplit filters
+    not_supported = 801                                                # hipErrorNotSupported
+    assert launch(params, plan, None, ctypes.byref(name)) == not_supported and not name.value
