@@ -590,6 +590,12 @@ __global__ __launch_bounds__(256) void conv_direct_narrow(ConvParams p, TileRows
     rows_body<S, MULTI, 1>(p, t);
 }
 
+// GSPC_NO_DWPLANES (tuning aid): depthwise layers on the strip, flat and generic kernels only
+static bool planes_off() {
+    static const bool off = std::getenv("GSPC_NO_DWPLANES") != nullptr;
+    return off;
+}
+
 static_assert(sizeof(TileRows) <= sizeof(int) * kDwInst, "plan storage too small");
 
 // The band height, or the planes per wavefront, with the shortest estimated launch: a wavefront's instructions (120, 10 per
@@ -599,7 +605,7 @@ static_assert(sizeof(TileRows) <= sizeof(int) * kDwInst, "plan storage too small
 // 52 / 17, 86x86 with 4480 179 / 45, 27x79 at stride 2 with 18400 82 / 29, 43x43 with 3264 16.3 / 13.0 (stride 2 9.5 / 7.9),
 // 23x23 with 11424 15.0 / 11.9 (9.4 / 6.5), 15x15 with 26688 15.2 / 12.8 (10.2 / 6.2), 9x9 with 74112 16.9 / 15.7 (11.0 / 9.2).
 bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
-    if (p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2))
+    if (planes_off() || p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 || (p.stride != 1 && p.stride != 2))
         return false;
     const int R = kRowsStrip, S = p.stride, HW = p.H * p.W, limit = kRowsSlots * 256;
     const double planes = (double)p.N * p.Cin, xb = planes * HW * 4, yb = planes * p.Hout * p.Wout * 4;
@@ -699,8 +705,7 @@ hipError_t launch_dw_rows(const ConvParams &p, const TileRows &t, hipStream_t s)
 }
 
 bool plan_dw_planes(const ConvParams &p, DwPlan *out) {
-    static const bool off = std::getenv("GSPC_NO_DWPLANES") != nullptr;   // tuning aid
-    if (off || p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 ||
+    if (planes_off() || p.CPG != 1 || p.KPG != 1 || p.in_bf16 || p.KH != 3 || p.KW != 3 || p.pad != 1 ||
         (p.stride != 1 && p.stride != 2))
         return false;
     if (plan_dw_wave(p, out)) return true;

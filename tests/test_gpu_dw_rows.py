@@ -129,3 +129,26 @@ def test_rows_infinity(gpu):
         want[0, 0, 2:5, W - 2:] = True
         want[0, 0, H - 2:, :2] = True
         assert (bad == want).all()
+
+
+def test_plane_kernels_can_be_switched_off(gpu):
+    """GSPC_NO_DWPLANES leaves depthwise layers to the strip and flat kernels (read once per process, hence the child)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = f"""
+import sys
+sys.path.insert(0, {root!r})
+import torch
+from paper_2006_09791_amd import binding as b
+for N, C, H in ((20, 64, 15), (20, 64, 16), (128, 64, 14)):
+    pw = b.gspc_pack_weights(torch.randn(C, 1, 3, 3, device="cuda"), C)
+    b.gspc_conv2d_grouped(torch.randn(N, C, H, H, device="cuda"), pw, N, C, H, H, C, 3, 3, 1, 1, C)
+    torch.cuda.synchronize()
+    print(b.gspc_last_kernel())
+"""
+    out = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, GSPC_NO_DWPLANES="1"), check=True,
+                         capture_output=True, text=True).stdout
+    names = [l.split("<")[0] for l in out.splitlines() if l.startswith("conv_")]
+    assert names == ["conv_direct_flat", "conv_direct_small", "conv_direct_flat"], out
