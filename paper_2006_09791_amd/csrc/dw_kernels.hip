@@ -469,7 +469,7 @@ hipError_t launch_dw_band(int inst, const ConvParams &p, const TileW &t, hipStre
 //
 // conv_direct_narrow is the same with R = 1: one output per item and nine words read for it, but every store of a wavefront is
 // one contiguous piece, where strips of four rows write segments of a row each time, and four stores fill a line.  Beyond
-// the last-level cache such partial lines cost memory bandwidth.  It has the launches of rows shorter than a line's half.
+// the last-level cache such partial lines cost memory bandwidth.  It has the larger launches of rows shorter than 16 outputs.
 struct TileRows {
     unsigned chunks, planes;      // wavefronts with work, planes
     int NBD, BR, G;               // bands per plane, output rows per band; planes per wavefront
@@ -646,9 +646,17 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         br = b;
         consider(1, br);
     }
-    // several planes, where that leaves no compute unit idle
-    if (planes > 4 * kNumCU)
-        for (int g = std::min(32, (limit - 3) / HW); g > 1; g = g > 8 ? g / 2 : g - 1) consider(g, round_up(p.Hout, R));
+    // several planes, where that leaves no compute unit idle.  Rows shorter than 16 outputs from 60 MB of input and output on (40 MB at
+    // stride 2): the launch waits for memory, a compute unit holds 16 wavefronts of 8 KB regions and 32 of smaller ones, and the
+    // estimate's single small planes load too little each.  With buffers that take turns over 2 GB, us, 8 KB or as estimated / the
+    // most planes of 3 KB (planes of up to 256 elements) or 4 KB: 8x8 at 95 MB 31.0 / 27.0, 9x9 at stride 2 at 94 MB 29.3 / 24.3; over 360
+    // random layers 0.88 .. 1.00 of the time by size and stride, below these bounds 1.04.
+    const bool narrow = p.Wout < 16 && xb + yb >= (S == 1 ? 60e6 : 40e6);
+    const int group = !narrow ? limit : HW <= 256 ? 768 : 1024;
+    if (planes > 4 * kNumCU) {
+        if (narrow && HW <= 256) best = 0.0;
+        for (int g = std::min(32, (group - 3) / HW); g > 1; g = narrow ? 1 : g > 8 ? g / 2 : g - 1) consider(g, round_up(p.Hout, R));
+    }
     if (best == 0.0) return false;
     // Few planes of more than about 40x40: a wavefront works through its band for longer than a launch with a thread per output
     // takes (both in microseconds, fitted to 122 launches of up to 3 million outputs: of 24 that were slower here, by up to
@@ -660,14 +668,13 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         const double rows = 1.53 + best_wave * (0.00439 + 0.0013 * (sets - 1.0)) + 0.332e-6 * planes * HW;
         if (rows > 0.95 * (2.51 + 7.76e-6 * outputs)) return false;
     }
-    // Past the last-level cache (256 MB, most of which one layer's input and output take), rows shorter than 16 outputs: us, four output rows per
-    // item / one: 87x9 at 459 MB 120 / 84, 33x11 at 650 MB 157 / 117, 79x15 at 694 MB 157 / 128, 11x10 at stride 2 at 898 MB
-    // 176 / 168, 19x19 and longer rows level; below it four are ahead (12x8 at 216 MB 44 / 53), and several planes of whole
-    // quads as well (12x12 at 876 MB 180 / 188), and single planes of a few hundred elements (15x15 at 244 MB 57 / 63).
-    // (a block that copied whole planes and stored them contiguously took 89, 130 and 132 on the first three;
-    // planes as tall as 47x6 in groups, 124 us at 553 MB, were 112 there)
+    // The same layers with one output row per item, bands from 60 MB and groups of planes from 100 MB on, where buffers have left the
+    // last-level cache when a program comes back to them.  Buffers that take turns over 2 GB, us, four rows / one (and a block
+    // that copied whole planes and stored them contiguously): 86x9 at 176 MB 48.7 / 37.1 (41.7), 65x6 at 228 MB 60.2 / 45.8 (53.9), 8x8 at
+    // 130 MB 36.2 / 31.9 (34.0), 13x13 at 331 MB 81.6 / 71.1 (74.7), 15x15 at stride 2 at 129 MB 26.3 / 26.0 (30.4).  On one buffer that
+    // stays in the cache bands are level and groups of 100 .. 240 MB 0.97 (12x12 at 133 MB 23.9 / 28.8); 17x17 and longer rows keep four.
     t.R = kRowsStrip;
-    if (p.Wout < 16 && xb + yb >= 240e6 && (t.G == 1 ? HW > 256 : p.W % 4 != 0 || p.W < 8)) {
+    if (narrow && xb + yb >= (t.G == 1 ? 60e6 : 100e6)) {
         t.R = 1;       // (bands, planes and LDS as above: the windows reach less far)
         t.witem = p.Hout * p.Wout;
     }

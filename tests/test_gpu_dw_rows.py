@@ -71,13 +71,18 @@ def test_launches_of_few_planes(gpu, s, kernel):
 @pytest.mark.parametrize("s,kernel", [
     (dw(230, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # whole-quad rows from 60 MB on
     (dw(225, 512, 8, 8, 1), "conv_direct_small<1,1,1,4,f32>"),
-    (dw(1000, 512, 8, 8, 1), "conv_direct_rows<1,true>"),
+    (dw(395, 512, 8, 8, 1), "conv_direct_narrow<1,true>"),       # ... and from 100 MB with one output row per item
+    (dw(380, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # 99.6 MB
     (dw(76, 512, 28, 32, 1), "conv_direct_rows<1,false>"),
-    (dw(800, 512, 8, 8, 2), "conv_direct_rows<2,true>"),
+    (dw(800, 512, 8, 8, 2), "conv_direct_narrow<2,true>"),
+    (dw(250, 511, 9, 9, 2), "conv_direct_rows<2,true>"),         # regions of 3 KB
     (dw(90, 512, 87, 9, 1), "conv_direct_narrow<1,false>"),      # short rows: one output row per item, bands
     (dw(701, 511, 11, 9, 1), "conv_direct_narrow<1,true>"),      # several planes, the last wavefront with fewer
     (dw(100, 512, 90, 13, 2), "conv_direct_narrow<2,false>"),
-    (dw(530, 511, 25, 8, 2), "conv_direct_rows<2,true>"),
+    (dw(19, 512, 87, 9, 1), "conv_direct_narrow<1,false>"),      # bands from 60 MB on
+    (dw(18, 512, 87, 9, 1), "conv_direct_rows<1,false>"),
+    (dw(240, 272, 15, 15, 1), "conv_direct_narrow<1,true>"),     # never one small plane per wavefront
+    (dw(530, 511, 25, 8, 2), "conv_direct_narrow<2,true>"),
     (dw(530, 511, 25, 9, 2), "conv_direct_narrow<2,true>"),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_launches_past_the_cache(gpu, s, kernel):
