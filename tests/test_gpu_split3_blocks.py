@@ -160,11 +160,111 @@ def test_scales(gpu, s, xs, ws):
     torch, b = gpu
     x = wl.make_input((s.N, s.Cin, s.H, s.W), 92)
     w = wl.make_weight(s.Cout, s.Cin // s.groups, 3, 3, 92)
+    cpg = s.Cin // s.groups
+    # from the second image on: one channel per group and every third pixel, which give sums of one term
+    one = np.zeros((s.N, cpg, s.H, s.W), bool)
+    for n in range(1, s.N):
+        one[n, n % cpg, 1::3, 1::3] = True
+    one[0] = True
+    x = np.where(np.tile(one, (1, s.groups, 1, 1)), x, np.float32(0))
+    x, w = (np.ldexp(np.ldexp(a, e), -e) for a, e in ((x, xs), (w, ws)))   # (what 2^-110 leaves of the smallest values)
     xd = torch.from_numpy(np.ldexp(x, xs)).cuda()
     pw = b.gspc_pack_weights(torch.from_numpy(np.ldexp(w, ws)).cuda(), s.groups)
     y = b.gspc_conv2d_grouped(xd, pw, s.N, s.Cin, s.H, s.W, s.Cout, 3, 3, s.stride, s.pad, s.groups).cpu().numpy()
     assert b.gspc_last_kernel().startswith("conv_split3<"), b.gspc_last_kernel()
     ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
-    m = err_metrics(np.ldexp(y.astype(np.float64), -xs - ws), ref, absum)
-    # (a plain sum rounds once per term: 9 * channels roundings of at most the sum of magnitudes)
-    assert m["bound"] < 9 * s.Cin // s.groups * 2.0 ** -24, m
+    err = np.abs(np.ldexp(y.astype(np.float64), -xs - ws) - ref) * 2.0 ** 24
+    if xs + ws < 100:
+        assert np.max(err[0] / absum[0]) < split_bound(9 * cpg + 16) * 2.0 ** 24
+    else:   # (a plain sum rounds once per term: 9 * channels roundings of at most the sum of magnitudes)
+        assert np.max(err[0] / absum[0]) < 9 * cpg
+    # one term: three dropped products of half a unit and a rounding per product kept; without an operand's third part up to 128
+    assert np.max(err[1:] - 7.5 * absum[1:]) <= 0.0, np.max(err[1:] / np.maximum(absum[1:], 1e-30))
+
+
+FEW = [
+    (S(30, 56, 46, 46, 56, 3, 3, 1, 1, 2), "2,4,1,4,1,", "f32"),       # 32 filters x 256 pixels
+    (S(25, 160, 33, 33, 24, 3, 3, 1, 1, 2), "1,4,1,4,1,", "f32"),      # 16 x 256
+    (S(12, 64, 55, 55, 64, 3, 3, 1, 1, 4), "1,4,1,4,1,", "plain"),     # filters split in the kernel
+    (S(200, 60, 31, 31, 36, 3, 3, 2, 1, 4), "1,2,1,4,1,", "plain"),    # 16 x 128
+    (S(39, 33, 29, 29, 66, 3, 3, 1, 1, 3), "2,4,1,4,1,", "bf16"),
+    (S(102, 68, 10, 10, 68, 3, 3, 1, 1, 1), "1,4,1,4,1,", "bf16"),
+]
+
+
+@pytest.mark.parametrize("s,block,form", FEW, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_blocks_epilogue_and_buffer_ends(gpu, s, block, form):
+    """Residual and ReLU; tensors inside larger buffers of NaN: nothing outside is written or read into a result."""
+    torch, b = gpu
+    x, w = wl.make_input((s.N, s.Cin, s.H, s.W), 98), wl.make_weight(s.Cout, s.Cin // s.groups, 3, 3, 99)
+    bf16 = form == "bf16"
+    if bf16:
+        x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    res = wl.make_input(ref.shape, 100)
+    guard = 4096
+    big = [torch.full((a.size + 2 * guard,), float("nan"), device="cuda", dtype=torch.bfloat16 if bf16 and a is x else torch.float32)
+           for a in (x, res, res)]
+    xd, rd, yd = (t[guard:guard + a.size] for t, a in zip(big, (x, res, res)))
+    xd.copy_(torch.from_numpy(x).reshape(-1))
+    rd.copy_(torch.from_numpy(res).reshape(-1))
+    pw = b.gspc_pack_weights(torch.from_numpy(w).cuda(), s.groups, b.GSPC_BF16 if bf16 else b.GSPC_F32)
+    layer = wl.Layer("conv", 0, 1, 2, s.N, s.Cin, s.H, s.W, s.Cout, 3, 3, s.stride, 1, s.groups, True, 0)
+    b.gspc_run_layer_chain(b.LayerChain([layer], [pw], [xd.view(torch.int16) if bf16 else xd, rd, yd]))
+    torch.cuda.synchronize()
+    name = b.gspc_last_kernel()
+    assert name.startswith("conv_split3<" + block) and form in name, name
+    out = big[2].cpu().numpy()
+    assert np.isnan(out[:guard]).all() and np.isnan(out[guard + res.size:]).all()
+    y = out[guard:guard + res.size].reshape(res.shape).astype(np.float64)
+    # (and the rounding of the sum with the residual)
+    bound = (split_bound(9 * s.Cin // s.groups + 16) + 2.0 ** -24) * (absum + np.abs(res))
+    assert (np.abs(y - oracle.relu(oracle.add(ref, res))) < bound).all()
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, np.finfo(np.float32).max])
+@pytest.mark.parametrize("s,block,form", FEW[:4], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_blocks_of_values_that_do_not_split(gpu, s, block, form, value):
+    """An infinity, NaN or largest number among inputs or weights: the plain sum, and no other output changes."""
+    torch, b = gpu
+    cpg, kpg = s.Cin // s.groups, s.Cout // s.groups
+    x, w = wl.make_input((s.N, s.Cin, s.H, s.W), 101), wl.make_weight(s.Cout, cpg, 3, 3, 102)
+    w[:, 3] = np.float32(0.5)                                   # lower parts are zero
+    x[:, -1] = np.where(np.abs(x[:, -1]) < 0.01, np.float32(0.01), x[:, -1])
+    x[0, 3, 0, 0] = x[s.N - 1, cpg + 3, s.H - 1, s.W - 1] = x[7, 3, 5, 6] = value
+    # (the centre tap never meets the padding; a sixteenth of the largest number, so that no plain sum overflows)
+    w[s.Cout - 1, cpg - 1, 1, 1] = value if not np.isfinite(value) else value / np.float32(16)
+    y = b.gspc_conv2d_grouped(torch.from_numpy(x).cuda(), b.gspc_pack_weights(torch.from_numpy(w).cuda(), s.groups),
+                              s.N, s.Cin, s.H, s.W, s.Cout, 3, 3, s.stride, 1, s.groups).cpu().numpy().astype(np.float64)
+    name = b.gspc_last_kernel()
+    assert name.startswith("conv_split3<" + block) and form in name, name
+    with np.errstate(invalid="ignore"):
+        ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+        assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+        assert np.array_equal(np.sign(y[np.isinf(y)]), np.sign(ref[np.isinf(ref)]))
+        ok = np.isfinite(ref)
+        # (sums that are recomputed as plain ones round once per term)
+        assert np.max(np.abs(y[ok] - ref[ok]) / absum[ok]) < 9 * cpg * 2.0 ** -24
+        # those of the filters and images without such a value keep the split's bound
+        calm = np.s_[1:7, :s.Cout - 1]
+        assert np.max(np.abs(y[calm] - ref[calm]) / absum[calm]) < split_bound(9 * cpg + 16)
+
+
+@pytest.mark.parametrize("s,form", [
+    (S(18, 8, 65, 65, 226, 3, 3, 2, 1, 2), "f32,false,false>"),            # 4 channels, 113 filters
+    (S(36, 24, 35, 35, 840, 3, 3, 2, 1, 8), "f32,false,false>"),           # 3 and 105
+    (S(31, 2, 89, 89, 113, 3, 3, 1, 1, 1), "bf16,false,false>"),           # 2 and 113
+    (S(156, 4, 65, 65, 28, 3, 3, 2, 1, 1), "bf16,false,false>"),           # 4 and 28
+    (S(47, 12, 83, 83, 33, 3, 3, 1, 1, 3), "bf16,false,false>"),           # three groups of 4 and 11
+    (S(33, 48, 12, 18, 208, 3, 3, 2, 1, 16), "f32,true,false>/plain"),     # 3 and 13, split in the kernel
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_few_channels(gpu, s, form):
+    """Groups of 2 to 4 channels: three quarters and more of a unit of the reduction are zeros."""
+    torch, b = gpu
+    bf16 = form.startswith("bf16")
+    y, x, w, name = run_conv(gpu, s, seed=103, dtype=b.GSPC_BF16 if bf16 else b.GSPC_F32)
+    assert name.startswith("conv_split3<") and name.endswith(form), name
+    if bf16:
+        x, w = wl.round_to_bf16(x)[1], wl.round_to_bf16(w)[1]
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < split_bound(9 * s.Cin // s.groups + 16), name
