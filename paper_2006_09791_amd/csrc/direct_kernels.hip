@@ -205,7 +205,8 @@ __global__ __launch_bounds__(256) void conv_direct_small(ConvParams p, TileS t) 
 
 // ---------------------------------------------------------------------------
 // Flat 3x3 kernel for the shapes the strip kernel cannot take (planes whose
-// width is not a multiple of 4, e.g. 14x14 and 7x7 depthwise layers): one thread
+// width is not a multiple of 4): few channels per group, channel multipliers, bf16
+// depthwise, and the fp32 depthwise launches that dw_kernels.hip leaves.  One thread
 // per output pixel of one (image, group), all KPG <= 4 filters of the group,
 // planes treated as flat memory so that neighbouring lanes read neighbouring
 // addresses even when a row is only 7 elements long.

@@ -10,7 +10,11 @@
 //
 //   conv_dw_wave      whole 56x56, 28x28, 14x14 and 7x7 planes, launches that fill the chip;
 //   conv_dw_band      112x112 planes, a band of 16 rows per wavefront;
-//   conv_direct_rows  every other plane that the strip kernel (conv_direct_small) does not take.
+//   conv_direct_rows  fp32 planes that the strip kernel (conv_direct_small) does not take and four output rows of which need at
+//                     most 2048 floats of input (rows of up to 340 elements at stride 1 and 227 at stride 2, wider on planes of
+//                     few rows), but for launches of few large planes; small and large launches of small planes that it would take;
+//   conv_direct_narrow  the same with one output row at a time, larger launches of short rows.
+// Other planes and bf16 inputs stay on conv_direct_flat.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -459,7 +463,7 @@ hipError_t launch_dw_band(int inst, const ConvParams &p, const TileW &t, hipStre
 }
 
 // ---- bands of rows or groups of planes per wavefront, any plane ----------------------------------------
-// Planes that none of the forms above takes: a wavefront owns one band of BR output rows of one plane or, of small
+// Planes that the forms above do not take: a wavefront owns one band of BR output rows of one plane or, of small
 // planes, G whole ones (MULTI).  Either way its input is one contiguous range of memory, which goes flat, from the 16-byte
 // boundary at or below its start, straight into a wave-private LDS region (16 bytes per lane, no registers in between).  Rows
 // above and below the plane are overwritten with zeros there, or, between planes, selected to zero.  A lane takes one

@@ -210,7 +210,7 @@ struct SplitPlan {
 bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan *out);
 hipError_t launch_split(const ConvParams &p, const SplitPlan &plan, hipStream_t s, const char **name);
 
-// fp32 3x3 layers on the bf16 matrix instruction through the exact three-way split (split3_kernels.hip).
+// 3x3 layers on the bf16 matrix instruction (split3_kernels.hip): fp32 ones through the exact three-way split, bf16 ones as they are.
 struct Split3Plan {
     int inst, cgs;
     int plain;       // the handle's filters are not split yet (not in `data`, the kernel's argument: it has a template argument)
@@ -241,13 +241,13 @@ struct Mfma4Plan {
 bool plan_mfma4(const ConvParams &p, const PackGeom &g, Mfma4Plan *out);
 hipError_t launch_mfma4(const ConvParams &p, const Mfma4Plan &plan, hipStream_t s, const char **name);
 
-// Depthwise 3x3 on whole small planes (dw_kernels.hip); plan is opaque to the caller.
+// Depthwise fp32 3x3 with whole planes or bands of rows per wavefront (dw_kernels.hip); plan is opaque to the caller.
 struct DwPlan {
     int data[24];
 };
 double generic_estimate(const ConvParams &p);          // microseconds on the generic direct kernel, fp32 3x3
 bool plan_dw_planes(const ConvParams &p, DwPlan *out);
-bool plan_dw_rows(const ConvParams &p, DwPlan *out);   // bands of rows per wavefront, any plane
+bool plan_dw_rows(const ConvParams &p, DwPlan *out);   // bands or planes of any size whose rows fit its LDS region
 hipError_t launch_dw_planes(const ConvParams &p, const DwPlan &plan, hipStream_t s, const char **name);
 
 // Fused run of consecutive grouped 3x3 layers (fused_kernels.hip).

@@ -760,12 +760,13 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     // (GSPC_TILE16, a tuning aid, fixes the tile of the staged kernel: the layers that it shares with these are its own)
     static const bool tile16 = std::getenv("GSPC_TILE16") != nullptr;
     const bool any = fam == '\0' && !tile16;
-    // fp32 3x3 layers with few filters per group, on rows of a multiple of 4, where only the channels per group are odd:
-    // the split kernel's tiles have 64 filters, so a group of 16 leaves three of four rows empty, and the staged kernel
-    // still reads four elements at a time.  Split / staged, us: 16 filters, 11 channels on 32x32, g = 2, N = 155 44.7 /
-    // 18.3, 18 on 24x24, g = 4, N = 72 34.5 / 21.7, 21 at stride 2 on 32x32, g = 8, N = 148 81 / 51, from 25 on level or
-    // the split kernel's (27 on 20x20 at stride 1, g = 2, N = 183 29.8 / 39.9); 24 filters, 9 channels on 32x32, g = 4,
-    // N = 32 20.6 / 14.9, 28 filters, 10 channels g = 4, N = 170 100 / 63.
+    // fp32 3x3 layers with few filters per group, on rows of a multiple of 4, where only the channels per group are odd, stay on the
+    // staged kernel, which still reads four elements at a time.  The line was drawn against blocks of 64 filters, which these groups
+    // leave mostly empty, and at stride 2 that is what they would get: us, split / staged, 17 channels and 16 filters on 60x60, g = 32,
+    // N = 20 202 / 96, 11 and 26, g = 4, N = 34 33 / 17, 10 and 27 on 29x28, g = 32, N = 13 22 / 16.  At stride 1, in the blocks of 16 and 32
+    // filters, the split kernel would be ahead on most (13 and 12 on 40x40, g = 8, N = 40 28 / 62, 10 and 27 on 12x12, g = 32, N = 67 28 / 48;
+    // 190 random layers 1.2 in the geometric mean) and behind on some (10 and 18 on 8x8, g = 32, N = 65 19.4 / 16.2, 10 and 16 on 64x64,
+    // g = 32, N = 12 93 / 78): the line is not the best one there.
     const auto few_filters = [&] {
         int idx;
         Tile16 t;

@@ -6,8 +6,8 @@
 // tile needs are then one contiguous range of P (rows -1 and H of an image are zeros), whatever the plane
 // and wherever images meet, and no pixel of a tile is padding.  Per chunk of 8*CGS channels the block
 // stages that range once, split and channel-innermost - [part][8 channels][row][column] units of 16 bytes -
-// and multiplies it nine taps long; the filters are split at packing time and go from memory (L2) straight
-// into the registers of the wave that multiplies them.
+// and multiplies it nine taps long; the filters go from memory (L2) straight into the registers of the wave that
+// multiplies them, split at packing time or (PLAIN: up to 256 weights per tap and group) by that wave.
 //
 // A unit of the reduction is 8 channels at one tap; a k-step is four units: with CGS = 4 one tap, the lane
 // group lane/16 picks the channels; with CGS = 2 (tiles too large for four, or fewer channels) two taps.
@@ -548,7 +548,7 @@ double f32_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t,
 // 47 / 40, 512 -> 512 on 7x7 g = 2 47 / 43, 128 -> 128 on 8x8 11.2 / 10.8, 50 -> 75 on 31x23 at N = 100 66 / 58 and 69 / 65
 // for the next best shape).
 //
-// Which layers (N = 64 unless stated, us, before / with this kernel):
+// Which layers (N = 64 unless stated, us, before / with this kernel; channels and filters are the layer's):
 //  - rows that are not a multiple of 4 or channels per group that are not: the fp32 kernels stage those 4 bytes at a
 //    time, or in one chunk: 256 -> 256 on 14x14 g = 2 68 / 40, g = 4 38 / 24, 512 -> 512 on 7x7 g = 2 89 / 43,
 //    192 -> 192 on 13x17 g = 2 104 / 33, 50 -> 75 on 31x23 at N = 100 423 / 58, 110 -> 100 on 40x40 stride 2 at N = 20
@@ -564,19 +564,19 @@ double f32_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t,
 //  - other stride-1 layers: with at least 128 channels per group where neither Winograd (64 -> 64 on 16x16 at N = 256
 //    25.6 / 25.3) nor a launch of more blocks than the chip holds covers the fp32
 //    kernel's waits: 128 -> 128 on 8x8 13.4 / 10.3 (64 channels per group: 8.6 / 10.2).
+// (from here on channels and filters are per group)
 //  - other planes whose 2x2 tiles do not fill Winograd's blocks whole, where the estimate here is shorter than Winograd's:
-//    32 -> 32 per group on 18x18, g = 32 138 / 75, 92 on 24x24, g = 2, N = 198 325 / 176, 112 on 36x36, g = 3, N = 40 330 / 203,
+//    32 -> 32 on 18x18, g = 32 138 / 75, 92 on 24x24, g = 2, N = 198 325 / 176, 112 on 36x36, g = 3, N = 40 330 / 203,
 //    16 on 72x72, g = 32, N = 5 67.5 / 47.  Planes that fill them stay: 16 -> 16 on 32x32, g = 2 8.9 / 10.4, 32 -> 32 at N = 256
 //    34.9 / 34.4;
-//  - odd rows or channels with few weights, the same way against 9.5 Tera-products per second, which is the best of the kernels
-//    that these layers have otherwise: 16 -> 16 on 98x98, g = 16, N = 13 418 / 112, 32 -> 10 on 33x33, g = 4 41.6 / 23.9 with
+//  - odd rows or channels with few weights, against the estimates of the kernels that these layers have otherwise: 16 -> 16 on 98x98, g = 16, N = 13 418 / 112, 32 -> 10 on 33x33, g = 4 41.6 / 23.9 with
 //    72, 126 -> 12 on 38x38, g = 3, N = 4 258 / 15, 80 -> 12 on 85x85, g = 2, N = 27 641 / 89; not: 8 -> 8 per group, which the
 //    4x4x1 kernel takes (29x29, g = 32, N = 143 106 / 219), and up to 256 weights per tap on small planes (16 -> 16 on 17x19,
 //    g = 2, N = 207 18.1 / 16.8, which is level where launches are smaller).
 // With Winograd switched off (gspc_set_winograd(0)) every fp32 3x3 layer stays on the fp32 instruction.
 //
-// (Blocks of 128 filters x 128 pixels and 64 x 256 for bf16 layers, with half the operand reads per product: 41.1 and 45.7 us
-// against 41.4 on the 14x14 layer below, up to 1.6 times the time elsewhere.)
+// (Blocks of 128 filters x 128 pixels and 64 x 256 for bf16 layers, with half the operand reads per product: 0.99 and 1.10 times
+// the time on the 14x14 layer below, up to 1.6 times elsewhere.)
 //
 // bf16 layers that the 16x16x32 kernel takes too, where the estimate here is shorter than that kernel's as well (738 random
 // layers of these kinds: level with the faster of the two within 0.4 % in the geometric mean; without the estimates 102 of them
@@ -588,7 +588,7 @@ double f32_estimate(const ConvParams &p, const CfgH &c, int cgs, const TileH &t,
 //    151 / 83, 112 on 25x25 281 / 169; 16 channels 0.5-0.9 of its speed), below 80 channels on rows of an even length only (48 on
 //    21x21 18.5 / 21.3);
 //  - from 64 channels in chunks of 32 at stride 1, on rows it loads in less than 16 bytes (96 on 71x75 137 / 93): 128 -> 128 on 14x14, g = 2, N = 256
-//    51.7 / 42.7, on 18x18 59 / 40, 64 on 52x52 18.7 / 13.9; rows of whole octets (32 on 56x56 72 / 91, 128 on 48x48 at stride 2
+//    45.3 / 36.0, on 18x18 59 / 40, 64 on 52x52 18.7 / 13.9; rows of whole octets (32 on 56x56 72 / 91, 128 on 48x48 at stride 2
 //    83 / 104), long rows (96 on 110x110 61 / 75) and 7x7 planes (44 / 55) stay.
 bool prefers_split3_bf16(const ConvParams &p, const PackGeom &g) {
     if (!p.in_bf16 || !p.wh || !g.bf16_bytes) return false;
@@ -673,8 +673,8 @@ bool plan_split3(const ConvParams &p, const PackGeom &g, int when, Split3Plan *o
         WinoPlan px;
         return plan_wino(p, g, true, &px) && (g.h3_plain ? best + 4.0 : 0.82 * best + 3.0) < wino_estimate(p, px);
     }
-    // (what is left runs at up to 9.5 Tera-products per second; with no other matrix-core kernel at 0.13 us or more per
-    // term of a sum: 40 -> 2 on 44x44, g = 3, N = 7 51 / 13 before / with this kernel, 100 -> 3 on 9x9, N = 8
+    // (a first bound, before the estimates of those kernels: what is left runs at up to 9.5 Tera-products per second; with no
+    // other matrix-core kernel at 0.13 us or more per term of a sum: 40 -> 2 on 44x44, g = 3, N = 7 51 / 13 before / with this kernel, 100 -> 3 on 9x9, N = 8
     // 119 / 11, 300 -> 6 on 17x17, g = 3, N = 40 in bf16 168 / 14)
     const double macs = (double)p.N * p.Cout * p.Hout * p.Wout * g.CPG * 9;
     if (when == kSplit3Else && !large) return 0.87 * best < 3.0 + macs / 9.5e6;

@@ -55,7 +55,7 @@ def test_split3(gpu, s, kind):
     (S(40, 26, 24, 24, 56, 3, 3, 1, 1, 2), "conv_split3<"),       # 13 channels
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_layers_of_few_filters(gpu, s, kernel):
-    """Few filters per group leave most of the 64-filter tiles empty: the staged kernel, where it reads whole quads."""
+    """Few filters per group, which would leave most of a 64-filter tile empty: the staged kernel, where it reads whole quads."""
     y, x, w, name = run_conv(gpu, s, seed=72)
     assert name.startswith(kernel), name
     ref, absum = oracle.conv2d_grouped(x, w, s.stride, 1, s.groups, return_abs=True, threads=8)
