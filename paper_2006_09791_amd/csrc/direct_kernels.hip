@@ -368,13 +368,14 @@ hipError_t launch_direct(const ConvParams &p, hipStream_t s, const char **name) 
     // Whole-quad planes of up to about 40x40 that the bands kernel has before the strip kernel (us, strip / bands):
     //  - small launches of planes of up to 8x8 at stride 1, which the strip kernel covers with one strip per lane of few waves
     //    (8x8 with 460 planes 3.6 / 2.9, 4x4 with 434 3.7 / 3.3; level from a few thousand planes on);
-    //  - from 60 MB of input and output together, where buffers are no longer in the last-level cache when a program comes back to
+    //  - from 30 MB of input and output together, where buffers are no longer in the last-level cache when a program comes back to
     //    them, and the strip kernel's rows of 16 bytes per lane cost memory bandwidth.  With buffers that take turns over 800 MB:
-    //    12x12 at 96 MB 33.4 / 25, 8x8 at 178 MB 62 / 47, 20x20 at 187 MB 54.7 / 45, 8x8 at stride 2 at 104 MB 38.6 / 29; over 45
-    //    random layers 1.12 .. 1.38 from 60 to 300 MB, and 0.98 .. 1.17 on one buffer in the cache (30 .. 60 MB: 1.13 and 0.99).  Past
-    //    the cache one buffer shows the same: 8x8 at 467 MB 157 / 108, 24x24 at 394 MB 98 / 74, 40x40 at 472 MB 114 / 86.
+    //    36x36 at 35 MB 14.8 / 11.0, 13x68 at 35 MB 16.0 / 12.6, 8x12 at 50 MB 18.1 / 14.5, 8x102 at stride 2 at 32 MB 15.7 / 11.2, 12x12 at
+    //    96 MB 33.4 / 25, 20x20 at 187 MB 54.7 / 45; 1.09 .. 1.18 by stride and width from 30 to 60 MB, 1.12 .. 1.38 above.  On one buffer
+    //    in the cache 0.98 .. 1.01 from 30 to 60 MB (at 15 to 30 MB 1.02 .. 1.06 with buffers that take turns and 0.91 .. 0.99 on one).
+    //    Past the cache one buffer shows the same: 8x8 at 467 MB 157 / 108, 24x24 at 394 MB 98 / 74, 40x40 at 472 MB 114 / 86.
     const double planes = (double)p.N * p.Cin, moved = planes * ((double)p.H * p.W + (double)p.Hout * p.Wout);
-    if ((p.stride == 1 && p.H * p.W <= 64 && planes <= 4 * kNumCU) || ((p.H + 2) * (p.W + 2) <= 2048 && moved >= 15e6)) {
+    if ((p.stride == 1 && p.H * p.W <= 64 && planes <= 4 * kNumCU) || ((p.H + 2) * (p.W + 2) <= 2048 && moved >= 7.5e6)) {
         if (plan_dw_rows(p, &dw)) return launch_dw_planes(p, dw, s, name);
     }
     TileS ts;

@@ -69,8 +69,8 @@ def test_launches_of_few_planes(gpu, s, kernel):
 
 
 @pytest.mark.parametrize("s,kernel", [
-    (dw(230, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # whole-quad rows from 60 MB on
-    (dw(225, 512, 8, 8, 1), "conv_direct_small<1,1,1,4,f32>"),
+    (dw(115, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # whole-quad rows from 30 MB on
+    (dw(114, 512, 8, 8, 1), "conv_direct_small<1,1,1,4,f32>"),
     (dw(395, 512, 8, 8, 1), "conv_direct_narrow<1,true>"),       # ... and from 100 MB with one output row per item
     (dw(380, 512, 8, 8, 1), "conv_direct_rows<1,true>"),         # 99.6 MB
     (dw(76, 512, 28, 32, 1), "conv_direct_rows<1,false>"),
