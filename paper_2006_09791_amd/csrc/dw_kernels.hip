@@ -473,7 +473,7 @@ hipError_t launch_dw_band(int inst, const ConvParams &p, const TileW &t, hipStre
 //
 // conv_direct_narrow is the same with R = 1: one output per item and nine words read for it, but every store of a wavefront is
 // one contiguous piece, where strips of four rows write segments of a row each time, and four stores fill a line.  Beyond
-// the last-level cache such partial lines cost memory bandwidth.  It has the larger launches of rows shorter than 16 outputs.
+// the last-level cache such partial lines cost memory bandwidth.  It has the larger launches of short rows.
 struct TileRows {
     unsigned chunks, planes;      // wavefronts with work, planes
     int NBD, BR, G;               // bands per plane, output rows per band; planes per wavefront
@@ -650,12 +650,13 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
         br = b;
         consider(1, br);
     }
-    // several planes, where that leaves no compute unit idle.  Rows shorter than 16 outputs from 60 MB of input and output on (40 MB at
-    // stride 2): the launch waits for memory, a compute unit holds 16 wavefronts of 8 KB regions and 32 of smaller ones, and the
+    // several planes, where that leaves no compute unit idle.  Short rows from 60 MB of input and output on (40 MB at stride 2): fewer
+    // than 16 outputs, at stride 1 fewer than 24 on planes of up to 256 elements and than 18 on larger ones: the launch waits for memory, a compute unit holds 16 wavefronts of 8 KB regions and 32 of smaller ones, and the
     // estimate's single small planes load too little each.  With buffers that take turns over 2 GB, us, 8 KB or as estimated / the
-    // most planes of 3 KB (planes of up to 256 elements) or 4 KB: 8x8 at 95 MB 31.0 / 27.0, 9x9 at stride 2 at 94 MB 29.3 / 24.3; over 360
-    // random layers 0.88 .. 1.00 of the time by size and stride, below these bounds 1.04.
-    const bool narrow = p.Wout < 16 && xb + yb >= (S == 1 ? 60e6 : 40e6);
+    // most planes of 3 KB (planes of up to 256 elements) or 4 KB: 8x8 at 95 MB 31.0 / 27.0, 9x9 at stride 2 at 94 MB 29.3 / 24.3; over 520
+    // random layers 0.86 .. 1.00 of the time by size, width and stride, below these bounds 1.04.
+    const int longest = S == 2 ? 16 : HW <= 256 ? 24 : 18;
+    const bool narrow = p.Wout < longest && xb + yb >= (S == 1 ? 60e6 : 40e6);
     const int group = !narrow ? limit : HW <= 256 ? 768 : 1024;
     if (planes > 4 * kNumCU) {
         if (narrow && HW <= 256) best = 0.0;
@@ -676,9 +677,11 @@ bool plan_dw_rows(const ConvParams &p, DwPlan *out) {
     // last-level cache when a program comes back to them.  Buffers that take turns over 2 GB, us, four rows / one (and a block
     // that copied whole planes and stored them contiguously): 86x9 at 176 MB 48.7 / 37.1 (41.7), 65x6 at 228 MB 60.2 / 45.8 (53.9), 8x8 at
     // 130 MB 36.2 / 31.9 (34.0), 13x13 at 331 MB 81.6 / 71.1 (74.7), 15x15 at stride 2 at 129 MB 26.3 / 26.0 (30.4).  On one buffer that
-    // stays in the cache bands are level and groups of 100 .. 240 MB 0.97 (12x12 at 133 MB 23.9 / 28.8); 17x17 and longer rows keep four.
+    // stays in the cache bands are level and groups of 100 .. 240 MB 0.97 (12x12 at 133 MB 23.9 / 28.8).  Rows of
+    // 16 and 17 outputs at stride 1 on planes of more than 256 elements: 17x17 at 214 MB 53.4 / 48.4 (48.9), 28x17 at 214 MB 46.4 /
+    // 40.3 (45.9), 22x16 level; from 18 on four rows are ahead of that block, 0.95 with buffers that take turns and 1.05 on one.
     t.R = kRowsStrip;
-    if (narrow && xb + yb >= (t.G == 1 ? 60e6 : 100e6)) {
+    if (narrow && (p.Wout < 16 || HW > 256) && xb + yb >= (t.G == 1 ? 60e6 : 100e6)) {
         t.R = 1;       // (bands, planes and LDS as above: the windows reach less far)
         t.witem = p.Hout * p.Wout;
     }

@@ -81,6 +81,9 @@ def test_launches_of_few_planes(gpu, s, kernel):
     (dw(100, 512, 90, 13, 2), "conv_direct_narrow<2,false>"),
     (dw(19, 512, 87, 9, 1), "conv_direct_narrow<1,false>"),      # bands from 60 MB on
     (dw(18, 512, 87, 9, 1), "conv_direct_rows<1,false>"),
+    (dw(200, 512, 17, 17, 1), "conv_direct_narrow<1,true>"),     # 16 and 17 outputs on planes of more than 256 elements
+    (dw(170, 512, 13, 17, 1), "conv_direct_rows<1,true>"),
+    (dw(170, 512, 17, 18, 1), "conv_direct_rows<1,false>"),
     (dw(240, 272, 15, 15, 1), "conv_direct_narrow<1,true>"),     # never one small plane per wavefront
     (dw(530, 511, 25, 8, 2), "conv_direct_narrow<2,true>"),
     (dw(530, 511, 25, 9, 2), "conv_direct_narrow<2,true>"),
