@@ -228,7 +228,7 @@ hipError_t launch_split3(const ConvParams &p, const Split3Plan &plan, hipStream_
 // 16x16x4 MFMA kernel for small launches: no staging, the waves of a block split the reduction.
 struct UnitPlan {
     int nw;
-    int data[16];
+    alignas(8) int data[32];
 };
 bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out);
 hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name);

@@ -6,12 +6,23 @@
 // sums are added.  Such a launch is a chain of latencies - kernel start, addresses, one trip to memory,
 // products, the sum, the store - and conv_mfma16's chunks put three or four more trips into it.
 //
-// A unit of the reduction is four channels (lane / 16) and, for 3x3 layers, one kernel row: a lane loads the
-// three taps of its pixel (lane % 16) and the three weights of its filter with one 12-byte load each and
-// multiplies three times; for 1x1 layers sixteen channels, one 16-byte load of weights and four of inputs.
-// A unit costs the vector memory path two (1x1: five) instructions of up to 16 clocks for one tile, and nothing
-// is shared between tiles: that is what bounds it, and why the dispatch rule counts loads.  One 14x14 layer of
-// 256 channels in 4 groups at N = 1: 8.9 -> 3.5 us in the kernel trace.
+// A channel block is four channels (lane / 16); for 3x3 layers a lane loads the three taps of its pixel (lane % 16) and
+// the three weights of its filter in one kernel row with one 12-byte load each and multiplies three times; for 1x1
+// layers a block is sixteen channels, one 16-byte load of weights and four of inputs.  A row of a block costs the vector
+// memory path two (1x1: five) instructions of up to 16 clocks for one tile, and nothing is shared between tiles: that is
+// why the dispatch rule counts loads.
+//
+// What a launch takes beyond the 1.8 us of an empty one that depends on another is this chain, and instructions are a
+// large part of it: a block has up to 16 waves, which share four instruction streams, so that a hundred more per wave are
+// 0.2-0.7 us.  Hence: one struct of arguments, read in one round; divisions without branches, the tile's share of them in
+// scalar registers; an address per kernel row, which the channel blocks move by a scalar offset; validity as bits or'ed
+// into the address; the residual requested with the inputs; and no code for shared blocks where none are.  The trivial
+// kernel with the same blocks, loads, products and sum takes 4.1 us on cold weights in a graph (14x14, 64 channels per
+// group: 1.0 us of them the weights, 0.6 the inputs, 0.5 the products).  Per layer of the batch-1 ResNet-34-shaped chain,
+// g = 4: 4.4 -> 3.7 us (169 -> 145 us in all), MobileNetV2-shaped 236 -> 205, the pointwise form of the WRN stack 306 -> 238;
+// 60 -> 84 on 29x37, g = 3, N = 5 6.9 -> 5.5.  (One chain of products instead of two is level and
+// 5-20 % less exact.)
+#include <algorithm>
 #include <cstring>
 
 #include "conv_common.h"
@@ -21,137 +32,188 @@ namespace gspc {
 typedef float f32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 
+// What the kernel reads, in one piece: the scalar loads of its arguments are the first link of the chain, and a second
+// round of them another (so nothing is asked of the launch, such as the grid's size, that is not in here).
 struct TileUnit {
-    int units, cblks, mtiles;        // units of the reduction, blocks of four channels, filter tiles per group
-    unsigned npix, m_Wout;           // N * Hout * Wout; reciprocal
+    const float *x, *w;
+    float *y;
+    const float *res;
     unsigned x_bytes, w_bytes;
+    int blocks, parts;               // channel blocks: four channels, 1x1: sixteen; waves that share one (3x3)
+    int mtiles, CPG, KPG, Cin, Cout; // mtiles: filter tiles per group
+    int H, W, Wout;
+    unsigned HWo, npix;              // Hout * Wout, N * HWo
+    unsigned tiles, per_xcd, px_tiles;   // tiles of the launch, of an XCD's blocks, per filter tile
+    unsigned m_HWo, m_Wout, m_px, m_mt;  // reciprocals (unit_recip)
+    int relu;
 };
 static_assert(sizeof(TileUnit) <= sizeof(((UnitPlan *)0)->data), "plan storage too small");
 
-template <int NW, int KH, int S>
-__global__ __launch_bounds__(64 * NW) void conv_mfma16u(ConvParams p, TileUnit t) {
+// n / d with mul = unit_recip(d), exact while (n + 1) * d <= 2^32 and at most one too low beyond (up to n = 2^32 / 2); no
+// branch for d = 1, which would hold the loads behind it back.
+inline unsigned unit_recip(unsigned d) { return 0xffffffffu / d; }
+__device__ __forceinline__ unsigned unit_div(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
+
+// SHARE: two or three waves share a channel block (t.parts).
+template <int NW, int KH, int S, bool SHARE>
+__global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     constexpr bool ROW = KH == 3;
-    constexpr int UB = ROW ? 6 : 4;                     // units in flight per wave
-    __shared__ float part[NW][16][17];
+    constexpr int UB = ROW ? 2 : 4;                     // channel blocks in flight per wave
+    constexpr int KR = ROW ? 3 : 1, PR = ROW ? 3 : 4;   // kernel rows; products of a block's row
+    constexpr int OT = NW * 64 < 256 ? NW * 64 : 256, OPT = 256 / OT;   // threads that store, outputs of each
+    __shared__ f32x4 part[NW][64];
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned j = blockIdx.z, mt = blockIdx.y;
-    const unsigned HWo = p.Hout * p.Wout, HW = p.H * p.W;
+    // Tiles are numbered pixel tile innermost, and the blocks of one XCD (block % 8) take consecutive ones, so that few
+    // of the eight level-2 caches fetch a filter tile.
+    // (Up to seven blocks have no tile: they read and store nothing, but run along.)
+    const unsigned id = (blockIdx.x & 7) * t.per_xcd + (blockIdx.x >> 3);
+    const unsigned ft = unit_div(id, t.m_px), px = id - ft * t.px_tiles, j = unit_div(ft, t.m_mt), mt = ft - j * t.mtiles;
+    const unsigned HW = t.H * t.W;
 
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wu, t.w_bytes);
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(t.x, t.x_bytes);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(t.w, t.w_bytes);
 
-    // weights: [g][unit block][filter tile]([kernel row])[64 lanes][3 or 4]
-    constexpr unsigned WLANE = ROW ? 12 : 16, WUNIT = 64 * WLANE;
-    auto w_off = [&](int u) -> unsigned {               // wave-uniform
-        if (ROW) return ((j * t.cblks + u / 3) * t.mtiles + mt) * (3 * WUNIT) + (u % 3) * WUNIT;
-        return ((j * t.units + u) * t.mtiles + mt) * WUNIT;
-    };
-    u32x4 wv[UB];
+    // The wave's channel blocks are first, first + NW ..; where there are twice as many waves as blocks (3x3) two or three
+    // waves share one, kernel row by kernel row.
+    int first = wave, rows = 7;
+    if constexpr (SHARE) {
+        const int part = wave >= 2 * t.blocks ? 2 : wave >= t.blocks ? 1 : 0;
+        first = part < t.parts ? wave - part * t.blocks : t.blocks;
+        rows = t.parts == 3 ? 1 << part : part ? 4 : 3;
+    }
+    const auto off_row = [&](int k) -> unsigned { return !SHARE || rows >> k & 1 ? 0u : kOob; };   // (an address with these bits set is out of range)
+
+    // weights: [g][channel block][filter tile]([kernel row])[64 lanes][3 or 4].  (They do not wait for the pixel arithmetic.)
+    constexpr unsigned WLANE = ROW ? 12 : 16, WTILE = KR * 64 * WLANE;
+    u32x4 wv[UB][KR];
+    const unsigned wstep = t.mtiles * WTILE, wbase = (j * t.blocks * t.mtiles + mt) * WTILE;
     auto fetch_w = [&](int u, int s) __attribute__((always_inline)) {
-        const unsigned vo = u < t.units ? lane * WLANE : kOob;
-        if (ROW) {
-            const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(rw, vo, w_off(u), 0);
-            wv[s] = u32x4{v.x, v.y, v.z, 0u};
+        const unsigned vo = u < t.blocks ? lane * WLANE : kOob, so = wbase + u * wstep;
+        if constexpr (ROW) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(rw, vo | off_row(k), so + k * (64 * WLANE), 0);
+                wv[s][k] = u32x4{v.x, v.y, v.z, 0u};
+            }
         } else {
-            wv[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, w_off(u), 0);
+            wv[s][0] = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, so, 0);
         }
     };
 #pragma unroll
-    for (int s = 0; s < UB; ++s) fetch_w(wave + s * NW, s);   // (they do not wait for the pixel arithmetic)
+    for (int s = 0; s < UB; ++s) fetch_w(first + s * NW, s);
 
     // ---- this lane's pixel ------------------------------------------------------------------------
-    const unsigned q = blockIdx.x * 16 + li;
-    const bool live = q < t.npix;
-    const unsigned n = q / HWo, rem = q - n * HWo;
-    const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * p.Wout;
-    const int ih0 = (int)oh * S - p.pad, iw0 = (int)ow * S - p.pad;
+    // (the tile's first pixel in scalar registers; a tile spans images where planes are small)
+    unsigned n0 = unit_div(px * 16, t.m_HWo), r0 = px * 16 - n0 * t.HWo;
+    const bool low = r0 >= t.HWo;
+    n0 += low ? 1 : 0;
+    r0 -= low ? t.HWo : 0;
+    const unsigned dn = unit_div(r0 + li, t.m_HWo), n = n0 + dn, rem = r0 + li - dn * t.HWo;
+    const bool live = px * 16 + li < t.npix && id < t.tiles;
+    const unsigned oh = unit_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
+    const int ih0 = (int)oh * S - (ROW ? 1 : 0), iw0 = (int)ow * S - (ROW ? 1 : 0);
     // 3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
     // place up (down) and a zero takes the place of the column outside
-    const int start = ROW ? min(max(iw0, 0), p.W - 3) : iw0;
-    const int shift = start - iw0;
-    const unsigned xpix = ((n * p.Cin + j * p.CPG + lg) * HW + start) * 4u;
-    u32x3 xr[ROW ? UB : 1];
-    unsigned xs[ROW ? 1 : UB][4];
-    auto fetch_x = [&](int u, int s) __attribute__((always_inline)) {
-        if constexpr (ROW) {
-            const int cb = u / 3, ih = ih0 + u % 3;
-            const bool ok = live && u < t.units && cb * 4 + lg < p.CPG && (unsigned)ih < (unsigned)p.H;
-            xr[s] = __builtin_amdgcn_raw_buffer_load_b96(rx, ok ? xpix + (cb * 4 * HW + ih * p.W) * 4u : kOob, 0, 0);
-        } else {
+    const int start = ROW ? min(max(iw0, 0), t.W - 3) : iw0;
+    const unsigned xpix = ((n * t.Cin + j * t.CPG + lg) * HW + ih0 * t.W + start) * 4u;
+    unsigned xo[KR];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int cb = u * 4 + e;
-                const bool ok = live && cb * 4 + lg < p.CPG;
-                xs[s][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, ok ? xpix + (cb * 4 * HW + ih0 * p.W) * 4u : kOob, 0, 0);
-            }
+    for (int k = 0; k < KR; ++k)
+        xo[k] = (xpix + k * t.W * 4) | (live && (!ROW || (unsigned)(ih0 + k) < (unsigned)t.H) ? 0u : kOob) | (ROW ? off_row(k) : 0u);
+    u32x3 xr[UB][KR];
+    unsigned xs[UB][4];
+    // Channels past the group's have zero weights and must be zeros too (0 * inf): a lane's channels of a block are lg,
+    // 1x1: lg, lg + 4, lg + 8 and lg + 12 from the block's first on.
+    const int mine = t.CPG - lg;
+    auto fetch_x = [&](int u, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < (ROW ? 3 : 4); ++e) {
+            const int c = ROW ? u * 4 : u * 16 + 4 * e;      // (waves past the last block are past the channels)
+            const unsigned vo = xo[ROW ? e : 0] | (c < mine ? 0u : kOob), so = c * HW * 4;
+            if constexpr (ROW) xr[s][e] = __builtin_amdgcn_raw_buffer_load_b96(rx, vo, so, 0);
+            else xs[s][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, so, 0);
         }
     };
 #pragma unroll
-    for (int s = 0; s < UB; ++s) fetch_x(wave + s * NW, s);
+    for (int s = 0; s < UB; ++s) fetch_x(first + s * NW, s);
+
+    // ---- this thread's outputs: filters tid / 16 (+ 8) of the tile at the lane's pixel --------------
+    const unsigned f0 = mt * 16 + tid / 16;
+    const size_t at = (size_t)(n * t.Cout + j * t.KPG + f0) * t.HWo + rem;
+    float res[OPT];
+    if (t.res && tid < OT) {
+#pragma unroll
+        for (int o = 0; o < OPT; ++o) res[o] = live && f0 + o * (OT / 16) < (unsigned)t.KPG ? t.res[at + (size_t)o * (OT / 16) * t.HWo] : 0.f;
+    }
     __builtin_amdgcn_sched_barrier(0);
 
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int u0 = wave; u0 < t.units; u0 += UB * NW) {
-        const bool more = u0 + UB * NW < t.units;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};   // even and odd blocks: two chains of products
+    const bool left_end = start > iw0, right_end = start < iw0;
+    for (int u0 = first; u0 < t.blocks; u0 += UB * NW) {
 #pragma unroll
         for (int s = 0; s < UB; ++s) {
-            float b[4];
-            if constexpr (ROW) {
-                const float x0 = __uint_as_float(xr[s].x), x1 = __uint_as_float(xr[s].y), x2 = __uint_as_float(xr[s].z);
-                b[0] = shift > 0 ? 0.f : shift < 0 ? x1 : x0;
-                b[1] = shift > 0 ? x0 : shift < 0 ? x2 : x1;
-                b[2] = shift > 0 ? x1 : shift < 0 ? 0.f : x2;
-            } else {
+            const int u = u0 + s * NW;
+            if (u >= t.blocks) break;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) b[e] = __uint_as_float(xs[s][e]);
+            for (int k = 0; k < KR; ++k) {
+                if (SHARE && !(rows >> k & 1)) continue;
+                float b[4];
+                if constexpr (ROW) {
+                    const float x0 = __uint_as_float(xr[s][k].x), x1 = __uint_as_float(xr[s][k].y), x2 = __uint_as_float(xr[s][k].z);
+                    b[0] = left_end ? 0.f : right_end ? x1 : x0;
+                    b[1] = left_end ? x0 : right_end ? x2 : x1;
+                    b[2] = left_end ? x1 : right_end ? 0.f : x2;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[e] = __uint_as_float(xs[s][e]);
+                }
+#pragma unroll
+                for (int e = 0; e < PR; ++e) {
+                    f32x4 &c = s & 1 ? odd : acc;
+                    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wv[s][k][e]), b[e], c, 0, 0, 0);
+                }
             }
-#pragma unroll
-            for (int e = 0; e < (ROW ? 3 : 4); ++e)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wv[s][e]), b[e], acc, 0, 0, 0);
-            if (more) {
-                const int u = u0 + (s + UB) * NW;
-                fetch_w(u, s);
-                fetch_x(u, s);
+            if (u + UB * NW < t.blocks) {
+                fetch_w(u + UB * NW, s);
+                fetch_x(u + UB * NW, s);
             }
         }
     }
 
     // ---- the waves' partial sums; residual, ReLU, NCHW store ---------------------------------------
-#pragma unroll
-    for (int r = 0; r < 4; ++r) part[wave][4 * lg + r][li] = acc[r];
+    part[wave][lane] = acc + odd;
     __syncthreads();
-    constexpr int OT = NW * 64 < 256 ? NW * 64 : 256;    // threads that store
-    if (tid >= OT) return;
+    const float *sum = reinterpret_cast<const float *>(part) + (tid / 64 * 16 + li) * 4 + lg;   // filter tid / 16, pixel li
+    if (wave >= OT / 64) return;
 #pragma unroll
-    for (int o = tid; o < 256; o += OT) {
-        const int f = o >> 4, px = o & 15;
-        float v = part[0][f][px];
+    for (int o = 0; o < OPT; ++o) {
+        float v = sum[o * OT];
 #pragma unroll
-        for (int k = 1; k < NW; ++k) v += part[k][f][px];
-        const unsigned qo = blockIdx.x * 16 + px, fo = mt * 16 + f;
-        if (qo < t.npix && fo < (unsigned)p.KPG) {
-            const unsigned no = qo / HWo;
-            const size_t at = (size_t)(no * p.Cout + j * p.KPG + fo) * HWo + (qo - no * HWo);
-            if (p.res) v += p.res[at];
-            p.y[at] = p.relu ? fmaxf(v, 0.f) : v;
+        for (int k = 1; k < NW; ++k) v += sum[o * OT + k * 256];
+        if (live && f0 + o * (OT / 16) < (unsigned)t.KPG) {
+            if (t.res) v += res[o];
+            t.y[at + (size_t)o * (OT / 16) * t.HWo] = t.relu ? fmaxf(v, 0.f) : v;
         }
     }
 }
 
 namespace {
 
-template <int NW, int KH, int S>
-hipError_t launchU(const ConvParams &p, const TileUnit &t, hipStream_t s) {
-    hipLaunchKernelGGL((conv_mfma16u<NW, KH, S>), dim3((t.npix + 15) / 16, t.mtiles, p.groups), dim3(64 * NW), 0, s, p, t);
+template <int NW, int KH, int S, bool SHARE = false>
+hipError_t launchU(const TileUnit &t, hipStream_t s) {
+    if constexpr (KH == 3 && !SHARE) {
+        if (t.parts > 1) return launchU<NW, KH, S, true>(t, s);
+    }
+    hipLaunchKernelGGL((conv_mfma16u<NW, KH, S, SHARE>), dim3(8 * t.per_xcd), dim3(64 * NW), 0, s, t);
     return hipGetLastError();
 }
 
 template <int NW>
 hipError_t launchU_shape(const ConvParams &p, const TileUnit &t, hipStream_t s) {
-    if (p.KH == 3) return p.stride == 1 ? launchU<NW, 3, 1>(p, t, s) : launchU<NW, 3, 2>(p, t, s);
-    return p.stride == 1 ? launchU<NW, 1, 1>(p, t, s) : launchU<NW, 1, 2>(p, t, s);
+    if (p.KH == 3) return p.stride == 1 ? launchU<NW, 3, 1>(t, s) : launchU<NW, 3, 2>(t, s);
+    return p.stride == 1 ? launchU<NW, 1, 1>(t, s) : launchU<NW, 1, 2>(t, s);
 }
 
 }  // namespace
@@ -163,13 +225,25 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     const double npix = (double)p.N * p.Hout * p.Wout;
     const double xb = (double)p.N * p.Cin * p.H * p.W * 4;
     if (xb >= (double)kOob || npix >= 1e6 || (double)g.unit_bytes >= (double)kOob) return false;
-    if (p.groups > 65535 || g.mtiles > 65535 || (long)p.Hout * p.Wout >= 65536) return false;
+    if ((double)p.Hout * p.Wout * (p.Hout * p.Wout + 16.0) > 4294967296.0) return false;
     TileUnit t{};
-    t.cblks = g.CPGp / 4;
-    t.units = row ? t.cblks * 3 : (t.cblks + 3) / 4;
+    t.blocks = row ? g.CPGp / 4 : (g.CPGp + 15) / 16;
+    const int units = row ? 3 * t.blocks : t.blocks;     // of the reduction in the rules below: 3x3, a kernel row of a block
     t.mtiles = g.mtiles;
+    t.CPG = g.CPG;
+    t.KPG = g.KPG;
+    t.Cin = p.Cin;
+    t.Cout = p.Cout;
+    t.H = p.H;
+    t.W = p.W;
+    t.Wout = p.Wout;
+    t.HWo = p.Hout * p.Wout;
     t.npix = (unsigned)npix;
-    t.m_Wout = div_magic(p.Wout);
+    t.m_HWo = unit_recip(t.HWo);
+    t.m_Wout = unit_recip(p.Wout);
+    t.px_tiles = (t.npix + 15) / 16;
+    t.m_px = unit_recip(t.px_tiles);
+    t.m_mt = unit_recip(t.mtiles);
     t.x_bytes = (unsigned)xb;
     t.w_bytes = (unsigned)g.unit_bytes;
     // Where it pays (layers of the WRN-, ResNet-34- and MobileNet-shaped networks at N = 1 .. 64, us, conv_mfma16 with
@@ -190,14 +264,18 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     //    with up to 16 filters 37 layers are level;
     //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 9.0 / 5.9, N = 10 (2250) 8.7 / 9.8, and with nine 144 -> 24 on 64x64,
     //    N = 4 (2048) 6.5 / 9.7, 576 -> 96 on 32x32, g = 4 6.6 / 9.0.
-    const long tiles = (long)((t.npix + 15) / 16) * g.mtiles * p.groups;
-    const double loads = (double)tiles * t.units * (row ? 2 : 5);
+    const long tiles = (long)t.px_tiles * g.mtiles * p.groups;
+    if ((double)(tiles + 8) * t.px_tiles >= 4294967296.0 || (double)(g.mtiles * (double)p.groups + 1) * g.mtiles >= 4294967296.0)
+        return false;
+    t.tiles = (unsigned)tiles;
+    t.per_xcd = (t.tiles + 7) / 8;
+    const double loads = (double)tiles * units * (row ? 2 : 5);
     const bool wide = p.stride == 1 && (row ? p.W % 4 == 0 : (p.Hout * p.Wout) % 4 == 0);   // staged 16 bytes at a time
     if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
-    if (t.units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
-    if (row && p.stride == 1 && t.units < 9 && tiles > 8 * kNumCU) return false;
-    if (row && p.stride == 2 && t.units < 9 && g.KPG > 16 && tiles > 12 * kNumCU) return false;
-    if (!row && wide && t.units < 12 && tiles >= 8 * kNumCU) return false;
+    if (units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
+    if (row && p.stride == 1 && units < 9 && tiles > 8 * kNumCU) return false;
+    if (row && p.stride == 2 && units < 9 && g.KPG > 16 && tiles > 12 * kNumCU) return false;
+    if (!row && wide && units < 12 && tiles >= 8 * kNumCU) return false;
     // Odd pointwise planes handed over as one row are staged 16 bytes at a time as well:
     //  - 40 .. 63 pixels, which fill most of a 64-pixel tile: while the staged kernel has a block per image (see
     //    fills_image_tiles) it is ahead from 4 tiles per compute unit on: 384 -> 32 on 7x7, g = 2, N = 178 (1092 tiles)
@@ -211,7 +289,7 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     // still start together, eight per compute unit: one block too many costs its start anew (8 -> 16 on 12x12, g = 2,
     // N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time)
     int nw = 2;
-    while (nw < 16 && (t.units > nw * (row ? 6 : 4) || (tiles * nw * 2 <= 8 * kNumCU && t.units > nw))) nw *= 2;
+    while (nw < 16 && (units > nw * (row ? 6 : 4) || (tiles * nw * 2 <= 8 * kNumCU && units > nw))) nw *= 2;
     // Large 3x3 layers whose waves have places for a third more units than there are (9, 15, 18, 27, 30 of them) go to the
     // kernel that keeps its filters where that takes the layer and the rows fill its 16-pixel tiles: 20 -> 64 on 32x32,
     // N = 4, g = 2 (2048 tiles) 6.9 / 5.3 here / there, 144 -> 192 on 16x16, g = 4, N = 7 (1344) 8.6 / 6.5, 80 -> 256 on 16x16,
@@ -221,9 +299,10 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     // (1856) 4.8 / 4.3, 8 -> 128 on 14x16, N = 15 (1680) 4.8 / 4.3, with 4.5 tiles level; not on planes that the 32 pixels of
     // its two waves do not divide (16 -> 32 on 14x8, g = 2, N = 144 (2016) 4.9 / 5.3).
     Mfma16wPlan pw;
-    if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * t.units <= 3 * 6 * nw &&
-        tiles * nw >= (t.units < 9 && p.H * p.W % 32 == 0 ? 10 : 24) * kNumCU && plan_mfma16w(p, g, &pw))
+    if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * units <= 3 * 6 * nw &&
+        tiles * nw >= (units < 9 && p.H * p.W % 32 == 0 ? 10 : 24) * kNumCU && plan_mfma16w(p, g, &pw))
         return false;
+    t.parts = row && nw >= 2 * t.blocks ? std::min(nw / t.blocks, 3) : 1;
     out->nw = nw;
     std::memcpy(out->data, &t, sizeof(t));
     return true;
@@ -232,6 +311,11 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
 hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name) {
     TileUnit t;
     std::memcpy(&t, plan.data, sizeof(t));
+    t.x = static_cast<const float *>(p.x);
+    t.w = p.wu;
+    t.y = p.y;
+    t.res = p.res;
+    t.relu = p.relu;
     if (!*name)
         *name = intern_name("conv_mfma16u<" + std::to_string(plan.nw) + "," + std::to_string(p.KH) + "," + std::to_string(p.stride) + ">");
     switch (plan.nw) {

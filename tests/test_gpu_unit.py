@@ -24,6 +24,16 @@ SHAPES = [
     S(1, 960, 7, 7, 160, 1, 1, 1, 0, 1),
     S(3, 36, 5, 5, 20, 1, 1, 1, 0, 2),        # 18 channels and 10 filters per group
     S(17, 128, 4, 4, 64, 1, 1, 1, 0, 4),
+    # waves that share a channel block, by threes and by pairs, and more waves than blocks
+    S(1, 4, 9, 7, 16, 3, 3, 1, 1, 1),         # one block
+    S(2, 16, 8, 8, 32, 3, 3, 1, 1, 1),        # four
+    S(1, 23, 10, 9, 17, 3, 3, 2, 1, 1),       # six, the last one of three channels
+    S(1, 36, 12, 11, 16, 3, 3, 1, 1, 1),      # nine blocks, sixteen waves
+    # tiles that span images, and launches whose tiles are no multiple of the eight XCDs
+    S(71, 8, 3, 3, 12, 3, 3, 1, 1, 1),        # planes of nine pixels
+    S(31, 16, 3, 5, 16, 3, 3, 2, 1, 1),       # of six
+    S(45, 48, 1, 3, 40, 1, 1, 1, 0, 1),       # of three
+    S(1, 64, 5, 5, 48, 3, 3, 1, 1, 1),        # six tiles
 ]
 
 
