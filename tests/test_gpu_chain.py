@@ -221,3 +221,22 @@ def test_padded_filter_tile_with_residual_and_relu(s, batch, kernel):
     got = out[guard:guard + res.size].reshape(res.shape)
     ref = oracle.relu(oracle.add(oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, threads=8), res))
     assert rel_err(got, ref) < TOL_F32
+
+
+@pytest.mark.parametrize("N,C,H,W,k,stride,pad", [
+    (1, 1, 1, 1, 1, 1, 0), (2, 3, 2, 5, 2, 1, 1), (1, 5, 7, 3, 2, 2, 0), (3, 7, 9, 8, 3, 2, 1), (1, 64, 31, 33, 3, 1, 1),
+    (2, 2, 6, 11, 5, 3, 2), (1, 3, 1, 257, 3, 2, 1)])
+def test_maxpool_step(N, C, H, W, k, stride, pad):
+    """Windows clipped at every border, on planes of one row and of one element: the oracle's values exactly."""
+    import torch
+    from paper_2006_09791_amd import binding as b
+    ch = wl.Chain("pool", (N, C, H, W))
+    ho, wo = wl.out_size(H, k, stride, pad), wl.out_size(W, k, stride, pad)
+    ch.maxpool(0, 1, N, C, H, W, k, stride, pad)
+    x0 = wl.make_input(ch.input_shape, 17) - 2.0          # all negative: a zero border would win
+    lc, bufs = gpu_chain(ch, x0, [])
+    b.gspc_run_layer_chain(lc)
+    torch.cuda.synchronize()
+    got = bufs[1][:N * C * ho * wo].cpu().numpy().reshape(N, C, ho, wo)
+    import oracle
+    assert np.array_equal(got, oracle.maxpool2d(x0, k, stride, pad).astype(np.float32))
