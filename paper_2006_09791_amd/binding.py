@@ -1,4 +1,5 @@
-"""ctypes binding of libgspc.so: argument marshalling only.
+"""ctypes binding of libgspc.so: argument marshalling only (in C, csrc/pycall.c, for the call that a program makes
+for every layer).
 
 Function names and argument order mirror include/gspc.h.  Device buffers are
 torch tensors (PyTorch is used for device memory and streams, nothing else);
@@ -44,11 +45,12 @@ class GspcLayer(ctypes.Structure):
 
 
 _lib = None
+_conv = None     # gspc_conv2d_grouped through _gspc_call
 
 
 def load():
     """Loads libgspc.so (must have been built in-tree) and sets prototypes."""
-    global _lib
+    global _lib, _conv
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -96,6 +98,9 @@ def load():
     lib.gspc_run_layer_chain.restype = i
     lib.gspc_run_layer_chain.argtypes = [ctypes.POINTER(GspcLayer), i, ctypes.POINTER(vp),
                                          ctypes.POINTER(sz), i, ctypes.POINTER(ctypes.c_float)]
+    from . import _gspc_call
+    _gspc_call.bind(ctypes.cast(lib.gspc_conv2d_grouped, vp).value)
+    _conv = _gspc_call.conv
     _lib = lib
     return lib
 
@@ -204,12 +209,18 @@ def gspc_pack_input_bf16(x):
 def gspc_conv2d_grouped(input, packed_weight, N, Cin, H, W, Cout, KH, KW, stride, pad, groups,
                         output=None):
     """Returns the fp32 output tensor [N, Cout, Hout, Wout] (allocated if not given)."""
-    import torch
+    if _lib is None:
+        load()
     if output is None:
+        import torch
         ho, wo = gspc_output_dims(H, W, KH, KW, stride, pad)
         output = torch.empty((N, Cout, ho, wo), dtype=torch.float32, device=input.device)
-    _check(load().gspc_conv2d_grouped(_ptr(input), packed_weight.handle, N, Cin, H, W, Cout, KH,
-                                      KW, stride, pad, groups, _ptr(output)))
+    rc = _conv(input, packed_weight.handle, N, Cin, H, W, Cout, KH, KW, stride, pad, groups, output)
+    if rc is NotImplemented:
+        rc = _lib.gspc_conv2d_grouped(_ptr(input), packed_weight.handle, N, Cin, H, W, Cout, KH, KW, stride, pad, groups,
+                                      _ptr(output))
+    if rc:
+        _check(rc)
     return output
 
 

@@ -1,7 +1,8 @@
-"""Build libgspc.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libgspc.so (HIP, gfx950 only) in-tree with hipcc, and _gspc_call.so, the binding's argument marshalling."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -9,6 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgspc.so")
+CALL = os.path.join(HERE, "_gspc_call.so")
 
 SOURCES = ["gspc_api.cpp", "pack_kernels.hip", "chain_kernels.hip",
            "direct_kernels.hip", "mfma_kernels.hip", "mfma4_kernels.hip", "mfmab_kernels.hip",
@@ -46,12 +48,21 @@ def _compile(src):
     return obj, warn
 
 
+def _build_call():
+    cmd = ["gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pycall.c"), "-o", CALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"gcc failed on pycall.c:\n{r.stdout}\n{r.stderr}")
+
+
 def build(force=True, verbose=False):
-    """Compiles every source and links libgspc.so.  With force=False an
-    up-to-date library is reused."""
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _deps_mtime():
+    """Compiles every source and links libgspc.so and _gspc_call.so.  With force=False
+    up-to-date libraries are reused."""
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, CALL)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
+    _build_call()
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         results = list(ex.map(_compile, SOURCES))
     objs = [o for o, _ in results]

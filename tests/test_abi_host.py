@@ -193,3 +193,30 @@ def test_autotuner_rejects_a_candidate_whose_output_differs():
     assert not autotune.agrees({"sample": [1.0, 2.0, -3.001], "rms": 2.0}, base)
     assert autotune.agrees({"sample": [1.0, 2.0, -3.001], "rms": 2.0}, base, tol=1e-3)
     assert not autotune.agrees({"sample": [1.0, 2.0], "rms": 2.0}, base)
+
+
+@pytest.mark.parametrize("n", [1, True, 2 ** 40 + 1], ids=["int", "bool", "wide"])
+def test_conv_call_marshalling(n):
+    """The call of one layer goes through C for plain numbers and through ctypes for others: the same checks, the same codes."""
+    import ctypes
+
+    import torch
+    x = torch.zeros(16)
+    class Packed:
+        handle = None
+    args = (n, 64, 32, 32, 64, 3, 3, 1, 1, 4)
+    with pytest.raises(b.GspcError) as e:
+        b.gspc_conv2d_grouped(x, Packed, *args, output=x)
+    assert e.value.code == -1                                  # no weights
+    Packed.handle = ctypes.c_void_p(x.data_ptr())
+    with pytest.raises(b.GspcError) as e:
+        b.gspc_conv2d_grouped(None, Packed, *args, output=x)
+    assert e.value.code == -1                                  # no input
+    with pytest.raises(b.GspcError) as e:
+        b.gspc_conv2d_grouped(x, Packed, *args, output=x)
+    assert e.value.code == -5                                  # sixteen zeros are no handle
+    with pytest.raises(b.GspcError) as e:
+        b.gspc_conv2d_grouped(x[1:], Packed, *args, output=x)
+    assert e.value.code == -8                                  # four bytes off
+    with pytest.raises(ctypes.ArgumentError):
+        b.gspc_conv2d_grouped(x, Packed, 1.0, *args[1:], output=x)
