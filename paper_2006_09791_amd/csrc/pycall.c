@@ -3,8 +3,8 @@
  *
  * A call of the library for a small layer is a launch of 3-4 us on the GPU; through ctypes, which converts
  * thirteen arguments by type and builds an object for each pointer, the call took 4.6 us of host time, 2.5-2.8 of them
- * in Python (64 -> 64 on 32x32, g = 4, N = 1).  Here it takes 3.0 in all.  The library is not linked: binding.py hands over
- * the address of the function that it loaded.
+ * in Python (64 -> 64 on 32x32, g = 4, N = 1).  Here they are 0.4, and the call takes 3.8 in all.  The library is not
+ * linked: binding.py hands over the address of the function that it loaded.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>

@@ -51,6 +51,11 @@ struct TileX {
 
 constexpr int kTmaxX = 4;
 
+// n / d with mul = recip(d), exact while (n + 1) * d <= 2^32.  (fast_div's branch for d = 1 would split the arithmetic
+// before a block's first load into a dozen pieces.)
+inline unsigned recip(unsigned d) { return 0xffffffffu / d; }
+__device__ __forceinline__ unsigned div_recip(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
+
 template <int MI, int NI, int WM, int WP, int CKB, bool RT>
 __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX t) {
     static_assert(!RT || (MI == 1 && NI == 1), "the register transform serves one product tile per wave");
@@ -66,9 +71,9 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WP, wp = wave % WP;
-    const unsigned ib = fast_div(blockIdx.x, t.m_rowb);
+    const unsigned ib = div_recip(blockIdx.x, t.m_rowb);
     const int rb = blockIdx.x - ib * t.row_blocks;
-    const unsigned j = fast_div(blockIdx.y, t.m_ocb);
+    const unsigned j = div_recip(blockIdx.y, t.m_ocb);
     const int ob = blockIdx.y - j * t.oc_blocks;
     const int n0 = ib * t.NB, tr0 = rb * t.TR, ih0 = 2 * tr0 - 1;
     const unsigned HW = p.H * p.W;
@@ -90,8 +95,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
         xoff[k] = kOob;
         xlds[k] = spare;
         if (k < t.xslots && task < t.tasks && colv * vw < p.W) {
-            const int cimg = fast_div(task, t.m_IHt), r = task - cimg * t.IHt;
-            const int c = fast_div(cimg, t.m_NB), img = cimg - c * t.NB;
+            const int cimg = div_recip(task, t.m_IHt), r = task - cimg * t.IHt;
+            const int c = div_recip(cimg, t.m_NB), img = cimg - c * t.NB;
             const int ih = ih0 + r, n = n0 + img;
             // rows above and below the image load as zero: the halo rows are rewritten with every chunk
             if (n < p.N && ih >= 0 && ih < p.H)
@@ -129,22 +134,30 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
     int pbase;
     {
         const int qq = tq < t.P ? tq : 0;
-        const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
-        const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
+        const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
+        const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
         pbase = img * t.IMG + 2 * tr * t.LW + (t.XO - 1) + 2 * tc;
     }
 
-    // Halo columns left and right of a staged row are never written by the staging: clear them once.
-    {
-        const int rows = CK * t.NB * t.IHt, right = t.XO + p.W;
-        for (int i = tid; i < (RT ? 2 : 1) * rows; i += NT) {
-            const int b = i >= rows, ii = i - b * rows;
-            const int cimg = fast_div(ii, t.m_IHt), r = ii - cimg * t.IHt;
-            const int c = fast_div(cimg, t.m_NB), img = cimg - c * t.NB;
-            float *row = raw + b * t.raw_floats + c * t.PLANE + img * t.IMG + r * t.LW;
-            for (int x = 0; x < t.XO; ++x) row[x] = 0.f;
-            for (int x = right; x < t.LW; ++x) row[x] = 0.f;
-        }
+    // Halo columns left and right of a staged row are never written by the staging: the lane of a row's first column
+    // clears them once.
+    if (colv == 0) {
+        const int right = p.W, pads = t.LW - t.XO - p.W;     // (from the first column on)
+#pragma unroll
+        for (int k = 0; k < TMAX; ++k)
+            if (k < t.xslots && xlds[k] != spare) {
+#pragma unroll
+                for (int b = 0; b < (RT ? 2 : 1); ++b) {
+                    float *row = raw + b * t.raw_floats + xlds[k] / 4;
+                    if (t.vec) {
+                        *reinterpret_cast<f32x4 *>(row - 4) = f32x4{0.f, 0.f, 0.f, 0.f};
+                        for (int x = 0; x < pads; x += 4) *reinterpret_cast<f32x4 *>(row + right + x) = f32x4{0.f, 0.f, 0.f, 0.f};
+                    } else {
+                        row[-1] = 0.f;
+                        for (int x = 0; x < pads; ++x) row[right + x] = 0.f;
+                    }
+                }
+            }
     }
 
     f32x4 acc[16][MI][NI];
@@ -155,14 +168,53 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) acc[xn][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // ---- outputs: byte offsets of a lane's two output rows (first filter of the block's first tile), and whether the tile
+    // has a second column (always, for even widths)
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
+    const unsigned oc0 = (ob * MIWM + wm * MI) * 16;
+    struct Out {
+        unsigned o0, o1;
+        bool c1;
+    };
+    auto out_at = [&](int ni) -> Out {
+        const int q = (wp * NI + ni) * 16 + (lane & 15);
+        const int qq = q < t.P ? q : 0;
+        const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
+        const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
+        const int n = n0 + img, oh = 2 * (tr0 + tr), ow = 2 * tc;
+        const bool ok = q < t.P && n < p.N && oh < p.H;
+        const unsigned o0 = ok ? (((unsigned)n * p.Cout + j * p.KPG + 4 * (lane >> 4)) * HW + oh * p.W + ow) * 4 : kOob;
+        return {o0, ok && oh + 1 < p.H ? o0 + p.W * 4 : kOob, ow + 1 < p.W};
+    };
+    Out out_rt{};
+    // The residual of even planes is requested before the products: after them its trip to memory is one more link of the
+    // chain, 0.7 us of 9.8 in the layers that have one (64 -> 64 on 16x16, g = 2, N = 64).
+    u32x2 ra[RT && CKB == 2 ? 4 : 1], rb2[RT && CKB == 2 ? 4 : 1];
+    constexpr bool ER = RT && CKB == 2;          // (with one channel block they would cost a third wave per SIMD)
+    const bool early_res = ER && p.res && !t.wodd;
+    if constexpr (RT) {
+        out_rt = out_at(0);
+    }
+    if constexpr (ER) {
+        if (early_res) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool fk = oc0 + 4 * (lane >> 4) + r < (unsigned)p.KPG;
+                ra[r] = __builtin_amdgcn_raw_buffer_load_b64(rr, fk ? out_rt.o0 : kOob, (oc0 + r) * HW * 4, 0);
+                rb2[r] = __builtin_amdgcn_raw_buffer_load_b64(rr, fk ? out_rt.o1 : kOob, (oc0 + r) * HW * 4, 0);
+            }
+        }
+    }
+
     if constexpr (RT) {
         // ---- register transform: this lane's patch (channel lane/16 of the k-step, tile lane%16 of the wave) ----
         int pbase_r;
         {
             const int q = wp * 16 + (lane & 15);
             const int qq = q < t.P ? q : 0;
-            const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
-            const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
+            const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
+            const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
             pbase_r = (lane >> 4) * t.PLANE + img * t.IMG + 2 * tr * t.LW + (t.XO - 1) + 2 * tc;
         }
         f32x4 ub[2][CKB][4];   // U of this chunk and of the next one
@@ -326,20 +378,11 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
 
     // ---- inverse transform Y = A^T M A, optional residual and ReLU, NCHW stores ----
     // Register r of an accumulator is filter 16*(tile row) + 4*(lane/16) + r at tile lane%16.
-    const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res ? p.res : p.y, t.y_bytes);
-    const unsigned oc0 = (ob * MIWM + wm * MI) * 16;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
-        const int q = (wp * NI + ni) * 16 + (lane & 15);
-        const int qq = q < t.P ? q : 0;
-        const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
-        const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
-        const int n = n0 + img, oh = 2 * (tr0 + tr), ow = 2 * tc;
-        const bool ok = q < t.P && n < p.N && oh < p.H;
-        const unsigned o0 = ok ? (((unsigned)n * p.Cout + j * p.KPG + 4 * (lane >> 4)) * HW + oh * p.W + ow) * 4 : kOob;
-        const unsigned o1 = ok && oh + 1 < p.H ? o0 + p.W * 4 : kOob;
-        const bool c1 = ow + 1 < p.W;   // second column exists (always, for even widths)
+        const Out out = RT ? out_rt : out_at(ni);
+        const unsigned o0 = out.o0, o1 = out.o1;
+        const bool c1 = out.c1;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -360,12 +403,14 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
                 const unsigned p0 = fk ? o0 : kOob, p1 = fk ? o1 : kOob;
                 if (!t.wodd) {
                     if (p.res) {
-                        const u32x2 ra = __builtin_amdgcn_raw_buffer_load_b64(rr, p0, so, 0);
-                        const u32x2 rb2 = __builtin_amdgcn_raw_buffer_load_b64(rr, p1, so, 0);
-                        y00 += __uint_as_float(ra.x);
-                        y01 += __uint_as_float(ra.y);
-                        y10 += __uint_as_float(rb2.x);
-                        y11 += __uint_as_float(rb2.y);
+                        if constexpr (!ER) {
+                            ra[0] = __builtin_amdgcn_raw_buffer_load_b64(rr, p0, so, 0);
+                            rb2[0] = __builtin_amdgcn_raw_buffer_load_b64(rr, p1, so, 0);
+                        }
+                        y00 += __uint_as_float(ra[ER ? r : 0].x);
+                        y01 += __uint_as_float(ra[ER ? r : 0].y);
+                        y10 += __uint_as_float(rb2[ER ? r : 0].x);
+                        y11 += __uint_as_float(rb2[ER ? r : 0].y);
                     }
                     if (p.relu) {
                         y00 = fmaxf(y00, 0.f);
@@ -477,12 +522,12 @@ bool planx_cfg(const ConvParams &p, const PackGeom &g, const CfgX &c, int ckb, b
     t.oc_blocks = (t.mtiles + MIWM - 1) / MIWM;
     t.wodd = p.W % 2;
     t.rt = rt;
-    t.m_IHt = div_magic(t.IHt);
-    t.m_NB = div_magic(t.NB);
-    t.m_tpi = div_magic(t.tpi);
-    t.m_TC = div_magic(t.TC);
-    t.m_rowb = div_magic(t.row_blocks);
-    t.m_ocb = div_magic(t.oc_blocks);
+    t.m_IHt = recip(t.IHt);
+    t.m_NB = recip(t.NB);
+    t.m_tpi = recip(t.tpi);
+    t.m_TC = recip(t.TC);
+    t.m_rowb = recip(t.row_blocks);
+    t.m_ocb = recip(t.oc_blocks);
     const double xb = (double)p.N * p.Cin * p.H * p.W * 4, yb = (double)p.N * p.Cout * p.H * p.W * 4;
     const double ub = (double)p.groups * t.cblks * t.mtiles * 4096;
     if (xb >= (double)kOob || yb >= (double)kOob || ub >= (double)kOob) return false;
@@ -490,7 +535,7 @@ bool planx_cfg(const ConvParams &p, const PackGeom &g, const CfgX &c, int ckb, b
     t.y_bytes = (unsigned)yb;
     t.u_bytes = (unsigned)ub;
     if ((long)t.row_blocks * t.img_blocks > 2147483647L || p.groups * t.oc_blocks > 65535) return false;
-    // fast_div exactness: numerator * divisor < 2^32
+    // exact divisions: numerator * divisor < 2^32
     if ((double)t.row_blocks * t.img_blocks * t.row_blocks >= 4.0e9 ||
         (double)p.groups * t.oc_blocks * t.oc_blocks >= 4.0e9 || (double)t.tasks * t.IHt >= 4.0e9 ||
         (double)t.tasks * t.NB >= 4.0e9 || (double)PT * t.tpi >= 4.0e9)
