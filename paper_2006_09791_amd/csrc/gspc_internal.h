@@ -230,7 +230,8 @@ struct UnitPlan {
     int nw;
     alignas(8) int data[32];
 };
-bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out);
+// more: how far beyond the bound on a launch's loads it may go.
+bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double more = 1.0);
 hipError_t launch_unit(const ConvParams &p, const UnitPlan &plan, hipStream_t s, const char **name);
 
 // 4x4x1 MFMA kernel (weights held in registers); plan is opaque to the caller.

@@ -819,6 +819,17 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     else if (plan_mfma4(p, g, &pl.p4)) pl.kind = 4;
     else if (may_split && plan_split(p, g, true, &pl.ps)) pl.kind = 18;
     else if (any && may_split && plan_split3(p, g, kSplit3Rest, &pl.ph) && (p.in_bf16 || pl.ph.us < 0.95 * generic_estimate(p))) pl.kind = 20;
+    // Larger launches go to the kernel without staging from those that read fp32 operands 4 bytes at a time or have few blocks
+    // (random layers of 1 .. 12 times the bound on its loads, time there / here, geometric mean):
+    //  - the generic kernel: 3.3 at any size measured (37 layers, 1.03 and more; 126 -> 144 on 12x93 at stride 2, g = 3,
+    //    N = 140 377 / 84 us);
+    //  - the staged kernel, 1x1 up to four times the bound: stride 2 2.2 (23 layers, two of them 2 and 4 % behind), stride 1 2.1
+    //    (30, likewise; 692 -> 24 on 21x21, N = 28 90 / 18.7, 700 -> 112 on 14x14, N = 10 14.6 / 11.5), except odd planes that
+    //    it stages as single rows: there it reads 16 bytes at a time.
+    // (3x3 layers stay: up to twice the bound 1.4, but a tenth of them behind.)
+    const bool single_rows = p.stride == 1 && p.H == 1 && p.W % 4 != 0 && g.CPG % 4 == 0;
+    const double more = pl.kind == 0 ? 12.0 : pl.kind == 16 && p.KH == 1 && !single_rows ? 4.0 : 0.0;
+    if (any && !p.in_bf16 && more > 0.0 && plan_unit(p, g, &pl.pu, more)) pl.kind = 19;
     return pl;
 }
 

@@ -218,7 +218,7 @@ hipError_t launchU_shape(const ConvParams &p, const TileUnit &t, hipStream_t s) 
 
 }  // namespace
 
-bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
+bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double more) {
     if (!p.wu || p.in_bf16 || (p.stride != 1 && p.stride != 2)) return false;
     const bool row = p.KH == 3;
     if (row ? p.pad != 1 || p.W < 3 : p.pad != 0) return false;
@@ -271,7 +271,7 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out) {
     t.per_xcd = (t.tiles + 7) / 8;
     const double loads = (double)tiles * units * (row ? 2 : 5);
     const bool wide = p.stride == 1 && (row ? p.W % 4 == 0 : (p.Hout * p.Wout) % 4 == 0);   // staged 16 bytes at a time
-    if (loads > (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
+    if (loads > more * (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
     if (units < (row || wide ? 6 : 4) && tiles > 4 * kNumCU) return false;
     if (row && p.stride == 1 && units < 9 && tiles > 8 * kNumCU) return false;
     if (row && p.stride == 2 && units < 9 && g.KPG > 16 && tiles > 12 * kNumCU) return false;

@@ -106,6 +106,24 @@ def test_large_launches_return_to_staging(gpu, s, kernel):
     assert err_metrics(y, ref, absum)["bound"] < (9 * s.Cin // s.groups + 17) * 2.0 ** -24, name
 
 
+@pytest.mark.parametrize("s,kernel", [
+    # (the bound on the loads, tiles x units x loads of a unit, is 200k, for 1x1 on whole quads of pixels at stride 1 180k)
+    (S(5, 256, 86, 86, 256, 3, 3, 2, 1, 16), "conv_mfma16u<"),    # generic, 222k
+    (S(46, 126, 12, 93, 60, 3, 3, 2, 1, 3), "conv_mfma16u<"),     # padded channels and filters, 321k
+    (S(190, 96, 27, 27, 40, 1, 1, 2, 0, 1), "conv_mfma16u<"),     # 1x1, stride 2, 210k
+    (S(40, 500, 28, 30, 36, 1, 1, 2, 0, 1), "conv_mfma16u<"),     # 252k
+    (S(10, 700, 14, 14, 112, 1, 1, 1, 0, 1), "conv_mfma16u<"),    # whole quads of pixels, 189k
+    (S(28, 692, 21, 21, 24, 1, 1, 1, 0, 1), "conv_mfma16u<"),     # odd planes, 340k
+    (S(1, 644, 25, 25, 477, 1, 1, 1, 0, 1), "conv_mfma16u<"),     # 258k
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
+def test_beyond_the_bound(gpu, s, kernel):
+    """Layers that the generic or the staged kernel would serve 4 bytes at a time."""
+    y, x, w, name = run_conv(gpu, s, seed=66)
+    assert name.startswith(kernel), name
+    ref, absum = oracle.conv2d_grouped(x, w, s.stride, s.pad, s.groups, return_abs=True, threads=8)
+    assert err_metrics(y, ref, absum)["bound"] < (s.KH * s.KW * s.Cin // s.groups + 17) * 2.0 ** -24, name
+
+
 @pytest.mark.parametrize("s", [S(2, 48, 9, 7, 40, 3, 3, 1, 1, 2), S(3, 40, 7, 7, 24, 1, 1, 2, 0, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_unit_kernel_epilogue_and_buffer_ends(gpu, s):
