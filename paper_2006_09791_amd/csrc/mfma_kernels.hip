@@ -824,11 +824,16 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     //  - the generic kernel: 3.3 at any size measured (37 layers, 1.03 and more; 126 -> 144 on 12x93 at stride 2, g = 3,
     //    N = 140 377 / 84 us);
     //  - the staged kernel, 1x1 up to four times the bound: stride 2 2.2 (23 layers, two of them 2 and 4 % behind), stride 1 2.1
-    //    (30, likewise; 692 -> 24 on 21x21, N = 28 90 / 18.7, 700 -> 112 on 14x14, N = 10 14.6 / 11.5), except odd planes that
-    //    it stages as single rows: there it reads 16 bytes at a time.
+    //    (30, likewise; 692 -> 24 on 21x21, N = 28 90 / 18.7, 700 -> 112 on 14x14, N = 10 14.6 / 11.5).  Odd planes handed over
+    //    as single rows it stages 16 bytes at a time where they fill its tiles; those stay while the reduction takes few
+    //    chunks, each with its barrier (five: 640 -> 108 on 6x5, N = 106 12.9 / 15.8; eight: 864 -> 100 on 5x5, N = 73
+    //    13.4 / 12.8).  Twenty and more, which is what few divisors of the channel count and large planes come to: 56 layers 1.15
+    //    and more, most of them 2 to 4 (1024 -> 530 on 13x13, N = 7, 64 chunks 69 / 31; 988 -> 64 on 7x11, N = 107, 247 chunks
+    //    121 / 27).
     // (3x3 layers stay: up to twice the bound 1.4, but a tenth of them behind.)
     const bool single_rows = p.stride == 1 && p.H == 1 && p.W % 4 != 0 && g.CPG % 4 == 0;
-    const double more = pl.kind == 0 ? 12.0 : pl.kind == 16 && p.KH == 1 && !single_rows ? 4.0 : 0.0;
+    const bool narrow = p.KH == 1 && (!single_rows || pl.t16.nchunks >= 20);
+    const double more = pl.kind == 0 ? 12.0 : pl.kind == 16 && narrow ? 4.0 : 0.0;
     if (any && !p.in_bf16 && more > 0.0 && plan_unit(p, g, &pl.pu, more)) pl.kind = 19;
     return pl;
 }

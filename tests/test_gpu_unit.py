@@ -115,6 +115,10 @@ def test_large_launches_return_to_staging(gpu, s, kernel):
     (S(10, 700, 14, 14, 112, 1, 1, 1, 0, 1), "conv_mfma16u<"),    # whole quads of pixels, 189k
     (S(28, 692, 21, 21, 24, 1, 1, 1, 0, 1), "conv_mfma16u<"),     # odd planes, 340k
     (S(1, 644, 25, 25, 477, 1, 1, 1, 0, 1), "conv_mfma16u<"),     # 258k
+    # odd planes that are staged as single rows: twenty chunks of the reduction, ten
+    (S(12, 640, 11, 11, 236, 1, 1, 1, 0, 1), "conv_mfma16u<"),
+    (S(164, 320, 11, 11, 32, 1, 1, 1, 0, 1), "conv_mfma16<"),
+    (S(12, 628, 6, 11, 544, 1, 1, 1, 0, 1), "conv_mfma16u<"),     # 157 chunks
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v)
 def test_beyond_the_bound(gpu, s, kernel):
     """Layers that the generic or the staged kernel would serve 4 bytes at a time."""
