@@ -11,9 +11,15 @@ namespace gspc {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// n / d with mul = floor(2^32 / d) + 1 (mul = 0 encodes d = 1); exact while n * d < 2^32.
-__device__ __forceinline__ unsigned fast_div(unsigned n, unsigned mul) {
-    return mul ? __umulhi(n, mul) : n;
+// n / d with mul = div_magic(d) = floor((2^32 - 1) / d): exact while (n + 1) * d <= 2^32, and at most one too low for any
+// larger n below 2^32 - 1.  Without a special case for d = 1: its branch (or select) stood in every kernel's index arithmetic
+// before the first load.
+__device__ __forceinline__ unsigned fast_div(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
+
+// The same for all n below 2^32 - 1.
+__device__ __forceinline__ unsigned fast_div_any(unsigned n, unsigned d, unsigned mul) {
+    const unsigned q = fast_div(n, mul);
+    return n - q * d >= d ? q + 1 : q;
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -73,7 +79,7 @@ inline bool fills_image_tiles(const ConvParams &p, int mtiles) {
            (long)((p.N + 1) / 2) * mtiles * p.groups < 3 * kNumCU / 2;
 }
 
-inline unsigned div_magic(int d) { return d > 1 ? (unsigned)(0xffffffffu / (unsigned)d + 1u) : 0u; }
+inline unsigned div_magic(unsigned d) { return 0xffffffffu / d; }
 
 // Splits the output into NB images x TH rows per block for a pixel capacity PB.
 inline bool split_pixels(const ConvParams &p, int PB, int *NB, int *TH) {

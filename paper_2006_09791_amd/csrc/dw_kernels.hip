@@ -94,7 +94,8 @@ __global__ __launch_bounds__(256) void conv_dw_wave(ConvParams p, TileW t) {
         const int q = lane + 64 * j;
         pin[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, q * 4 < Q::IN ? gbase + q * 16 : kOob, 0, 0));
     }
-    // ---- the lane's plane, rows and weights ----
+    // ---- the lane's plane, rows and weights (not in front of the input's loads) ----
+    __builtin_amdgcn_sched_barrier(0);
     const bool active = lane < Q::G * Q::LP;
     const int la = active ? lane : 0;
     const int pl = Q::LP == 1 ? la : la / Q::LP;
@@ -326,7 +327,9 @@ __global__ __launch_bounds__(256) void conv_dw_band(ConvParams p, TileW t) {
         const int q = lane + 64 * j;
         pin[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, q * 4 < Q::IN ? gbase + q * 16 : kOob, 0, 0));
     }
-    // ---- weights: uniform over the wave ----
+    // ---- weights: uniform over the wave (requested after the input: moved in front of it they cost 12 %, 448 channels on
+    // 56x56, N = 6 14.1 / 15.8 us) ----
+    __builtin_amdgcn_sched_barrier(0);
     float w[9];
     {
         const unsigned c = plane - fast_div(plane, t.m_C) * p.Cin;
@@ -514,7 +517,7 @@ __device__ __forceinline__ void rows_body(const ConvParams &p, const TileRows &t
     float *wl = reg + t.region - t.G * 9;                             // (MULTI) the planes' weights
     if constexpr (MULTI) {
         for (unsigned i = lane; i < np * 9; i += 64) {
-            const unsigned pl = fast_div(i, 0x1c71c71du), pg = plane + pl;   // i / 9, exact for i < 2^16
+            const unsigned pl = fast_div(i, 0x1c71c71cu), pg = plane + pl;   // i / 9, exact for i < 2^16
             wl[i] = p.wd[((pg - fast_div(pg, t.m_C) * p.Cin) * 9 + (i - pl * 9)) * p.KPGd];
         }
     } else {

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, 2) void conv_dwpw(DwPwParams p, TileP t) {
     {
         const __amdgpu_buffer_rsrc_t rwd = make_rsrc(p.wdw, t.wdw_bytes);
         for (int i = tid; i < p.C * 9; i += NT) {
-            const int c = fast_div(i, 0x1c71c71du), k = i - c * 9;   // i / 9, exact for i < 2^16
+            const int c = fast_div(i, 0x1c71c71cu), k = i - c * 9;   // i / 9, exact for i < 2^16
             wl[c * 12 + k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rwd, (unsigned)i * (p.kpgd * 4), 0, 0));
         }
         const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wpw, t.wpw_bytes);

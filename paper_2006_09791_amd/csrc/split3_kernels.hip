@@ -32,7 +32,7 @@ struct TileH {
     int oc_blocks, px_blocks;
     int LW, PW, ROWS, PLANE;      // row pitch in units, column pairs per row, rows allocated, units per 8 channels
     unsigned npix, HWo;
-    unsigned m_HWo, m_Wout, m_PW, m_H2;
+    unsigned m_HWo, m_Wout, m_PW, m_H2, m_ocb;
     unsigned x_bytes, w_bytes, y_bytes;
 };
 static_assert(sizeof(TileH) <= sizeof(((Split3Plan *)0)->data), "plan storage too small");
@@ -56,10 +56,10 @@ __global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p
     const unsigned per = gridDim.x >> 3;
     const unsigned id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (id >= (unsigned)(t.px_blocks * t.oc_blocks)) return;
-    const unsigned pt = id / (unsigned)t.oc_blocks, ob = id - pt * t.oc_blocks;
+    const unsigned pt = fast_div_any(id, t.oc_blocks, t.m_ocb), ob = id - pt * t.oc_blocks;
     const unsigned j = blockIdx.y;
     const unsigned q0 = pt * PB;
-    const unsigned n0 = q0 / t.HWo, r0 = q0 - n0 * t.HWo;
+    const unsigned n0 = fast_div_any(q0, t.HWo, t.m_HWo), r0 = q0 - n0 * t.HWo;
     const unsigned H2 = p.H + 2, HW = p.H * p.W;
     const unsigned P0 = fast_div(r0, t.m_Wout) * S;              // first padded row, relative to image n0
     // pixel q0 + d: its image relative to n0, row and column
@@ -501,6 +501,7 @@ bool planH_cfg(const ConvParams &p, const PackGeom &g, const CfgH &c, int cgs, T
     t.LW = p.W + 2;
     t.PW = (p.W + 1) / 2;
     t.PLANE = t.ROWS * t.LW;
+    t.m_ocb = div_magic(t.oc_blocks);
     t.m_HWo = div_magic(t.HWo);
     t.m_Wout = div_magic(p.Wout);
     t.m_PW = div_magic(t.PW);

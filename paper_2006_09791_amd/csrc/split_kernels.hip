@@ -31,7 +31,7 @@ struct TileSplit {
     int oc_blocks, px_blocks;
     int pre;                      // fp32: the packed filters are split
     unsigned HW, npix;            // plane size, N * HW
-    unsigned m_HW;                // reciprocal for offsets inside a block (below HW + block pixels)
+    unsigned m_HW, m_ocb;
     unsigned x_bytes, w_bytes, y_bytes;
 };
 static_assert(sizeof(TileSplit) <= sizeof(((SplitPlan *)0)->data), "plan storage too small");
@@ -62,9 +62,9 @@ __global__ __launch_bounds__(64 * WM * WP, WM * WP / 2) void conv_mfma16s(ConvPa
     const unsigned per = gridDim.x >> 3;
     const unsigned id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (id >= (unsigned)(t.px_blocks * t.oc_blocks)) return;
-    const unsigned pt = id / (unsigned)t.oc_blocks, ob = id - pt * t.oc_blocks;
+    const unsigned pt = fast_div_any(id, t.oc_blocks, t.m_ocb), ob = id - pt * t.oc_blocks;
     const unsigned j = blockIdx.y;
-    const unsigned q0 = pt * PB, n0 = q0 / t.HW, r0 = q0 - n0 * t.HW;
+    const unsigned q0 = pt * PB, n0 = fast_div_any(q0, t.HW, t.m_HW), r0 = q0 - n0 * t.HW;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.x, t.x_bytes);
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.ws, t.w_bytes);
@@ -423,6 +423,7 @@ bool plan_split(const ConvParams &p, const PackGeom &g, bool any_size, SplitPlan
         if (best && cost >= best) continue;
         best = cost;
         t.oc_blocks = ocb;
+        t.m_ocb = div_magic(ocb);
         t.px_blocks = (int)pxb;
         out->inst = i;
         std::memcpy(out->data, &t, sizeof(t));

@@ -44,15 +44,10 @@ struct TileUnit {
     int H, W, Wout;
     unsigned HWo, npix;              // Hout * Wout, N * HWo
     unsigned tiles, per_xcd, px_tiles;   // tiles of the launch, of an XCD's blocks, per filter tile
-    unsigned m_HWo, m_Wout, m_px, m_mt;  // reciprocals (unit_recip)
+    unsigned m_HWo, m_Wout, m_px, m_mt;  // reciprocals (div_magic)
     int relu;
 };
 static_assert(sizeof(TileUnit) <= sizeof(((UnitPlan *)0)->data), "plan storage too small");
-
-// n / d with mul = unit_recip(d), exact while (n + 1) * d <= 2^32 and at most one too low beyond (up to n = 2^32 / 2); no
-// branch for d = 1, which would hold the loads behind it back.
-inline unsigned unit_recip(unsigned d) { return 0xffffffffu / d; }
-__device__ __forceinline__ unsigned unit_div(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
 
 // SHARE: two or three waves share a channel block (t.parts).
 template <int NW, int KH, int S, bool SHARE>
@@ -69,7 +64,7 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     // of the eight level-2 caches fetch a filter tile.
     // (Up to seven blocks have no tile: they read and store nothing, but run along.)
     const unsigned id = (blockIdx.x & 7) * t.per_xcd + (blockIdx.x >> 3);
-    const unsigned ft = unit_div(id, t.m_px), px = id - ft * t.px_tiles, j = unit_div(ft, t.m_mt), mt = ft - j * t.mtiles;
+    const unsigned ft = fast_div(id, t.m_px), px = id - ft * t.px_tiles, j = fast_div(ft, t.m_mt), mt = ft - j * t.mtiles;
     const unsigned HW = t.H * t.W;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(t.x, t.x_bytes);
@@ -106,13 +101,13 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
 
     // ---- this lane's pixel ------------------------------------------------------------------------
     // (the tile's first pixel in scalar registers; a tile spans images where planes are small)
-    unsigned n0 = unit_div(px * 16, t.m_HWo), r0 = px * 16 - n0 * t.HWo;
+    unsigned n0 = fast_div(px * 16, t.m_HWo), r0 = px * 16 - n0 * t.HWo;
     const bool low = r0 >= t.HWo;
     n0 += low ? 1 : 0;
     r0 -= low ? t.HWo : 0;
-    const unsigned dn = unit_div(r0 + li, t.m_HWo), n = n0 + dn, rem = r0 + li - dn * t.HWo;
+    const unsigned dn = fast_div(r0 + li, t.m_HWo), n = n0 + dn, rem = r0 + li - dn * t.HWo;
     const bool live = px * 16 + li < t.npix && id < t.tiles;
-    const unsigned oh = unit_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
+    const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
     const int ih0 = (int)oh * S - (ROW ? 1 : 0), iw0 = (int)ow * S - (ROW ? 1 : 0);
     // 3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
     // place up (down) and a zero takes the place of the column outside
@@ -239,11 +234,11 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double mor
     t.Wout = p.Wout;
     t.HWo = p.Hout * p.Wout;
     t.npix = (unsigned)npix;
-    t.m_HWo = unit_recip(t.HWo);
-    t.m_Wout = unit_recip(p.Wout);
+    t.m_HWo = div_magic(t.HWo);
+    t.m_Wout = div_magic(p.Wout);
     t.px_tiles = (t.npix + 15) / 16;
-    t.m_px = unit_recip(t.px_tiles);
-    t.m_mt = unit_recip(t.mtiles);
+    t.m_px = div_magic(t.px_tiles);
+    t.m_mt = div_magic(t.mtiles);
     t.x_bytes = (unsigned)xb;
     t.w_bytes = (unsigned)g.unit_bytes;
     // Where it pays (layers of the WRN-, ResNet-34- and MobileNet-shaped networks at N = 1 .. 64, us, conv_mfma16 with

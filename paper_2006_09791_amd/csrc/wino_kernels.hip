@@ -51,11 +51,6 @@ struct TileX {
 
 constexpr int kTmaxX = 4;
 
-// n / d with mul = recip(d), exact while (n + 1) * d <= 2^32.  (fast_div's branch for d = 1 would split the arithmetic
-// before a block's first load into a dozen pieces.)
-inline unsigned recip(unsigned d) { return 0xffffffffu / d; }
-__device__ __forceinline__ unsigned div_recip(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
-
 template <int MI, int NI, int WM, int WP, int CKB, bool RT>
 __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX t) {
     static_assert(!RT || (MI == 1 && NI == 1), "the register transform serves one product tile per wave");
@@ -71,9 +66,9 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WP, wp = wave % WP;
-    const unsigned ib = div_recip(blockIdx.x, t.m_rowb);
+    const unsigned ib = fast_div(blockIdx.x, t.m_rowb);
     const int rb = blockIdx.x - ib * t.row_blocks;
-    const unsigned j = div_recip(blockIdx.y, t.m_ocb);
+    const unsigned j = fast_div(blockIdx.y, t.m_ocb);
     const int ob = blockIdx.y - j * t.oc_blocks;
     const int n0 = ib * t.NB, tr0 = rb * t.TR, ih0 = 2 * tr0 - 1;
     const unsigned HW = p.H * p.W;
@@ -95,8 +90,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
         xoff[k] = kOob;
         xlds[k] = spare;
         if (k < t.xslots && task < t.tasks && colv * vw < p.W) {
-            const int cimg = div_recip(task, t.m_IHt), r = task - cimg * t.IHt;
-            const int c = div_recip(cimg, t.m_NB), img = cimg - c * t.NB;
+            const int cimg = fast_div(task, t.m_IHt), r = task - cimg * t.IHt;
+            const int c = fast_div(cimg, t.m_NB), img = cimg - c * t.NB;
             const int ih = ih0 + r, n = n0 + img;
             // rows above and below the image load as zero: the halo rows are rewritten with every chunk
             if (n < p.N && ih >= 0 && ih < p.H)
@@ -134,8 +129,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
     int pbase;
     {
         const int qq = tq < t.P ? tq : 0;
-        const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
-        const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
+        const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
+        const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
         pbase = img * t.IMG + 2 * tr * t.LW + (t.XO - 1) + 2 * tc;
     }
 
@@ -146,8 +141,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
         const int rows = CK * t.NB * t.IHt, right = t.XO + p.W;
         for (int i = tid; i < (RT ? 2 : 1) * rows; i += NT) {
             const int b = i >= rows, ii = i - b * rows;
-            const int cimg = div_recip(ii, t.m_IHt), r = ii - cimg * t.IHt;
-            const int c = div_recip(cimg, t.m_NB), img = cimg - c * t.NB;
+            const int cimg = fast_div(ii, t.m_IHt), r = ii - cimg * t.IHt;
+            const int c = fast_div(cimg, t.m_NB), img = cimg - c * t.NB;
             float *row = raw + b * t.raw_floats + c * t.PLANE + img * t.IMG + r * t.LW;
             for (int x = 0; x < t.XO; ++x) row[x] = 0.f;
             for (int x = right; x < t.LW; ++x) row[x] = 0.f;
@@ -174,8 +169,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
     auto out_at = [&](int ni) -> Out {
         const int q = (wp * NI + ni) * 16 + (lane & 15);
         const int qq = q < t.P ? q : 0;
-        const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
-        const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
+        const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
+        const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
         const int n = n0 + img, oh = 2 * (tr0 + tr), ow = 2 * tc;
         const bool ok = q < t.P && n < p.N && oh < p.H;
         const unsigned o0 = ok ? (((unsigned)n * p.Cout + j * p.KPG + 4 * (lane >> 4)) * HW + oh * p.W + ow) * 4 : kOob;
@@ -207,8 +202,8 @@ __global__ __launch_bounds__(64 * WM * WP, 2) void conv_wino(ConvParams p, TileX
         {
             const int q = wp * 16 + (lane & 15);
             const int qq = q < t.P ? q : 0;
-            const int img = div_recip(qq, t.m_tpi), rem = qq - img * t.tpi;
-            const int tr = div_recip(rem, t.m_TC), tc = rem - tr * t.TC;
+            const int img = fast_div(qq, t.m_tpi), rem = qq - img * t.tpi;
+            const int tr = fast_div(rem, t.m_TC), tc = rem - tr * t.TC;
             pbase_r = (lane >> 4) * t.PLANE + img * t.IMG + 2 * tr * t.LW + (t.XO - 1) + 2 * tc;
         }
         f32x4 ub[2][CKB][4];   // U of this chunk and of the next one
@@ -516,12 +511,12 @@ bool planx_cfg(const ConvParams &p, const PackGeom &g, const CfgX &c, int ckb, b
     t.oc_blocks = (t.mtiles + MIWM - 1) / MIWM;
     t.wodd = p.W % 2;
     t.rt = rt;
-    t.m_IHt = recip(t.IHt);
-    t.m_NB = recip(t.NB);
-    t.m_tpi = recip(t.tpi);
-    t.m_TC = recip(t.TC);
-    t.m_rowb = recip(t.row_blocks);
-    t.m_ocb = recip(t.oc_blocks);
+    t.m_IHt = div_magic(t.IHt);
+    t.m_NB = div_magic(t.NB);
+    t.m_tpi = div_magic(t.tpi);
+    t.m_TC = div_magic(t.TC);
+    t.m_rowb = div_magic(t.row_blocks);
+    t.m_ocb = div_magic(t.oc_blocks);
     const double xb = (double)p.N * p.Cin * p.H * p.W * 4, yb = (double)p.N * p.Cout * p.H * p.W * 4;
     const double ub = (double)p.groups * t.cblks * t.mtiles * 4096;
     if (xb >= (double)kOob || yb >= (double)kOob || ub >= (double)kOob) return false;
