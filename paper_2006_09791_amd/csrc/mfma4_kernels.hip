@@ -32,8 +32,10 @@ constexpr int kTmax4 = 12;   // staged rows per thread
 
 // Block = 4 waves; a wave owns NTILE runs of 64 pixels and all KPG = 4*MT
 // filters of the group.  Grid: x = (image block, row block), y = group.
+// (Waves per SIMD: staging the input takes 72 registers; with four more for an accumulator tile or two the compiler would go
+// past a step of eight and lose one of seven or six waves: 16 -> 16 on 77x77, g = 4, N = 155 61 / 65 us.)
 template <int CPG, int MT, int NTILE, int S, typename TIN>
-__global__ __launch_bounds__(256) void conv_mfma4r(ConvParams p, Tile4 t) {
+__global__ __launch_bounds__(256, NTILE * MT == 1 ? 7 : NTILE * MT == 2 ? 6 : 1) void conv_mfma4r(ConvParams p, Tile4 t) {
     constexpr int NT = 256, TAPS = 9, ES = (int)sizeof(TIN);
     extern __shared__ f32x4 smem4[];
     float *xs = reinterpret_cast<float *>(smem4);
