@@ -295,6 +295,7 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
     // this lane's pixel; the 4*(lane/16) part already sits in ooff.
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
     const unsigned oc0 = ob * MI * 16;
+    f32x4 res[MI][NI];   // (!PERSIST)
     auto epilogue = [&](const unsigned (&ooff)[NI]) __attribute__((always_inline)) {
     if (p.res) {
         const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res, t.y_bytes);
@@ -304,8 +305,9 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    acc[mi][ni][r] += __uint_as_float(
-                        __builtin_amdgcn_raw_buffer_load_b32(rr, ooff[ni], (oc0 + mi * 16 + r) * HWo * 4, 0));
+                    acc[mi][ni][r] += !PERSIST ? res[mi][ni][r]
+                                               : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                                     rr, ooff[ni], (oc0 + mi * 16 + r) * HWo * 4, 0));
     }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -319,6 +321,19 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
                                                       (oc0 + mi * 16 + r) * HWo * 4, 0);
             }
     };
+
+    // The residual of a block's only tile is requested before the products: after them its trip to memory is one more link
+    // of the chain (WRN-40-2-style chain, g = 2, N = 64 328.2 -> 326.4 us with five such layers).
+    if (!PERSIST && p.res) {
+        const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res, t.y_bytes);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    res[mi][ni][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rr, ooff[ni], (oc0 + mi * 16 + r) * HWo * 4, 0));
+    }
 
     steady();
 #ifdef GSPC_PHASE_TIMING
