@@ -24,6 +24,12 @@
 
 namespace gspc {
 
+// n / d with mul = floor(2^32 / d) + 1, 0 for d = 1, while n * d < 2^32.  In the wave kernels the branch (or select) keeps the loads of the
+// weights behind those of the input: with fast_div the compiler moves them in front, 448 channels on 56x56, N = 6 14.6 / 15.8 us
+// (14.9 with a scheduling barrier between them).
+__device__ __forceinline__ unsigned div_in_order(unsigned n, unsigned mul) { return mul ? __umulhi(n, mul) : n; }
+inline unsigned magic_in_order(unsigned d) { return d > 1 ? 0xffffffffu / d + 1u : 0u; }
+
 // ---- whole planes per wavefront -------------------------------------------------------------
 // For the square planes of the network tails (28x28, 14x14, 7x7) a wavefront takes G consecutive
 // planes by itself: their floats are one contiguous, 16-byte aligned piece of the input and their
@@ -94,8 +100,7 @@ __global__ __launch_bounds__(256) void conv_dw_wave(ConvParams p, TileW t) {
         const int q = lane + 64 * j;
         pin[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, q * 4 < Q::IN ? gbase + q * 16 : kOob, 0, 0));
     }
-    // ---- the lane's plane, rows and weights (not in front of the input's loads) ----
-    __builtin_amdgcn_sched_barrier(0);
+    // ---- the lane's plane, rows and weights ----
     const bool active = lane < Q::G * Q::LP;
     const int la = active ? lane : 0;
     const int pl = Q::LP == 1 ? la : la / Q::LP;
@@ -110,14 +115,14 @@ __global__ __launch_bounds__(256) void conv_dw_wave(ConvParams p, TileW t) {
                 const int wp = i / 9, k = i - wp * 9;
                 unsigned pg = chunk * Q::G + wp;
                 pg = pg < t.planes ? pg : t.planes - 1;
-                const unsigned c = pg - fast_div(pg, t.m_C) * p.Cin;
+                const unsigned c = pg - div_in_order(pg, t.m_C) * p.Cin;
                 wts[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ((c * 9 + k) * p.KPGd) * 4, 0, 0));
             }
         }
     } else {
         unsigned pg = chunk * Q::G + pl;
         pg = pg < t.planes ? pg : t.planes - 1;
-        const unsigned c = pg - fast_div(pg, t.m_C) * p.Cin;
+        const unsigned c = pg - div_in_order(pg, t.m_C) * p.Cin;
 #pragma unroll
         for (int k = 0; k < 9; ++k)
             w[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, ((c * 9 + k) * p.KPGd) * 4, 0, 0));
@@ -246,7 +251,7 @@ bool plan_dw_wave_inst(const ConvParams &p, DwPlan *out) {
     TileW t{};
     t.planes = (unsigned)planes;
     t.chunks = (unsigned)((t.planes + Q::G - 1) / Q::G);
-    t.m_C = div_magic(p.Cin);
+    t.m_C = magic_in_order(p.Cin);
     t.x_bytes = (unsigned)xb;
     t.y_bytes = (unsigned)yb;
     t.w_bytes = (unsigned)wb;
@@ -327,12 +332,10 @@ __global__ __launch_bounds__(256) void conv_dw_band(ConvParams p, TileW t) {
         const int q = lane + 64 * j;
         pin[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, q * 4 < Q::IN ? gbase + q * 16 : kOob, 0, 0));
     }
-    // ---- weights: uniform over the wave (requested after the input: moved in front of it they cost 12 %, 448 channels on
-    // 56x56, N = 6 14.1 / 15.8 us) ----
-    __builtin_amdgcn_sched_barrier(0);
+    // ---- weights: uniform over the wave ----
     float w[9];
     {
-        const unsigned c = plane - fast_div(plane, t.m_C) * p.Cin;
+        const unsigned c = plane - div_in_order(plane, t.m_C) * p.Cin;
 #pragma unroll
         for (int k = 0; k < 9; ++k) w[k] = p.wd[(c * 9 + k) * p.KPGd];
     }
@@ -436,7 +439,7 @@ bool plan_dw_band(const ConvParams &p, DwPlan *out) {
         TileW t{};
         t.planes = (unsigned)planes;
         t.chunks = (unsigned)chunks;
-        t.m_C = div_magic(p.Cin);
+        t.m_C = magic_in_order(p.Cin);
         t.x_bytes = (unsigned)xb;
         t.y_bytes = (unsigned)yb;
         t.w_bytes = (unsigned)wb;
