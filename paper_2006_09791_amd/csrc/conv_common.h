@@ -5,30 +5,17 @@
 #include <set>
 #include <string>
 
+#include "divide.h"
 #include "gspc_internal.h"
 
 namespace gspc {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// n / d with mul = div_magic(d) = floor((2^32 - 1) / d): exact while (n + 1) * d <= 2^32, and at most one too low for any
-// larger n below 2^32 - 1.  Without a special case for d = 1: its branch (or select) stood in every kernel's index arithmetic
-// before the first load.
-__device__ __forceinline__ unsigned fast_div(unsigned n, unsigned mul) { return __umulhi(n + 1, mul); }
-
-// The same for all n below 2^32 - 1.
-__device__ __forceinline__ unsigned fast_div_any(unsigned n, unsigned d, unsigned mul) {
-    const unsigned q = fast_div(n, mul);
-    return n - q * d >= d ? q + 1 : q;
-}
-
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Buffer descriptors: raw (stride 0) buffers whose out-of-range loads return
-// zero and whose out-of-range stores are dropped by the hardware, so invalid
-// lanes are given the byte offset kOob instead of being branched around.
-constexpr unsigned kOob = 0xffffff00u;
+// Buffer descriptors: raw (stride 0) buffers (see kOob).
 constexpr int kRsrcFlags = 0x00020000;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes) {
@@ -78,8 +65,6 @@ inline bool fills_image_tiles(const ConvParams &p, int mtiles) {
     return p.KH == 1 && p.stride == 1 && p.pad == 0 && p.H == 1 && p.W % 4 != 0 && p.W >= 40 && p.W < 64 && p.CPG % 4 == 0 &&
            (long)((p.N + 1) / 2) * mtiles * p.groups < 3 * kNumCU / 2;
 }
-
-inline unsigned div_magic(unsigned d) { return 0xffffffffu / d; }
 
 // Splits the output into NB images x TH rows per block for a pixel capacity PB.
 inline bool split_pixels(const ConvParams &p, int PB, int *NB, int *TH) {

@@ -1,0 +1,86 @@
+// What a block of conv_mfma16u works on and which bytes its lanes read.  Host and device, without a header of HIP: a test walks
+// whole launches with the host's compiler and checks every offset against its buffer.
+#pragma once
+
+#include "divide.h"
+
+namespace gspc {
+
+// What the kernel reads, in one piece: the scalar loads of its arguments are the first link of the chain, and a second
+// round of them another (so nothing is asked of the launch, such as the grid's size, that is not in here).
+struct TileUnit {
+    const float *x, *w;
+    float *y;
+    const float *res;
+    unsigned x_bytes, w_bytes;
+    int blocks, parts;               // channel blocks: four channels, 1x1: sixteen; waves that share one (3x3)
+    int mtiles, CPG, KPG, Cin, Cout; // mtiles: filter tiles per group
+    int H, W, Wout;
+    unsigned HWo, npix;              // Hout * Wout, N * HWo
+    unsigned tiles, per_xcd, px_tiles;   // tiles of the launch, of an XCD's blocks, per filter tile
+    unsigned m_HWo, m_Wout, m_px, m_mt;  // reciprocals (div_magic)
+    int relu;
+};
+
+// The geometry of a layer and its launch: K x K filters at stride S, channel blocks and filter tiles as packed.
+inline void unit_layer(TileUnit &t, int N, int Cin, int H, int W, int Cout, int groups, int K, int Hout, int Wout, int mtiles) {
+    t.CPG = Cin / groups;
+    t.KPG = Cout / groups;
+    t.blocks = K == 3 ? (t.CPG + 3) / 4 : (t.CPG + 15) / 16;
+    t.mtiles = mtiles;
+    t.Cin = Cin;
+    t.Cout = Cout;
+    t.H = H;
+    t.W = W;
+    t.Wout = Wout;
+    t.HWo = Hout * Wout;
+    t.npix = (unsigned)N * t.HWo;
+    t.m_HWo = div_magic(t.HWo);
+    t.m_Wout = div_magic(Wout);
+    t.px_tiles = (t.npix + 15) / 16;
+    t.m_px = div_magic(t.px_tiles);
+    t.m_mt = div_magic(mtiles);
+    t.tiles = t.px_tiles * mtiles * groups;
+    t.per_xcd = (t.tiles + 7) / 8;
+    t.x_bytes = (unsigned)N * Cin * H * W * 4;
+}
+
+// Tiles are numbered pixel tile innermost, and the blocks of one XCD (block % 8) take consecutive ones, so that few
+// of the eight level-2 caches fetch a filter tile.  Up to seven blocks have no tile: they run along on the last one's operands and
+// store nothing.  (With tile numbers past the last one their filters lay up to seven groups behind the buffer.)
+struct UnitTileAt {
+    unsigned px, mt, j;              // pixel tile, filter tile of the group, group
+    bool live;
+};
+GSPC_HD UnitTileAt unit_tile(const TileUnit &t, unsigned block) {
+    const unsigned at = (block & 7) * t.per_xcd + (block >> 3), id = at < t.tiles ? at : t.tiles - 1;
+    const unsigned ft = fast_div(id, t.m_px), px = id - ft * t.px_tiles, j = fast_div(ft, t.m_mt);
+    return {px, ft - j * t.mtiles, j, at < t.tiles};
+}
+
+// A wave's channel blocks are first, first + waves ..; where there are twice as many waves as blocks (3x3, t.parts) two or three
+// waves share one, kernel row by kernel row (bits of rows).
+struct UnitWave {
+    int first, rows;
+};
+GSPC_HD UnitWave unit_share(const TileUnit &t, int wave) {
+    const int part = wave >= 2 * t.blocks ? 2 : wave >= t.blocks ? 1 : 0;
+    return {part < t.parts ? wave - part * t.blocks : t.blocks, t.parts == 3 ? 1 << part : part ? 4 : 3};
+}
+
+// Weights: [g][channel block][filter tile]([kernel row])[64 lanes][3 or 4], KR kernel rows of WLANE bytes per lane.  Scalar offset
+// of the tile's first channel block, and from there to the next one; then the lane's offset in a kernel row that its wave multiplies.
+template <int KR, unsigned WLANE>
+GSPC_HD unsigned unit_w_base(const TileUnit &t, const UnitTileAt &a) {
+    return (a.j * t.blocks * t.mtiles + a.mt) * (KR * 64 * WLANE);
+}
+template <int KR, unsigned WLANE>
+GSPC_HD unsigned unit_w_step(const TileUnit &t) {
+    return t.mtiles * (KR * 64 * WLANE);
+}
+template <unsigned WLANE>
+GSPC_HD unsigned unit_w_lane(const TileUnit &t, int u, bool on, unsigned lane) {
+    return (u < t.blocks ? lane * WLANE : kOob) | (on ? 0u : kOob);
+}
+
+}  // namespace gspc

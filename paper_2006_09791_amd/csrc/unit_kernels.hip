@@ -26,27 +26,13 @@
 #include <cstring>
 
 #include "conv_common.h"
+#include "unit_index.h"
 
 namespace gspc {
 
 typedef float f32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
 
-// What the kernel reads, in one piece: the scalar loads of its arguments are the first link of the chain, and a second
-// round of them another (so nothing is asked of the launch, such as the grid's size, that is not in here).
-struct TileUnit {
-    const float *x, *w;
-    float *y;
-    const float *res;
-    unsigned x_bytes, w_bytes;
-    int blocks, parts;               // channel blocks: four channels, 1x1: sixteen; waves that share one (3x3)
-    int mtiles, CPG, KPG, Cin, Cout; // mtiles: filter tiles per group
-    int H, W, Wout;
-    unsigned HWo, npix;              // Hout * Wout, N * HWo
-    unsigned tiles, per_xcd, px_tiles;   // tiles of the launch, of an XCD's blocks, per filter tile
-    unsigned m_HWo, m_Wout, m_px, m_mt;  // reciprocals (div_magic)
-    int relu;
-};
 static_assert(sizeof(TileUnit) <= sizeof(((UnitPlan *)0)->data), "plan storage too small");
 
 // SHARE: two or three waves share a channel block (t.parts).
@@ -60,40 +46,36 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Tiles are numbered pixel tile innermost, and the blocks of one XCD (block % 8) take consecutive ones, so that few
-    // of the eight level-2 caches fetch a filter tile.
-    // (Up to seven blocks have no tile: they read and store nothing, but run along.)
-    const unsigned id = (blockIdx.x & 7) * t.per_xcd + (blockIdx.x >> 3);
-    const unsigned ft = fast_div(id, t.m_px), px = id - ft * t.px_tiles, j = fast_div(ft, t.m_mt), mt = ft - j * t.mtiles;
+    const UnitTileAt tile = unit_tile(t, blockIdx.x);
+    const unsigned px = tile.px, mt = tile.mt, j = tile.j;
     const unsigned HW = t.H * t.W;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(t.x, t.x_bytes);
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(t.w, t.w_bytes);
 
-    // The wave's channel blocks are first, first + NW ..; where there are twice as many waves as blocks (3x3) two or three
-    // waves share one, kernel row by kernel row.
     int first = wave, rows = 7;
     if constexpr (SHARE) {
-        const int part = wave >= 2 * t.blocks ? 2 : wave >= t.blocks ? 1 : 0;
-        first = part < t.parts ? wave - part * t.blocks : t.blocks;
-        rows = t.parts == 3 ? 1 << part : part ? 4 : 3;
+        const UnitWave shared = unit_share(t, wave);
+        first = shared.first;
+        rows = shared.rows;
     }
-    const auto off_row = [&](int k) -> unsigned { return !SHARE || rows >> k & 1 ? 0u : kOob; };   // (an address with these bits set is out of range)
+    const auto row_on = [&](int k) { return !SHARE || (rows >> k & 1); };
+    const auto off_row = [&](int k) -> unsigned { return row_on(k) ? 0u : kOob; };   // (an address with these bits set is out of range)
 
-    // weights: [g][channel block][filter tile]([kernel row])[64 lanes][3 or 4].  (They do not wait for the pixel arithmetic.)
-    constexpr unsigned WLANE = ROW ? 12 : 16, WTILE = KR * 64 * WLANE;
+    // ---- weights (they do not wait for the pixel arithmetic) ---------------------------------------
+    constexpr unsigned WLANE = ROW ? 12 : 16;
     u32x4 wv[UB][KR];
-    const unsigned wstep = t.mtiles * WTILE, wbase = (j * t.blocks * t.mtiles + mt) * WTILE;
+    const unsigned wstep = unit_w_step<KR, WLANE>(t), wbase = unit_w_base<KR, WLANE>(t, tile);
     auto fetch_w = [&](int u, int s) __attribute__((always_inline)) {
-        const unsigned vo = u < t.blocks ? lane * WLANE : kOob, so = wbase + u * wstep;
-        if constexpr (ROW) {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(rw, vo | off_row(k), so + k * (64 * WLANE), 0);
+        for (int k = 0; k < KR; ++k) {
+            const unsigned vo = unit_w_lane<WLANE>(t, u, row_on(k), lane), so = wbase + u * wstep + k * (64 * WLANE);
+            if constexpr (ROW) {
+                const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(rw, vo, so, 0);
                 wv[s][k] = u32x4{v.x, v.y, v.z, 0u};
+            } else {
+                wv[s][k] = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, so, 0);
             }
-        } else {
-            wv[s][0] = __builtin_amdgcn_raw_buffer_load_b128(rw, vo, so, 0);
         }
     };
 #pragma unroll
@@ -106,7 +88,7 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     n0 += low ? 1 : 0;
     r0 -= low ? t.HWo : 0;
     const unsigned dn = fast_div(r0 + li, t.m_HWo), n = n0 + dn, rem = r0 + li - dn * t.HWo;
-    const bool live = px * 16 + li < t.npix && id < t.tiles;
+    const bool live = px * 16 + li < t.npix && tile.live;
     const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
     const int ih0 = (int)oh * S - (ROW ? 1 : 0), iw0 = (int)ow * S - (ROW ? 1 : 0);
     // 3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
@@ -221,25 +203,12 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double mor
     const double xb = (double)p.N * p.Cin * p.H * p.W * 4;
     if (xb >= (double)kOob || npix >= 1e6 || (double)g.unit_bytes >= (double)kOob) return false;
     if ((double)p.Hout * p.Wout * (p.Hout * p.Wout + 16.0) > 4294967296.0) return false;
+    const long px_tiles = ((long)npix + 15) / 16, tiles = px_tiles * g.mtiles * p.groups;
+    if ((double)(tiles + 8) * px_tiles >= 4294967296.0 || (double)(g.mtiles * (double)p.groups + 1) * g.mtiles >= 4294967296.0)
+        return false;
     TileUnit t{};
-    t.blocks = row ? g.CPGp / 4 : (g.CPGp + 15) / 16;
+    unit_layer(t, p.N, p.Cin, p.H, p.W, p.Cout, p.groups, p.KH, p.Hout, p.Wout, g.mtiles);
     const int units = row ? 3 * t.blocks : t.blocks;     // of the reduction in the rules below: 3x3, a kernel row of a block
-    t.mtiles = g.mtiles;
-    t.CPG = g.CPG;
-    t.KPG = g.KPG;
-    t.Cin = p.Cin;
-    t.Cout = p.Cout;
-    t.H = p.H;
-    t.W = p.W;
-    t.Wout = p.Wout;
-    t.HWo = p.Hout * p.Wout;
-    t.npix = (unsigned)npix;
-    t.m_HWo = div_magic(t.HWo);
-    t.m_Wout = div_magic(p.Wout);
-    t.px_tiles = (t.npix + 15) / 16;
-    t.m_px = div_magic(t.px_tiles);
-    t.m_mt = div_magic(t.mtiles);
-    t.x_bytes = (unsigned)xb;
     t.w_bytes = (unsigned)g.unit_bytes;
     // Where it pays (layers of the WRN-, ResNet-34- and MobileNet-shaped networks at N = 1 .. 64, us, conv_mfma16 with
     // staging / this kernel): 2 x 256 -> 256 on 14x14, g = 4 7.2 / 4.8; 1024 -> 1024 pointwise on 7x7, N = 1 19.1 / 6.6;
@@ -259,11 +228,6 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double mor
     //    with up to 16 filters 37 layers are level;
     //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 9.0 / 5.9, N = 10 (2250) 8.7 / 9.8, and with nine 144 -> 24 on 64x64,
     //    N = 4 (2048) 6.5 / 9.7, 576 -> 96 on 32x32, g = 4 6.6 / 9.0.
-    const long tiles = (long)t.px_tiles * g.mtiles * p.groups;
-    if ((double)(tiles + 8) * t.px_tiles >= 4294967296.0 || (double)(g.mtiles * (double)p.groups + 1) * g.mtiles >= 4294967296.0)
-        return false;
-    t.tiles = (unsigned)tiles;
-    t.per_xcd = (t.tiles + 7) / 8;
     const double loads = (double)tiles * units * (row ? 2 : 5);
     const bool wide = p.stride == 1 && (row ? p.W % 4 == 0 : (p.Hout * p.Wout) % 4 == 0);   // staged 16 bytes at a time
     if (loads > more * (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
