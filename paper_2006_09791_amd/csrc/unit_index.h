@@ -80,7 +80,39 @@ GSPC_HD unsigned unit_w_step(const TileUnit &t) {
 }
 template <unsigned WLANE>
 GSPC_HD unsigned unit_w_lane(const TileUnit &t, int u, bool on, unsigned lane) {
-    return (u < t.blocks ? lane * WLANE : kOob) | (on ? 0u : kOob);
+    return ((u < t.blocks) & on) ? lane * WLANE : kOob;
 }
+
+// Pixel li of a tile: image, place in the output plane, first row and column of its window in the input plane, and the column
+// that is loaded first.  3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
+// place up (down) and a zero takes the place of the column outside.
+struct UnitPixel {
+    unsigned n, rem;
+    int ih0, iw0, start;
+    bool live;
+};
+template <int KH, int S>
+GSPC_HD UnitPixel unit_pixel(const TileUnit &t, const UnitTileAt &a, unsigned li) {
+    // (the tile's first pixel in scalar registers; a tile spans images where planes are small)
+    unsigned n0 = fast_div(a.px * 16, t.m_HWo), r0 = a.px * 16 - n0 * t.HWo;
+    const bool low = r0 >= t.HWo;
+    n0 += low ? 1 : 0;
+    r0 -= low ? t.HWo : 0;
+    const unsigned dn = fast_div(r0 + li, t.m_HWo), rem = r0 + li - dn * t.HWo;
+    const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
+    const int ih0 = (int)oh * S - KH / 2, iw0 = (int)ow * S - KH / 2;
+    const int inside = iw0 < 0 ? 0 : iw0, last = t.W - 3;
+    return {n0 + dn, rem, ih0, iw0, KH == 3 && inside > last ? last : inside, a.px * 16 + li < t.npix && a.live};
+}
+
+// Inputs: the lane's offset in row k of the window, in the group's channel lg, or kOob; and with the first channel of a load, c channels
+// further by a scalar offset.  A lane's channels of a block are lg, 1x1: lg, lg + 4, lg + 8 and lg + 12; past the group's they have
+// zero weights and must be zeros too (0 * inf).
+template <int KH>
+GSPC_HD unsigned unit_x_row(const TileUnit &t, const UnitTileAt &a, const UnitPixel &p, unsigned lg, int k, bool on) {
+    const unsigned at = ((p.n * t.Cin + a.j * t.CPG + lg) * (unsigned)(t.H * t.W) + p.ih0 * t.W + p.start) * 4u + k * t.W * 4;
+    return (p.live & on & ((KH == 1) | ((unsigned)(p.ih0 + k) < (unsigned)t.H))) ? at : kOob;   // (&: a choice, not branches)
+}
+GSPC_HD unsigned unit_x_lane(const TileUnit &t, unsigned row, unsigned lg, int c) { return c < t.CPG - (int)lg ? row : kOob; }
 
 }  // namespace gspc

@@ -15,8 +15,8 @@
 // What a launch takes beyond the 1.8 us of an empty one that depends on another is this chain, and instructions are a
 // large part of it: a block has up to 16 waves, which share four instruction streams, so that a hundred more per wave are
 // 0.2-0.7 us.  Hence: one struct of arguments, read in one round; divisions without branches, the tile's share of them in
-// scalar registers; an address per kernel row, which the channel blocks move by a scalar offset; validity as bits or'ed
-// into the address; the residual requested with the inputs; and no code for shared blocks where none are.  The trivial
+// scalar registers; an address per kernel row, which the channel blocks move by a scalar offset; validity as a choice
+// of address; the residual requested with the inputs; and no code for shared blocks where none are.  The trivial
 // kernel with the same blocks, loads, products and sum takes 4.1 us on cold weights in a graph (14x14, 64 channels per
 // group: 1.0 us of them the weights, 0.6 the inputs, 0.5 the products).  Per layer of the batch-1 ResNet-34-shaped chain,
 // g = 4: 4.4 -> 3.7 us (169 -> 145 us in all), MobileNetV2-shaped 236 -> 205, the pointwise form of the WRN stack 306 -> 238;
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const UnitTileAt tile = unit_tile(t, blockIdx.x);
-    const unsigned px = tile.px, mt = tile.mt, j = tile.j;
+    const unsigned mt = tile.mt, j = tile.j;
     const unsigned HW = t.H * t.W;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(t.x, t.x_bytes);
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
         rows = shared.rows;
     }
     const auto row_on = [&](int k) { return !SHARE || (rows >> k & 1); };
-    const auto off_row = [&](int k) -> unsigned { return row_on(k) ? 0u : kOob; };   // (an address with these bits set is out of range)
 
     // ---- weights (they do not wait for the pixel arithmetic) ---------------------------------------
     constexpr unsigned WLANE = ROW ? 12 : 16;
@@ -82,33 +81,19 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     for (int s = 0; s < UB; ++s) fetch_w(first + s * NW, s);
 
     // ---- this lane's pixel ------------------------------------------------------------------------
-    // (the tile's first pixel in scalar registers; a tile spans images where planes are small)
-    unsigned n0 = fast_div(px * 16, t.m_HWo), r0 = px * 16 - n0 * t.HWo;
-    const bool low = r0 >= t.HWo;
-    n0 += low ? 1 : 0;
-    r0 -= low ? t.HWo : 0;
-    const unsigned dn = fast_div(r0 + li, t.m_HWo), n = n0 + dn, rem = r0 + li - dn * t.HWo;
-    const bool live = px * 16 + li < t.npix && tile.live;
-    const unsigned oh = fast_div(rem, t.m_Wout), ow = rem - oh * t.Wout;
-    const int ih0 = (int)oh * S - (ROW ? 1 : 0), iw0 = (int)ow * S - (ROW ? 1 : 0);
-    // 3x3 (padding 1): the three columns are loaded from inside the row; at its left (right) end they move one
-    // place up (down) and a zero takes the place of the column outside
-    const int start = ROW ? min(max(iw0, 0), t.W - 3) : iw0;
-    const unsigned xpix = ((n * t.Cin + j * t.CPG + lg) * HW + ih0 * t.W + start) * 4u;
+    const UnitPixel pix = unit_pixel<KH, S>(t, tile, li);
+    const unsigned n = pix.n, rem = pix.rem;
+    const bool live = pix.live;
     unsigned xo[KR];
 #pragma unroll
-    for (int k = 0; k < KR; ++k)
-        xo[k] = (xpix + k * t.W * 4) | (live && (!ROW || (unsigned)(ih0 + k) < (unsigned)t.H) ? 0u : kOob) | (ROW ? off_row(k) : 0u);
+    for (int k = 0; k < KR; ++k) xo[k] = unit_x_row<KH>(t, tile, pix, lg, k, row_on(k));
     u32x3 xr[UB][KR];
     unsigned xs[UB][4];
-    // Channels past the group's have zero weights and must be zeros too (0 * inf): a lane's channels of a block are lg,
-    // 1x1: lg, lg + 4, lg + 8 and lg + 12 from the block's first on.
-    const int mine = t.CPG - lg;
     auto fetch_x = [&](int u, int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < (ROW ? 3 : 4); ++e) {
             const int c = ROW ? u * 4 : u * 16 + 4 * e;      // (waves past the last block are past the channels)
-            const unsigned vo = xo[ROW ? e : 0] | (c < mine ? 0u : kOob), so = c * HW * 4;
+            const unsigned vo = unit_x_lane(t, xo[ROW ? e : 0], lg, c), so = c * HW * 4;
             if constexpr (ROW) xr[s][e] = __builtin_amdgcn_raw_buffer_load_b96(rx, vo, so, 0);
             else xs[s][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, vo, so, 0);
         }
@@ -127,7 +112,7 @@ __global__ __launch_bounds__(64 * NW, 8) void conv_mfma16u(TileUnit t) {
     __builtin_amdgcn_sched_barrier(0);
 
     f32x4 acc = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};   // even and odd blocks: two chains of products
-    const bool left_end = start > iw0, right_end = start < iw0;
+    const bool left_end = pix.start > pix.iw0, right_end = pix.start < pix.iw0;
     for (int u0 = first; u0 < t.blocks; u0 += UB * NW) {
 #pragma unroll
         for (int s = 0; s < UB; ++s) {

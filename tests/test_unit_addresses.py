@@ -20,6 +20,7 @@ SHAPES = [
     S(1, 23, 10, 9, 17, 3, 3, 2, 1, 1),
     S(71, 8, 3, 3, 12, 3, 3, 1, 1, 1),        # tiles that span images
     S(45, 48, 1, 3, 40, 1, 1, 1, 0, 1),
+    S(3, 24, 6, 5, 24, 3, 3, 2, 1, 2),
 ]
 
 PROGRAM = r"""
@@ -32,11 +33,12 @@ using namespace gspc;
 static long bad;
 // An access of size bytes at the lane's offset vo and the scalar offset so.
 static bool inside(unsigned vo, unsigned so, unsigned size, unsigned bytes) { return (unsigned long long)vo + so + size <= bytes; }
-static bool dropped(unsigned vo, unsigned bytes) { return vo >= bytes; }
+// (and no word of a dropped access may lie past 2^32, where its offset would be small again)
+static bool dropped(unsigned vo, unsigned size, unsigned bytes) { return vo >= bytes && (unsigned long long)vo + size <= 1ull << 32; }
 
-template <int K> void walk(const TileUnit &t, int nw) {
+template <int K, int S> void walk(const TileUnit &t, int nw) {
     constexpr int KR = K == 3 ? 3 : 1, UB = K == 3 ? 2 : 4;
-    constexpr unsigned WLANE = K == 3 ? 12 : 16;
+    constexpr unsigned WLANE = K == 3 ? 12 : 16, XSIZE = K == 3 ? 12 : 4;
     for (unsigned block = 0; block < 8 * t.per_xcd; ++block)
         for (int wave = 0; wave < nw; ++wave) {
             const UnitTileAt tile = unit_tile(t, block);
@@ -47,8 +49,26 @@ template <int K> void walk(const TileUnit &t, int nw) {
                     for (unsigned lane = 0; lane < 64; ++lane) {
                         const bool on = w.rows >> k & 1;
                         const unsigned vo = unit_w_lane<WLANE>(t, u, on, lane), so = base + u * step + k * 64 * WLANE;
-                        bad += u < t.blocks && on ? !inside(vo, so, WLANE, t.w_bytes) : !dropped(vo, t.w_bytes);
+                        bad += u < t.blocks && on ? !inside(vo, so, WLANE, t.w_bytes) : !dropped(vo, WLANE, t.w_bytes);
                     }
+            for (unsigned lane = 0; lane < 64; ++lane) {
+                const unsigned lg = lane / 16, q = tile.px * 16 + lane % 16;
+                const UnitPixel pix = unit_pixel<K, S>(t, tile, lane % 16);
+                const int n = q / t.HWo, oh = q % t.HWo / t.Wout, ow = q % t.Wout;   // what the definition reads
+                for (int r = 0, u = w.first; r < UB || u < t.blocks; ++r, u += nw)
+                    for (int e = 0; e < (K == 3 ? 3 : 4); ++e) {
+                        const int k = K == 3 ? e : 0, c = K == 3 ? u * 4 : u * 16 + 4 * e;
+                        const bool on = w.rows >> k & 1;
+                        const unsigned row = unit_x_row<K>(t, tile, pix, lg, k, on), vo = unit_x_lane(t, row, lg, c), so = c * t.H * t.W * 4;
+                        const int ih = oh * S - K / 2 + k, ch = c + (int)lg, col = K == 3 ? std::min(std::max(ow * S - 1, 0), t.W - 3) : ow * S;
+                        if (tile.live && q < t.npix && on && ch < t.CPG && ih >= 0 && ih < t.H) {
+                            const unsigned want = (((n * t.Cin + tile.j * t.CPG + ch) * t.H + ih) * t.W + col) * 4;
+                            bad += !inside(vo, so, XSIZE, t.x_bytes) || vo + so != want;
+                        } else {
+                            bad += !dropped(vo, XSIZE, t.x_bytes);
+                        }
+                    }
+            }
         }
 }
 
@@ -61,7 +81,7 @@ int main(int, char **a) {
     t.w_bytes = (unsigned)(groups * t.blocks * t.mtiles) * (K == 3 ? 2304 : 1024);
     for (int nw = 2; nw <= 16; nw *= 2)
         for (t.parts = 1; t.parts <= (K == 3 && nw >= 2 * t.blocks ? std::min(nw / t.blocks, 3) : 1); ++t.parts)
-            K == 3 ? walk<3>(t, nw) : walk<1>(t, nw);
+            K == 3 ? S == 1 ? walk<3, 1>(t, nw) : walk<3, 2>(t, nw) : S == 1 ? walk<1, 1>(t, nw) : walk<1, 2>(t, nw);
     std::printf("%ld\n", bad);
 }
 """
