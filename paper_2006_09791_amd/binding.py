@@ -45,7 +45,12 @@ class GspcLayer(ctypes.Structure):
 
 
 _lib = None
-_conv = None     # gspc_conv2d_grouped through _gspc_call
+_conv = None     # gspc_conv2d_grouped through _gspc_call, or _no_conv
+
+
+def _no_conv(*args):
+    """Every call of gspc_conv2d_grouped is one that only ctypes converts."""
+    return NotImplemented
 
 
 def load():
@@ -98,9 +103,13 @@ def load():
     lib.gspc_run_layer_chain.restype = i
     lib.gspc_run_layer_chain.argtypes = [ctypes.POINTER(GspcLayer), i, ctypes.POINTER(vp),
                                          ctypes.POINTER(sz), i, ctypes.POINTER(ctypes.c_float)]
-    from . import _gspc_call
-    _gspc_call.bind(ctypes.cast(lib.gspc_conv2d_grouped, vp).value)
-    _conv = _gspc_call.conv
+    try:
+        from . import _gspc_call
+    except ImportError:          # not built for this interpreter
+        _conv = _no_conv
+    else:
+        _gspc_call.bind(ctypes.cast(lib.gspc_conv2d_grouped, vp).value)
+        _conv = _gspc_call.conv
     _lib = lib
     return lib
 

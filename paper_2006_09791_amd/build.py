@@ -1,5 +1,6 @@
-"""Build libgspc.so (HIP, gfx950 only) in-tree with hipcc, and _gspc_call.so, the binding's argument marshalling."""
+"""Build libgspc.so (HIP, gfx950 only) in-tree with hipcc, and _gspc_call, the binding's argument marshalling."""
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -10,7 +11,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgspc.so")
-CALL = os.path.join(HERE, "_gspc_call.so")
+# (named after the interpreter that it is built for: another one does not find it and calls through ctypes)
+CALL = os.path.join(HERE, "_gspc_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["gspc_api.cpp", "pack_kernels.hip", "chain_kernels.hip",
            "direct_kernels.hip", "mfma_kernels.hip", "mfma4_kernels.hip", "mfmab_kernels.hip",
@@ -48,7 +50,17 @@ def _compile(src):
     return obj, warn
 
 
+def _can_build_call():
+    return shutil.which("gcc") and os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
+
+
 def _build_call():
+    if not _can_build_call():
+        print("no gcc or no Python.h: the binding will call through ctypes alone", file=sys.stderr)
+        return
+    untagged = os.path.join(HERE, "_gspc_call.so")      # an earlier build's, which any interpreter would load
+    if os.path.exists(untagged):
+        os.remove(untagged)
     cmd = ["gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "pycall.c"), "-o", CALL]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -57,9 +69,10 @@ def _build_call():
 
 
 def build(force=True, verbose=False):
-    """Compiles every source and links libgspc.so and _gspc_call.so.  With force=False
-    up-to-date libraries are reused."""
-    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, CALL)):
+    """Compiles every source and links libgspc.so and, where a C compiler and Python's headers are there, _gspc_call.
+    With force=False up-to-date libraries are reused."""
+    made = (LIB, CALL) if _can_build_call() else (LIB,)
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in made):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     _build_call()

@@ -220,3 +220,33 @@ def test_conv_call_marshalling(n):
     assert e.value.code == -8                                  # four bytes off
     with pytest.raises(ctypes.ArgumentError):
         b.gspc_conv2d_grouped(x, Packed, 1.0, *args[1:], output=x)
+
+
+def test_library_serves_without_the_call_extension():
+    """An interpreter that the C form of the call is not built for loads the library and calls through ctypes."""
+    import subprocess
+    import sys
+    program = """
+import sys
+sys.modules["paper_2006_09791_amd._gspc_call"] = None      # its import raises ImportError
+import ctypes, torch
+from paper_2006_09791_amd import binding as b
+x = torch.zeros(16)
+class Packed:
+    handle = ctypes.c_void_p(x.data_ptr())
+try:
+    b.gspc_conv2d_grouped(x, Packed, 1, 64, 32, 32, 64, 3, 3, 1, 1, 4, output=x)
+except b.GspcError as e:
+    print(e.code)
+"""
+    r = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True)
+    assert r.stdout.strip() == "-5", r.stderr                   # sixteen zeros are no handle
+
+
+def test_call_extension_is_named_after_its_interpreter():
+    import sysconfig
+
+    from paper_2006_09791_amd import build
+    b.load()
+    assert build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert not os.path.exists(os.path.join(os.path.dirname(build.CALL), "_gspc_call.so"))   # any interpreter would load that
