@@ -295,7 +295,14 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
     // this lane's pixel; the 4*(lane/16) part already sits in ooff.
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.y, t.y_bytes);
     const unsigned oc0 = ob * MI * 16;
-    f32x4 res[MI][NI];   // (!PERSIST)
+    // The residual of a block's only tile is requested before the products: after them its trip to memory is one more link
+    // of the chain (WRN-40-2-style chain, g = 2, N = 64 328.2 -> 326.4 us with five such layers; 80 -> 64 on 32x32 at stride 2,
+    // g = 2, N = 64 11.9 -> 11.0).  Not in the one instance whose LDS leaves room for three blocks per compute unit and whose
+    // registers then would for two: a launch that grid_x_w takes for one round runs in two (8 -> 64 on 36x20, g = 2, N = 122, with
+    // its residual 15.6 us for 12.4, without one 12.2 for 10.8).  Of the others none keeps fewer blocks than
+    // its launches ask for (300 000 random layers).
+    constexpr bool EARLY = !PERSIST && !(MI * NI == 8 && S == 1 && CKB == 1 && XS == kTmaxW);
+    f32x4 res[MI][NI];   // (EARLY)
     auto epilogue = [&](const unsigned (&ooff)[NI]) __attribute__((always_inline)) {
     if (p.res) {
         const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res, t.y_bytes);
@@ -305,9 +312,9 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    acc[mi][ni][r] += !PERSIST ? res[mi][ni][r]
-                                               : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                                                     rr, ooff[ni], (oc0 + mi * 16 + r) * HWo * 4, 0));
+                    acc[mi][ni][r] += EARLY ? res[mi][ni][r]
+                                            : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                                  rr, ooff[ni], (oc0 + mi * 16 + r) * HWo * 4, 0));
     }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -322,9 +329,7 @@ __global__ __launch_bounds__(256) void conv_mfma16w(ConvParams p, Tile16w t) {
             }
     };
 
-    // The residual of a block's only tile is requested before the products: after them its trip to memory is one more link
-    // of the chain (WRN-40-2-style chain, g = 2, N = 64 328.2 -> 326.4 us with five such layers).
-    if (!PERSIST && p.res) {
+    if (EARLY && p.res) {
         const __amdgpu_buffer_rsrc_t rr = make_rsrc(p.res, t.y_bytes);
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)

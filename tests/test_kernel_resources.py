@@ -55,3 +55,15 @@ def test_split_kernel_refuses_a_plan_without_an_instance(inst):
     plan[0], plan[1], plan[2] = inst, 4, 1                              # shape, 32 channels per chunk, unsplit filters
     not_supported = 801                                                # hipErrorNotSupported
     assert launch(params, plan, None, ctypes.byref(name)) == not_supported and not name.value
+
+
+def waves(k):
+    """Waves per SIMD that a kernel's registers leave room for."""
+    return min(8, 512 // max(8, (k[".vgpr_count"] + 7) // 8 * 8))
+
+
+def test_resident_filters_keep_three_blocks_per_compute_unit():
+    """Eight tiles per wave, one channel block per chunk at stride 1: LDS leaves room for three blocks and four, and
+    a launch that fits by LDS is taken for one round: the registers must leave room for three."""
+    k, = [v for n, v in kernels().items() if n.startswith("_ZN4gspc12conv_mfma16wILi2ELi4ELi1ELi1ELb0ELi4E")]
+    assert waves(k) >= 3, k[".vgpr_count"]
