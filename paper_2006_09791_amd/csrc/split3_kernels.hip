@@ -37,8 +37,13 @@ struct TileH {
 };
 static_assert(sizeof(TileH) <= sizeof(((Split3Plan *)0)->data), "plan storage too small");
 
+// Waves per SIMD.  The bf16 instances of 16 channels per chunk, even rows and 4-byte stores come out one register past the step of
+// five (four) waves if they are left to it: 384 -> 240 on 33x34 at stride 2, g = 8, N = 110 35.5 us for 25.8.
+template <int MI, int CGS, typename TIN, bool EVEN, bool VO>
+constexpr int kWavesH = sizeof(TIN) == 2 && CGS == 2 && EVEN && !VO ? (MI == 1 ? 5 : 4) : 2;
+
 template <int MI, int NI, int WM, int WP, int WK, int CGS, int S, typename TIN, bool EVEN, bool VO, bool PLAIN>
-__global__ __launch_bounds__(64 * WM * WP * WK, 2) void conv_split3(ConvParams p, TileH t) {
+__global__ __launch_bounds__(64 * WM * WP * WK, (kWavesH<MI, CGS, TIN, EVEN, VO>)) void conv_split3(ConvParams p, TileH t) {
     constexpr int NP = sizeof(TIN) == 4 ? 3 : 1, ES = (int)sizeof(TIN);
     constexpr int NT = 64 * WM * WP, PB = 16 * NI * WP, KS = CGS == 4 ? 9 : 5;
     constexpr int NA = 3;           // filter sets: k-step ks in set ks % NA, requested NA - 1 k-steps ahead

@@ -67,3 +67,11 @@ def test_resident_filters_keep_three_blocks_per_compute_unit():
     a launch that fits by LDS is taken for one round: the registers must leave room for three."""
     k, = [v for n, v in kernels().items() if n.startswith("_ZN4gspc12conv_mfma16wILi2ELi4ELi1ELi1ELb0ELi4E")]
     assert waves(k) >= 3, k[".vgpr_count"]
+
+
+@pytest.mark.parametrize("shape,least", [("1ELi4ELi1ELi4", 5), ("2ELi4ELi1ELi4", 4), ("2ELi4ELi2ELi2", 4)])
+@pytest.mark.parametrize("stride", [1, 2])
+def test_bf16_split_blocks_keep_their_waves(shape, least, stride):
+    """16 channels per chunk, even rows, 4-byte stores: left to the compiler these are one register past a step."""
+    k, = [v for n, v in kernels().items() if n.startswith(f"_ZN4gspc11conv_split3ILi{shape}ELi1ELi2ELi{stride}EtLb1ELb0E")]
+    assert waves(k) >= least, k[".vgpr_count"]
