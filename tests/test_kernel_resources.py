@@ -75,3 +75,9 @@ def test_bf16_split_blocks_keep_their_waves(shape, least, stride):
     """16 channels per chunk, even rows, 4-byte stores: left to the compiler these are one register past a step."""
     k, = [v for n, v in kernels().items() if n.startswith(f"_ZN4gspc11conv_split3ILi{shape}ELi1ELi2ELi{stride}EtLb1ELb0E")]
     assert waves(k) >= least, k[".vgpr_count"]
+
+
+def test_bf16_strips_keep_their_waves():
+    """bf16 depthwise at stride 2: left to the compiler it is two registers past the step of six waves."""
+    k, = [v for n, v in kernels().items() if n.startswith("_ZN4gspc17conv_direct_smallILi1ELi1ELi2ELi2Et")]
+    assert waves(k) >= 6 and k[".vgpr_spill_count"] == 0, k[".vgpr_count"]
