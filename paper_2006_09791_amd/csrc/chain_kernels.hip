@@ -1,14 +1,9 @@
 // Non-convolution steps of the residual stacks of Section IV-A of
 // arXiv 2006.09791: ReLU, element-wise add, max pooling.  All fp32.
+#include "divide.h"
 #include "gspc_internal.h"
 
 namespace gspc {
-
-// n / d for any 32-bit n: the product with mul = floor((2^32 - 1) / d) is at most one too low.
-__device__ __forceinline__ unsigned exact_div(unsigned n, unsigned d, unsigned mul) {
-    const unsigned q = __umulhi(n, mul);
-    return n - q * d >= d ? q + 1 : q;
-}
 
 __global__ void relu_kernel(const float *__restrict__ x, float *__restrict__ y, size_t count) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -36,7 +31,7 @@ __global__ void maxpool_kernel(const float *__restrict__ x, float *__restrict__ 
     const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
     const int k = K ? K : Kany;
-    const unsigned r = exact_div(i, Wout, m_Wout), plane = exact_div(r, Hout, m_Hout);   // n * C + c
+    const unsigned r = fast_div_any(i, Wout, m_Wout), plane = fast_div_any(r, Hout, m_Hout);   // n * C + c
     const int iw0 = (int)(i - r * Wout) * stride - pad, ih0 = (int)(r - plane * Hout) * stride - pad;
     const float *xp = x + (size_t)plane * H * W;
     float m = -INFINITY;
@@ -85,7 +80,7 @@ hipError_t launch_maxpool(const float *x, float *y, int N, int C, int H, int W, 
     for (size_t at = 0; at < planes; at += step) {
         const unsigned total = (unsigned)((planes - at < step ? planes - at : step) * plane);
         hipLaunchKernelGGL(kern, dim3((total + 255) / 256), dim3(256), 0, s, x + at * H * W, y + at * plane, H, W, K, stride, pad,
-                           Hout, Wout, total, 0xffffffffu / Wout, 0xffffffffu / Hout);
+                           Hout, Wout, total, div_magic(Wout), div_magic(Hout));
     }
     return hipGetLastError();
 }
