@@ -250,3 +250,28 @@ def test_call_extension_is_named_after_its_interpreter():
     b.load()
     assert build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
     assert not os.path.exists(os.path.join(os.path.dirname(build.CALL), "_gspc_call.so"))   # any interpreter would load that
+
+
+def test_conv_call_takes_the_c_route():
+    """Plain ints go through the C form, in the order of the prototype; what only ctypes converts is handed back to it."""
+    import torch
+
+    from paper_2006_09791_amd import _gspc_call
+    lib = b.load()
+    assert b._conv is _gspc_call.conv
+    x, y = torch.zeros(16), torch.zeros(16)
+    handle, seen = ctypes.c_void_p(4096), []
+    types = [ctypes.c_void_p] * 2 + [ctypes.c_int] * 10 + [ctypes.c_void_p]
+    record = ctypes.CFUNCTYPE(ctypes.c_int, *types)(lambda *a: seen.append(a) or -3)
+    dims = tuple(range(11, 21))
+    _gspc_call.bind(ctypes.cast(record, ctypes.c_void_p).value)
+    try:
+        assert b._conv(x, handle, *dims, y) == -3
+        assert b._conv(None, None, *dims, None) == -3
+        for odd in (True, 1.0, 2 ** 31, 2 ** 40 + 1):
+            for at in range(10):
+                assert b._conv(x, handle, *dims[:at], odd, *dims[at + 1:], y) is NotImplemented
+        assert b._conv(x, 4096, *dims, y) is NotImplemented            # a handle that is no c_void_p
+    finally:
+        _gspc_call.bind(ctypes.cast(lib.gspc_conv2d_grouped, ctypes.c_void_p).value)
+    assert seen == [(x.data_ptr(), 4096) + dims + (y.data_ptr(),), (None, None) + dims + (None,)]
