@@ -822,14 +822,14 @@ MfmaPlan choose(const ConvParams &p, const PackGeom &g, char fam) {
     // Larger launches go to the kernel without staging from those that read fp32 operands 4 bytes at a time or have few blocks
     // (random layers of 1 .. 12 times the bound on its loads, time there / here, geometric mean):
     //  - the generic kernel: 3.3 at any size measured (37 layers, 1.03 and more; 126 -> 144 on 12x93 at stride 2, g = 3,
-    //    N = 140 377 / 84 us);
+    //    N = 140 388 / 75 us);
     //  - the staged kernel, 1x1 up to four times the bound: stride 2 2.2 (23 layers, two of them 2 and 4 % behind), stride 1 2.1
-    //    (30, likewise; 692 -> 24 on 21x21, N = 28 90 / 18.7, 700 -> 112 on 14x14, N = 10 14.6 / 11.5).  Odd planes handed over
+    //    (30, likewise; 692 -> 24 on 21x21, N = 28 90 / 17.2, 700 -> 112 on 14x14, N = 10 13.4 / 10.9).  Odd planes handed over
     //    as single rows it stages 16 bytes at a time where they fill its tiles; those stay while the reduction takes few
-    //    chunks, each with its barrier (five: 640 -> 108 on 6x5, N = 106 12.9 / 15.8; eight: 864 -> 100 on 5x5, N = 73
-    //    13.4 / 12.8).  Twenty and more, which is what few divisors of the channel count and large planes come to: 56 layers 1.15
-    //    and more, most of them 2 to 4 (1024 -> 530 on 13x13, N = 7, 64 chunks 69 / 31; 988 -> 64 on 7x11, N = 107, 247 chunks
-    //    121 / 27).
+    //    chunks, each with its barrier (five: 640 -> 108 on 6x5, N = 106 11.8 / 14.8; eight: 864 -> 100 on 5x5, N = 73
+    //    13.2 / 12.1).  Twenty and more, which is what few divisors of the channel count and large planes come to: 56 layers 1.15
+    //    and more, most of them 2 to 4 (988 -> 64 on 7x11, N = 107, 247 chunks 121 / 27; just past four times the bound, where it
+    //    stays, 1024 -> 530 on 13x13, N = 7, 64 chunks 69 / 29).
     // (3x3 layers stay: up to twice the bound 1.4, but a tenth of them behind.)
     const bool single_rows = p.stride == 1 && p.H == 1 && p.W % 4 != 0 && g.CPG % 4 == 0;
     const bool narrow = p.KH == 1 && (!single_rows || pl.t16.nchunks >= 20);

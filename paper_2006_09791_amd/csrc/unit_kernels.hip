@@ -195,24 +195,25 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double mor
     unit_layer(t, p.N, p.Cin, p.H, p.W, p.Cout, p.groups, p.KH, p.Hout, p.Wout, g.mtiles);
     const int units = row ? 3 * t.blocks : t.blocks;     // of the reduction in the rules below: 3x3, a kernel row of a block
     t.w_bytes = (unsigned)g.unit_bytes;
-    // Where it pays (layers of the WRN-, ResNet-34- and MobileNet-shaped networks at N = 1 .. 64, us, conv_mfma16 with
-    // staging / this kernel): 2 x 256 -> 256 on 14x14, g = 4 7.2 / 4.8; 1024 -> 1024 pointwise on 7x7, N = 1 19.1 / 6.6;
-    // 60 -> 84 on 29x37, g = 3, N = 5 9.1 / 6.9.  Operands are loaded once per tile that uses them, so the loads decide:
-    //  - 3x3, stride 1, rows of a multiple of 4 (16-byte staging on the other side): 75k loads 8.3 / 6.5 and 9.4 / 6.6,
-    //    150k 9.1 / 10.0 and 13.1 / 10.0, 300k 13.4 / 16.6;
-    //  - stride 2, other widths, 1x1: 150k 12.7 / 10.2 and 18.2 / 9.9, 200k (32 -> 64 on 32x32 at stride 2) 10.2 / 11.4,
-    //    300k 16.7 / 18.0 and 20.0 / 22.2; pointwise on planes of a multiple of 4 174k 15.4 / 11.6, 189k 13.9 / 16.8.
+    // Where it pays (us per layer of a recorded chain, the kernel that has the layer otherwise / this one): 256 -> 256 on 14x14, g = 4,
+    // N = 2 6.5 / 4.3; 1024 -> 1024 pointwise on 7x7, N = 1 19.5 / 4.9; 60 -> 84 on 29x37, g = 3, N = 5 8.8 / 5.6.  The lines below were
+    // drawn for a form of this kernel that took 1.05 to 2 times as long, 1x1 most of all: where the far side of one has this kernel
+    // ahead, marked *, it could lie further out.  Operands are loaded once per tile that uses them, so the loads decide:
+    //  - 3x3, stride 1, rows of a multiple of 4 (16-byte staging on the other side): 75k loads 6.2 / 5.7 (256 -> 256 on 28x28, g = 8,
+    //    N = 2) and 6.6 / 6.0 (on 14x14, g = 4, N = 4), twice the batch 8.9 / 8.8 and 8.5 / 9.6, four times 10.3 / 15.1 and 11.3 / 15.6;
+    //  - stride 2, other widths, 1x1: 32 -> 64 on 32x32 at stride 2, g = 2 98k 7.8 / 6.8, 147k 9.4 / 9.1, 197k 11.3 / 11.6, 295k
+    //    16.5 / 15.9; 256 -> 256 on 15x15, g = 2, N = 6 (261k) 13.5 / 14.0; 1x1 on planes of a multiple of 4, 512 -> 128 on 14x14 173k
+    //    16.0 / 8.8, *188k 15.0 / 9.4 and 251k 14.6 / 11.8, which choose() gives to this kernel after all.
     // With few units a block is mostly its start and its sum, and once the blocks no longer run together that counts:
-    //  - fewer than six: 3 -> 32 on 32x32, N = 8 4.9 / 4.7, N = 32 5.2 / 6.8; pointwise on planes that are staged 16 bytes
-    //    at a time 64 -> 64 on 16x16, N = 16 (1024 tiles) 5.0 / 4.7, 64 -> 128 (2048) 5.0 / 5.3, 64 -> 64 on 56x56, N = 3
-    //    (2352) 5.4 / 6.6, on other planes 64 -> 80 on 55x55, N = 2 (1895) 8.0 / 6.5;
-    //  - six, 3x3 with stride 1: 64 -> 64, g = 8 on 16-pixel rows (2048) 4.8 / 4.7, on 20x20, N = 16 (3200) 5.1 / 6.1, on
-    //    13x13, N = 50 (4232) 6.6 / 7.7; with nine 96 -> 96, g = 8 on 17x17 (2312) 7.4 / 5.9;
-    //  - six at stride 2, from 17 filters per group on, which the other side then multiplies out of one staged tile: 32 -> 192
-    //    on 40x40, g = 4, N = 14 (4200) 7.5 / 8.6, 32 -> 128 on 16x16, g = 4, N = 187 (5984) 7.2 / 10.1, 78 layers 0.82;
-    //    with up to 16 filters 37 layers are level;
-    //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 9.0 / 5.9, N = 10 (2250) 8.7 / 9.8, and with nine 144 -> 24 on 64x64,
-    //    N = 4 (2048) 6.5 / 9.7, 576 -> 96 on 32x32, g = 4 6.6 / 9.0.
+    //  - fewer than six: 3 -> 32 on 32x32, N = 8 3.5 / 3.0, N = 32 5.1 / 5.5; pointwise on planes that are staged 16 bytes
+    //    at a time 64 -> 64 on 16x16, N = 16 (1024 tiles) 4.2 / 3.1, *64 -> 128 (2048) 4.8 / 4.2, *64 -> 64 on 56x56, N = 3
+    //    (2352) 5.3 / 4.9, on other planes 64 -> 80 on 55x55, N = 2 (1895) 6.9 / 4.2;
+    //  - six, 3x3 with stride 1: 64 -> 64, g = 8 on 16-pixel rows (2048) 5.0 / 3.7, on 20x20, N = 16 (3200) 4.8 / 4.8, *on
+    //    13x13, N = 50 (4232) 6.7 / 5.5; with nine 96 -> 96, g = 8 on 17x17 (2312) 7.2 / 4.8;
+    //  - six at stride 2, from 17 filters per group on, which the other side then multiplies out of one staged tile: *32 -> 192
+    //    on 40x40, g = 4, N = 14 (4200) 7.3 / 5.9, 32 -> 128 on 16x16, g = 4, N = 187 (5984) 6.8 / 7.5;
+    //  - ten, pointwise: 160 -> 144 on 20x20, N = 5 (1125) 8.7 / 4.4, *N = 10 (2250) 8.1 / 6.1, and with nine *144 -> 24 on 64x64,
+    //    N = 4 (2048) 6.0 / 5.5, 576 -> 96 on 32x32, g = 4 (512) 4.7 / 3.0.
     const double loads = (double)tiles * units * (row ? 2 : 5);
     const bool wide = p.stride == 1 && (row ? p.W % 4 == 0 : (p.Hout * p.Wout) % 4 == 0);   // staged 16 bytes at a time
     if (loads > more * (row ? wide ? 80e3 : p.W % 4 == 0 ? 160e3 : 200e3 : wide ? 180e3 : 200e3)) return false;
@@ -221,27 +222,28 @@ bool plan_unit(const ConvParams &p, const PackGeom &g, UnitPlan *out, double mor
     if (row && p.stride == 2 && units < 9 && g.KPG > 16 && tiles > 12 * kNumCU) return false;
     if (!row && wide && units < 12 && tiles >= 8 * kNumCU) return false;
     // Odd pointwise planes handed over as one row are staged 16 bytes at a time as well:
-    //  - 40 .. 63 pixels, which fill most of a 64-pixel tile: while the staged kernel has a block per image (see
-    //    fills_image_tiles) it is ahead from 4 tiles per compute unit on: 384 -> 32 on 7x7, g = 2, N = 178 (1092 tiles)
-    //    10.5 / 7.3 here / staged, 768 -> 192, g = 8, N = 27 (1328) 7.8 / 5.3, 192 -> 48, g = 2, N = 150 (1840) 9.3 / 6.4;
-    //  - more: from 12 on: 256 -> 40 on 9x9, g = 4, N = 170 (3444) 11.2 / 7.9, 512 -> 48 on 11x11, g = 4, N = 133 (4024)
-    //    18.0 / 11.5 (one of 19 layers the other way round: 320 -> 48 on 11x11, N = 212 19.1 / 26.5).
+    //  - 40 .. 63 pixels, which fill most of a 64-pixel tile, while the staged kernel has a block per image (see
+    //    fills_image_tiles), from 4 tiles per compute unit on: *384 -> 32 on 7x7, g = 2, N = 178 (1092 tiles) 6.9 / 4.8,
+    //    *768 -> 192, g = 8, N = 27 (1328) 5.0 / 4.1, *192 -> 48, g = 2, N = 150 (1840) 5.7 / 4.6;
+    //  - more, from 12 on: *256 -> 40 on 9x9, g = 4, N = 170 (3444) 6.5 / 5.7, *512 -> 48 on 11x11, g = 4, N = 133 (4024)
+    //    10.0 / 7.8; past the bound on the loads 320 -> 48 on 11x11, N = 212 19.4 / 21.2.
     if (!row && p.stride == 1 && p.H == 1 && p.W % 4 != 0 && p.W >= 64 && p.W <= 256 && g.CPG % 4 == 0 && tiles > 12 * kNumCU)
         return false;
     if (tiles > 4 * kNumCU && fills_image_tiles(p, g.mtiles)) return false;
     // waves per block: what lets every wave request all of its units at once, more as long as all of the launch's waves
-    // still start together, eight per compute unit: one block too many costs its start anew (8 -> 16 on 12x12, g = 2,
-    // N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time)
+    // still start together, eight per compute unit: one block too many costs its start anew (the kernel's earlier form, 8 -> 16
+    // on 12x12, g = 2, N = 21: 378 blocks of eight waves 4.4 us, of four 3.6; 230 layers with 230 .. 1000 tiles 0.81 of their time;
+    // now 2.8 with four)
     int nw = 2;
     while (nw < 16 && (units > nw * (row ? 6 : 4) || (tiles * nw * 2 <= 8 * kNumCU && units > nw))) nw *= 2;
     // Large 3x3 layers whose waves have places for a third more units than there are (9, 15, 18, 27, 30 of them) go to the
-    // kernel that keeps its filters where that takes the layer and the rows fill its 16-pixel tiles: 20 -> 64 on 32x32,
-    // N = 4, g = 2 (2048 tiles) 6.9 / 5.3 here / there, 144 -> 192 on 16x16, g = 4, N = 7 (1344) 8.6 / 6.5, 80 -> 256 on 16x16,
-    // g = 2, N = 5 (1280) 7.8 / 6.6; 128 layers 0.84.  On rows of 12, 20, 24, 28 and 40 pixels 28 layers are level (0.83 ..
-    // 1.09), and so are 12 and 24 units, which leave no place empty.
+    // kernel that keeps its filters where that takes the layer and the rows fill its 16-pixel tiles (there / here): 144 -> 192 on
+    // 16x16, g = 4, N = 7 (1344 tiles) 6.3 / 6.6, *80 -> 256 on 16x16, g = 2, N = 5 (1280) 6.3 / 6.1.  On rows of 12, 20, 24, 28
+    // and 40 pixels 28 layers were level with this kernel's earlier form (0.83 .. 1.09), and so were 12 and 24 units, which leave no
+    // place empty.
     // Six units leave half of the places empty, and five tiles per compute unit are enough: 16 -> 64 on 16x16, g = 2, N = 29
-    // (1856) 4.8 / 4.3, 8 -> 128 on 14x16, N = 15 (1680) 4.8 / 4.3, with 4.5 tiles level; not on planes that the 32 pixels of
-    // its two waves do not divide (16 -> 32 on 14x8, g = 2, N = 144 (2016) 4.9 / 5.3).
+    // (1856) 3.9 / 3.9, *8 -> 128 on 14x16, N = 15 (1680) 3.9 / 3.7; not on planes that the 32 pixels of its two waves do not
+    // divide (16 -> 32 on 14x8, g = 2, N = 144 (2016) 5.1 / 4.0).
     Mfma16wPlan pw;
     if (row && wide && (16 % p.W == 0 || p.W % 16 == 0) && 4 * units <= 3 * 6 * nw &&
         tiles * nw >= (units < 9 && p.H * p.W % 32 == 0 ? 10 : 24) * kNumCU && plan_mfma16w(p, g, &pw))
