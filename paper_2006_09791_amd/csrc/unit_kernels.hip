@@ -168,7 +168,7 @@ hipError_t launchU(const TileUnit &t, hipStream_t s) {
     if constexpr (KH == 3 && !SHARE) {
         if (t.parts > 1) return launchU<NW, KH, S, true>(t, s);
     }
-    hipLaunchKernelGGL((conv_mfma16u<NW, KH, S, SHARE>), dim3(8 * t.per_xcd), dim3(64 * NW), 0, s, t);
+    hipLaunchKernelGGL((conv_mfma16u<NW, KH, S, SHARE>), dim3(unit_blocks(t)), dim3(64 * NW), 0, s, t);
     return hipGetLastError();
 }
 

@@ -11,7 +11,7 @@ S = wl.ConvShape
 SHAPES = [
     # N Cin H W Cout KH KW stride pad groups
     S(1, 64, 32, 32, 64, 3, 3, 1, 1, 4),
-    S(1, 1024, 4, 4, 16, 1, 1, 1, 0, 1),      # one tile: seven blocks without one, 64 KB of filters
+    S(1, 1024, 4, 4, 16, 1, 1, 1, 0, 1),      # one tile, 64 KB of filters
     S(1, 16, 1, 3, 16, 3, 3, 1, 1, 1),
     S(3, 70, 9, 5, 33, 3, 3, 1, 1, 1),        # padded channels and filters
     S(5, 60, 29, 37, 84, 3, 3, 1, 1, 3),
@@ -27,6 +27,7 @@ PROGRAM = r"""
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 #include "unit_index.h"
 using namespace gspc;
 
@@ -39,7 +40,13 @@ static bool dropped(unsigned vo, unsigned size, unsigned bytes) { return vo >= b
 template <int K, int S> void walk(const TileUnit &t, int nw) {
     constexpr int KR = K == 3 ? 3 : 1, UB = K == 3 ? 2 : 4;
     constexpr unsigned WLANE = K == 3 ? 12 : 16, XSIZE = K == 3 ? 12 : 4;
-    for (unsigned block = 0; block < 8 * t.per_xcd; ++block)
+    std::vector<char> seen(t.tiles);                              // every tile is some block's, once
+    for (unsigned block = 0; block < unit_blocks(t); ++block) {
+        const UnitTileAt a = unit_tile(t, block);
+        const unsigned id = (a.j * t.mtiles + a.mt) * t.px_tiles + a.px;
+        bad += a.px >= t.px_tiles || a.mt >= (unsigned)t.mtiles || id >= t.tiles || seen[id]++;
+    }
+    for (unsigned block = 0; block < unit_blocks(t); ++block)
         for (int wave = 0; wave < nw; ++wave) {
             const UnitTileAt tile = unit_tile(t, block);
             const UnitWave w = t.parts > 1 ? unit_share(t, wave) : UnitWave{wave, 7};
@@ -61,7 +68,7 @@ template <int K, int S> void walk(const TileUnit &t, int nw) {
                         const bool on = w.rows >> k & 1;
                         const unsigned row = unit_x_row<K>(t, tile, pix, lg, k, on), vo = unit_x_lane(t, row, lg, c), so = c * t.H * t.W * 4;
                         const int ih = oh * S - K / 2 + k, ch = c + (int)lg, col = K == 3 ? std::min(std::max(ow * S - 1, 0), t.W - 3) : ow * S;
-                        if (tile.live && q < t.npix && on && ch < t.CPG && ih >= 0 && ih < t.H) {
+                        if (q < t.npix && on && ch < t.CPG && ih >= 0 && ih < t.H) {
                             const unsigned want = (((n * t.Cin + tile.j * t.CPG + ch) * t.H + ih) * t.W + col) * 4;
                             bad += !inside(vo, so, XSIZE, t.x_bytes) || vo + so != want;
                         } else {
